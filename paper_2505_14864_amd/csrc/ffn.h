@@ -1,5 +1,5 @@
-// Pieces shared by the grouped-FFN kernels: the ragged row-tile lookup, the
-// SwiGLU backward formula, and the entry points of the two kernel families.
+// Pieces shared by the grouped-FFN kernels: the row-tile bound, the SwiGLU backward
+// formula, and the entry points of the two kernel families.
 #pragma once
 
 #include "common.h"
@@ -14,27 +14,6 @@ inline int max_m_tiles(const dynmo_desc* d, int BM) {
   const int64_t full = rows / BM;
   const int64_t partial = d->E < rows ? d->E : rows;
   return (int)(full + partial);
-}
-
-// Maps a flat row-tile index to (expert, first row, end row) by walking the
-// segment offsets.  Returns false for an index past the last tile.
-__device__ __forceinline__ bool find_m_tile(const int32_t* __restrict__ seg, int E, int tile, int BM, int* e_out,
-                                            int* m0, int* m_end) {
-  int first = 0;
-  int begin = seg[0];
-  for (int e = 0; e < E; ++e) {
-    const int end = seg[e + 1];
-    const int nt = (end - begin + BM - 1) / BM;
-    if (tile < first + nt) {
-      *e_out = e;
-      *m0 = begin + (tile - first) * BM;
-      *m_end = end;
-      return true;
-    }
-    first += nt;
-    begin = end;
-  }
-  return false;
 }
 
 // Given dA and the saved pre-activations: A = silu(g) u, dG = dA u silu'(g), dU = dA silu(g).
@@ -60,10 +39,11 @@ struct FoldedCombine {
 // In both forward families `gather` is NULL (x_p holds the expert-sorted rows) or the
 // slot index: row p is then x_p[gather[p] / k], x_p being the token-ordered input.
 // `fc` is NULL or the folded combine; y_p (forward) / dx_p (backward) may be NULL only with it.
-int32_t ffn_fwd_generic(const dynmo_desc* d, const void* x_p, const int32_t* gather, const int32_t* seg, const void* Wg,
+// fp32 matrix-core kernels
+int32_t ffn_fwd_f32(const dynmo_desc* d, const void* x_p, const int32_t* gather, const int32_t* seg, const void* Wg,
                         const void* Wu, const void* Wd, void* y_p, void* G, void* U, void* A, const FoldedCombine* fc,
                         hipStream_t st);
-int32_t ffn_bwd_generic(const dynmo_desc* d, const void* dy_p, const void* x_p, const void* G, const void* U,
+int32_t ffn_bwd_f32(const dynmo_desc* d, const void* dy_p, const void* x_p, const void* G, const void* U,
                         const int32_t* seg, const void* Wg, const void* Wu, const void* Wd, void* dx_p, void* dWg,
                         void* dWu, void* dWd, void* dG, void* dU, void* A, const FoldedCombine* fc, hipStream_t st);
 

@@ -41,8 +41,9 @@ static int32_t ffn_fwd_entry(const dynmo_desc* d, const void* rows, const int32_
   if (ffn_mfma_supported(d))
     return ffn_fwd_mfma(d, rows, gather, seg_offsets, Wg, Wu, Wd, y_p, G_save, U_save, A, (char*)A + act_bytes(d),
                         fc, (hipStream_t)stream);
-  if (max_m_tiles(d, 64) > 65535) return DYNMO_EUNSUPPORTED;  // the generic kernels put row tiles on grid y
-  return ffn_fwd_generic(d, rows, gather, seg_offsets, Wg, Wu, Wd, y_p, G_save, U_save, A, fc, (hipStream_t)stream);
+  if (d->dtype != DYNMO_F32) return DYNMO_EUNSUPPORTED;       // more tiles than the bf16 kernels can count (70 TB of G)
+  if (max_m_tiles(d, 64) > 65535) return DYNMO_EUNSUPPORTED;  // the fp32 kernels put row tiles on grid y
+  return ffn_fwd_f32(d, rows, gather, seg_offsets, Wg, Wu, Wd, y_p, G_save, U_save, A, fc, (hipStream_t)stream);
 }
 }  // namespace dynmo
 
@@ -98,8 +99,9 @@ static int32_t ffn_bwd_entry(const dynmo_desc* d, const void* dy_p, const void* 
   if (ffn_mfma_supported(d))
     return ffn_bwd_mfma(d, dy_p, x_p, G_save, U_save, seg_offsets, Wg, Wu, Wd, dx_p, dWg, dWu, dWd, dG, dU, A,
                         base + 3 * act_bytes(d), fc, (hipStream_t)stream);
-  if (max_m_tiles(d, 64) > 65535) return DYNMO_EUNSUPPORTED;  // the generic kernels put row tiles on grid y
-  return ffn_bwd_generic(d, dy_p, x_p, G_save, U_save, seg_offsets, Wg, Wu, Wd, dx_p, dWg, dWu, dWd, dG, dU, A, fc,
+  if (d->dtype != DYNMO_F32) return DYNMO_EUNSUPPORTED;       // more tiles than the bf16 kernels can count (70 TB of G)
+  if (max_m_tiles(d, 64) > 65535) return DYNMO_EUNSUPPORTED;  // the fp32 kernels put row tiles on grid y
+  return ffn_bwd_f32(d, dy_p, x_p, G_save, U_save, seg_offsets, Wg, Wu, Wd, dx_p, dWg, dWu, dWd, dG, dU, A, fc,
                          (hipStream_t)stream);
 }
 }  // namespace dynmo

@@ -1,0 +1,464 @@
+// Grouped SwiGLU FFN in fp32 on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands,
+// fp32 accumulate, no conversion anywhere).
+//
+// One device routine serves the five products of the layer; an operand is described by how
+// it lies in memory: K contiguous ([row][k]: activations and the forward's weights) or rows
+// contiguous ([k][row]: the backward's weights and both operands of a weight gradient).
+//
+// Bound: the fp32 matrix rate is a sixteenth of the bf16 one (one 16x16x4 MFMA occupies its
+// SIMD for 32 cycles and needs one dword per lane and operand), so neither LDS nor L2
+// bandwidth is near its limit even for a 64x64 tile; what costs is latency.  Hence small
+// tiles and several workgroups per compute unit (36 KB of LDS each): 64x64 outputs, four
+// wavefronts of 32x32 (2x2 blocks), k in steps of 32 through two LDS stages, with two
+// further k tiles on their way in registers.  Vector fp32 instructions reach half of the
+// MFMA rate at best.
+//
+// Measured against a 64x64 vector-ALU kernel with one k step of 16 in flight:
+//   T=1500 H=516 F=1030 E=8 k=2   gate/up 275 -> 96 us, down 242 -> 61, dA 151 -> 61, dX 467 -> 105, dW 179 -> 50 each
+//                                 (52 to 66 TFLOP/s; a large dense fp32 product of the vendor's library: 142)
+//   T=256 H=128 F=256 E=4 k=2     gate/up 40 -> 8 us, down 37 -> 11, dA 26 -> 12, dX 74 -> 16, dW 31 -> 6 each
+#include "common.h"
+#include "ffn.h"
+#include "profile.h"
+
+namespace dynmo {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int TM = 64, TN = 64, TK = 32;  // output tile and k step
+constexpr int kThreads = 256;             // 2 x 2 wavefronts of 32 x 32 outputs
+// LDS layouts of an operand tile (64 rows x 32 k).  [row][k]: 36 floats per row, so that the
+// 16-byte reads of sixteen rows fall into sixteen different bank groups (36 s mod 64).
+// [k][row]: 68 floats per k-row, so that k-rows 4 apart -- the four lane groups of a fragment
+// -- are 16 banks apart.
+constexpr int kPitchRowK = TK + 4;
+constexpr int kPitchKRow = TM + 4;
+constexpr int kOperandFloats = TM * kPitchRowK;
+static_assert(kOperandFloats >= TK * kPitchKRow, "either layout fits");
+constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond every record count: the load delivers zero
+
+// Finds row tile `tile` of the expert segments.  Lane e of every wavefront counts the tiles of
+// expert e and a prefix sum and a ballot find the owner: one load latency, however many experts.
+struct RowTile {
+  int e, m0, m_end;
+};
+__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, int E, int tile, RowTile* t) {
+  const int lane = threadIdx.x & 63;
+  const int begin = lane < E ? seg[lane] : 0, end = lane < E ? seg[lane + 1] : 0;
+  const int n = (end - begin + TM - 1) / TM;
+  int upto = n;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(upto, d, 64);
+    if (lane >= d) upto += o;
+  }
+  const unsigned long long owners = __ballot(upto > tile);
+  if (owners == 0) return false;  // past the last tile
+  t->e = __builtin_ctzll(owners);
+  t->m0 = __builtin_amdgcn_readlane(begin, t->e) + (tile - __builtin_amdgcn_readlane(upto - n, t->e)) * TM;
+  t->m_end = __builtin_amdgcn_readlane(end, t->e);
+  return true;
+}
+
+// One operand of a product: 64 rows by k.
+//   KROW = false: element (row, k) at base + row * ld + k, with `rows` valid rows.  With `rowmap`, row r is row
+//     rowmap[r] / rowdiv.  PAIR: LDS rows 0..31 are 32 rows of one matrix and rows 32..63 the same rows of
+//     another one (`base2`): every thread's first chunk then belongs to the one and its second to the other.
+//   KROW = true: element (row, k) at base + k * ld + row.
+// VEC = floats per load: the largest of 4, 2, 1 that divides ld (and so every offset and limit).
+template <bool KROW, int VEC, bool PAIR = false>
+struct Operand {
+  const float *base, *base2;  // (row 0, k 0) of the tile, wave-uniform
+  long ld;
+  uint32_t off[2];    // byte offsets of this thread's two chunks of four floats, from (row 0, k 0 of the k tile)
+  int kpos[2];        // their k inside the k tile
+  int left[2];        // [k][row]: valid floats from there on (<= 0: none); [row][k]: valid row or not
+
+  __device__ __forceinline__ void init(const float* b, long ld_, int rows, const float* b2 = nullptr,
+                                       const int32_t* rowmap = nullptr, int rowdiv = 1) {
+    base = b;
+    base2 = b2;
+    ld = ld_;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = threadIdx.x + i * kThreads;
+      if constexpr (KROW) {
+        kpos[i] = c / (TM / 4);
+        const int row = c % (TM / 4) * 4;
+        off[i] = (uint32_t)(kpos[i] * ld + row) * 4;
+        left[i] = rows - row;
+      } else {
+        kpos[i] = c % (TK / 4) * 4;
+        int row = c / (TK / 4) - (PAIR && i ? TM / 2 : 0);
+        left[i] = row < rows;
+        if (rowmap != nullptr) row = left[i] ? rowmap[row] / rowdiv : 0;
+        off[i] = (uint32_t)(row * ld + kpos[i]) * 4;
+      }
+    }
+  }
+
+  // the two chunks of the k tile that starts at k0 (`k_left` valid k from there on); `shift`: floats to add to the base
+  __device__ __forceinline__ void fetch(f32x4_t (&r)[2], long k0, int k_left, long shift) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float* p = (PAIR && i ? base2 : base) + shift + (KROW ? k0 * ld : k0);
+      __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7ffffffe, 0x00020000);
+      const bool ok = KROW ? kpos[i] < k_left : left[i] != 0;
+      const int n = !ok ? 0 : KROW ? left[i] : k_left - kpos[i];  // valid floats of the chunk
+      if constexpr (VEC == 4) {
+        r[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(d, n > 0 ? off[i] : kOutside, 0, 0));
+      } else if constexpr (VEC == 2) {
+        const u32x2 lo = __builtin_amdgcn_raw_buffer_load_b64(d, n > 0 ? off[i] : kOutside, 0, 0);
+        const u32x2 hi = __builtin_amdgcn_raw_buffer_load_b64(d, n > 2 ? off[i] + 8 : kOutside, 0, 0);
+        r[i] = f32x4_t{__uint_as_float(lo.x), __uint_as_float(lo.y), __uint_as_float(hi.x), __uint_as_float(hi.y)};
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          r[i][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(d, n > j ? off[i] + 4 * j : kOutside, 0, 0));
+      }
+    }
+  }
+
+  __device__ __forceinline__ void put(float* s, const f32x4_t (&r)[2]) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = threadIdx.x + i * kThreads;
+      const int at = KROW ? c / (TM / 4) * kPitchKRow + c % (TM / 4) * 4 : c / (TK / 4) * kPitchRowK + kpos[i];
+      *(f32x4_t*)(s + at) = r[i];
+    }
+  }
+
+  // The fragments of the 16-row block at `row16` for sixteen k from 16 kk on: lane l holds, for row l % 16, the
+  // four k 4 (l / 16) .. + 3; MFMA j of the four that follow takes element j (both operands alike, so together
+  // they cover the sixteen k, in an order that does not matter to the sum's terms).
+  __device__ __forceinline__ static f32x4_t frag(const float* s, int row16, int kk) {
+    const int lane = threadIdx.x & 63, row = row16 + (lane & 15), k = kk * 16 + (lane >> 4) * 4;
+    if constexpr (!KROW) {
+      return *(const f32x4_t*)(s + row * kPitchRowK + k);
+    } else {
+      f32x4_t f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * kPitchKRow + row];
+      return f;
+    }
+  }
+};
+
+// acc[i][j] += sum over k of A(row block i) * B(row block j); the k range is `phases` stretches of K, the second
+// one at (A + a_shift, B + b_shift).  Wavefront (wm, wn): A rows 32 wm + 16 i, B rows b_row[j].
+template <typename OpA, typename OpB>
+__device__ __forceinline__ void mac(f32x4_t (&acc)[2][2], const OpA& a, const OpB& b, int K, int phases, long a_shift,
+                                    long b_shift, int a_row, const int (&b_row)[2], float* lds) {
+  const int per_phase = (K + TK - 1) / TK, n_kt = per_phase * phases;
+  if (n_kt == 0) return;
+  f32x4_t ra[2][2], rb[2][2];  // two k tiles on their way
+  // past the last k tile nothing is fetched (zeros)
+  auto fetch = [&](int kt, int set) {
+    const bool second = kt >= per_phase && phases > 1;
+    const int k0 = (second ? kt - per_phase : kt) * TK;
+    const int k_left = kt < n_kt ? K - k0 : 0;
+    a.fetch(ra[set], k0, k_left, second ? a_shift : 0);
+    b.fetch(rb[set], k0, k_left, second ? b_shift : 0);
+  };
+  auto put = [&](int set, int stage) {
+    a.put(lds + stage * 2 * kOperandFloats, ra[set]);
+    b.put(lds + stage * 2 * kOperandFloats + kOperandFloats, rb[set]);
+  };
+  fetch(0, 0);
+  fetch(1, 1);
+  put(0, 0);
+  fetch(2, 0);
+  __syncthreads();
+  // k tile kt is in LDS stage kt % 2, tiles kt + 1 and kt + 2 are on their way
+  auto step = [&](int kt, int stage) {
+    put(1 - stage, 1 - stage);
+    fetch(kt + 3, 1 - stage);
+    __builtin_amdgcn_sched_barrier(0);  // the loads go out before the MFMAs, not when registers fall free
+    const float* sa = lds + stage * 2 * kOperandFloats;
+    const float* sb = sa + kOperandFloats;
+#pragma unroll
+    for (int kk = 0; kk < TK / 16; ++kk) {
+      f32x4_t fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fa[i] = OpA::frag(sa, a_row + 16 * i, kk);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) fb[j] = OpB::frag(sb, b_row[j], kk);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  };
+  for (int kt = 0; kt + 1 < n_kt; kt += 2) {
+    step(kt, 0);
+    step(kt + 1, 1);
+  }
+  if (n_kt & 1) step(n_kt - 1, 0);
+}
+
+// Position of this wavefront and lane in the output tile: block (i, j) holds rows row + 16 i + r, r = 0..3.
+struct OutPos {
+  int wm, wn, row, col;
+  __device__ __forceinline__ OutPos() {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wm = wave >> 1;
+    wn = wave & 1;
+    row = wm * 32 + (lane >> 4) * 4;
+    col = lane & 15;
+  }
+};
+
+struct F32Params {
+  const int32_t* seg;
+  int E, H, F;
+  const float *x, *dy, *G, *U, *A;  // inputs by name (A, dG, dU: written by one kernel, read by the next)
+  const float *Wg, *Wu, *Wd;
+  float *outG, *outU, *outA;        // GATEUP: G, U, A; DA: dG, dU, A
+  float* C;                         // DOWN: y_p, DX: dx_p (may be nullptr when folded)
+  const float *dG, *dU;
+  float *dWg, *dWu, *dWd;
+  const int32_t* gather;            // GATEUP: row p is x[gather[p] / gather_div], or nullptr
+  int gather_div;
+  FoldedCombine fold;               // scatter == nullptr: nothing folded
+};
+
+__device__ __forceinline__ void store_row_product(const F32Params& p, const f32x4_t (&acc)[2][2], const RowTile& t, int n0,
+                                                  int N) {
+  const OutPos o;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = t.m0 + o.row + 16 * i + r;
+      if (m >= t.m_end) continue;
+      const int token = p.fold.scatter ? p.fold.scatter[m] : 0;
+      const float scale = p.fold.scatter && p.fold.scale ? p.fold.scale[token] : 1.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + o.wn * 32 + 16 * j + o.col;
+        if (n >= N) continue;
+        const float v = acc[i][j][r];
+        if (p.C) p.C[(long)m * N + n] = v;
+        if (p.fold.scatter) {
+          const long at = (long)token * N + n;
+          const float* res = (const float*)p.fold.res;
+          ((float*)p.fold.out)[at] = (res ? res[at] : 0.f) + scale * v;
+        }
+      }
+    }
+}
+
+// G = X Wg^T, U = X Wu^T, A = silu(G) U: 64 rows x 32 columns of each.  LDS rows 0..31 of operand B are gate
+// rows, 32..63 the matching up rows, and a wavefront takes sixteen of either.
+__global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  RowTile t;
+  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * (TN / 2);
+  const long first = ((long)t.e * p.F + n0) * p.H;
+  Operand<false, 4> a;
+  Operand<false, 4, true> b;
+  if (p.gather) a.init(p.x, p.H, t.m_end - t.m0, nullptr, p.gather + t.m0, p.gather_div);
+  else a.init(p.x + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
+  b.init(p.Wg + first, p.H, p.F - n0, p.Wu + first);
+  f32x4_t acc[2][2] = {};
+  const OutPos o;
+  const int b_row[2] = {o.wn * 16, 32 + o.wn * 16};
+  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 32, b_row, lds);
+  const int n = n0 + o.wn * 16 + o.col;
+  if (n >= p.F) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = t.m0 + o.row + 16 * i + r;
+      if (m >= t.m_end) continue;
+      const long at = (long)m * p.F + n;
+      const float g = acc[i][0][r], u = acc[i][1][r];
+      p.outG[at] = g;
+      p.outU[at] = u;
+      p.outA[at] = g * sigmoidf_(g) * u;
+    }
+}
+
+// Y = A Wd^T
+template <int VF>
+__global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  RowTile t;
+  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * TN;
+  Operand<false, VF> a, b;
+  a.init(p.A + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
+  b.init(p.Wd + ((long)t.e * p.H + n0) * p.F, p.F, p.H - n0);
+  f32x4_t acc[2][2] = {};
+  const OutPos o;
+  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
+  mac(acc, a, b, p.F, 1, 0, 0, o.wm * 32, b_row, lds);
+  store_row_product(p, acc, t, n0, p.H);
+}
+
+// dA = dY Wd; with the saved G, U: A, dG, dU
+template <int VF>
+__global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  RowTile t;
+  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * TN;
+  Operand<false, 4> a;
+  Operand<true, VF> b;
+  a.init(p.dy + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
+  b.init(p.Wd + (long)t.e * p.H * p.F + n0, p.F, p.F - n0);
+  f32x4_t acc[2][2] = {};
+  const OutPos o;
+  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
+  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 32, b_row, lds);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = t.m0 + o.row + 16 * i + r;
+      if (m >= t.m_end) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + b_row[j] + o.col;
+        if (n >= p.F) continue;
+        const long at = (long)m * p.F + n;
+        swiglu_bwd(acc[i][j][r], p.G[at], p.U[at], p.outA + at, p.outG + at, p.outU + at);
+      }
+    }
+}
+
+// dX = dG Wg + dU Wu
+template <int VF>
+__global__ __launch_bounds__(kThreads) void f32_dX_kernel(const F32Params p) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  RowTile t;
+  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * TN;
+  Operand<false, VF> a;
+  Operand<true, 4> b;
+  a.init(p.dG + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
+  b.init(p.Wg + (long)t.e * p.F * p.H + n0, p.H, p.H - n0);
+  f32x4_t acc[2][2] = {};
+  const OutPos o;
+  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
+  mac(acc, a, b, p.F, 2, p.dU - p.dG, p.Wu - p.Wg, o.wm * 32, b_row, lds);
+  store_row_product(p, acc, t, n0, p.H);
+}
+
+// dW[m, n] = sum over the rows of an expert of P[row, m] Q[row, n]   (zeros if it has none)
+template <int VM, int VN>
+__device__ __forceinline__ void weight_grad(const float* P, int M, const float* Q, int N, float* dW, int k_begin, int k_end,
+                                            int m0, int n0, float* lds) {
+  Operand<true, VM> a;
+  Operand<true, VN> b;
+  a.init(P + (long)k_begin * M + m0, M, M - m0);
+  b.init(Q + (long)k_begin * N + n0, N, N - n0);
+  f32x4_t acc[2][2] = {};
+  const OutPos o;
+  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
+  mac(acc, a, b, k_end - k_begin, 1, 0, 0, o.wm * 32, b_row, lds);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + o.row + 16 * i + r;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = n0 + b_row[j] + o.col;
+        if (m < M && n < N) dW[(long)m * N + n] = acc[i][j][r];
+      }
+    }
+}
+
+// WHICH: 0 = dWd (P = dY, Q = A), 1 = dWg (dG, x_p), 2 = dWu (dU, x_p)
+template <int VF, int WHICH>
+__global__ __launch_bounds__(kThreads) void f32_dW_kernel(const F32Params p) {
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  const int e = blockIdx.z, m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+  const int k_begin = p.seg[e], k_end = p.seg[e + 1];
+  const long FH = (long)p.F * p.H * e;
+  if constexpr (WHICH == 0) weight_grad<4, VF>(p.dy, p.H, p.A, p.F, p.dWd + FH, k_begin, k_end, m0, n0, lds);
+  else weight_grad<VF, 4>(WHICH == 1 ? p.dG : p.dU, p.F, p.x, p.H, (WHICH == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
+}
+
+template <int VF>
+static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const unsigned m_tiles = max_m_tiles(d, TM);
+  if (m_tiles == 0) return DYNMO_OK;
+  DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st, f32_gateup_kernel<<<dim3((d->F + TN / 2 - 1) / (TN / 2), m_tiles), dim3(kThreads), 0, st>>>(p));
+  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<VF><<<dim3((d->H + TN - 1) / TN, m_tiles), dim3(kThreads), 0, st>>>(p));
+  return DYNMO_OK;
+}
+
+template <int VF>
+static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const unsigned m_tiles = max_m_tiles(d, TM), tf = (d->F + TN - 1) / TN, th = (d->H + TN - 1) / TN;
+  if (m_tiles > 0) {
+    DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
+    DYNMO_TIMED_LAUNCH(K_FFN_DX, st, f32_dX_kernel<VF><<<dim3(th, m_tiles), dim3(kThreads), 0, st>>>(p));
+  }
+  // the weight gradients are written for every expert, rows or not
+  DYNMO_TIMED_LAUNCH(K_FFN_DWD, st, f32_dW_kernel<VF, 0><<<dim3(tf, th, d->E), dim3(kThreads), 0, st>>>(p));
+  DYNMO_TIMED_LAUNCH(K_FFN_DWG, st, f32_dW_kernel<VF, 1><<<dim3(th, tf, d->E), dim3(kThreads), 0, st>>>(p));
+  DYNMO_TIMED_LAUNCH(K_FFN_DWU, st, f32_dW_kernel<VF, 2><<<dim3(th, tf, d->E), dim3(kThreads), 0, st>>>(p));
+  return DYNMO_OK;
+}
+
+static F32Params params_of(const dynmo_desc* d, const int32_t* seg, const void* Wg, const void* Wu, const void* Wd,
+                           const FoldedCombine* fc) {
+  F32Params p = {};
+  p.seg = seg;
+  p.E = d->E;
+  p.H = d->H;
+  p.F = d->F;
+  p.Wg = (const float*)Wg;
+  p.Wu = (const float*)Wu;
+  p.Wd = (const float*)Wd;
+  if (fc) p.fold = *fc;
+  return p;
+}
+
+int32_t ffn_fwd_f32(const dynmo_desc* d, const void* x_p, const int32_t* gather, const int32_t* seg, const void* Wg,
+                    const void* Wu, const void* Wd, void* y_p, void* G, void* U, void* A, const FoldedCombine* fc,
+                    hipStream_t st) {
+  F32Params p = params_of(d, seg, Wg, Wu, Wd, fc);
+  p.x = (const float*)x_p;
+  p.gather = gather;
+  p.gather_div = d->k;
+  p.outG = (float*)G;
+  p.outU = (float*)U;
+  p.outA = (float*)A;
+  p.A = (const float*)A;
+  p.C = (float*)y_p;
+  // rows of length F can be loaded four, two or one float at a time, whichever divides F; H is a multiple of four
+  return d->F % 4 == 0 ? fwd_f32<4>(d, p, st) : d->F % 2 == 0 ? fwd_f32<2>(d, p, st) : fwd_f32<1>(d, p, st);
+}
+
+int32_t ffn_bwd_f32(const dynmo_desc* d, const void* dy_p, const void* x_p, const void* G, const void* U,
+                    const int32_t* seg, const void* Wg, const void* Wu, const void* Wd, void* dx_p, void* dWg, void* dWu,
+                    void* dWd, void* dG, void* dU, void* A, const FoldedCombine* fc, hipStream_t st) {
+  F32Params p = params_of(d, seg, Wg, Wu, Wd, fc);
+  p.x = (const float*)x_p;
+  p.dy = (const float*)dy_p;
+  p.G = (const float*)G;
+  p.U = (const float*)U;
+  p.outG = (float*)dG;
+  p.outU = (float*)dU;
+  p.outA = (float*)A;
+  p.A = (const float*)A;
+  p.dG = (const float*)dG;
+  p.dU = (const float*)dU;
+  p.C = (float*)dx_p;
+  p.dWg = (float*)dWg;
+  p.dWu = (float*)dWu;
+  p.dWd = (float*)dWd;
+  return d->F % 4 == 0 ? bwd_f32<4>(d, p, st) : d->F % 2 == 0 ? bwd_f32<2>(d, p, st) : bwd_f32<1>(d, p, st);
+}
+
+}  // namespace dynmo

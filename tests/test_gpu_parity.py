@@ -226,6 +226,21 @@ def test_moe_layer_small(w):
     say("  errs " + " ".join("%s=%.1e" % kv for kv in errs.items()))
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [(1, 4, 1, 1, 1), (65, 68, 33, 3, 2), (64, 32, 64, 1, 1), (130, 100, 127, 5, 3),
+                                       (200, 260, 130, 4, 2), (63, 64, 31, 64, 8)])
+def test_f32_layer_tile_edges(T, H, F, E, k):
+    """The fp32 kernels at the edges of their 64 x 64 tiles and k steps of 32: F divisible by four, two and
+    neither (vector loads of four, two and one float), one row, one k tile more or less, experts without rows."""
+    say("f32 tile edges T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
+    w = wl.scaled(wl.CONFIGS[1], T=T, H=H, F=F, E=E, k=k, bias=(), zipf_s=1.1, seed=8700 + T)
+    inp = wl.make_inputs(w, threads=1)
+    layer = run_moe(w, inp)
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    assert np.array_equal(to_host(layer.expert_idx), ref["expert_idx"])
+    check_layer_full(layer, ref, w.dtype)
+
+
 def test_moe_layer_empty_expert_zero_dw():
     say("moe empty expert")
     w = wl.scaled(wl.CONFIGS[2], T=200, H=64, F=96, E=4, k=2, seed=21)
@@ -532,7 +547,7 @@ def test_peak_reference_kernels():
 
 
 GATHER_CASES = [
-    ("moe", wl.CONFIGS[1]),                                                       # fp32, the generic kernels
+    ("moe", wl.CONFIGS[1]),                                                       # fp32
     ("moe", wl.scaled(wl.CONFIGS[2], T=700, H=256, F=448, seed=61)),              # bf16 MFMA, several tiles + tail
     ("moe", wl.scaled(wl.CONFIGS[3], T=640, H=128, F=88, seed=62)),               # k = 4: four slots share a token row
     ("mod", wl.scaled(wl.CONFIGS[4], T=4 * 256, B=4, S=256, cap=32, H=128, F=256, seed=63)),  # most tokens unrouted
