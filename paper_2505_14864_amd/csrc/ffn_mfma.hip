@@ -33,19 +33,9 @@
 // last round of a row-segmented product would fill at most half of the chip, its tiles
 // are split along k over several XCDs and a small second kernel adds the fp32 partial
 // tiles in a fixed order (ffn_split_reduce_kernel).
-#include <type_traits>
-#include <utility>
-
-#include "common.h"
-#include "ffn.h"
-#include "profile.h"
+#include "ffn_gemm.h"
 
 namespace dynmo {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-typedef __attribute__((ext_vector_type(8))) short s16x8_t;
 
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int kMfmaThreads = 512;              // eight wavefronts: two per SIMD
@@ -74,40 +64,6 @@ static_assert(2 * kStageBytes <= kLdsBytes, "the two stages must fit in front of
 static_assert(kLdsTotal <= 160 * 1024, "LDS of one compute unit");
 static_assert(kPieces * kWaves == 32, "a tile is 32 pieces of 1 KB");
 
-// MODE_DOWN_FOLD is MODE_DOWN with the weighted combine of a one-slot layer in its stores;
-// MODE_DX_FOLD is MODE_DX with the scatter back to token order (weight 1) in its stores
-enum { MODE_GATEUP = 0, MODE_DOWN = 1, MODE_DA = 2, MODE_DX = 3, MODE_DW = 4, MODE_DOWN_FOLD = 5, MODE_DX_FOLD = 6 };
-
-struct GemmParams {
-  const int32_t* seg;
-  int E;
-  int M;  // rows of the output (MODE_DW only; the other modes take rows from seg)
-  int N;  // columns of the output (for GATEUP: F, and a tile spans 128 of them twice)
-  int K;  // contraction length per phase (MODE_DW: taken from seg)
-  const bf16_t* A1;
-  const bf16_t* A2;
-  long lda;
-  const bf16_t* B1;
-  const bf16_t* B2;
-  long ldb;
-  long b_expert_stride;
-  bf16_t* C0;
-  bf16_t* C1;
-  bf16_t* C2;
-  long ldc;
-  const bf16_t* G;
-  const bf16_t* U;
-  float* partial;     // kMaxPersistent fp32 partial tiles, then kSplitHdrInts ints (modes that may split k)
-  const int32_t* gather;  // MODE_GATEUP: row p of operand A is row gather[p] / gather_div of A1, or nullptr
-  int gather_div;
-  // MODE_DOWN_FOLD / MODE_DX_FOLD (k = 1): row p also goes to row t = scatter[p] of out as
-  // res[t] + scale[t] * value (res nullptr = 0; res may be out; scale nullptr = 1); C0 may then be nullptr
-  const int32_t* scatter;
-  const float* scale;
-  const bf16_t* res;
-  bf16_t* out;
-};
-
 // ---- global memory -> LDS ---------------------------------------------------------
 // An operand tile is 256 "rows" x 64 k = 32 pieces of 1 KB.  One buffer load with an
 // LDS destination moves a piece: lane l fetches 16 bytes from its own global offset and
@@ -123,33 +79,6 @@ struct GemmParams {
 //   [k][row]: 512 bytes per k-row in eight 64-byte blocks of 32 rows; block b of k-row k
 //             sits at k * 512 + (((b & 4) | ((b ^ k) & 3)) << 6), and its two 32-byte halves
 //             (16 rows each) are swapped when bit 3 of k is set
-constexpr uint32_t kOob = 0x80000000u;
-
-// raw buffer descriptor (wave-uniform): base address, stride 0, record count in bytes
-typedef uint32_t desc_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ desc_t make_desc(const bf16_t* p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  desc_t d;
-  d.x = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  d.y = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-  d.z = __builtin_amdgcn_readfirstlane(bytes);
-  d.w = 0x00020000u;
-  return d;
-}
-
-// One piece: global -> LDS.  Written as assembly so that the compiler sees neither a
-// load (it would count it against its own waits) nor an LDS write (it would make every
-// transposed LDS read wait for all outstanding loads); the k loop waits for these loads
-// itself, once per k tile.  The memory clobber keeps LDS reads from moving across it.
-// The LDS destination is `lds_base` (wave-uniform, in a scalar register) + LDS_CONST.
-template <int LDS_CONST>
-__device__ __forceinline__ void load_to_lds(desc_t d, uint32_t lds_base, uint32_t global_offset) {
-  asm volatile("s_add_i32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(lds_base), "v"(global_offset), "s"(d), "n"(LDS_CONST)
-               : "memory", "scc");
-}
-
 // A prefetch into L2: four bytes per lane (one lane per 128-byte line) through the same path
 // as the real loads, so that it retires in order with them; the data is dropped in LDS.
 __device__ __forceinline__ void touch_to_lds(desc_t d, uint32_t lds_offset, uint32_t global_offset) {
@@ -479,30 +408,6 @@ __device__ __forceinline__ Tile decode_tile(const int* table, const TileTable& t
   t.k_begin = begin;  // MODE_DW contracts over the expert's rows
   t.k_end = end;
   return t;
-}
-
-template <int... Is, typename F>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), fully unrolled
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// The logistic function for results that are rounded to bf16: the hardware reciprocal (1 ulp) instead of a
-// correctly rounded division, which is ten instructions per element in epilogues that are bound by their
-// vector arithmetic.
-__device__ __forceinline__ float sigmoid_bf16(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-__device__ __forceinline__ float silu_mul(float g, float u) { return g * sigmoid_bf16(g) * u; }
-// swiglu_bwd() of ffn.h with that reciprocal
-__device__ __forceinline__ void swiglu_bwd_bf16(float dA, float g, float u, float* a, float* dg, float* du) {
-  const float s = sigmoid_bf16(g);
-  const float gs = g * s;
-  *a = gs * u;
-  *dg = dA * u * (s * (1.f + g * (1.f - s)));
-  *du = dA * gs;
 }
 
 // WHOLE_K: the contraction length is a multiple of the k tile, so the [row][k] operands need no
@@ -1263,6 +1168,51 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
   return launch_mfma_as<MODE, false>(p, max_tiles, id, st);
 }
 
+// Which kernel takes a product: 256 = this file's, 128 or 64 = ffn_tile.hip with that tile.  The host knows
+// rows, experts and sizes, not the segments: an expert is counted with half a row tile for its ragged end.
+//   * While the 256 x 256 tiles of a product fill about half of the chip or less, smaller tiles win, by more
+//     the fewer they are.  Measured (us, 256 / 128 / 64; rows x H x F, experts):
+//       gate/up  512 x 512 x 1024, 1:  22 / 13 /  9     2048 x 512 x 1024, 1: 23 / 15 / 17
+//                2048 x 1024 x 2048, 1 (128 tiles): 33 / 31 / 42     2048 x 1024 x 2048, 8 (192): 37 / 39 / 45
+//       dA       2048 x 2048 x 4096, 1 (128 tiles): 70 / 49 / 72     6144 x 2048 x 4096, 1 (384): 143 / 144 / 212
+//       down     2048 x 1024 x 2048, 1: 45 / 26 / 24     6144 x 2048 x 4096, 1 (192 tiles): 97 / 131 / 214
+//     64-wide tiles where 128-wide ones would still leave half of the compute units without work.
+//   * down and dX with more than 4096 of k stay here, where k can be split (2048 x 2048 x 4096, 8 experts, dX:
+//     151 / 190 / 202 us).
+//   * The three weight gradients go in one launch there, and the 256 x 256 kernel's epilogue has nothing to hide
+//     behind when an expert has few rows, so the line lies higher, and higher the more experts there are, whose
+//     uneven rows leave its fixed tile lists uneven (us for all three, 256 / 128 / 64): 1 expert, 6144 x 2048 x 4096,
+//     128 tiles: 403 / 320 / 586, 8192 x 3072 x 3072, 144: 561 / 682; 2, 8192 x 2048 x 4096, 256: 414 / 422; 4,
+//     4096 x 2048 x 4096, 512: 227 / 242; 16, 16384 x 2048 x 1024, 512: 327 / 255; 8, 2048 x 2048 x 4096, 1024:
+//     179 / 218 / 285; 1, 6144 x 512 x 1024, 8: 337 / 173 / 106.
+//   * dA cannot split k: a second round of its tiles that is nearly empty is worth avoiding (8192 x 2048 x 2048, 8,
+//     288 tiles: 136 / 116).
+static int tile_for(const dynmo_desc* d, int mode, int N, int K) {
+  const double rows = (double)d->T * d->k;
+  const double ragged = d->E > 1 ? 0.5 * (d->E < rows ? d->E : rows) : 0.0;
+  auto cols = [](int n, int tile) { return (double)((n + tile - 1) / tile); };
+  if (mode == MODE_DW) {
+    if (d->E * cols(d->H, BM) * cols(d->F, BM) > (d->E == 1 ? 128 : d->E < 5 ? 100 * d->E : 512)) return BM;
+    return 3 * d->E * cols(d->H, 128) * cols(d->F, 128) > 512 ? 128 : 64;
+  }
+  if (mode == MODE_GATEUP) N *= 2;
+  const double tiles = (rows / BM + ragged) * cols(N, BM);
+  const bool down_or_dx = mode != MODE_GATEUP && mode != MODE_DA;
+  const bool is_dx = mode == MODE_DX || mode == MODE_DX_FOLD;
+  if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return BM;
+  const bool short_second_round = mode == MODE_DA && tiles > 256 && tiles <= 300;
+  if (tiles > (mode == MODE_DA ? 180 : 140) && !short_second_round) return BM;
+  return (rows / 128 + ragged) * cols(N, 128) > 128 ? 128 : 64;
+}
+
+template <int MODE>
+static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st) {
+  const int tile = tile_for(d, MODE, p.N, p.K);
+  if (tile != BM) return ffn_tile_rows(MODE, tile, p, max_m_tiles(d, tile), id, st);
+  constexpr int tile_n = MODE == MODE_GATEUP ? BN / 2 : BN;
+  return launch_mfma<MODE>(p, max_m_tiles(d, BM) * ((p.N + tile_n - 1) / tile_n), id, st);
+}
+
 bool ffn_mfma_supported(const dynmo_desc* d) {
   return d->dtype == DYNMO_BF16 && d->H % 8 == 0 && d->F % 8 == 0 &&
          (int64_t)max_m_tiles(d, BM) * ((d->F + 127) / 128) < (1 << 30);
@@ -1271,7 +1221,6 @@ bool ffn_mfma_supported(const dynmo_desc* d) {
 int32_t ffn_fwd_mfma(const dynmo_desc* d, const void* x_p, const int32_t* gather, const int32_t* seg, const void* Wg,
                      const void* Wu, const void* Wd, void* y_p, void* G, void* U, void* A, void* scratch,
                      const FoldedCombine* fc, hipStream_t st) {
-  const int mt = max_m_tiles(d, BM);
   const long FH = (long)d->F * d->H;
   GemmParams p = {};
   p.seg = seg;
@@ -1291,7 +1240,7 @@ int32_t ffn_fwd_mfma(const dynmo_desc* d, const void* x_p, const int32_t* gather
   p.C1 = (bf16_t*)U;
   p.C2 = (bf16_t*)A;
   p.ldc = d->F;
-  int32_t rc = launch_mfma<MODE_GATEUP>(p, mt * ((d->F + 127) / 128), K_FFN_GATEUP, st);
+  int32_t rc = launch_rows_product<MODE_GATEUP>(d, p, K_FFN_GATEUP, st);
   if (rc) return rc;
   // Y = A Wd^T
   GemmParams q = {};
@@ -1312,18 +1261,16 @@ int32_t ffn_fwd_mfma(const dynmo_desc* d, const void* x_p, const int32_t* gather
     q.scale = fc->scale;
     q.res = (const bf16_t*)fc->res;
     q.out = (bf16_t*)fc->out;
-    return launch_mfma<MODE_DOWN_FOLD>(q, mt * ((d->H + BN - 1) / BN), K_FFN_DOWN, st);
+    return launch_rows_product<MODE_DOWN_FOLD>(d, q, K_FFN_DOWN, st);
   }
-  return launch_mfma<MODE_DOWN>(q, mt * ((d->H + BN - 1) / BN), K_FFN_DOWN, st);
+  return launch_rows_product<MODE_DOWN>(d, q, K_FFN_DOWN, st);
 }
 
 int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, const void* G, const void* U,
                      const int32_t* seg, const void* Wg, const void* Wu, const void* Wd, void* dx_p, void* dWg,
                      void* dWu, void* dWd, void* dG, void* dU, void* A, void* scratch, const FoldedCombine* fc,
                      hipStream_t st) {
-  const int mt = max_m_tiles(d, BM);
   const long FH = (long)d->F * d->H;
-  const int tH = (d->H + BN - 1) / BN, tF = (d->F + BN - 1) / BN;
   int32_t rc;
   {  // dA = dY Wd, epilogue -> A, dG, dU
     GemmParams p = {};
@@ -1342,7 +1289,7 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
     p.ldc = d->F;
     p.G = (const bf16_t*)G;
     p.U = (const bf16_t*)U;
-    if ((rc = launch_mfma<MODE_DA>(p, mt * tF, K_FFN_DA, st))) return rc;
+    if ((rc = launch_rows_product<MODE_DA>(d, p, K_FFN_DA, st))) return rc;
   }
   // weight gradients: contraction over the rows of each expert
   auto dw = [&](const void* P, int M, const void* Q, int N, void* out, KernelId id) -> int32_t {
@@ -1361,9 +1308,16 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
   };
   // Order: the three weight gradients first, dX last, so that the pass that follows the
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.
-  if ((rc = dw(dy_p, d->H, A, d->F, dWd, K_FFN_DWD))) return rc;
-  if ((rc = dw(dG, d->F, x_p, d->H, dWg, K_FFN_DWG))) return rc;
-  if ((rc = dw(dU, d->F, x_p, d->H, dWu, K_FFN_DWU))) return rc;
+  const int dw_tile = tile_for(d, MODE_DW, 0, 0);
+  if (dw_tile != BM) {
+    rc = ffn_tile_dw(dw_tile, seg, d->E, d->H, d->F, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
+                     (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);
+    if (rc) return rc;
+  } else {
+    if ((rc = dw(dy_p, d->H, A, d->F, dWd, K_FFN_DWD))) return rc;
+    if ((rc = dw(dG, d->F, x_p, d->H, dWg, K_FFN_DWG))) return rc;
+    if ((rc = dw(dU, d->F, x_p, d->H, dWu, K_FFN_DWU))) return rc;
+  }
   {  // dX = dG Wg + dU Wu
     GemmParams p = {};
     p.partial = (float*)scratch;
@@ -1385,9 +1339,9 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
       p.scale = fc->scale;
       p.res = (const bf16_t*)fc->res;
       p.out = (bf16_t*)fc->out;
-      return launch_mfma<MODE_DX_FOLD>(p, mt * tH, K_FFN_DX, st);
+      return launch_rows_product<MODE_DX_FOLD>(d, p, K_FFN_DX, st);
     }
-    return launch_mfma<MODE_DX>(p, mt * tH, K_FFN_DX, st);
+    return launch_rows_product<MODE_DX>(d, p, K_FFN_DX, st);
   }
 }
 

@@ -759,6 +759,45 @@ def test_tile_order_mixed_row_tile_counts(counts):
     check_layer_full(layer, ref, w.dtype)
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [(600, 520, 1032, 8, 2), (1100, 264, 4104, 3, 1), (129, 72, 2056, 1, 1), (900, 1032, 200, 33, 4),
+                                       (64, 2056, 136, 2, 1)])
+def test_small_products_tile_edges(T, H, F, E, k):
+    """Products that go to the 128 and 64 tiles (and, beside them, down and dX of a long k that do not): k not a
+    multiple of the k step, one row or column block past a tile, experts without rows; rows gathered inside the
+    first product give the same bits."""
+    say("small products T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=k, zipf_s=1.5, seed=8800 + T)
+    inp = wl.make_inputs(w, threads=2)
+    layer = run_moe(w, inp)
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(layer, ref, w.dtype)
+    out = layer.out.clone()
+    dev = {n: to_device(a) for n, a in inp.items()}
+    layer.out.zero_()
+    layer.forward_gather(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+    assert torch.equal(layer.out, out)
+
+
+def test_large_tiles_every_row_block_count():
+    """Sixteen experts whose last 256-row tile holds 1 .. 16 blocks of sixteen rows, in a layer large enough for
+    the 256 x 256 tiles in all of its products; full check against the oracle."""
+    say("large tiles, every row block count")
+    counts = [256 + 16 * i + 1 + 7 * i % 16 for i in range(16)]
+    T, E = sum(counts), len(counts)
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=1280, F=2048, E=E, k=1, seed=8900)
+    inp = wl.make_inputs(w, threads=4)
+    rng = np.random.default_rng(w.seed)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[np.arange(T), rng.permutation(np.repeat(np.arange(E), counts))] += 20.0
+    inp["logits"] = logits
+    layer = run_moe(w, inp)
+    assert to_host(layer.seg_offsets).tolist() == np.concatenate([[0], np.cumsum(counts)]).tolist()
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(layer, ref, w.dtype)
+
+
 def test_layer_load_in_two_halves():
     """dynmo_layer_load_begin / _end (copy enqueued behind the permutation, read after an event) give the
     counts and the load of the synchronising dynmo_layer_load, also with more work queued behind the copy."""
