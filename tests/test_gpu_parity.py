@@ -779,6 +779,32 @@ def test_small_products_tile_edges(T, H, F, E, k):
     assert torch.equal(layer.out, out)
 
 
+@pytest.mark.parametrize("counts,H,F", [((1,), 72, 136), ((16,), 200, 520), ((1, 0, 17, 3), 264, 2056), ((40, 0, 2, 1, 3, 5, 2, 65), 520, 4104),
+                                        ((8, 8), 2048, 4096)])
+def test_few_rows_per_expert(counts, H, F):
+    """Forward products of experts with few rows (weights straight into the matrix operands, k dealt to the
+    wavefronts): one to four row blocks and a second pass over them, experts without rows, k and weight rows that
+    fill no wavefront's share; with the rows gathered, and with the combine folded into the last product."""
+    say("few rows per expert counts=%s H=%d F=%d" % (counts, H, F))
+    T, E = sum(counts), len(counts)
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=1, seed=9000 + T)
+    inp = wl.make_inputs(w, threads=2)
+    rng = np.random.default_rng(w.seed)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[np.arange(T), rng.permutation(np.repeat(np.arange(E), counts))] += 20.0
+    inp["logits"] = logits
+    layer = run_moe(w, inp)
+    assert to_host(layer.seg_offsets).tolist() == np.concatenate([[0], np.cumsum(counts)]).tolist()
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(layer, ref, w.dtype)
+    dev = {n: to_device(a) for n, a in inp.items()}
+    for forward in (layer.forward_gather, layer.forward_folded):
+        layer.out.zero_()
+        forward(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+        assert_close("out", to_host(layer.out), ref["out"], TOL["bf16"])
+
+
 def test_large_tiles_every_row_block_count():
     """Sixteen experts whose last 256-row tile holds 1 .. 16 blocks of sixteen rows, in a layer large enough for
     the 256 x 256 tiles in all of its products; full check against the oracle."""
