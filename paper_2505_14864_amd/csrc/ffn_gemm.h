@@ -101,11 +101,11 @@ __device__ __forceinline__ void swiglu_bwd_bf16(float dA, float g, float u, floa
   *du = dA * gs;
 }
 
-// ffn_tile.hip, tile = 128 or 64: a row-segmented product (any mode but MODE_DW) over at most
-// `max_row_tiles` row tiles of that height, and the three weight gradients
-int32_t ffn_tile_rows(int mode, int tile, const GemmParams& p, int max_row_tiles, KernelId id, hipStream_t st);
-int32_t ffn_tile_dw(int tile, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p, const bf16_t* A,
-                    const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
+// ffn_tile.hip: a row-segmented product (any mode but MODE_DW), and the three weight gradients
+enum TileKind { TILE_256, TILE_128x256, TILE_128, TILE_64 };  // TILE_256: ffn_mfma.hip
+int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st);
+int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
+                    const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
 
 // ffn_skinny.hip: MODE_GATEUP, MODE_DOWN or MODE_DOWN_FOLD with few rows per expert; at most `max_experts` experts have rows
 int32_t ffn_skinny_rows(int mode, const GemmParams& p, int max_experts, KernelId id, hipStream_t st);

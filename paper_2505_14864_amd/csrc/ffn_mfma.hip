@@ -1168,8 +1168,8 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
   return launch_mfma_as<MODE, false>(p, max_tiles, id, st);
 }
 
-// Which kernel takes a product: 256 = this file's, 128 or 64 = ffn_tile.hip with that tile.  The host knows
-// rows, experts and sizes, not the segments: an expert is counted with half a row tile for its ragged end.
+// Which kernel takes a product: this file's, or ffn_tile.hip with the given tile.  The host knows rows, experts and
+// sizes, not the segments: an expert is counted with half a row tile for its ragged end.
 //   * While the 256 x 256 tiles of a product fill about half of the chip or less, smaller tiles win, by more
 //     the fewer they are.  Measured (us, 256 / 128 / 64; rows x H x F, experts):
 //       gate/up  512 x 512 x 1024, 1:  22 / 13 /  9     2048 x 512 x 1024, 1: 23 / 15 / 17
@@ -1179,30 +1179,35 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //     64-wide tiles where 128-wide ones would still leave half of the compute units without work.
 //   * down and dX with more than 4096 of k stay here, where k can be split (2048 x 2048 x 4096, 8 experts, dX:
 //     151 / 190 / 202 us).
+//   * dA cannot split k: where several experts' tiles come out a little above one or two rounds of the chip,
+//     128 x 256 tiles avoid the nearly empty last round (256 / 128 x 256: 6000 x 2048 x 4096, 16 experts, 503 tiles:
+//     191 / 167; 4096 x 2048 x 8192, 4, 576: 206 / 188; 4096 x 1536 x 4096, 3, 280: 112 / 97; but 16384 x 1024 x 2048,
+//     8, 544: 145 / 146, and 32768 x 4096 x 688, 16, 408: 284 / 295).
 //   * The three weight gradients go in one launch there, and the 256 x 256 kernel's epilogue has nothing to hide
-//     behind when an expert has few rows, so the line lies higher, and higher the more experts there are, whose
-//     uneven rows leave its fixed tile lists uneven (us for all three, 256 / 128 / 64): 1 expert, 6144 x 2048 x 4096,
-//     128 tiles: 403 / 320 / 586, 8192 x 3072 x 3072, 144: 561 / 682; 2, 8192 x 2048 x 4096, 256: 414 / 422; 4,
-//     4096 x 2048 x 4096, 512: 227 / 242; 16, 16384 x 2048 x 1024, 512: 327 / 255; 8, 2048 x 2048 x 4096, 1024:
-//     179 / 218 / 285; 1, 6144 x 512 x 1024, 8: 337 / 173 / 106.
-//   * dA cannot split k: a second round of its tiles that is nearly empty is worth avoiding (8192 x 2048 x 2048, 8,
-//     288 tiles: 136 / 116).
-static int tile_for(const dynmo_desc* d, int mode, int N, int K) {
+//     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts (us for all three, 256 /
+//     128 x 256): 16 experts, 32768 x 4096 x 688, 768 tiles: 669 / 604; 64, 16384 x 2048 x 1024, 2048: 404 / 384; 8,
+//     8192 x 2048 x 4096, 1024: 441 / 406.  Not for long sums that fill the chip (4, 16384 x 4096 x 4096, 1024 tiles:
+//     1245 / 1339), many tiles (8, 8192 x 4096 x 14336, 7168 tiles: 2634 / 2773) or a single expert, whose tiles
+//     all take the same time (8192 x 2048 x 8192, 256: 603 / 679); there smaller tiles pay up to 128 tiles (256 / 128 / 64;
+//     6144 x 2048 x 4096, 128: 403 / 320 / 586; 8192 x 3072 x 3072, 144: 561 / 682; 6144 x 512 x 1024, 8: 337 / 173 / 106).
+static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
   const double rows = (double)d->T * d->k;
   const double ragged = d->E > 1 ? 0.5 * (d->E < rows ? d->E : rows) : 0.0;
   auto cols = [](int n, int tile) { return (double)((n + tile - 1) / tile); };
   if (mode == MODE_DW) {
-    if (d->E * cols(d->H, BM) * cols(d->F, BM) > (d->E == 1 ? 128 : d->E < 5 ? 100 * d->E : 512)) return BM;
-    return 3 * d->E * cols(d->H, 128) * cols(d->F, 128) > 512 ? 128 : 64;
+    const double tiles = d->E * cols(d->H, BM) * cols(d->F, BM);
+    if (tiles > (d->E == 1 ? 128 : 2048) || (tiles > 512 && rows > 2560.0 * d->E)) return TILE_256;
+    if (tiles >= 256) return TILE_128x256;
+    return 3 * d->E * cols(d->H, 128) * cols(d->F, 128) > 512 ? TILE_128 : TILE_64;
   }
   if (mode == MODE_GATEUP) N *= 2;
   const double tiles = (rows / BM + ragged) * cols(N, BM);
   const bool down_or_dx = mode != MODE_GATEUP && mode != MODE_DA;
   const bool is_dx = mode == MODE_DX || mode == MODE_DX_FOLD;
-  if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return BM;
-  const bool short_second_round = mode == MODE_DA && tiles > 256 && tiles <= 300;
-  if (tiles > (mode == MODE_DA ? 180 : 140) && !short_second_round) return BM;
-  return (rows / 128 + ragged) * cols(N, 128) > 128 ? 128 : 64;
+  if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return TILE_256;
+  if (mode == MODE_DA && d->E > 1 && ((tiles > 220 && tiles <= 320) || (tiles > 480 && tiles <= 600))) return TILE_128x256;
+  if (tiles > (mode == MODE_DA ? 150 : 140)) return TILE_256;
+  return (rows / 128 + ragged) * cols(N, 128) > 128 ? TILE_128 : TILE_64;
 }
 
 // Whether ffn_skinny.hip takes a forward product: on average at most 16 rows (down: 8) per expert in use, and either
@@ -1228,8 +1233,8 @@ static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, Ker
   if constexpr (MODE == MODE_GATEUP || MODE == MODE_DOWN || MODE == MODE_DOWN_FOLD) {
     if (skinny_for(d, MODE, p.N, p.K)) return ffn_skinny_rows(MODE, p, (int)(d->E < (int64_t)d->T * d->k ? d->E : d->T * d->k), id, st);
   }
-  const int tile = tile_for(d, MODE, p.N, p.K);
-  if (tile != BM) return ffn_tile_rows(MODE, tile, p, max_m_tiles(d, tile), id, st);
+  const TileKind kind = tile_for(d, MODE, p.N, p.K);
+  if (kind != TILE_256) return ffn_tile_rows(MODE, kind, d, p, id, st);
   constexpr int tile_n = MODE == MODE_GATEUP ? BN / 2 : BN;
   return launch_mfma<MODE>(p, max_m_tiles(d, BM) * ((p.N + tile_n - 1) / tile_n), id, st);
 }
@@ -1329,9 +1334,9 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
   };
   // Order: the three weight gradients first, dX last, so that the pass that follows the
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.
-  const int dw_tile = tile_for(d, MODE_DW, 0, 0);
-  if (dw_tile != BM) {
-    rc = ffn_tile_dw(dw_tile, seg, d->E, d->H, d->F, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
+  const TileKind dw_kind = tile_for(d, MODE_DW, 0, 0);
+  if (dw_kind != TILE_256) {
+    rc = ffn_tile_dw(dw_kind, seg, d->E, d->H, d->F, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
                      (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);
     if (rc) return rc;
   } else {

@@ -1,20 +1,21 @@
 // Grouped SwiGLU FFN on the gfx950 matrix cores (bf16 in, fp32 accumulate): the kernel for products
 // that are too small, or cut into too many short pieces, for the 256 x 256 tiles of ffn_mfma.hip.
 //
-// One workgroup of four wavefronts (2 x 2) per output tile of 128 x 128 (64 x 64 per wavefront) or
-// 64 x 64 (32 x 32), not persistent: the hardware deals the workgroups, and two (five) of them share a
-// compute unit, so that one's prologue and epilogue run under the other's matrix instructions.  The
-// 256 x 256 kernel keeps one workgroup per compute unit and cannot overlap them; it needs less LDS and
-// L2 traffic per MFMA and wins where a tile's k range is long and the tiles fill the chip.
+// One workgroup of four wavefronts (2 x 2) per output tile of 128 x 256 (64 x 128 per wavefront), 128 x 128
+// (64 x 64) or 64 x 64 (32 x 32), not persistent: the hardware deals the workgroups, and two (three, five) of
+// them share a compute unit, so that one's prologue and epilogue run under the other's matrix instructions.
+// The 256 x 256 kernel keeps one workgroup per compute unit and cannot overlap them; it needs two thirds of the L2
+// traffic per MFMA and wins where a tile's k range is long and the tiles fill the chip.
 //
-// k goes in steps of 32 (one MFMA deep) through a ring of five (four) LDS stages; buffer loads with an
-// LDS destination fill a stage four (three) steps before it is read, because a stage's sixteen (four)
-// MFMAs per wavefront are much shorter than the memory latency.  Operands that lie [row][k] in memory
+// k goes in steps of 32 (one MFMA deep) through a ring of three (64 x 64: four) LDS stages; buffer loads with an
+// LDS destination fill a stage two (three) steps before it is read.  A third workgroup per compute unit is worth
+// more to the 128 x 128 tile than two further stages (weight gradients of 64 experts, 256 rows each, 2048 x 1024:
+// 428 -> 377 us; 128 x 256 tiles, same LDS traffic per MFMA as 256 x 256: 358).  Operands that lie [row][k] in memory
 // keep that layout in LDS, operands that lie [k][row] are read with ds_read_b64_tr_b16; 16-byte pieces
 // are placed so that both reads are free of bank conflicts:
 //   [row][k]: 64 bytes per row; the piece with k = 8 c .. of row r sits at r * 64 + ((c ^ ((r >> 2) & 3)) << 4)
-//   [k][row]: 64-byte blocks of 32 rows; block b of k-row k is stored as block b ^ (k & 3) (128 rows) or
-//             b ^ ((k >> 1) & 1) (64 rows), its two 32-byte halves swapped when bit 3 of k is set
+//   [k][row]: 64-byte blocks of 32 rows; block b of k-row k is stored as block b ^ (k & 3) (64 rows:
+//             b ^ ((k >> 1) & 1)), its two 32-byte halves swapped when bit 3 of k is set
 #include "ffn_gemm.h"
 
 namespace dynmo {
@@ -29,24 +30,26 @@ struct DwSet {
   const bf16_t* Q;
   bf16_t* C;
   int M, N;
+  int tiles;  // output tiles per expert
 };
 
 struct TileParams {
   GemmParams g;
-  DwSet dw[3];  // MODE_DW: the products of this launch, with equally many tiles each
+  DwSet dw[3];  // MODE_DW: the products of this launch
   int sets;
   int group;    // consecutive tiles of the list that go to one XCD
 };
 
-template <int WB>
+// WBM x WBN blocks of 16 x 16 per wavefront
+template <int WBM, int WBN>
 struct TileShape {
-  static constexpr int kTile = 32 * WB;                 // rows and columns of the output tile
-  static constexpr int kStages = WB == 4 ? 5 : 4;
-  static constexpr int kOperandBytes = kTile * kTileK * 2;
-  static constexpr int kStage = 2 * kOperandBytes;
-  static constexpr int kPiecesPerWave = kOperandBytes / 1024 / 4;
-  static constexpr int kLoads = 2 * kPiecesPerWave;     // loads a wavefront issues per stage
-  static constexpr int kPitch = 16 * WB + 4;            // floats per row of an epilogue patch
+  static constexpr int kRows = 32 * WBM, kCols = 32 * WBN;  // of the output tile
+  static constexpr int kStages = WBN == 2 ? 4 : 3;
+  static constexpr int kBytesA = kRows * kTileK * 2, kBytesB = kCols * kTileK * 2;
+  static constexpr int kStage = kBytesA + kBytesB;
+  static constexpr int kPiecesA = kBytesA / 4096, kPiecesB = kBytesB / 4096;  // pieces of 1 KB a wavefront loads per stage
+  static constexpr int kLoads = kPiecesA + kPiecesB;
+  static constexpr int kPitch = 16 * WBN + 4;           // floats per row of an epilogue patch
   static constexpr int kPatchBytes = 16 * kPitch * 4;
   static constexpr int kLds = kStages * kStage;
   static_assert(4 * kPatchBytes <= kLds, "the epilogue patches reuse the stages");
@@ -59,11 +62,17 @@ __device__ __forceinline__ void wait_stage() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
 }
 
+// [k][row]: where block `b` of k-row `k` is stored, and the other way round
+template <int ROWS>
+__device__ __forceinline__ int swizzled(int b, int k) {
+  return ROWS == 64 ? b ^ ((k >> 1) & 1) : b ^ (k & 3);
+}
+
 // Byte offsets, from the tile's (row 0, k 0) element, of the 16 bytes this lane moves in each of the
 // wavefront's pieces (kOob: nothing), and their k.
-template <int WB, bool KROW>
+template <int ROWS, bool KROW>
 struct TilePieces {
-  static constexpr int N = TileShape<WB>::kPiecesPerWave;
+  static constexpr int N = ROWS * kTileK * 2 / 4096;
   uint32_t off[N];
   int kpos[N];
 
@@ -81,10 +90,10 @@ struct TilePieces {
         off[j] = ok ? (uint32_t)row * ld_bytes + c * 16 : kOob;
         kpos[j] = c * 8;
       } else {
-        constexpr int kLanesPerK = TileShape<WB>::kTile * 2 / 16;
+        constexpr int kLanesPerK = ROWS * 2 / 16;
         const int k = q * (64 / kLanesPerK) + lane / kLanesPerK, slot = lane % kLanesPerK;
         const int stored = slot >> 2;
-        const int blk = WB == 4 ? stored ^ (k & 3) : stored ^ ((k >> 1) & 1);
+        const int blk = swizzled<ROWS>(stored, k);
         const int col = blk * 32 + ((slot & 3) ^ (((k >> 3) & 1) << 1)) * 8;
         off[j] = col < rows_left ? (uint32_t)k * ld_bytes + col * 2 : kOob;
         kpos[j] = k;
@@ -95,7 +104,7 @@ struct TilePieces {
 
 // LDS byte offsets (inside an operand's stage) from which this lane reads its fragments: lane l holds, for row
 // l % 16 of a 16-row block, the eight k values (l / 16) * 8 .. + 7.
-template <int WB, bool KROW>
+template <int ROWS, bool KROW>
 __device__ __forceinline__ uint32_t frag_offset(int block16) {
   const int lane = threadIdx.x & 63, s = lane & 15, g = lane >> 4;
   if constexpr (!KROW) {
@@ -103,21 +112,21 @@ __device__ __forceinline__ uint32_t frag_offset(int block16) {
   } else {
     const int k = g * 8 + (s >> 2);
     const int blk = block16 >> 1, half = block16 & 1;
-    const int stored = WB == 4 ? blk ^ (k & 3) : blk ^ ((k >> 1) & 1);
-    return k * (TileShape<WB>::kTile * 2) + stored * 64 + (((g & 1) ^ half) << 5) + (s & 3) * 8;
+    const int stored = swizzled<ROWS>(blk, k);
+    return k * (ROWS * 2) + stored * 64 + (((g & 1) ^ half) << 5) + (s & 3) * 8;
   }
 }
 
 typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
 
-template <int WB, bool KROW>
+template <int ROWS, bool KROW>
 __device__ __forceinline__ bf16x8_t read_tile_frag(uint32_t addr) {
   if constexpr (!KROW) {
     return *(const lds_bf16x8_t*)(uintptr_t)addr;
   } else {
     const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)addr);
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)(addr + 4 * TileShape<WB>::kTile * 2));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)(addr + 4 * ROWS * 2));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
 }
@@ -131,15 +140,15 @@ __device__ __forceinline__ void tile_of(int r, int mt, int nt, int* mi, int* ni)
   *mi = c * kChunkTiles + r - *ni * h;
 }
 
-template <int MODE, int WB, bool WHOLE_K>
-__global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel(const TileParams tp) {
-  using S = TileShape<WB>;
+template <int MODE, int WBM, int WBN, bool WHOLE_K>
+__global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void ffn_tile_kernel(const TileParams tp) {
+  using S = TileShape<WBM, WBN>;
   __shared__ __attribute__((aligned(1024))) char smem[S::kLds];
   constexpr bool A_KROW = MODE == MODE_DW;
   constexpr bool IS_DX = MODE == MODE_DX || MODE == MODE_DX_FOLD;
   constexpr bool FOLDS = MODE == MODE_DOWN_FOLD || MODE == MODE_DX_FOLD;
   constexpr bool B_KROW = MODE == MODE_DA || IS_DX || MODE == MODE_DW;
-  constexpr int TM = S::kTile, TILE_N = MODE == MODE_GATEUP ? S::kTile / 2 : S::kTile;
+  constexpr int TM = S::kRows, TILE_N = MODE == MODE_GATEUP ? S::kCols / 2 : S::kCols;
   const GemmParams& p = tp.g;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -155,21 +164,19 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   bf16_t* C0 = p.C0;
   long lda = p.lda, ldb = p.ldb, ldc = p.ldc;
   if constexpr (MODE == MODE_DW) {
-    const int mt0 = (tp.dw[0].M + TM - 1) / TM, nt0 = (tp.dw[0].N + TM - 1) / TM;
-    const int per_set = mt0 * nt0;
-    e = pos / (per_set * tp.sets);
+    const int per_expert = tp.dw[0].tiles + (tp.sets > 1 ? tp.dw[1].tiles + tp.dw[2].tiles : 0);
+    e = pos / per_expert;
     if (e >= p.E) return;
-    int r = pos - e * per_set * tp.sets;
-    const int set = r / per_set;
-    r -= set * per_set;
+    int r = pos - e * per_expert, set = 0;
+    while (r >= tp.dw[set].tiles) r -= tp.dw[set++].tiles;
     const DwSet& w = tp.dw[set];
     int mi, ni;
-    tile_of(r, (w.M + TM - 1) / TM, (w.N + TM - 1) / TM, &mi, &ni);
+    tile_of(r, (w.M + TM - 1) / TM, (w.N + TILE_N - 1) / TILE_N, &mi, &ni);
     k_begin = __builtin_amdgcn_readfirstlane(p.seg[e]);
     k_end = __builtin_amdgcn_readfirstlane(p.seg[e + 1]);
     m0 = mi * TM;
     m_end = w.M;
-    n0 = ni * TM;
+    n0 = ni * TILE_N;
     n_end = w.N;
     A1 = w.P;
     B1 = w.Q;
@@ -203,9 +210,9 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   const uint32_t lda_b = (uint32_t)lda * 2, ldb_b = (uint32_t)ldb * 2;
   const bool gathered = MODE == MODE_GATEUP && p.gather != nullptr;
   const bool second_b = MODE == MODE_GATEUP && wave >= 2;  // operand B: gate rows, then the matching up rows
-  TilePieces<WB, A_KROW> pa;
-  TilePieces<WB, B_KROW> pb;
-  pa.init(lda_b, m_end - m0, S::kTile, gathered ? p.gather + m0 : nullptr, p.gather_div);
+  TilePieces<S::kRows, A_KROW> pa;
+  TilePieces<S::kCols, B_KROW> pb;
+  pa.init(lda_b, m_end - m0, S::kRows, gathered ? p.gather + m0 : nullptr, p.gather_div);
   pb.init(ldb_b, n_end - n0, TILE_N, nullptr, 1);
   const long b_off = MODE == MODE_DW ? 0 : (long)e * p.b_expert_stride;
   auto a_at = [&](const bf16_t* A, int k) { return A_KROW ? A + (long)k * lda + m0 : A + (gathered ? 0 : (long)m0 * lda) + k; };
@@ -216,7 +223,6 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   const bf16_t* nb = b_at(second_b ? p.B2 : B1, k_begin);
   int k_left = k_end - k_begin, issued = 0;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-  const uint32_t my_pieces = lds0 + wave * S::kPiecesPerWave * 1024;
   // the next k step into the stage at byte `stage`; past the last one the loads fetch nothing
   auto issue = [&](uint32_t stage) {
     const int left = issued < n_kt ? k_left : 0;
@@ -224,14 +230,15 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
     const uint32_t any = left > 0 ? 0x7ffffffeu : 0u;
     // a [k][row] operand's k-rows are whole records, so the record count is its k mask
     const desc_t da = make_desc(na, A_KROW ? k_rows * lda_b : any), db = make_desc(nb, B_KROW ? k_rows * ldb_b : any);
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(my_pieces + stage);
-    static_for<S::kPiecesPerWave>([&](auto J) {
+    const uint32_t to_a = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesA * 1024);
+    const uint32_t to_b = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesB * 1024);
+    static_for<S::kPiecesA>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      load_to_lds<j * 1024>(da, dst, A_KROW || WHOLE_K || pa.kpos[j] < left ? pa.off[j] : kOob);
+      load_to_lds<j * 1024>(da, to_a, A_KROW || WHOLE_K || pa.kpos[j] < left ? pa.off[j] : kOob);
     });
-    static_for<S::kPiecesPerWave>([&](auto J) {
+    static_for<S::kPiecesB>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      load_to_lds<S::kOperandBytes + j * 1024>(db, dst, B_KROW || WHOLE_K || pb.kpos[j] < left ? pb.off[j] : kOob);
+      load_to_lds<S::kBytesA + j * 1024>(db, to_b, B_KROW || WHOLE_K || pb.kpos[j] < left ? pb.off[j] : kOob);
     });
     ++issued;
     na += A_KROW ? (long)kTileK * lda : kTileK;
@@ -245,20 +252,20 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   };
 
   // ---- fragments.  Wavefront (wm, wn): 16-row blocks wm, wm + 2, .. of the tile (in a ragged tile the valid
-  // rows are a prefix, and every wavefront keeps its share) and columns 16 WB wn .. .
-  uint32_t fa0 = lds0 + frag_offset<WB, A_KROW>(wm);
-  uint32_t fa[WB], fb[WB];
+  // rows are a prefix, and every wavefront keeps its share) and columns 16 WBN wn .. .
+  uint32_t fa[WBM], fb[WBN];
 #pragma unroll
-  for (int i = 0; i < WB; ++i) {
-    fa[i] = A_KROW ? lds0 + frag_offset<WB, A_KROW>(wm + 2 * i) : fa0 + i * 2 * 1024;
-    const int n16 = MODE != MODE_GATEUP ? wn * WB + i : i < WB / 2 ? wn * (WB / 2) + i : WB + wn * (WB / 2) + i - WB / 2;
-    fb[i] = lds0 + S::kOperandBytes + frag_offset<WB, B_KROW>(n16);
+  for (int i = 0; i < WBM; ++i) fa[i] = lds0 + frag_offset<S::kRows, A_KROW>(wm + 2 * i);
+#pragma unroll
+  for (int j = 0; j < WBN; ++j) {
+    const int n16 = MODE != MODE_GATEUP ? wn * WBN + j : j < WBN / 2 ? wn * (WBN / 2) + j : WBN + wn * (WBN / 2) + j - WBN / 2;
+    fb[j] = lds0 + S::kBytesA + frag_offset<S::kCols, B_KROW>(n16);
   }
-  const int valid16 = min(2 * WB, (m_end - m0 + 15) / 16);
+  const int valid16 = min(2 * WBM, (m_end - m0 + 15) / 16);
   const bool cols_ok = n0 + wn * (TILE_N / 2) < n_end;
   const int my_rows = cols_ok && valid16 > wm ? (valid16 - wm + 1) / 2 : 0;  // row blocks with work
 
-  f32x4_t acc[WB][WB] = {};
+  f32x4_t acc[WBM][WBN] = {};
   for (int s = 0; s + 1 < S::kStages; ++s) issue(s * S::kStage);
   auto loop = [&](auto ROWS_C) {
     constexpr int ROWS = decltype(ROWS_C)::value;
@@ -269,14 +276,14 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
       wait_stage<(S::kStages - 2) * S::kLoads>();
       __builtin_amdgcn_s_barrier();
       issue(freed);
-      bf16x8_t a[WB], b[WB];
+      bf16x8_t a[WBM], b[WBN];
       if constexpr (ROWS > 0) {
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) a[i] = read_tile_frag<WB, A_KROW>(fa[i] + stage);
+        for (int i = 0; i < ROWS; ++i) a[i] = read_tile_frag<S::kRows, A_KROW>(fa[i] + stage);
 #pragma unroll
-        for (int j = 0; j < WB; ++j) b[j] = read_tile_frag<WB, B_KROW>(fb[j] + stage);
+        for (int j = 0; j < WBN; ++j) b[j] = read_tile_frag<S::kCols, B_KROW>(fb[j] + stage);
 #pragma unroll
-        for (int j = 0; j < WB; ++j)
+        for (int j = 0; j < WBN; ++j)
 #pragma unroll
           for (int i = 0; i < ROWS; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
       }
@@ -284,10 +291,10 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
       stage = stage + S::kStage == S::kLds ? 0 : stage + S::kStage;
     }
   };
-  if (my_rows == WB) loop(std::integral_constant<int, WB>{});
+  if (my_rows == WBM) loop(std::integral_constant<int, WBM>{});
   else if (my_rows == 0) loop(std::integral_constant<int, 0>{});
-  else if (WB == 2 || my_rows == 1) loop(std::integral_constant<int, 1>{});
-  else if constexpr (WB == 4) {
+  else if (WBM == 2 || my_rows == 1) loop(std::integral_constant<int, 1>{});
+  else if constexpr (WBM == 4) {
     if (my_rows == 2) loop(std::integral_constant<int, 2>{});
     else loop(std::integral_constant<int, 3>{});
   }
@@ -297,13 +304,13 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   // ---- epilogue.  A wavefront passes sixteen rows at a time through its own LDS patch (fp32), so that global
   // memory sees 16-byte accesses along rows; no barrier, a wavefront's LDS accesses complete in order.
   float* ep = (float*)(smem + wave * S::kPatchBytes);
-  constexpr int kLanesPerRow = 16 * WB / 8 / (MODE == MODE_GATEUP ? 2 : 1);
+  constexpr int kLanesPerRow = 16 * WBN / 8 / (MODE == MODE_GATEUP ? 2 : 1);
   constexpr int kRowsPerPass = 64 / kLanesPerRow < 16 ? 64 / kLanesPerRow : 16;
   constexpr int kPasses = 16 / kRowsPerPass;
   const int c0 = lane % kLanesPerRow * 8;
   const int col = n0 + wn * (TILE_N / 2) + c0;
 #pragma unroll
-  for (int i = 0; i < WB; ++i) {
+  for (int i = 0; i < WBM; ++i) {
     if (i >= my_rows) break;
     const int band = m0 + (2 * i + wm) * 16;
     bool ok[kPasses];
@@ -332,7 +339,7 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
       for (int s = 0; s < kPasses; ++s) token[s] = ok[s] ? p.scatter[band + s * kRowsPerPass + lane / kLanesPerRow] : 0;
     }
 #pragma unroll
-    for (int j = 0; j < WB; ++j)
+    for (int j = 0; j < WBN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) ep[((lane >> 4) * 4 + r) * S::kPitch + j * 16 + (lane & 15)] = acc[i][j][r];
     float weight[kPasses];
@@ -356,7 +363,7 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
         float u[8], a_[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          u[q] = row[8 * WB + q];
+          u[q] = row[8 * WBN + q];
           a_[q] = silu_mul(v[q], u[q]);
         }
         *(u32x4*)(C0 + at[s]) = pack16<bf16_t>(v);
@@ -385,60 +392,70 @@ __global__ __launch_bounds__(kTileThreads, WB == 4 ? 2 : 4) void ffn_tile_kernel
   }
 }
 
-template <int MODE, int WB>
-static int32_t launch_tile(const TileParams& tp, int tiles, KernelId id, hipStream_t st) {
+template <int MODE, int WBM, int WBN>
+static int32_t launch_tile(TileParams tp, int tiles, KernelId id, hipStream_t st) {
+  tp.group = tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
   const int run = 8 * tp.group;
   const unsigned blocks = (unsigned)((tiles + run - 1) / run * run);
-  bool whole = tp.g.K % kTileK == 0;
   if constexpr (MODE != MODE_DW) {
-    if (whole) {
-      DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WB, true><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
+    if (tp.g.K % kTileK == 0) {
+      DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, true><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
       return DYNMO_OK;
     }
   }
-  DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WB, false><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
+  DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, false><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
   return DYNMO_OK;
 }
 
-static int group_of(int tiles) { return tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1; }
+template <int MODE>
+static int32_t launch_shape(TileKind kind, const TileParams& tp, int tiles, KernelId id, hipStream_t st) {
+  switch (kind) {
+    case TILE_128x256: return launch_tile<MODE, 4, 8>(tp, tiles, id, st);
+    case TILE_128: return launch_tile<MODE, 4, 4>(tp, tiles, id, st);
+    default: return launch_tile<MODE, 2, 2>(tp, tiles, id, st);
+  }
+}
 
-int32_t ffn_tile_rows(int mode, int tile, const GemmParams& p, int max_row_tiles, KernelId id, hipStream_t st) {
-  if (max_row_tiles <= 0) return DYNMO_OK;
+static int rows_of(TileKind kind) { return kind == TILE_64 ? 64 : 128; }
+static int cols_of(TileKind kind) { return kind == TILE_64 ? 64 : kind == TILE_128 ? 128 : 256; }
+
+int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st) {
+  const int row_tiles = max_m_tiles(d, rows_of(kind));
+  if (row_tiles <= 0) return DYNMO_OK;
   TileParams tp = {};
   tp.g = p;
-  const int tile_n = mode == MODE_GATEUP ? tile / 2 : tile;
-  const int tiles = max_row_tiles * ((p.N + tile_n - 1) / tile_n);
-  tp.group = group_of(tiles);
-#define DYNMO_TILE_MODE(M) \
-  case M: return tile == 128 ? launch_tile<M, 4>(tp, tiles, id, st) : launch_tile<M, 2>(tp, tiles, id, st)
+  const int cols = cols_of(kind) / (mode == MODE_GATEUP ? 2 : 1);
+  const int tiles = row_tiles * ((p.N + cols - 1) / cols);
   switch (mode) {
-    DYNMO_TILE_MODE(MODE_GATEUP);
-    DYNMO_TILE_MODE(MODE_DOWN);
-    DYNMO_TILE_MODE(MODE_DOWN_FOLD);
-    DYNMO_TILE_MODE(MODE_DA);
-    DYNMO_TILE_MODE(MODE_DX);
-    DYNMO_TILE_MODE(MODE_DX_FOLD);
+    case MODE_GATEUP: return launch_shape<MODE_GATEUP>(kind, tp, tiles, id, st);
+    case MODE_DOWN: return launch_shape<MODE_DOWN>(kind, tp, tiles, id, st);
+    case MODE_DOWN_FOLD: return launch_shape<MODE_DOWN_FOLD>(kind, tp, tiles, id, st);
+    case MODE_DA: return launch_shape<MODE_DA>(kind, tp, tiles, id, st);
+    case MODE_DX: return launch_shape<MODE_DX>(kind, tp, tiles, id, st);
+    case MODE_DX_FOLD: return launch_shape<MODE_DX_FOLD>(kind, tp, tiles, id, st);
   }
-#undef DYNMO_TILE_MODE
   return DYNMO_EINVAL;
 }
 
-int32_t ffn_tile_dw(int tile, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p, const bf16_t* A,
-                    const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st) {
-  const DwSet all[3] = {{dy_p, A, dWd, H, F}, {dG, x_p, dWg, F, H}, {dU, x_p, dWu, F, H}};
+int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
+                    const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st) {
+  const int r = rows_of(kind), c = cols_of(kind);
+  const int hf = ((H + r - 1) / r) * ((F + c - 1) / c), fh = ((F + r - 1) / r) * ((H + c - 1) / c);
+  const DwSet all[3] = {{dy_p, A, dWd, H, F, hf}, {dG, x_p, dWg, F, H, fh}, {dU, x_p, dWu, F, H, fh}};
   const KernelId ids[3] = {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU};
   TileParams tp = {};
   tp.g.seg = seg;
   tp.g.E = E;
-  const int per_set = E * ((H + tile - 1) / tile) * ((F + tile - 1) / tile);
   // One launch for the three products; one each while the profiling step times them by name.
   const int sets = g_profile_on.load(std::memory_order_relaxed) ? 1 : 3;
   for (int s = 0; s < 3; s += sets) {
     tp.sets = sets;
-    for (int i = 0; i < sets; ++i) tp.dw[i] = all[s + i];
-    tp.group = group_of(per_set * sets);
-    const int32_t rc = tile == 128 ? launch_tile<MODE_DW, 4>(tp, per_set * sets, ids[s], st)
-                                   : launch_tile<MODE_DW, 2>(tp, per_set * sets, ids[s], st);
+    int tiles = 0;
+    for (int i = 0; i < sets; ++i) {
+      tp.dw[i] = all[s + i];
+      tiles += all[s + i].tiles;
+    }
+    const int32_t rc = launch_shape<MODE_DW>(kind, tp, E * tiles, ids[s], st);
     if (rc) return rc;
   }
   return DYNMO_OK;

@@ -760,9 +760,9 @@ def test_tile_order_mixed_row_tile_counts(counts):
 
 
 @pytest.mark.parametrize("T,H,F,E,k", [(600, 520, 1032, 8, 2), (1100, 264, 4104, 3, 1), (129, 72, 2056, 1, 1), (900, 1032, 200, 33, 4),
-                                       (64, 2056, 136, 2, 1)])
+                                       (64, 2056, 136, 2, 1), (700, 2056, 2056, 4, 2)])
 def test_small_products_tile_edges(T, H, F, E, k):
-    """Products that go to the 128 and 64 tiles (and, beside them, down and dX of a long k that do not): k not a
+    """Products that go to the 128 x 256, 128 and 64 tiles (and, beside them, down and dX of a long k that do not): k not a
     multiple of the k step, one row or column block past a tile, experts without rows; rows gathered inside the
     first product give the same bits."""
     say("small products T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
@@ -811,7 +811,7 @@ def test_large_tiles_every_row_block_count():
     say("large tiles, every row block count")
     counts = [256 + 16 * i + 1 + 7 * i % 16 for i in range(16)]
     T, E = sum(counts), len(counts)
-    w = wl.scaled(wl.CONFIGS[2], T=T, H=1280, F=2048, E=E, k=1, seed=8900)
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=1024, F=9216, E=E, k=1, seed=8900)
     inp = wl.make_inputs(w, threads=4)
     rng = np.random.default_rng(w.seed)
     logits = rng.standard_normal((T, E)).astype(np.float32)
