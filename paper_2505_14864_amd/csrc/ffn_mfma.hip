@@ -1211,7 +1211,7 @@ static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
 }
 
 // Whether ffn_skinny.hip takes a forward product: on average at most 16 rows (down: 8) per expert in use, and either
-//   * weights that must come from HBM: 5.4 instead of 4.6 TB/s (gate/up, 8 experts, 4096 x 14336, 16 rows each: 417 ->
+//   * weights that must come from HBM: 5.6 instead of 4.6 TB/s (gate/up, 8 experts, 4096 x 14336, 16 rows each: 417 ->
 //     348 us; 64 rows each: 426 -> 573).  From the Infinity Cache (256 MB) the tile kernels are the faster ones (gate/up,
 //     4 experts, 2048 x 8192, 8 rows each: 44 -> 55 us), down excepted, whose k is long and whose split needs a
 //     second pass there (the same layer's down: 43 -> 36 us; 1024 x 4096, 1 expert: 20 -> 10); or

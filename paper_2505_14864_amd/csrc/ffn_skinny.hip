@@ -10,8 +10,8 @@
 // workgroups, no second pass.  The rows of the expert (16, 32 or 64 at a time, more in further passes over the
 // weights, which then come from the caches) are read from L1 / L2 in the same layout.
 //
-// Measured, 64 rows over 8 experts, H=4096 F=14336: gate/up 410 -> 345 us (5.4 TB/s of weights), down 201 -> 187
-// (5.0 TB/s); 8 rows, H=1024 F=4096, down 20 -> 10.  Loading the two halves of a line with the lanes of one
+// Measured, 64 rows over 8 experts, H=4096 F=14336: gate/up 410 us on 256-row tiles -> 333 (5.6 TB/s of weights), down
+// 201 -> 168 (5.6 TB/s); 8 rows, H=1024 F=4096, down 20 -> 10.  Loading the two halves of a line with the lanes of one
 // instruction or of two, and three instead of two workgroups per compute unit, measured the same.
 #include "ffn_gemm.h"
 
@@ -31,6 +31,9 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const Gem
   const int s = lane & 15, g = lane >> 4;
   const int chunks = (p.K + 63) / 64;
   const int steps = (chunks + kSkinnyWaves - 1) / kSkinnyWaves;
+  // Workgroups start at different places of the k range (and go round): started together at k = 0, with weight rows
+  // a power of two apart, they would all ask the same few memory channels (H = 4096: gate/up 394 -> 333 us).
+  const int first_step = (blockIdx.x + blockIdx.y) % steps;
 
   const bf16_t* w1 = p.B1 + (long)e * p.b_expert_stride;
   const bf16_t* w2 = MODE == MODE_GATEUP ? p.B2 + (long)e * p.b_expert_stride : w1;
@@ -55,7 +58,8 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const Gem
     }
     u32x4 a[D][RB][2], b[D][CB][2];
     auto load = [&](int d, int step) {
-      const int c = step * kSkinnyWaves + wave, k = c * 64 + g * 8;
+      const int turn = step + first_step;  // past the last step: beyond K, nothing is loaded
+      const int c = (step >= steps ? steps : turn < steps ? turn : turn - steps) * kSkinnyWaves + wave, k = c * 64 + g * 8;
       const uint32_t at = (uint32_t)c * 128;
 #pragma unroll
       for (int j = 0; j < CB; ++j)
