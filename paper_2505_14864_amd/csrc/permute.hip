@@ -1,6 +1,6 @@
 // Permutation of routed token rows into contiguous per-expert segments, and its
 // backward.  The index part is a stable counting sort done without ordered
-// atomics: per-chunk histograms, a scan over chunks, then an in-chunk stable rank
+// atomics: for few slots in one launch together with the rows (permute_one_kernel), else per-chunk histograms, a scan over chunks, then an in-chunk stable rank
 // from wavefront ballots.  The row movement is a token-centric copy: each source
 // row is read once and written to its (up to k) destinations with 16-byte
 // accesses.
@@ -82,6 +82,20 @@ __global__ __launch_bounds__(kScanThreads) void permute_scan_kernel(int32_t* __r
   }
 }
 
+// The lanes of this wavefront that hold the same expert as this one (none if `ok` is false): one ballot per bit of
+// the expert index instead of one per expert (64 experts, 16384 slots: scatter 21 -> 8 us).
+__device__ __forceinline__ unsigned long long same_expert(int e, bool ok, int bits) {
+  unsigned long long m = __ballot(ok);
+  if (!ok) m = 0;
+  for (int b = 0; b < bits; ++b) {
+    const bool set = (e >> b) & 1;
+    const unsigned long long with = __ballot(set);
+    m &= set ? with : ~with;
+  }
+  return m;
+}
+__device__ __forceinline__ int bits_of(int E) { return 32 - __builtin_clz(E | 1); }  // enough for 0 .. E - 1
+
 // Stable rank of every slot inside its chunk, added to the chunk base.
 __global__ __launch_bounds__(kChunkThreads) void permute_scatter_kernel(const int32_t* __restrict__ expert_idx,
                                                                         int n_slots, int E,
@@ -103,12 +117,10 @@ __global__ __launch_bounds__(kChunkThreads) void permute_scatter_kernel(const in
       if (e >= E) e = -1;
     }
     // rank among lower lanes of this wavefront with the same expert
-    int rank = 0;
-    for (int q = 0; q < E; ++q) {
-      const unsigned long long m = __ballot(e == q);
-      if (e == q) rank = __popcll(m & ((1ull << lane) - 1ull));
-      if (lane == q) wave_cnt[wv][q] = __popcll(m);
-    }
+    const unsigned long long same = same_expert(e, e >= 0, bits_of(E));
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    wave_cnt[wv][lane] = 0;  // in order with the next line: a wavefront's own LDS row
+    if (e >= 0 && rank == 0) wave_cnt[wv][e] = __popcll(same);
     __syncthreads();
     if (e >= 0) {
       int pos = run[e] + rank;
@@ -161,6 +173,101 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const u32x4* __restri
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (c + u * 64 < row_vecs) x_p[dst[s] + c + u * 64] = v[u];
+      }
+    }
+  }
+}
+
+// The whole permutation in one launch, for few slots.  Every workgroup counts all slots by itself (an L2 read and
+// a few ballots per 64 of them), so nothing has to pass between workgroups and the three launches in front of the
+// row copy go; then it places the slots of its own `tokens` tokens and copies their rows.
+// Bound by latency: one chain of load, ballots, scan and copy instead of four.  All four launches together / this one
+// (us): 512 slots, H=128 fp32: 10.7 / 4.2; 3000, H=516 fp32: 20 / 7.3; 8192, one slot per token, H=2048: 20 / 8.5;
+// 8192, H=4096: 35 / 24.  Beyond 8192 slots the repeated counting (about 2 us there) would outgrow the launches.
+constexpr int kOneThreads = 1024;
+constexpr int kOneSlots = 8192;   // most slots that take it
+constexpr int kOneBlocks = 256;   // one workgroup per compute unit: the counting is repeated in each
+constexpr int kOneTokens = 4;     // fewest tokens of a workgroup
+
+__global__ __launch_bounds__(kOneThreads) void permute_one_kernel(const int32_t* __restrict__ expert_idx, const u32x4* __restrict__ x,
+                                                                  u32x4* __restrict__ x_p, int32_t* __restrict__ seg_offsets,
+                                                                  int32_t* __restrict__ src_slot, int32_t* __restrict__ dst_pos,
+                                                                  int T, int k, int E, int tokens, int row_vecs) {
+  constexpr int kWaves = kOneThreads / 64;
+  __shared__ int total[kMaxExperts], before[kMaxExperts];  // slots of expert e: all, and in front of this workgroup's
+  __shared__ int start[kMaxExperts];                       // where this workgroup's slots of expert e begin
+  __shared__ int wave_cnt[kWaves][kMaxExperts];
+  __shared__ int pos_of[kOneThreads];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, bits = bits_of(E);
+  const int n_slots = T * k, t0 = blockIdx.x * tokens, s0 = t0 * k, n_mine = min(tokens, T - t0) * k;
+  if (threadIdx.x < kMaxExperts) total[threadIdx.x] = before[threadIdx.x] = 0;
+  wave_cnt[wv][lane] = 0;
+  __syncthreads();
+  constexpr int kPasses = kOneSlots / kOneThreads;
+  int ids[kPasses];  // all loads are out before the first is used
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p) {
+    const int i = p * kOneThreads + threadIdx.x;
+    ids[p] = i < n_slots ? expert_idx[i] : -1;
+  }
+#pragma unroll
+  for (int p = 0; p < kPasses; ++p) {
+    const int i = p * kOneThreads + threadIdx.x;
+    if (i - lane >= n_slots) break;  // whole wavefronts
+    const int e = ids[p];
+    const bool ok = e >= 0 && e < E;
+    const unsigned long long same = same_expert(e, ok, bits);
+    if (ok && (same & ((1ull << lane) - 1ull)) == 0) {  // the first of them; integer sums: order-independent
+      atomicAdd(&total[e], __popcll(same));
+      const int in_front = s0 - (i - lane);  // slots of this wavefront's 64 that lie in front of the workgroup's
+      if (in_front > 0) atomicAdd(&before[e], __popcll(in_front >= 64 ? same : same & ((1ull << in_front) - 1ull)));
+    }
+  }
+  // this workgroup's own slots: at most one per thread
+  int e = (int)threadIdx.x < n_mine ? expert_idx[s0 + threadIdx.x] : -1;
+  if (e >= E) e = -1;
+  const unsigned long long same = same_expert(e, e >= 0, bits);
+  const int rank = __popcll(same & ((1ull << lane) - 1ull));
+  if (e >= 0 && rank == 0) wave_cnt[wv][e] = __popcll(same);
+  __syncthreads();
+  if (wv == 0) {
+    const int v = total[lane], inc = wave_inclusive_scan(v, lane);
+    start[lane] = inc - v + before[lane];
+    if (blockIdx.x == 0) {
+      if (lane < E) seg_offsets[lane] = inc - v;
+      if (lane == E - 1) seg_offsets[E] = inc;
+    }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < n_mine) {
+    int pos = -1;
+    if (e >= 0) {
+      pos = start[e] + rank;
+      for (int w = 0; w < wv; ++w) pos += wave_cnt[w][e];
+      src_slot[pos] = s0 + threadIdx.x;
+    }
+    dst_pos[s0 + threadIdx.x] = pos;
+    pos_of[threadIdx.x] = pos;
+  }
+  if (x_p == nullptr) return;
+  __syncthreads();
+  for (int t = wv; t < tokens && t0 + t < T; t += kWaves) {
+    const int* pos = pos_of + t * k;
+    const u32x4* src = x + (long)(t0 + t) * row_vecs;
+    bool any = false;
+    for (int s = 0; s < k; ++s) any |= pos[s] >= 0;
+    if (!any) continue;
+    for (int c = lane; c < row_vecs; c += 64 * 4) {
+      u32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u * 64 < row_vecs) v[u] = src[c + u * 64];
+      for (int s = 0; s < k; ++s) {
+        if (pos[s] < 0) continue;
+        u32x4* dst = x_p + (long)pos[s] * row_vecs;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (c + u * 64 < row_vecs) dst[c + u * 64] = v[u];
       }
     }
   }
@@ -278,6 +385,17 @@ static int32_t permute_run(const dynmo_desc* d, const void* x, const int32_t* ex
                            int32_t* src_slot, int32_t* dst_pos, int32_t* chunk_counts, hipStream_t st) {
   const int n_slots = d->T * d->k;
   const int nc = n_chunks_of(d);
+  // one launch for few slots; the profiling step times the parts by name
+  if (n_slots > 0 && n_slots <= kOneSlots && !g_profile_on.load(std::memory_order_relaxed)) {
+    int tokens = (d->T + kOneBlocks - 1) / kOneBlocks;
+    if (tokens < kOneTokens) tokens = kOneTokens;
+    const unsigned blocks = (unsigned)((d->T + tokens - 1) / tokens);
+    const int row_vecs = (int)((size_t)d->H * elem_bytes(d->dtype) / 16);
+    permute_one_kernel<<<dim3(blocks), dim3(kOneThreads), 0, st>>>(expert_idx, (const u32x4*)x, (u32x4*)x_p, seg_offsets, src_slot,
+                                                                   dst_pos, d->T, d->k, d->E, tokens, row_vecs);
+    DYNMO_LAUNCH_CHECK();
+    return DYNMO_OK;
+  }
   if (nc > 0) {
     DYNMO_TIMED_LAUNCH(K_PERMUTE_COUNT, st,
                        permute_count_kernel<<<dim3(nc), dim3(kChunkThreads), 0, st>>>(expert_idx, n_slots, d->E,

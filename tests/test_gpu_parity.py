@@ -138,7 +138,10 @@ def run_permute(x, ei, E, dtype):
 
 
 @pytest.mark.parametrize("T,E,k,H,dtype", [(1, 1, 1, 8, "bf16"), (256, 4, 2, 128, "f32"), (1000, 8, 2, 64, "bf16"),
-                                           (2049, 16, 4, 72, "bf16"), (5000, 64, 8, 8, "bf16"), (777, 3, 3, 12, "f32")])
+                                           (2049, 16, 4, 72, "bf16"), (5000, 64, 8, 8, "bf16"), (777, 3, 3, 12, "f32"),
+                                           # one launch up to 8192 slots: its ends, workgroups of 4 and more tokens, k = E
+                                           (128, 64, 64, 8, "bf16"), (8192, 33, 1, 2056, "bf16"), (8193, 5, 1, 16, "bf16"),
+                                           (1025, 7, 7, 1032, "bf16"), (2731, 64, 3, 24, "bf16"), (5, 2, 1, 4, "f32")])
 def test_permute_moe(T, E, k, H, dtype):
     say("permute T=%d E=%d k=%d H=%d %s" % (T, E, k, H, dtype))
     rng = np.random.default_rng(T + E)
