@@ -257,7 +257,9 @@ def test_moe_layer_empty_expert_zero_dw():
         assert not to_host(getattr(layer, n))[2].any()
 
 
-@pytest.mark.parametrize("Bn,S,cap,H,F", [(4, 256, 32, 128, 256), (3, 100, 100, 64, 72), (2, 130, 0, 64, 64)])
+# (2, 2048, ..): far fewer rows than the host must assume, row tiles of half height in gate/up and dA (300, 256 and 1 row)
+@pytest.mark.parametrize("Bn,S,cap,H,F", [(4, 256, 32, 128, 256), (3, 100, 100, 64, 72), (2, 130, 0, 64, 64),
+                                          (2, 2048, 150, 256, 2560), (2, 2048, 128, 264, 2568), (1, 4096, 1, 256, 2560)])
 def test_mod_layer_small(Bn, S, cap, H, F):
     say("mod layer B=%d S=%d cap=%d" % (Bn, S, cap))
     w = wl.scaled(wl.CONFIGS[4], T=Bn * S, B=Bn, S=S, cap=cap, H=H, F=F, seed=31)
