@@ -1192,6 +1192,17 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //     128 x 256 tiles avoid the nearly empty last round (256 / 128 x 256: 6000 x 2048 x 4096, 16 experts, 503 tiles:
 //     191 / 167; 4096 x 2048 x 8192, 4, 576: 206 / 188; 4096 x 1536 x 4096, 3, 280: 112 / 97; but 16384 x 1024 x 2048,
 //     8, 544: 145 / 146, and 32768 x 4096 x 688, 16, 408: 284 / 295).
+//   * Short sums: a 256 x 256 tile's stores, which nothing hides, weigh the more the fewer k tiles stand before them, and
+//     ragged ends the more the fewer rows an expert has.  128 x 256 tiles with several experts (256, with the second pass of a
+//     split / 128 x 256; rows x H x F, experts) for
+//       dX up to 1024 of k per phase: 32768 x 4096 x 688, 16: 417 / 391; 16384 x 2048 x 1024, 64: 214 / 197; 16384 x 2048 x
+//         512, 32: 113 / 90; 16384 x 4096 x 512, 4: 172 / 147; 65536 x 2048 x 768, 64: 441 / 435 (but 8192 x 2048 x 1408, 16:
+//         142 / 141; 16384 x 4096 x 1536, 32: 425 / 451);
+//       down up to 1024 of k and about four rounds of the chip: 16384 x 2048 x 1024, 64 (768 tiles): 123 / 112; 8192 x 4096 x
+//         1024, 64 (1024): 175 / 137; 16384 x 4096 x 512, 4 (1056): 107 / 95 (but 32768 x 4096 x 688, 16 (2176): 273 / 296;
+//         65536 x 2048 x 768, 64 (2304): 260 / 286);
+//       dA up to 2048 of k and 1024 rows per expert: 16384 x 2048 x 1024, 64: 155 / 146; 65536 x 2048 x 768, 64: 335 / 311;
+//         16384 x 2048 x 512, 32: 86 / 78 (but 16384 x 4096 x 1536, 32: 274 / 296).
 //   * The three weight gradients go in one launch there, and the 256 x 256 kernel's epilogue has nothing to hide
 //     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts (us for all three, 256 /
 //     128 x 256): 16 experts, 32768 x 4096 x 688, 768 tiles: 669 / 604; 64, 16384 x 2048 x 1024, 2048: 404 / 384; 8,
@@ -1215,7 +1226,10 @@ static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
   const bool is_dx = mode == MODE_DX || mode == MODE_DX_FOLD;
   if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return TILE_256;
   if (mode == MODE_DA && d->E > 1 && ((tiles > 220 && tiles <= 320) || (tiles > 480 && tiles <= 600))) return TILE_128x256;
-  if (tiles > (mode == MODE_DA ? 150 : 140)) return TILE_256;
+  if (tiles > (mode == MODE_DA ? 150 : 140)) {
+    const bool short_sum = mode == MODE_DA ? K <= 2048 && rows <= 1024.0 * d->E : down_or_dx && K <= 1024 && (is_dx || tiles <= 1100);
+    return d->E > 1 && short_sum ? TILE_128x256 : TILE_256;
+  }
   return (rows / 128 + ragged) * cols(N, 128) > 128 ? TILE_128 : TILE_64;
 }
 

@@ -765,7 +765,7 @@ def test_tile_order_mixed_row_tile_counts(counts):
 
 
 @pytest.mark.parametrize("T,H,F,E,k", [(600, 520, 1032, 8, 2), (1100, 264, 4104, 3, 1), (129, 72, 2056, 1, 1), (900, 1032, 200, 33, 4),
-                                       (64, 2056, 136, 2, 1), (700, 2056, 2056, 4, 2)])
+                                       (64, 2056, 136, 2, 1), (700, 2056, 2056, 4, 2), (1100, 2056, 520, 16, 4)])
 def test_small_products_tile_edges(T, H, F, E, k):
     """Products that go to the 128 x 256, 128 and 64 tiles (and, beside them, down and dX of a long k that do not): k not a
     multiple of the k step, one row or column block past a tile, experts without rows; rows gathered inside the
@@ -942,6 +942,7 @@ FOLDED_CASES = [
     ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 100, B=2, S=100, cap=100, H=36, F=50, dtype="f32", seed=95)),  # fp32 kernels
     ("moe", wl.scaled(wl.CONFIGS[2], T=330, H=256, F=4096, E=2, k=1, seed=96)),                  # top-1, no residual, split
     ("moe", wl.scaled(wl.CONFIGS[1], T=300, H=36, F=50, E=4, k=1, seed=97)),                     # top-1 fp32
+    ("moe", wl.scaled(wl.CONFIGS[2], T=8000, H=1032, F=264, E=8, k=1, seed=98)),                 # top-1, short sums: 128 x 256 tiles
 ]
 
 
