@@ -126,8 +126,9 @@ def _pinned_ptr(t, n):
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:  # torch.cuda.current_stream().cuda_stream without building the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _check(call, rc):
