@@ -17,6 +17,8 @@
 //   T=1500 H=516 F=1030 E=8 k=2   gate/up 275 -> 96 us, down 242 -> 61, dA 151 -> 61, dX 467 -> 105, dW 179 -> 50 each
 //                                 (52 to 66 TFLOP/s; a large dense fp32 product of the vendor's library: 142)
 //   T=256 H=128 F=256 E=4 k=2     gate/up 40 -> 8 us, down 37 -> 11, dA 26 -> 12, dX 74 -> 16, dW 31 -> 6 each
+#include <type_traits>
+
 #include "common.h"
 #include "ffn.h"
 #include "profile.h"
@@ -67,11 +69,14 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, i
 //     another one (`base2`): every thread's first chunk then belongs to the one and its second to the other.
 //   KROW = true: element (row, k) at base + k * ld + row.
 // VEC = floats per load: the largest of 4, 2, 1 that divides ld (and so every offset and limit).
-template <bool KROW, int VEC, bool PAIR = false>
+// WIDE: a tile may span 2 GiB and more (64 rows of at least 2^23 floats), where the 32-bit offsets and the record
+// count of a buffer load end; the loads are then ordinary ones from 64-bit addresses.
+template <bool KROW, int VEC, bool WIDE, bool PAIR = false>
 struct Operand {
+  using offset_t = std::conditional_t<WIDE, long, uint32_t>;
   const float *base, *base2;  // (row 0, k 0) of the tile, wave-uniform
   long ld;
-  uint32_t off[2];    // byte offsets of this thread's two chunks of four floats, from (row 0, k 0 of the k tile)
+  offset_t off[2];    // byte offsets of this thread's two chunks of four floats, from (row 0, k 0 of the k tile)
   int kpos[2];        // their k inside the k tile
   int left[2];        // [k][row]: valid floats from there on (<= 0: none); [row][k]: valid row or not
 
@@ -86,14 +91,14 @@ struct Operand {
       if constexpr (KROW) {
         kpos[i] = c / (TM / 4);
         const int row = c % (TM / 4) * 4;
-        off[i] = (uint32_t)(kpos[i] * ld + row) * 4;
+        off[i] = (offset_t)(kpos[i] * ld + row) * 4;
         left[i] = rows - row;
       } else {
         kpos[i] = c % (TK / 4) * 4;
         int row = c / (TK / 4) - (PAIR && i ? TM / 2 : 0);
         left[i] = row < rows;
         if (rowmap != nullptr) row = left[i] ? rowmap[row] / rowdiv : 0;
-        off[i] = (uint32_t)(row * ld + kpos[i]) * 4;
+        off[i] = (offset_t)(row * ld + kpos[i]) * 4;
       }
     }
   }
@@ -103,9 +108,21 @@ struct Operand {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const float* p = (PAIR && i ? base2 : base) + shift + (KROW ? k0 * ld : k0);
-      __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7ffffffe, 0x00020000);
       const bool ok = KROW ? kpos[i] < k_left : left[i] != 0;
       const int n = !ok ? 0 : KROW ? left[i] : k_left - kpos[i];  // valid floats of the chunk
+      if constexpr (WIDE) {
+        const float* q = (const float*)((const char*)p + off[i]);
+        r[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if constexpr (VEC == 4) {
+          if (n > 0) r[i] = *(const f32x4_t*)q;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (n > j) r[i][j] = q[j];
+        }
+        continue;
+      }
+      __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0x7ffffffe, 0x00020000);
       if constexpr (VEC == 4) {
         r[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(d, n > 0 ? off[i] : kOutside, 0, 0));
       } else if constexpr (VEC == 2) {
@@ -254,14 +271,17 @@ __device__ __forceinline__ void store_row_product(const F32Params& p, const f32x
 
 // G = X Wg^T, U = X Wu^T, A = silu(G) U: 64 rows x 32 columns of each.  LDS rows 0..31 of operand B are gate
 // rows, 32..63 the matching up rows, and a wavefront takes sixteen of either.
+template <bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
   RowTile t;
   if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
-  const int n0 = blockIdx.x * (TN / 2);
+  const long first_col = ((long)blockIdx.z * gridDim.x + blockIdx.x) * (TN / 2);
+  if (first_col >= p.F) return;
+  const int n0 = (int)first_col;
   const long first = ((long)t.e * p.F + n0) * p.H;
-  Operand<false, 4> a;
-  Operand<false, 4, true> b;
+  Operand<false, 4, WIDE> a;
+  Operand<false, 4, WIDE, true> b;
   if (p.gather) a.init(p.x, p.H, t.m_end - t.m0, nullptr, p.gather + t.m0, p.gather_div);
   else a.init(p.x + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
   b.init(p.Wg + first, p.H, p.F - n0, p.Wu + first);
@@ -286,13 +306,13 @@ __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p)
 }
 
 // Y = A Wd^T
-template <int VF>
+template <int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
   RowTile t;
   if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
   const int n0 = blockIdx.x * TN;
-  Operand<false, VF> a, b;
+  Operand<false, VF, WIDE> a, b;
   a.init(p.A + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
   b.init(p.Wd + ((long)t.e * p.H + n0) * p.F, p.F, p.H - n0);
   f32x4_t acc[2][2] = {};
@@ -303,14 +323,14 @@ __global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
 }
 
 // dA = dY Wd; with the saved G, U: A, dG, dU
-template <int VF>
+template <int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
   RowTile t;
   if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
   const int n0 = blockIdx.x * TN;
-  Operand<false, 4> a;
-  Operand<true, VF> b;
+  Operand<false, 4, WIDE> a;
+  Operand<true, VF, WIDE> b;
   a.init(p.dy + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
   b.init(p.Wd + (long)t.e * p.H * p.F + n0, p.F, p.F - n0);
   f32x4_t acc[2][2] = {};
@@ -346,14 +366,14 @@ __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
 }
 
 // dX = dG Wg + dU Wu, tile `tile` of the list (column tiles side by side)
-template <int VF>
+template <int VF, bool WIDE>
 __device__ __forceinline__ void input_grad(const F32Params& p, int tile, float* lds) {
   const int th = (p.H + TN - 1) / TN;
   RowTile t;
   if (!find_row_tile(p.seg, p.E, tile / th, &t)) return;
   const int n0 = tile % th * TN;
-  Operand<false, VF> a;
-  Operand<true, 4> b;
+  Operand<false, VF, WIDE> a;
+  Operand<true, 4, WIDE> b;
   a.init(p.dG + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
   b.init(p.Wg + (long)t.e * p.F * p.H + n0, p.H, p.H - n0);
   f32x4_t acc[2][2] = {};
@@ -364,11 +384,11 @@ __device__ __forceinline__ void input_grad(const F32Params& p, int tile, float* 
 }
 
 // dW[m, n] = sum over the rows of an expert of P[row, m] Q[row, n]   (zeros if it has none)
-template <int VM, int VN>
+template <int VM, int VN, bool WIDE>
 __device__ __forceinline__ void weight_grad(const float* P, int M, const float* Q, int N, float* dW, int k_begin, int k_end,
                                             int m0, int n0, float* lds) {
-  Operand<true, VM> a;
-  Operand<true, VN> b;
+  Operand<true, VM, WIDE> a;
+  Operand<true, VN, WIDE> b;
   a.init(P + (long)k_begin * M + m0, M, M - m0);
   b.init(Q + (long)k_begin * N + n0, N, N - n0);
   f32x4_t acc[2][2] = {};
@@ -393,12 +413,12 @@ __device__ __forceinline__ void weight_grad(const float* P, int M, const float* 
 //   T=1500 H=516 F=1030 E=8 k=2 (459 dX tiles, 3672 others):   four launches 242 us, one 204 (fp32 matrix rate: 131)
 //   T=256 H=128 F=256 E=4 k=2 (24 and 96):                      36, 17
 // This launch covers the list from `first` to `end`; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
-template <int VF>
+template <int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int first, int end, int dx_tiles, int dw_tiles) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
   int r = first + (int)(blockIdx.y * gridDim.x + blockIdx.x);
   if (r >= end) return;
-  if (r < dx_tiles) return input_grad<VF>(p, r, lds);
+  if (r < dx_tiles) return input_grad<VF, WIDE>(p, r, lds);
   r -= dx_tiles;
   const int which = r / dw_tiles;  // 0 = dWd (P = dY, Q = A), 1 = dWg (dG, x_p), 2 = dWu (dU, x_p)
   r -= which * dw_tiles;
@@ -407,28 +427,32 @@ __global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, 
   const int m0 = tile / width * TM, n0 = tile % width * TN;
   const int k_begin = p.seg[e], k_end = p.seg[e + 1];
   const long FH = (long)p.F * p.H * e;
-  if (which == 0) weight_grad<4, VF>(p.dy, p.H, p.A, p.F, p.dWd + FH, k_begin, k_end, m0, n0, lds);
-  else weight_grad<VF, 4>(which == 1 ? p.dG : p.dU, p.F, p.x, p.H, (which == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
+  if (which == 0) weight_grad<4, VF, WIDE>(p.dy, p.H, p.A, p.F, p.dWd + FH, k_begin, k_end, m0, n0, lds);
+  else weight_grad<VF, 4, WIDE>(which == 1 ? p.dG : p.dU, p.F, p.x, p.H, (which == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
 }
 
-template <int VF>
+constexpr unsigned kMaxWidth = 1 << 20;  // of a grid: its width in threads is a 32-bit number
+
+template <int VF, bool WIDE>
 static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
   const unsigned m_tiles = max_m_tiles(d, TM);
   if (m_tiles == 0) return DYNMO_OK;
-  DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st, f32_gateup_kernel<<<dim3((d->F + TN / 2 - 1) / (TN / 2), m_tiles), dim3(kThreads), 0, st>>>(p));
-  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<VF><<<dim3((d->H + TN - 1) / TN, m_tiles), dim3(kThreads), 0, st>>>(p));
+  const unsigned cols = (d->F + TN / 2 - 1) / (TN / 2), width = cols < kMaxWidth ? cols : kMaxWidth;
+  DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st,
+                     f32_gateup_kernel<WIDE><<<dim3(width, m_tiles, (cols + width - 1) / width), dim3(kThreads), 0, st>>>(p));
+  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<VF, WIDE><<<dim3((d->H + TN - 1) / TN, m_tiles), dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 
-template <int VF>
+template <int VF, bool WIDE>
 static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
   const unsigned m_tiles = max_m_tiles(d, TM), tf = (d->F + TN - 1) / TN, th = (d->H + TN - 1) / TN;
-  if (m_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
+  if (m_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF, WIDE><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
   // the weight gradients are written for every expert, rows or not
   const int dx_tiles = (int)(th * m_tiles), dw_tiles = (int)(tf * th * d->E);
   auto launch = [&](int first, int n) {
-    const int width = n < (1 << 20) ? n : 1 << 20;  // a grid's width in threads is a 32-bit number
-    f32_grads_kernel<VF><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(p, first, first + n, dx_tiles, dw_tiles);
+    const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
+    f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(p, first, first + n, dx_tiles, dw_tiles);
   };
   if (!g_profile_on.load(std::memory_order_relaxed)) {
     launch(0, dx_tiles + 3 * dw_tiles);
@@ -441,6 +465,9 @@ static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
   for (int s = 0; s < 3; ++s) DYNMO_TIMED_LAUNCH(ids[s], st, launch(dx_tiles + s * dw_tiles, dw_tiles));
   return DYNMO_OK;
 }
+
+// Whether 64 rows of an operand can span 2 GiB (the rows of a gathered input as a whole stay below that)
+static bool wide(const dynmo_desc* d) { return (d->H > d->F ? d->H : d->F) >= (1 << 23); }
 
 static F32Params params_of(const dynmo_desc* d, const int32_t* seg, const void* Wg, const void* Wu, const void* Wd,
                            const FoldedCombine* fc) {
@@ -469,7 +496,8 @@ int32_t ffn_fwd_f32(const dynmo_desc* d, const void* x_p, const int32_t* gather,
   p.A = (const float*)A;
   p.C = (float*)y_p;
   // rows of length F can be loaded four, two or one float at a time, whichever divides F; H is a multiple of four
-  return d->F % 4 == 0 ? fwd_f32<4>(d, p, st) : d->F % 2 == 0 ? fwd_f32<2>(d, p, st) : fwd_f32<1>(d, p, st);
+  if (wide(d)) return fwd_f32<1, true>(d, p, st);
+  return d->F % 4 == 0 ? fwd_f32<4, false>(d, p, st) : d->F % 2 == 0 ? fwd_f32<2, false>(d, p, st) : fwd_f32<1, false>(d, p, st);
 }
 
 int32_t ffn_bwd_f32(const dynmo_desc* d, const void* dy_p, const void* x_p, const void* G, const void* U,
@@ -490,7 +518,8 @@ int32_t ffn_bwd_f32(const dynmo_desc* d, const void* dy_p, const void* x_p, cons
   p.dWg = (float*)dWg;
   p.dWu = (float*)dWu;
   p.dWd = (float*)dWd;
-  return d->F % 4 == 0 ? bwd_f32<4>(d, p, st) : d->F % 2 == 0 ? bwd_f32<2>(d, p, st) : bwd_f32<1>(d, p, st);
+  if (wide(d)) return bwd_f32<1, true>(d, p, st);
+  return d->F % 4 == 0 ? bwd_f32<4, false>(d, p, st) : d->F % 2 == 0 ? bwd_f32<2, false>(d, p, st) : bwd_f32<1, false>(d, p, st);
 }
 
 }  // namespace dynmo

@@ -244,6 +244,57 @@ def test_f32_layer_tile_edges(T, H, F, E, k):
     check_layer_full(layer, ref, w.dtype)
 
 
+@pytest.mark.parametrize("T,H,F", [(64, 4, 8600001), (40, 4, 17500002), (40, 17500000, 3)])
+def test_f32_rows_beyond_32_bit_offsets(T, H, F):
+    """fp32 layers of which 64 rows span more than 2 GiB (8600001: from row 62 on, both operands [row][k]; 17.5 M: k-rows
+    from 31 on, operands [k][row]), forward and backward, against the same products in 64 bits on the GPU.
+    Tolerances, per token row (2-norm): a sum of n fp32 terms has a random-walk error of about 2^-24 sqrt(n / 2), times four;
+    never below 1e-5.  A row that was left out is off by its whole length."""
+    say("f32 rows beyond 32-bit offsets T=%d H=%d F=%d" % (T, H, F))
+    d = B.make_desc(T, H, F, 1, 1, "f32")
+    gen = torch.Generator(device="cuda").manual_seed(T + F)
+
+    def normal(sigma, *shape):
+        return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, sigma, generator=gen)
+
+    def empty(*shape):
+        return torch.empty(shape, dtype=torch.float32, device="cuda")
+
+    def check(name, got, ref, terms):
+        tol = max(1e-5, 4 * 2.0 ** -24 * (terms / 2) ** 0.5)
+        err = float(((got.double() - ref).norm(dim=1) / ref.norm(dim=1)).max())
+        assert err <= tol, "%s: %.2e > %.1e" % (name, err, tol)
+
+    x, dy = normal(1.0, T, H), normal(1.0, T, H)
+    Wg, Wu, Wd = normal(H ** -0.5, F, H), normal(H ** -0.5, F, H), normal(F ** -0.5, H, F)
+    seg = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    y, G, U = empty(T, H), empty(T, F), empty(T, F)
+    ws = torch.empty(max(B.dynmo_grouped_ffn_fwd_workspace_bytes(d), B.dynmo_grouped_ffn_bwd_workspace_bytes(d)),
+                     dtype=torch.uint8, device="cuda")
+    B.dynmo_grouped_ffn_fwd(d, x, seg, Wg, Wu, Wd, y, G, U, ws)
+    rG, rU = x.double() @ Wg.double().t(), x.double() @ Wu.double().t()
+    check("G", G, rG, H)
+    check("U", U, rU, H)
+    del rG, rU
+    g, u = G.double(), U.double()  # what the later products were given
+    sig = torch.sigmoid(g)
+    check("y", y, (g * sig * u) @ Wd.double().t(), F)
+    dx, dWg, dWu, dWd = empty(T, H), empty(F, H), empty(F, H), empty(H, F)
+    B.dynmo_grouped_ffn_bwd(d, dy, x, G, U, seg, Wg, Wu, Wd, dx, dWg, dWu, dWd, ws)
+    dA = dy.double() @ Wd.double()
+    # a weight gradient's rows can be three elements long and small against the terms they cancel from: one norm for the tensor
+    check("dWd", dWd.view(1, -1), (dy.double().t() @ (g * sig * u)).view(1, -1), T)
+    dG = dA * u * (sig * (1 + g * (1 - sig)))
+    del u
+    dU = dA * (g * sig)
+    del dA, g, sig
+    # dx carries the error of dA, a sum over H, relative to a typical row of dA; with F = 3 the smallest of 40 rows is
+    # about a quarter of a typical one (a factor of four in the bound is 16 times the terms)
+    check("dx", dx, dG @ Wg.double() + dU @ Wu.double(), 16 * max(2 * F, H))
+    for name, got, q in (("dWg", dWg, dG), ("dWu", dWu, dU)):
+        check(name, got.view(1, -1), (q.t() @ x.double()).view(1, -1), max(T, H))
+
+
 def test_moe_layer_empty_expert_zero_dw():
     say("moe empty expert")
     w = wl.scaled(wl.CONFIGS[2], T=200, H=64, F=96, E=4, k=2, seed=21)
