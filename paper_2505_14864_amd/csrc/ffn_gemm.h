@@ -107,7 +107,8 @@ int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmPa
 int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
                     const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
 
-// ffn_skinny.hip: MODE_GATEUP, MODE_DOWN or MODE_DOWN_FOLD with few rows per expert; at most `max_experts` experts have rows
-int32_t ffn_skinny_rows(int mode, const GemmParams& p, int max_experts, KernelId id, hipStream_t st);
+// ffn_skinny.hip: MODE_GATEUP, MODE_DOWN or MODE_DOWN_FOLD with few rows per expert; at most `max_experts` experts have
+// rows, none of them more than `max_rows` unless a token takes an expert twice (right in any case)
+int32_t ffn_skinny_rows(int mode, const GemmParams& p, int max_experts, int max_rows, KernelId id, hipStream_t st);
 
 }  // namespace dynmo

@@ -1234,27 +1234,36 @@ static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
 }
 
 // Whether ffn_skinny.hip takes a forward product: on average at most 16 rows (down: 8) per expert in use, and either
-//   * weights that must come from HBM: 5.6 instead of 4.6 TB/s (gate/up, 8 experts, 4096 x 14336, 16 rows each: 417 ->
-//     348 us; 64 rows each: 426 -> 573).  From the Infinity Cache (256 MB) the tile kernels are the faster ones (gate/up,
+//   * weights that must come from HBM: 5.6 instead of 4.6 TB/s (gate/up, 8 experts, 4096 x 14336, 16 rows each: 447 ->
+//     353 us; 64 rows each: 426 -> 573).  From the Infinity Cache (256 MB) the tile kernels are the faster ones (gate/up,
 //     4 experts, 2048 x 8192, 8 rows each: 44 -> 55 us), down excepted, whose k is long and whose split needs a
-//     second pass there (the same layer's down: 43 -> 36 us; 1024 x 4096, 1 expert: 20 -> 10); or
-//   * so few weight rows that tiles cannot occupy the chip (gate/up, 1 expert, 4096 x 1024: 21 -> 15 us; down, 8
-//     experts, 512 x 1024: 8.9 -> 6.8; 32 experts: 9.3 -> 10.7).
+//     second pass there (the same layer's down: 43 -> 36 us; 1024 x 4096, 1 expert: 20 -> 10).  Not for short sums, whose
+//     fixed costs then weigh (64 experts, 2 rows each: gate/up of k = 512 116 -> 122 us, down of k = 1024 51 -> 54); or
+//   * so few weight rows that tiles cannot occupy the chip, and few tokens (gate/up, 1 expert, 4096 x 1024: 21 -> 15 us; down,
+//     8 experts, 512 x 1024: 8.9 -> 6.8; 32 experts: 9.3 -> 10.7; gate/up, 8 experts, 512 x 512, 8 / 128 tokens: 7.4 -> 6.7 / 8.3 -> 14).
+// An expert can take all T tokens, whatever the average, and its rows then pass over its weights 64 at a time.  Each 64 rows are
+// workgroups of their own, and T is limited, so that a collapsed routing stays near the tile kernels (all tokens on the
+// same k experts, 256-row tiles / here: gate/up, 64 experts, 2048 x 1024, 512 tokens 49 / 38 us; 16, 4096 x 4096, 256: 91 / 66;
+// 8, k = 2, 4096 x 14336, 64: 124 / 140; down, 32, 2048 x 2048, 256: 37 / 37; 64, k = 2, 4096 x 1024, 128 and 256 tokens: 33 / 47 and 40 / 68;
+// half of the tokens there, the others dealt evenly: 81 / 73; dealt evenly: 131 / 99).
 static bool skinny_for(const dynmo_desc* d, int mode, int N, int K) {
   const int64_t rows = (int64_t)d->T * d->k, experts = d->E < rows ? d->E : rows;
   const int64_t widest = d->H > d->F ? d->H : d->F, limit = (int64_t)1 << 30;  // 32-bit byte offsets
   if ((int64_t)d->H * d->F >= limit || rows * widest >= limit || (int64_t)d->T * d->H >= limit) return false;
   const bool gateup = mode == MODE_GATEUP;
   const int64_t weight_rows = experts * N * (gateup ? 2 : 1);
-  if (rows > (gateup ? 16 : 8) * experts) return false;
-  if (gateup) return weight_rows <= 512 * 16 || weight_rows * K * 2 >= (int64_t)256 << 20;
-  return weight_rows <= 256 * 16 || K >= 2048 || weight_rows * K * 2 >= (int64_t)128 << 20;
+  if (rows > (gateup ? 16 : 8) * experts || d->T > (gateup ? 512 : 256)) return false;
+  if (gateup) return (weight_rows <= 512 * 16 && d->T <= 16) || (K >= 1024 && weight_rows * K * 2 >= (int64_t)256 << 20);
+  return weight_rows <= 256 * 16 || K >= 2048 || (K >= 1536 && weight_rows * K * 2 >= (int64_t)128 << 20);
 }
 
 template <int MODE>
 static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st) {
   if constexpr (MODE == MODE_GATEUP || MODE == MODE_DOWN || MODE == MODE_DOWN_FOLD) {
-    if (skinny_for(d, MODE, p.N, p.K)) return ffn_skinny_rows(MODE, p, (int)(d->E < (int64_t)d->T * d->k ? d->E : d->T * d->k), id, st);
+    if (skinny_for(d, MODE, p.N, p.K)) {
+      const int experts = (int)(d->E < (int64_t)d->T * d->k ? d->E : d->T * d->k);
+      return ffn_skinny_rows(MODE, p, experts, d->T, id, st);
+    }
   }
   const TileKind kind = tile_for(d, MODE, p.N, p.K);
   if (kind != TILE_256) return ffn_tile_rows(MODE, kind, d, p, id, st);

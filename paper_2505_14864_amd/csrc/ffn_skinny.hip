@@ -7,8 +7,9 @@
 // wavefronts takes 16 CB weight rows of one expert; the wavefronts deal the k range among them in
 // pieces of 64 (one 128-byte line of every weight row), so that together they stream 512 contiguous
 // bytes per row and step, and add their fp32 sums in LDS at the end, in a fixed order: no split over
-// workgroups, no second pass.  The rows of the expert (16, 32 or 64 at a time, more in further passes over the
-// weights, which then come from the caches) are read from L1 / L2 in the same layout.
+// workgroups, no second pass.  The rows of the expert are read from L1 / L2 in the same layout, 16, 32 or 64 at a
+// time; every 64 rows of an expert are workgroups of their own, so that an expert that took many rows keeps as many
+// workgroups busy as its rows need instead of walking its weights again and again.
 //
 // Measured, 64 rows over 8 experts, H=4096 F=14336: gate/up 410 us on 256-row tiles -> 333 (5.6 TB/s of weights), down
 // 201 -> 168 (5.6 TB/s); 8 rows, H=1024 F=4096, down 20 -> 10.  Loading the two halves of a line with the lanes of one
@@ -19,15 +20,34 @@ namespace dynmo {
 
 constexpr int kSkinnyThreads = 256;
 constexpr int kSkinnyWaves = kSkinnyThreads / 64;
+constexpr int kSkinnyRows = 64;  // rows that a workgroup takes at a time
+
+// Whether grid y counts the experts that have rows (else all experts); `chunks`: row chunks on grid z
+__host__ __device__ constexpr bool compacts(int mode, int chunks) { return mode != MODE_GATEUP && chunks == 1; }
 
 template <int MODE, int CB>
 __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const GemmParams p) {
   __shared__ f32x4_t part[kSkinnyWaves][CB][64];
   constexpr int PAIRS = MODE == MODE_GATEUP ? CB / 2 : CB;  // gate/up: blocks 0 .. CB/2 - 1 are gate, the others the matching up columns
-  const int e = blockIdx.y, n0 = blockIdx.x * 16 * PAIRS;
-  const int begin = p.seg[e], end = p.seg[e + 1];
-  if (begin >= end) return;
+  const int n0 = blockIdx.x * 16 * PAIRS;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // Which expert.  The down products of one row chunk count only the experts that have rows, so that the workgroups
+  // with work are the first ones and spread evenly over the compute units: they are few enough for that to matter
+  // (4 experts, two of them empty, 4096 x 14336, 32 rows: 89 -> 59 us).  It costs gate/up, whose workgroups are many, more than it gives.
+  int e = blockIdx.y, begin, end;
+  if (compacts(MODE, gridDim.z) && p.E > 1) {
+    const int first_row = p.seg[min(lane, p.E)], end_row = p.seg[min(lane + 1, p.E)];
+    const unsigned long long used = __ballot(first_row < end_row);
+    const unsigned long long mine = __ballot(first_row < end_row && __popcll(used & ((1ull << lane) - 1ull)) == e);
+    if (mine == 0) return;
+    e = __builtin_ctzll(mine);
+    begin = __builtin_amdgcn_readlane(first_row, e);
+    end = __builtin_amdgcn_readlane(end_row, e);
+  } else {
+    begin = p.seg[e];
+    end = p.seg[e + 1];
+  }
+  if (begin + kSkinnyRows * (int)blockIdx.z >= end) return;
   const int s = lane & 15, g = lane >> 4;
   const int chunks = (p.K + 63) / 64;
   const int steps = (chunks + kSkinnyWaves - 1) / kSkinnyWaves;
@@ -128,7 +148,7 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const Gem
       }
     }
   };
-  for (int row0 = 0; row0 < end - begin; row0 += 64) {
+  for (int row0 = kSkinnyRows * blockIdx.z; row0 < end - begin; row0 += kSkinnyRows * gridDim.z) {
     const int left = end - begin - row0;
     if (left <= 16) pass(row0, std::integral_constant<int, 1>{});
     else if (left <= 32) pass(row0, std::integral_constant<int, 2>{});
@@ -137,24 +157,33 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void ffn_skinny_kernel(const Gem
 }
 
 template <int MODE, int CB>
-static int32_t launch_skinny(const GemmParams& p, KernelId id, hipStream_t st) {
+static int32_t launch_skinny(const GemmParams& p, int max_experts, int max_rows, KernelId id, hipStream_t st) {
   constexpr int cols = 16 * (MODE == MODE_GATEUP ? CB / 2 : CB);
-  DYNMO_TIMED_LAUNCH(id, st, ffn_skinny_kernel<MODE, CB><<<dim3((p.N + cols - 1) / cols, p.E), dim3(kSkinnyThreads), 0, st>>>(p));
+  const int chunks = (max_rows + kSkinnyRows - 1) / kSkinnyRows;
+  const dim3 grid((p.N + cols - 1) / cols, compacts(MODE, chunks) ? max_experts : p.E, chunks);
+  DYNMO_TIMED_LAUNCH(id, st, ffn_skinny_kernel<MODE, CB><<<grid, dim3(kSkinnyThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 
-int32_t ffn_skinny_rows(int mode, const GemmParams& p, int max_experts, KernelId id, hipStream_t st) {
+int32_t ffn_skinny_rows(int mode, const GemmParams& p, int max_experts, int max_rows, KernelId id, hipStream_t st) {
   if (max_experts <= 0) return DYNMO_OK;
-  // 64 weight rows per workgroup, fewer where that would leave the chip (two workgroups per compute unit) short of work
+  // 64 weight rows per workgroup, fewer where that would leave the chip (two workgroups per compute unit) short of work.
+  // `blocks` assumes that every expert is in use.  When only few are, a down product with its long k is left with few
+  // workgroups, so it keeps four times as many as it needs otherwise, at no cost to an even routing (8 experts, 4096 x
+  // 14336, 16 rows on two of them / on all eight: 64 weight rows per workgroup 80 / 163 us, 32 49 / 159; 256-row tiles 59 / 188).
   const long blocks = (long)p.N * (mode == MODE_GATEUP ? 2 : 1) / 16 * max_experts;
   switch (mode) {
-    case MODE_GATEUP: return blocks >= 4 * 512 ? launch_skinny<MODE_GATEUP, 4>(p, id, st) : launch_skinny<MODE_GATEUP, 2>(p, id, st);
+    case MODE_GATEUP:
+      return blocks >= 4 * 512 ? launch_skinny<MODE_GATEUP, 4>(p, max_experts, max_rows, id, st)
+                               : launch_skinny<MODE_GATEUP, 2>(p, max_experts, max_rows, id, st);
     case MODE_DOWN:
-      return blocks >= 4 * 512 ? launch_skinny<MODE_DOWN, 4>(p, id, st)
-             : blocks >= 2 * 512 ? launch_skinny<MODE_DOWN, 2>(p, id, st) : launch_skinny<MODE_DOWN, 1>(p, id, st);
+      return blocks >= 12 * 512  ? launch_skinny<MODE_DOWN, 4>(p, max_experts, max_rows, id, st)
+             : blocks >= 2 * 512 ? launch_skinny<MODE_DOWN, 2>(p, max_experts, max_rows, id, st)
+                                 : launch_skinny<MODE_DOWN, 1>(p, max_experts, max_rows, id, st);
     case MODE_DOWN_FOLD:
-      return blocks >= 4 * 512 ? launch_skinny<MODE_DOWN_FOLD, 4>(p, id, st)
-             : blocks >= 2 * 512 ? launch_skinny<MODE_DOWN_FOLD, 2>(p, id, st) : launch_skinny<MODE_DOWN_FOLD, 1>(p, id, st);
+      return blocks >= 12 * 512  ? launch_skinny<MODE_DOWN_FOLD, 4>(p, max_experts, max_rows, id, st)
+             : blocks >= 2 * 512 ? launch_skinny<MODE_DOWN_FOLD, 2>(p, max_experts, max_rows, id, st)
+                                 : launch_skinny<MODE_DOWN_FOLD, 1>(p, max_experts, max_rows, id, st);
   }
   return DYNMO_EINVAL;
 }
