@@ -410,9 +410,12 @@ static int32_t launch_tile(TileParams tp, int tiles, KernelId id, hipStream_t st
 template <int MODE>
 static int32_t launch_shape(TileKind kind, const TileParams& tp, int tiles, KernelId id, hipStream_t st) {
   switch (kind) {
-    case TILE_128x256: return launch_tile<MODE, 4, 8>(tp, tiles, id, st);
+    case TILE_128x256:
+      if constexpr (MODE == MODE_GATEUP) return DYNMO_EINVAL;  // never picked
+      else return launch_tile<MODE, 4, 8>(tp, tiles, id, st);
     case TILE_128: return launch_tile<MODE, 4, 4>(tp, tiles, id, st);
-    default: return launch_tile<MODE, 2, 2>(tp, tiles, id, st);
+    case TILE_64: return launch_tile<MODE, 2, 2>(tp, tiles, id, st);
+    default: return DYNMO_EINVAL;
   }
 }
 
