@@ -235,6 +235,26 @@ int32_t dynmo_grouped_ffn_bwd_scatter(const dynmo_desc* d, const void* dy_p, con
                                       void* dx_p, void* dWg, void* dWu, void* dWd, void* workspace,
                                       size_t workspace_bytes, void* stream);
 
+/* Which kernel takes a product of the grouped calls above for this descriptor (a DYNMO_KERNEL_* value,
+ * or a negative DYNMO_E* code): host arithmetic on the sizes, for tests and for reading profiles.
+ * Nothing but speed and the order of fp32 sums depends on it, and it may differ from version to version. */
+enum {
+  DYNMO_PRODUCT_GATEUP = 0,
+  DYNMO_PRODUCT_DOWN = 1,
+  DYNMO_PRODUCT_DA = 2,
+  DYNMO_PRODUCT_DX = 3,
+  DYNMO_PRODUCT_DW = 4 /* the three weight gradients */
+};
+enum {
+  DYNMO_KERNEL_F32 = 0,     /* the fp32 kernels */
+  DYNMO_KERNEL_256x256 = 1, /* bf16, persistent 256 x 256 tiles; down and dX split a sparse last round along k */
+  DYNMO_KERNEL_128x256 = 2, /* bf16, one workgroup per tile */
+  DYNMO_KERNEL_128x128 = 3,
+  DYNMO_KERNEL_64x64 = 4,
+  DYNMO_KERNEL_FEW_ROWS = 5 /* bf16, weights straight into the matrix operands */
+};
+int32_t dynmo_grouped_ffn_kernel(const dynmo_desc* d, int32_t product);
+
 /* ---- combine ----------------------------------------------------------- */
 
 /* out[t] = base[t] + sum over routed slots s (ascending) of gate_w[t,s] y_p[dst_pos[t,s]].

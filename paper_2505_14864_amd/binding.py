@@ -62,6 +62,7 @@ SIGNATURES = {
     "dynmo_grouped_ffn_bwd_workspace_bytes": (C.c_size_t, [_D]),
     "dynmo_grouped_ffn_bwd": (_I, [_D] + [_P] * 13 + [C.c_size_t, _P]),
     "dynmo_grouped_ffn_bwd_scatter": (_I, [_D] + [_P] * 16 + [C.c_size_t, _P]),
+    "dynmo_grouped_ffn_kernel": (_I, [_D, _I]),
     "dynmo_combine": (_I, [_D, _P, _P, _P, _P, _P, _P]),
     "dynmo_combine_bwd": (_I, [_D, _P, _P, _P, _P, _P, _P, _P]),
     "dynmo_layer_load": (_I, [_D, _P, C.c_double, C.POINTER(C.c_int32), C.POINTER(C.c_double), _P]),
@@ -252,6 +253,18 @@ def dynmo_grouped_ffn_bwd_scatter(d, dy_p, x_p, G_save, U_save, seg_offsets, src
         C.byref(d), _ptr(dy_p), _ptr(x_p), _ptr(G_save), _ptr(U_save), _ptr(seg_offsets), _ptr(src_slot), _ptr(Wg),
         _ptr(Wu), _ptr(Wd), _ptr(dbase), _ptr(dx), _ptr(dx_p), _ptr(dWg), _ptr(dWu), _ptr(dWd), _ptr(workspace),
         workspace.numel(), _stream(stream)))
+
+
+FFN_PRODUCTS = ("gateup", "down", "dA", "dX", "dW")
+FFN_KERNELS = ("f32", "256x256", "128x256", "128x128", "64x64", "few_rows")
+
+
+def dynmo_grouped_ffn_kernel(d, product):
+    """Name (FFN_KERNELS) of the kernel that takes a product (FFN_PRODUCTS) of this layer."""
+    rc = lib().dynmo_grouped_ffn_kernel(C.byref(d), FFN_PRODUCTS.index(product))
+    if rc < 0:
+        raise DynmoError("dynmo_grouped_ffn_kernel", rc)
+    return FFN_KERNELS[rc]
 
 
 def dynmo_combine(d, y_p, dst_pos, gate_w, base, out, stream=None):

@@ -47,9 +47,9 @@ int32_t ffn_bwd_f32(const dynmo_desc* d, const void* dy_p, const void* x_p, cons
                         const int32_t* seg, const void* Wg, const void* Wu, const void* Wd, void* dx_p, void* dWg,
                         void* dWu, void* dWd, void* dG, void* dU, void* A, const FoldedCombine* fc, hipStream_t st);
 
-
 // bf16 matrix-core kernels
 bool ffn_mfma_supported(const dynmo_desc* d);
+int32_t ffn_mfma_kernel_of(const dynmo_desc* d, int32_t product);  // DYNMO_KERNEL_* of a DYNMO_PRODUCT_*
 size_t ffn_mfma_scratch_bytes();  // 256-byte aligned device scratch both calls below need
 int32_t ffn_fwd_mfma(const dynmo_desc* d, const void* x_p, const int32_t* gather, const int32_t* seg, const void* Wg,
                      const void* Wu, const void* Wd, void* y_p, void* G, void* U, void* A, void* scratch,

@@ -16,6 +16,15 @@ static size_t mfma_scratch(const dynmo_desc* d) { return ffn_mfma_supported(d) ?
 extern "C" int32_t dynmo_version(void) { return 1; }
 extern "C" int32_t dynmo_last_hip_error(void) { return g_last_hip_error; }
 
+extern "C" int32_t dynmo_grouped_ffn_kernel(const dynmo_desc* d, int32_t product) {
+  const int32_t rc = check_desc(d);
+  if (rc) return rc;
+  if (product < DYNMO_PRODUCT_GATEUP || product > DYNMO_PRODUCT_DW) return DYNMO_EINVAL;
+  if (ffn_mfma_supported(d)) return ffn_mfma_kernel_of(d, product);
+  if (d->dtype != DYNMO_F32 || max_m_tiles(d, 64) > 65535) return DYNMO_EUNSUPPORTED;
+  return DYNMO_KERNEL_F32;
+}
+
 extern "C" size_t dynmo_grouped_ffn_fwd_workspace_bytes(const dynmo_desc* d) {
   if (check_desc(d)) return 0;
   return act_bytes(d) + mfma_scratch(d) + 256;  // A = silu(G) U

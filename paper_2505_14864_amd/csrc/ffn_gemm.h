@@ -1,4 +1,4 @@
-// What the two bf16 grouped-GEMM kernels share: the product's parameters, the global -> LDS
+// What the bf16 grouped-GEMM kernels (ffn_mfma.hip, ffn_tile.hip, ffn_skinny.hip) share: the product's parameters, the global -> LDS
 // loads, and the element-wise parts of their epilogues.
 #pragma once
 
@@ -101,8 +101,16 @@ __device__ __forceinline__ void swiglu_bwd_bf16(float dA, float g, float u, floa
   *du = dA * gs;
 }
 
-// ffn_tile.hip: a row-segmented product (any mode but MODE_DW), and the three weight gradients
-enum TileKind { TILE_256, TILE_128x256, TILE_128, TILE_64 };  // TILE_256: ffn_mfma.hip
+// Which kernel takes a product (the DYNMO_KERNEL_* values of dynmo.h): ffn_mfma.hip, ffn_tile.hip with one of its tiles, ffn_skinny.hip
+enum TileKind {
+  TILE_256 = DYNMO_KERNEL_256x256,
+  TILE_128x256 = DYNMO_KERNEL_128x256,
+  TILE_128 = DYNMO_KERNEL_128x128,
+  TILE_64 = DYNMO_KERNEL_64x64,
+  FEW_ROWS = DYNMO_KERNEL_FEW_ROWS
+};
+// ffn_tile.hip: a row-segmented product (any mode but MODE_DW; MODE_GATEUP not on 128 x 256 tiles), and the three weight gradients.
+// DYNMO_EINVAL for a kind that is none of its tiles.
 int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st);
 int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
                     const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);

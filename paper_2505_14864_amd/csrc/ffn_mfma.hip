@@ -1257,15 +1257,34 @@ static bool skinny_for(const dynmo_desc* d, int mode, int N, int K) {
   return weight_rows <= 256 * 16 || K >= 2048 || (K >= 1536 && weight_rows * K * 2 >= (int64_t)128 << 20);
 }
 
+// The kernel of a product (MODE_DW: of the three weight gradients)
+static TileKind kernel_for(const dynmo_desc* d, int mode) {
+  const bool wide = mode == MODE_GATEUP || mode == MODE_DA;  // F columns and H of k, or the other way round
+  const int N = wide ? d->F : d->H, K = wide ? d->H : d->F;
+  if ((mode == MODE_GATEUP || mode == MODE_DOWN || mode == MODE_DOWN_FOLD) && skinny_for(d, mode, N, K)) return FEW_ROWS;
+  return tile_for(d, mode, N, K);
+}
+
+int32_t ffn_mfma_kernel_of(const dynmo_desc* d, int32_t product) {
+  switch (product) {
+    case DYNMO_PRODUCT_GATEUP: return kernel_for(d, MODE_GATEUP);
+    case DYNMO_PRODUCT_DOWN: return kernel_for(d, MODE_DOWN);
+    case DYNMO_PRODUCT_DA: return kernel_for(d, MODE_DA);
+    case DYNMO_PRODUCT_DX: return kernel_for(d, MODE_DX);
+    case DYNMO_PRODUCT_DW: return kernel_for(d, MODE_DW);
+  }
+  return DYNMO_EINVAL;
+}
+
 template <int MODE>
 static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st) {
+  const TileKind kind = kernel_for(d, MODE);
   if constexpr (MODE == MODE_GATEUP || MODE == MODE_DOWN || MODE == MODE_DOWN_FOLD) {
-    if (skinny_for(d, MODE, p.N, p.K)) {
+    if (kind == FEW_ROWS) {
       const int experts = (int)(d->E < (int64_t)d->T * d->k ? d->E : d->T * d->k);
       return ffn_skinny_rows(MODE, p, experts, d->T, id, st);
     }
   }
-  const TileKind kind = tile_for(d, MODE, p.N, p.K);
   if (kind != TILE_256) return ffn_tile_rows(MODE, kind, d, p, id, st);
   constexpr int tile_n = MODE == MODE_GATEUP ? BN / 2 : BN;
   return launch_mfma<MODE>(p, max_m_tiles(d, BM) * ((p.N + tile_n - 1) / tile_n), id, st);
@@ -1366,7 +1385,7 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
   };
   // Order: the three weight gradients first, dX last, so that the pass that follows the
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.
-  const TileKind dw_kind = tile_for(d, MODE_DW, 0, 0);
+  const TileKind dw_kind = kernel_for(d, MODE_DW);
   if (dw_kind != TILE_256) {
     rc = ffn_tile_dw(dw_kind, seg, d->E, d->H, d->F, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
                      (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);

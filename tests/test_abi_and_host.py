@@ -94,6 +94,27 @@ def test_bad_arguments_are_rejected_without_a_gpu():
         B.dynmo_repack([1, 1], [1.0, 1.0], [1, -1], 1, 10.0)
 
 
+def kernels_of(T, H, F, E, k, dtype="bf16"):
+    d = B.make_desc(T, H, F, E, k, dtype)
+    return [B.dynmo_grouped_ffn_kernel(d, p) for p in B.FFN_PRODUCTS]
+
+
+def test_kernel_of_a_product():
+    """The kernel query: one answer for every product, the fp32 kernels for fp32, errors as the grouped calls give them."""
+    assert kernels_of(4096, 4096, 14336, 8, 2) == ["256x256"] * 5
+    assert kernels_of(256, 128, 256, 4, 2, "f32") == ["f32"] * 5
+    assert kernels_of(32, 4096, 14336, 8, 2)[:2] == ["few_rows"] * 2
+    assert kernels_of(0, 64, 64, 2, 1)[0] in B.FFN_KERNELS
+    d = B.make_desc(64, 64, 64, 2, 1, "bf16")
+    lib = B.lib()
+    assert lib.dynmo_grouped_ffn_kernel(B.C.byref(d), 5) == -1 and lib.dynmo_grouped_ffn_kernel(B.C.byref(d), -1) == -1
+    assert lib.dynmo_grouped_ffn_kernel(None, 0) == -1
+    for bad in (B.make_desc(64, 64, 60, 2, 1, "bf16"), B.make_desc(65536 * 64, 64, 64, 2, 1, "f32")):
+        with pytest.raises(B.DynmoError) as e:
+            B.dynmo_grouped_ffn_kernel(bad, "down")
+        assert e.value.status == -2
+
+
 def test_diffusion_and_repack_edge_cases():
     assert B.dynmo_diffusion([5.0], [0, 1]) == ([0, 1], 0, 0.0, 0.0)
     assert B.dynmo_diffusion([5.0, 3.0], [0, 1, 2]) == ([0, 1, 2], 0, 2.0, 2.0)  # one layer each: nothing may move
