@@ -33,6 +33,8 @@
 // last round of a row-segmented product would fill at most half of the chip, its tiles
 // are split along k over several XCDs and a small second kernel adds the fp32 partial
 // tiles in a fixed order (ffn_split_reduce_kernel).
+#include <math.h>
+
 #include "ffn_gemm.h"
 
 namespace dynmo {
@@ -1188,21 +1190,18 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //     64-wide tiles where 128-wide ones would still leave half of the compute units without work.
 //   * down and dX with more than 4096 of k stay here, where k can be split (2048 x 2048 x 4096, 8 experts, dX:
 //     151 / 190 / 202 us).
-//   * dA cannot split k: where several experts' tiles come out a little above one or two rounds of the chip,
-//     128 x 256 tiles avoid the nearly empty last round (256 / 128 x 256: 6000 x 2048 x 4096, 16 experts, 503 tiles:
-//     191 / 167; 4096 x 2048 x 8192, 4, 576: 206 / 188; 4096 x 1536 x 4096, 3, 280: 112 / 97; but 16384 x 1024 x 2048,
-//     8, 544: 145 / 146, and 32768 x 4096 x 688, 16, 408: 284 / 295).
-//   * Short sums: a 256 x 256 tile's stores, which nothing hides, weigh the more the fewer k tiles stand before them, and
-//     ragged ends the more the fewer rows an expert has.  128 x 256 tiles with several experts (256, with the second pass of a
-//     split / 128 x 256; rows x H x F, experts) for
-//       dX up to 1024 of k per phase: 32768 x 4096 x 688, 16: 417 / 391; 16384 x 2048 x 1024, 64: 214 / 197; 16384 x 2048 x
-//         512, 32: 113 / 90; 16384 x 4096 x 512, 4: 172 / 147; 65536 x 2048 x 768, 64: 441 / 435 (but 8192 x 2048 x 1408, 16:
-//         142 / 141; 16384 x 4096 x 1536, 32: 425 / 451);
-//       down up to 1024 of k and about four rounds of the chip: 16384 x 2048 x 1024, 64 (768 tiles): 123 / 112; 8192 x 4096 x
-//         1024, 64 (1024): 175 / 137; 16384 x 4096 x 512, 4 (1056): 107 / 95 (but 32768 x 4096 x 688, 16 (2176): 273 / 296;
-//         65536 x 2048 x 768, 64 (2304): 260 / 286);
-//       dA up to 2048 of k and 1024 rows per expert: 16384 x 2048 x 1024, 64: 155 / 146; 65536 x 2048 x 768, 64: 335 / 311;
-//         16384 x 2048 x 512, 32: 86 / 78 (but 16384 x 4096 x 1536, 32: 274 / 296).
+//   * 128 x 256 tiles with several experts, for dA and, up to 1024 of k per phase, dX and down (a tile's stores, which nothing
+//     hides, weigh the more the fewer k tiles stand before them; with longer sums their fewer operand bytes per MFMA win):
+//       - where the 256 x 256 tiles come out at up to half a round of the chip above whole rounds, which the smaller tiles
+//         need not wait for.  In whole rounds or nearly so 256 x 256 is the faster one.  Segments drawn from skewed
+//         routings, 256 / 128 x 256, by tiles: dA 2048 x 2048, 16 experts: 240 (in one round) 83 / 95, 288 136 / 91, 416
+//         153 / 157, 512 159 / 178, 536 217 / 190, 696 231 / 240, 816 289 / 247; dX 2048 x 1024, 64 experts: 3.1 rounds -3 %, 3.4
+//         -16 %, 3.9 -13 %, 5.1 +4 %.  Down, whose stores are the smallest part, up to 3.7 rounds, and only with whole k steps
+//         (4096 columns, k = 688, 64 experts: +14 to +18 % throughout);
+//       - where experts have so few rows that the half-empty last row tiles are a good part of the work.
+//     Over 3374 shapes (3 to 64 experts, k 512 to 4096, 0.5 to 9 rounds) the time is 0.944 (dA), 0.937 (dX) and 0.954 (down) of
+//     256 x 256 tiles alone on average, and more than 5 % above theirs for 18, 35 and 45 of them: the host knows the rows, not
+//     the segments, and estimates the tiles.
 //   * The three weight gradients go in one launch there, and the 256 x 256 kernel's epilogue has nothing to hide
 //     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts (us for all three, 256 /
 //     128 x 256): 16 experts, 32768 x 4096 x 688, 768 tiles: 669 / 604; 64, 16384 x 2048 x 1024, 2048: 404 / 384; 8,
@@ -1225,10 +1224,13 @@ static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
   const bool down_or_dx = mode != MODE_GATEUP && mode != MODE_DA;
   const bool is_dx = mode == MODE_DX || mode == MODE_DX_FOLD;
   if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return TILE_256;
-  if (mode == MODE_DA && d->E > 1 && ((tiles > 220 && tiles <= 320) || (tiles > 480 && tiles <= 600))) return TILE_128x256;
   if (tiles > (mode == MODE_DA ? 150 : 140)) {
-    const bool short_sum = mode == MODE_DA ? K <= 2048 && rows <= 1024.0 * d->E : down_or_dx && K <= 1024 && (is_dx || tiles <= 1100);
-    return d->E > 1 && short_sum ? TILE_128x256 : TILE_256;
+    if (d->E == 1 || (mode != MODE_DA && (!down_or_dx || K > 1024 || (!is_dx && K % 32 != 0)))) return TILE_256;
+    const double rounds = tiles / kMaxPersistent, last = rounds - floor(rounds);
+    const bool sparse_end = rounds > 1 && last > 0 && last <= 0.5 && (mode == MODE_DA || is_dx || rounds <= 3.7);
+    const double halved = (rows / BM + 0.5 * ragged) * cols(N, BM) / kMaxPersistent;  // the work on 128-row tiles, in rounds
+    const bool few = rows <= (rounds > 1 ? 384.0 : 128.0) * d->E && 1.1 * halved < ceil(rounds);
+    return sparse_end || few ? TILE_128x256 : TILE_256;
   }
   return (rows / 128 + ragged) * cols(N, 128) > 128 ? TILE_128 : TILE_64;
 }

@@ -115,6 +115,29 @@ def test_kernel_of_a_product():
         assert e.value.status == -2
 
 
+@pytest.mark.parametrize("product,T,H,F,E,k,kernel", [
+    # dA: 256x256 tiles that fill whole rounds of 256 compute units (or nearly so) stay on them (83 us; 128x256: 95) ...
+    ("dA", 2732, 2048, 2048, 16, 2, "256x256"),       # about 235 tiles, one round
+    ("dA", 6828, 2048, 2048, 16, 2, "256x256"),       # 491, nearly two
+    # ... a last round that is at most half full does not (217 / 190), in whichever round it falls
+    ("dA", 7676, 2048, 2048, 16, 2, "128x256"),       # 544
+    ("dA", 11776, 2048, 2048, 16, 2, "128x256"),      # 800
+    ("dA", 9984, 2048, 2048, 16, 2, "256x256"),       # 688
+    ("dA", 7676, 2048, 2048, 1, 1, "256x256"),        # a single expert's tiles are counted exactly and cost the same
+    # dX and down: short sums only, down only with whole k steps and up to 3.7 rounds
+    ("dX", 7552, 2048, 1024, 16, 2, "128x256"), ("dX", 7552, 2048, 1032, 16, 2, "256x256"),
+    ("down", 7552, 2048, 1024, 16, 2, "128x256"), ("down", 7552, 2048, 1008, 16, 2, "256x256"),
+    ("dX", 32672, 2048, 1024, 8, 2, "128x256"), ("down", 32672, 2048, 1024, 8, 2, "256x256"),  # 8.1 rounds
+    ("down", 15895, 1920, 896, 3, 1, "256x256"),      # 509 of 512: two full rounds (65 / 78 us)
+    # few rows per expert: the half-empty last row tiles weigh
+    ("dX", 2048, 2048, 1024, 64, 8, "128x256"), ("down", 2048, 2048, 1024, 64, 8, "128x256"),
+    ("dA", 1024, 2048, 2048, 32, 2, "128x256"), ("dA", 3000, 2048, 2048, 16, 2, "256x256"),  # 64, 375 rows per expert, one round
+])
+def test_tile_shape_by_the_last_round(product, T, H, F, E, k, kernel):
+    """Which of the two large tiles takes a product, on both sides of every line of the rule."""
+    assert B.dynmo_grouped_ffn_kernel(B.make_desc(T, H, F, E, k, "bf16"), product) == kernel
+
+
 def test_diffusion_and_repack_edge_cases():
     assert B.dynmo_diffusion([5.0], [0, 1]) == ([0, 1], 0, 0.0, 0.0)
     assert B.dynmo_diffusion([5.0, 3.0], [0, 1, 2]) == ([0, 1, 2], 0, 2.0, 2.0)  # one layer each: nothing may move
