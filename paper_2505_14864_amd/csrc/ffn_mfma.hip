@@ -1188,6 +1188,9 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //       dA       2048 x 2048 x 4096, 1 (128 tiles): 70 / 49 / 72     6144 x 2048 x 4096, 1 (384): 143 / 144 / 212
 //       down     2048 x 1024 x 2048, 1: 45 / 26 / 24     6144 x 2048 x 4096, 1 (192 tiles): 97 / 131 / 214
 //     64-wide tiles where 128-wide ones would still leave half of the compute units without work.
+//     A single expert's tiles are counted exactly, and gate/up and down of more than 1024 of k gain nothing from smaller ones
+//     beyond 128 (8652 x 1536 x 512, gate/up, 136: 42 / 52; 8960 x 1024 x 4000, down, 140: 117 / 135; but dX there 202 / 185, and
+//     down 8300 x 1024 x 1024, 132: 33 / 34, 34000 x 256 x 768, 133: 40 / 32).
 //   * down and dX with more than 4096 of k stay here, where k can be split (2048 x 2048 x 4096, 8 experts, dX:
 //     151 / 190 / 202 us).
 //   * 128 x 256 tiles with several experts, for dA and, up to 1024 of k per phase, dX and down (a tile's stores, which nothing
@@ -1224,7 +1227,8 @@ static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
   const bool down_or_dx = mode != MODE_GATEUP && mode != MODE_DA;
   const bool is_dx = mode == MODE_DX || mode == MODE_DX_FOLD;
   if (down_or_dx && (is_dx ? 2.0 : 1.0) * K > 4096) return TILE_256;
-  if (tiles > (mode == MODE_DA ? 150 : 140)) {
+  const bool one_round = d->E == 1 && (mode == MODE_GATEUP || (down_or_dx && !is_dx && K > 1024));
+  if (tiles > (mode == MODE_DA ? 150 : one_round ? 128 : 140)) {
     if (d->E == 1 || (mode != MODE_DA && (!down_or_dx || K > 1024 || (!is_dx && K % 32 != 0)))) return TILE_256;
     const double rounds = tiles / kMaxPersistent, last = rounds - floor(rounds);
     const bool sparse_end = rounds > 1 && last > 0 && last <= 0.5 && (mode == MODE_DA || is_dx || rounds <= 3.7);

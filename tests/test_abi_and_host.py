@@ -132,6 +132,10 @@ def test_kernel_of_a_product():
     # few rows per expert: the half-empty last row tiles weigh
     ("dX", 2048, 2048, 1024, 64, 8, "128x256"), ("down", 2048, 2048, 1024, 64, 8, "128x256"),
     ("dA", 1024, 2048, 2048, 32, 2, "128x256"), ("dA", 3000, 2048, 2048, 16, 2, "256x256"),  # 64, 375 rows per expert, one round
+    # a single expert's 132 tiles stay on 256x256 tiles (down 58 us; 128x128: 73), 128 do not; dX has the line at 140
+    ("down", 6737, 1280, 2432, 1, 1, "256x256"), ("down", 8192, 1024, 2432, 1, 1, "128x128"),
+    ("down", 8300, 1024, 1024, 1, 1, "128x128"), ("dX", 8300, 1024, 1024, 1, 1, "128x128"),
+    ("gateup", 8652, 1536, 512, 1, 1, "256x256"), ("gateup", 8192, 1536, 512, 1, 1, "128x128"),
 ])
 def test_tile_shape_by_the_last_round(product, T, H, F, E, k, kernel):
     """Which of the two large tiles takes a product, on both sides of every line of the rule."""
