@@ -363,7 +363,11 @@ int32_t dynmo_repack(int32_t n_workers, int32_t* active_host, double* mem_usage_
  * timed per layer and the times feed the "by Time" balancers).  While enabled,
  * every kernel the library launches is bracketed by a hipEvent pair on its
  * stream; totals are kept per kernel role (dynmo_profile_kernel_name) and are
- * process-wide.  dynmo_profile_read waits for the recorded launches of that role
+ * process-wide.  The launches are those of a step without profiling: where one does the
+ * work of several roles (the permutation of few rows, the gradients of small layers) its
+ * duration is divided among them in proportion to their flops or bytes and it counts as
+ * one launch of each, so the sum over the roles is what the layer takes in a step.
+ * dynmo_profile_read waits for the recorded launches of that role
  * to finish, then returns their summed duration in milliseconds and their count
  * (HOST pointers).  dynmo_profile_reset waits likewise and zeroes all totals. */
 int32_t dynmo_profile_enable(int32_t on);

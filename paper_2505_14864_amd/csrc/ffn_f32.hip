@@ -412,12 +412,12 @@ __device__ __forceinline__ void weight_grad(const float* P, int M, const float* 
 // are long (2 F) and whose tiles are few, then dWd, dWg and dWu, which fill the compute units meanwhile.
 //   T=1500 H=516 F=1030 E=8 k=2 (459 dX tiles, 3672 others):   four launches 242 us, one 204 (fp32 matrix rate: 131)
 //   T=256 H=128 F=256 E=4 k=2 (24 and 96):                      36, 17
-// This launch covers the list from `first` to `end`; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
+// `n` tiles in all; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
 template <int VF, bool WIDE>
-__global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int first, int end, int dx_tiles, int dw_tiles) {
+__global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int n, int dx_tiles, int dw_tiles) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
-  int r = first + (int)(blockIdx.y * gridDim.x + blockIdx.x);
-  if (r >= end) return;
+  int r = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (r >= n) return;
   if (r < dx_tiles) return input_grad<VF, WIDE>(p, r, lds);
   r -= dx_tiles;
   const int which = r / dw_tiles;  // 0 = dWd (P = dY, Q = A), 1 = dWg (dG, x_p), 2 = dWu (dU, x_p)
@@ -450,19 +450,12 @@ static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
   if (m_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF, WIDE><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
   // the weight gradients are written for every expert, rows or not
   const int dx_tiles = (int)(th * m_tiles), dw_tiles = (int)(tf * th * d->E);
-  auto launch = [&](int first, int n) {
-    const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
-    f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(p, first, first + n, dx_tiles, dw_tiles);
-  };
-  if (!g_profile_on.load(std::memory_order_relaxed)) {
-    launch(0, dx_tiles + 3 * dw_tiles);
-    DYNMO_LAUNCH_CHECK();
-    return DYNMO_OK;
-  }
-  // one by one while the profiling step times them by name
-  if (dx_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DX, st, launch(0, dx_tiles));
-  const KernelId ids[3] = {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU};
-  for (int s = 0; s < 3; ++s) DYNMO_TIMED_LAUNCH(ids[s], st, launch(dx_tiles + s * dw_tiles, dw_tiles));
+  ProfRoles roles;  // by flops
+  if (dx_tiles > 0) roles.add(K_FFN_DX, 2.0);
+  for (KernelId id : {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU}) roles.add(id, 1.0);
+  const int n = dx_tiles + 3 * dw_tiles, width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
+  DYNMO_TIMED_LAUNCH(roles, st, f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(
+                                    p, n, dx_tiles, dw_tiles));
   return DYNMO_OK;
 }
 

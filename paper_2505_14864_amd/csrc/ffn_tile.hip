@@ -393,7 +393,7 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void
 }
 
 template <int MODE, int WBM, int WBN>
-static int32_t launch_tile(TileParams tp, int tiles, KernelId id, hipStream_t st) {
+static int32_t launch_tile(TileParams tp, int tiles, const ProfRoles& id, hipStream_t st) {
   tp.group = tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
   const int run = 8 * tp.group;
   const unsigned blocks = (unsigned)((tiles + run - 1) / run * run);
@@ -408,7 +408,7 @@ static int32_t launch_tile(TileParams tp, int tiles, KernelId id, hipStream_t st
 }
 
 template <int MODE>
-static int32_t launch_shape(TileKind kind, const TileParams& tp, int tiles, KernelId id, hipStream_t st) {
+static int32_t launch_shape(TileKind kind, const TileParams& tp, int tiles, const ProfRoles& id, hipStream_t st) {
   switch (kind) {
     case TILE_128x256:
       if constexpr (MODE == MODE_GATEUP) return DYNMO_EINVAL;  // never picked
@@ -449,19 +449,15 @@ int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, cons
   TileParams tp = {};
   tp.g.seg = seg;
   tp.g.E = E;
-  // One launch for the three products; one each while the profiling step times them by name.
-  const int sets = g_profile_on.load(std::memory_order_relaxed) ? 1 : 3;
-  for (int s = 0; s < 3; s += sets) {
-    tp.sets = sets;
-    int tiles = 0;
-    for (int i = 0; i < sets; ++i) {
-      tp.dw[i] = all[s + i];
-      tiles += all[s + i].tiles;
-    }
-    const int32_t rc = launch_shape<MODE_DW>(kind, tp, E * tiles, ids[s], st);
-    if (rc) return rc;
+  tp.sets = 3;
+  int tiles = 0;
+  ProfRoles roles;  // equal flops
+  for (int i = 0; i < 3; ++i) {
+    tp.dw[i] = all[i];
+    tiles += all[i].tiles;
+    roles.add(ids[i], 1.0);
   }
-  return DYNMO_OK;
+  return launch_shape<MODE_DW>(kind, tp, E * tiles, roles, st);
 }
 
 }  // namespace dynmo

@@ -385,15 +385,20 @@ static int32_t permute_run(const dynmo_desc* d, const void* x, const int32_t* ex
                            int32_t* src_slot, int32_t* dst_pos, int32_t* chunk_counts, hipStream_t st) {
   const int n_slots = d->T * d->k;
   const int nc = n_chunks_of(d);
-  // one launch for few slots; the profiling step times the parts by name
-  if (n_slots > 0 && n_slots <= kOneSlots && !g_profile_on.load(std::memory_order_relaxed)) {
+  if (n_slots > 0 && n_slots <= kOneSlots) {  // one launch for few slots
     int tokens = (d->T + kOneBlocks - 1) / kOneBlocks;
     if (tokens < kOneTokens) tokens = kOneTokens;
     const unsigned blocks = (unsigned)((d->T + tokens - 1) / tokens);
     const int row_vecs = (int)((size_t)d->H * elem_bytes(d->dtype) / 16);
-    permute_one_kernel<<<dim3(blocks), dim3(kOneThreads), 0, st>>>(expert_idx, (const u32x4*)x, (u32x4*)x_p, seg_offsets, src_slot,
-                                                                   dst_pos, d->T, d->k, d->E, tokens, row_vecs);
-    DYNMO_LAUNCH_CHECK();
+    ProfRoles roles;  // by the bytes each part reads and writes
+    roles.add(K_PERMUTE_COUNT, 4.0 * n_slots);
+    roles.add(K_PERMUTE_SCAN, 4.0 * (d->E + 1));
+    roles.add(K_PERMUTE_SCATTER, 8.0 * n_slots);
+    if (x_p) roles.add(K_PERMUTE_ROWS, ((double)d->T + n_slots) * row_vecs * 16);
+    DYNMO_TIMED_LAUNCH(roles, st,
+                       permute_one_kernel<<<dim3(blocks), dim3(kOneThreads), 0, st>>>(expert_idx, (const u32x4*)x, (u32x4*)x_p,
+                                                                                      seg_offsets, src_slot, dst_pos, d->T, d->k,
+                                                                                      d->E, tokens, row_vecs));
     return DYNMO_OK;
   }
   if (nc > 0) {

@@ -32,20 +32,35 @@ enum KernelId {
   K_COUNT
 };
 
+// The roles a launch fills.  Profiling must time the launches that a step makes, so a launch that does the work of several
+// roles stays one launch; its duration is divided among them in proportion to their work (flops or bytes).
+struct ProfRoles {
+  static constexpr int kMax = 4;
+  int n = 0;
+  KernelId id[kMax];
+  double work[kMax];
+  ProfRoles(KernelId only) { add(only, 1.0); }
+  ProfRoles() {}
+  void add(KernelId role, double amount) {
+    id[n] = role;
+    work[n++] = amount;
+  }
+};
+
 extern std::atomic<bool> g_profile_on;
-// profile_begin records the start event of a new pair for kernel role `id` and returns the
+// profile_begin records the start event of a new pair for the given kernel roles and returns the
 // pair's stop event (nullptr if no pair could be made: too many pending, or no event);
 // profile_end records exactly that stop event, so concurrent launches of one role from
 // several host threads cannot mix up each other's pairs.
-hipEvent_t profile_begin(KernelId id, hipStream_t st);
+hipEvent_t profile_begin(const ProfRoles& roles, hipStream_t st);
 void profile_end(hipEvent_t stop, hipStream_t st);
 
 // Brackets one kernel launch with an event pair when profiling is enabled.
 struct ProfScope {
   hipStream_t st;
   hipEvent_t stop;
-  ProfScope(KernelId id, hipStream_t st_) : st(st_), stop(nullptr) {
-    if (g_profile_on.load(std::memory_order_relaxed)) stop = profile_begin(id, st);
+  ProfScope(const ProfRoles& roles, hipStream_t st_) : st(st_), stop(nullptr) {
+    if (g_profile_on.load(std::memory_order_relaxed)) stop = profile_begin(roles, st);
   }
   ~ProfScope() {
     if (stop) profile_end(stop, st);

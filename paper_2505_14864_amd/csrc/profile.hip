@@ -1,6 +1,7 @@
 #include "profile.h"
 
 #include <mutex>
+#include <new>
 #include <vector>
 
 namespace dynmo {
@@ -8,8 +9,16 @@ namespace dynmo {
 std::atomic<bool> g_profile_on{false};
 
 namespace {
+struct Pair {
+  hipEvent_t start, stop;
+  int holders;  // slots that have not folded it yet
+};
+struct Pending {
+  Pair* pair;
+  double share;  // of the pair's duration
+};
 struct Slot {
-  std::vector<hipEvent_t> start, stop;
+  std::vector<Pending> pending;
   double total_ms = 0.0;
   int64_t launches = 0;
 };
@@ -38,33 +47,41 @@ hipEvent_t get_event() {
 
 // Folds finished event pairs of one slot into its totals.  Waits for each stop event.
 int32_t drain(Slot& s) {
-  for (size_t i = 0; i < s.stop.size(); ++i) {
-    DYNMO_HIP_TRY(hipEventSynchronize(s.stop[i]));
+  for (const Pending& q : s.pending) {
+    DYNMO_HIP_TRY(hipEventSynchronize(q.pair->stop));
     float ms = 0.f;
-    DYNMO_HIP_TRY(hipEventElapsedTime(&ms, s.start[i], s.stop[i]));
-    s.total_ms += ms;
+    DYNMO_HIP_TRY(hipEventElapsedTime(&ms, q.pair->start, q.pair->stop));
+    s.total_ms += ms * q.share;
     s.launches += 1;
-    g_free.push_back(s.start[i]);
-    g_free.push_back(s.stop[i]);
   }
-  s.start.clear();
-  s.stop.clear();
+  for (const Pending& q : s.pending) {
+    if (--q.pair->holders > 0) continue;
+    g_free.push_back(q.pair->start);
+    g_free.push_back(q.pair->stop);
+    delete q.pair;
+  }
+  s.pending.clear();
   return DYNMO_OK;
 }
 }  // namespace
 
-hipEvent_t profile_begin(KernelId id, hipStream_t st) {
+hipEvent_t profile_begin(const ProfRoles& roles, hipStream_t st) {
   std::lock_guard<std::mutex> lk(g_mu);
-  Slot& s = g_slots[id];
-  if (s.start.size() >= kMaxPending) return nullptr;
-  hipEvent_t a = get_event(), b = get_event();
+  double all = 0.0;
+  for (int i = 0; i < roles.n; ++i) {
+    if (g_slots[roles.id[i]].pending.size() >= kMaxPending) return nullptr;
+    all += roles.work[i];
+  }
+  Pair* pair = new (std::nothrow) Pair;
+  hipEvent_t a = pair ? get_event() : nullptr, b = pair ? get_event() : nullptr;
   if (!a || !b) {
     if (a) g_free.push_back(a);
     if (b) g_free.push_back(b);
+    delete pair;
     return nullptr;
   }
-  s.start.push_back(a);
-  s.stop.push_back(b);
+  *pair = Pair{a, b, roles.n};
+  for (int i = 0; i < roles.n; ++i) g_slots[roles.id[i]].pending.push_back(Pending{pair, roles.work[i] / all});
   (void)hipEventRecord(a, st);
   return b;
 }

@@ -560,6 +560,50 @@ def test_profiling_step_reports_every_kernel():
     B.dynmo_profile_reset()
 
 
+@pytest.mark.parametrize("dtype,rows_copied", [("f32", True), ("bf16", True), ("bf16", False)])
+def test_profiling_step_times_the_launches_of_a_step(dtype, rows_copied):
+    """A launch that does the work of several roles is one launch with profiling on as well, its time divided by flops or
+    bytes: the roles' times stand in exactly that proportion, which separate launches never do, and their sum is the
+    launch's."""
+    say("profiling step, shared launches %s %s" % (dtype, rows_copied))
+    T, H, F, E, k = 256, 128, 256, 4, 2
+    w = wl.scaled(wl.CONFIGS[1], T=T, H=H, F=F, E=E, k=k, dtype=dtype, bias=(), seed=54)
+    inp = wl.make_inputs(w, threads=1)
+    dev = {n: to_device(a) for n, a in inp.items()}
+    layer = RoutedFFNLayer(T, H, F, E, k, dtype, "moe")
+
+    def step():
+        layer.route_topk(dev["logits"])
+        layer.forward(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+        layer.backward(dev["dout"], dev["Wg"], dev["Wu"], dev["Wd"])
+        if not rows_copied:
+            layer.forward_gather(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+
+    step()
+    B.dynmo_profile_enable(False)
+    B.dynmo_profile_reset()
+    B.dynmo_profile_enable(True)
+    for _ in range(3):
+        step()
+    B.dynmo_profile_enable(False)
+    got = {B.dynmo_profile_kernel_name(i): B.dynmo_profile_read(i) for i in range(B.dynmo_profile_kernel_count())}
+    B.dynmo_profile_reset()
+
+    def same(a, b):
+        return abs(a - b) <= 1e-9 * max(a, b)
+
+    (dwd, n), (dwg, _), (dwu, _), (dx, _) = (got["ffn_" + r] for r in ("dWd", "dWg", "dWu", "dX"))
+    assert n == 3 and dwd > 0.0 and same(dwd, dwg) and same(dwd, dwu)
+    if dtype == "f32":
+        assert same(dx, 2.0 * dwd)  # and so are the four together
+    permutes = 3 if rows_copied else 6
+    count, scan, scatter, rows = (got["permute_" + r] for r in ("count", "scan", "scatter", "rows"))
+    assert count[1] == scan[1] == scatter[1] == permutes and rows[1] == 3
+    assert same(scatter[0], 2.0 * count[0]) and same(scan[0] * T * k, count[0] * (E + 1))
+    if rows_copied:
+        assert same(rows[0] * 4 * T * k, count[0] * (T + T * k) * H * (4 if dtype == "f32" else 2))
+
+
 def test_bad_arguments_on_the_gpu():
     d = B.make_desc(64, 64, 64, 4, 2, "bf16")
     x = torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda")
