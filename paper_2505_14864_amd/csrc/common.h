@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "../../include/dynmo.h"
 
 namespace dynmo {
@@ -45,6 +47,20 @@ inline int32_t check_desc(const dynmo_desc* d) {
 template <typename... P>
 inline bool misaligned16(P... ptrs) {
   return (((uintptr_t)(const void*)ptrs | ...) & 15) != 0;
+}
+
+// Whether any of the `written` buffers shares memory with any of the `read` ones (null ones aside).  A launch that stands
+// for several launches in a row must not be taken then: a caller may write a result over an input that the
+// launches before it were the last to read.
+struct Buffer {
+  const void* p;
+  size_t bytes;
+};
+inline bool any_overlap(std::initializer_list<Buffer> written, std::initializer_list<Buffer> read) {
+  for (const Buffer& w : written)
+    for (const Buffer& r : read)
+      if (w.p && r.p && (uintptr_t)w.p < (uintptr_t)r.p + r.bytes && (uintptr_t)r.p < (uintptr_t)w.p + w.bytes) return true;
+  return false;
 }
 
 inline size_t elem_bytes(int32_t dtype) { return dtype == DYNMO_BF16 ? 2 : 4; }

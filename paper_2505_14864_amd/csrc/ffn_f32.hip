@@ -412,12 +412,12 @@ __device__ __forceinline__ void weight_grad(const float* P, int M, const float* 
 // are long (2 F) and whose tiles are few, then dWd, dWg and dWu, which fill the compute units meanwhile.
 //   T=1500 H=516 F=1030 E=8 k=2 (459 dX tiles, 3672 others):   four launches 242 us, one 204 (fp32 matrix rate: 131)
 //   T=256 H=128 F=256 E=4 k=2 (24 and 96):                      36, 17
-// `n` tiles in all; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
+// This launch covers the list from `first` to `end`; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
 template <int VF, bool WIDE>
-__global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int n, int dx_tiles, int dw_tiles) {
+__global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int first, int end, int dx_tiles, int dw_tiles) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
-  int r = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-  if (r >= n) return;
+  int r = first + (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (r >= end) return;
   if (r < dx_tiles) return input_grad<VF, WIDE>(p, r, lds);
   r -= dx_tiles;
   const int which = r / dw_tiles;  // 0 = dWd (P = dY, Q = A), 1 = dWg (dG, x_p), 2 = dWu (dU, x_p)
@@ -450,13 +450,27 @@ static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
   if (m_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF, WIDE><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
   // the weight gradients are written for every expert, rows or not
   const int dx_tiles = (int)(th * m_tiles), dw_tiles = (int)(tf * th * d->E);
+  auto launch = [&](const ProfRoles& roles, int first, int n) -> int32_t {
+    if (n == 0) return DYNMO_OK;
+    const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
+    DYNMO_TIMED_LAUNCH(roles, st, f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(
+                                      p, first, first + n, dx_tiles, dw_tiles));
+    return DYNMO_OK;
+  };
+  const KernelId ids[3] = {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU};
+  const size_t rows = (size_t)d->T * d->k * d->H * 4, tokens = (size_t)d->T * d->H * 4, weights = (size_t)d->E * d->F * d->H * 4;
+  if (any_overlap({{p.dWd, weights}, {p.dWg, weights}, {p.dWu, weights}},
+                  {{p.dy, rows}, {p.x, rows}, {p.Wg, weights}, {p.Wu, weights}, {p.fold.res, tokens}}) ||
+      any_overlap({{p.C, rows}, {p.fold.out, tokens}}, {{p.dy, rows}, {p.x, rows}})) {
+    // one after the other if one product's result is to be written over another's input
+    int32_t rc = launch(K_FFN_DX, 0, dx_tiles);
+    for (int s = 0; s < 3 && rc == DYNMO_OK; ++s) rc = launch(ids[s], dx_tiles + s * dw_tiles, dw_tiles);
+    return rc;
+  }
   ProfRoles roles;  // by flops
   if (dx_tiles > 0) roles.add(K_FFN_DX, 2.0);
-  for (KernelId id : {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU}) roles.add(id, 1.0);
-  const int n = dx_tiles + 3 * dw_tiles, width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
-  DYNMO_TIMED_LAUNCH(roles, st, f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(
-                                    p, n, dx_tiles, dw_tiles));
-  return DYNMO_OK;
+  for (KernelId id : ids) roles.add(id, 1.0);
+  return launch(roles, 0, dx_tiles + 3 * dw_tiles);
 }
 
 // Whether 64 rows of an operand can span 2 GiB (the rows of a gathered input as a whole stay below that)

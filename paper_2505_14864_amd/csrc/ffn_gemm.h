@@ -112,7 +112,7 @@ enum TileKind {
 // ffn_tile.hip: a row-segmented product (any mode but MODE_DW; MODE_GATEUP not on 128 x 256 tiles), and the three weight gradients.
 // DYNMO_EINVAL for a kind that is none of its tiles.
 int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st);
-int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
+int32_t ffn_tile_dw(TileKind kind, const dynmo_desc* d, const int32_t* seg, const bf16_t* dy_p, const bf16_t* x_p,
                     const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
 
 // ffn_skinny.hip: MODE_GATEUP, MODE_DOWN or MODE_DOWN_FOLD with few rows per expert; at most `max_experts` experts have

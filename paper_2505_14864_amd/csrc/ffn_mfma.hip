@@ -1393,7 +1393,7 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.
   const TileKind dw_kind = kernel_for(d, MODE_DW);
   if (dw_kind != TILE_256) {
-    rc = ffn_tile_dw(dw_kind, seg, d->E, d->H, d->F, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
+    rc = ffn_tile_dw(dw_kind, d, seg, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
                      (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);
     if (rc) return rc;
   } else {

@@ -440,8 +440,9 @@ int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmPa
   return DYNMO_EINVAL;
 }
 
-int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, const bf16_t* dy_p, const bf16_t* x_p,
+int32_t ffn_tile_dw(TileKind kind, const dynmo_desc* d, const int32_t* seg, const bf16_t* dy_p, const bf16_t* x_p,
                     const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st) {
+  const int E = d->E, H = d->H, F = d->F;
   const int r = rows_of(kind), c = cols_of(kind);
   const int hf = ((H + r - 1) / r) * ((F + c - 1) / c), fh = ((F + r - 1) / r) * ((H + c - 1) / c);
   const DwSet all[3] = {{dy_p, A, dWd, H, F, hf}, {dG, x_p, dWg, F, H, fh}, {dU, x_p, dWu, F, H, fh}};
@@ -449,15 +450,21 @@ int32_t ffn_tile_dw(TileKind kind, const int32_t* seg, int E, int H, int F, cons
   TileParams tp = {};
   tp.g.seg = seg;
   tp.g.E = E;
-  tp.sets = 3;
-  int tiles = 0;
-  ProfRoles roles;  // equal flops
-  for (int i = 0; i < 3; ++i) {
-    tp.dw[i] = all[i];
-    tiles += all[i].tiles;
-    roles.add(ids[i], 1.0);
+  // One launch for the three products; one each if a gradient is to be written over the rows
+  const size_t rows = (size_t)d->T * d->k * H * 2, weights = (size_t)E * F * H * 2;
+  tp.sets = any_overlap({{dWd, weights}, {dWg, weights}, {dWu, weights}}, {{dy_p, rows}, {x_p, rows}}) ? 1 : 3;
+  for (int s = 0; s < 3; s += tp.sets) {
+    int tiles = 0;
+    ProfRoles roles;  // equal flops
+    for (int i = 0; i < tp.sets; ++i) {
+      tp.dw[i] = all[s + i];
+      tiles += all[s + i].tiles;
+      roles.add(ids[s + i], 1.0);
+    }
+    const int32_t rc = launch_shape<MODE_DW>(kind, tp, E * tiles, roles, st);
+    if (rc) return rc;
   }
-  return launch_shape<MODE_DW>(kind, tp, E * tiles, roles, st);
+  return DYNMO_OK;
 }
 
 }  // namespace dynmo

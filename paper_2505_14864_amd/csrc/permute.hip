@@ -385,7 +385,10 @@ static int32_t permute_run(const dynmo_desc* d, const void* x, const int32_t* ex
                            int32_t* src_slot, int32_t* dst_pos, int32_t* chunk_counts, hipStream_t st) {
   const int n_slots = d->T * d->k;
   const int nc = n_chunks_of(d);
-  if (n_slots > 0 && n_slots <= kOneSlots) {  // one launch for few slots
+  // One launch for few slots, unless dst_pos or x_p are to be written over expert_idx, which all of its workgroups read.
+  const size_t index_bytes = (size_t)n_slots * sizeof(int32_t);
+  if (n_slots > 0 && n_slots <= kOneSlots &&
+      !any_overlap({{dst_pos, index_bytes}, {x_p, (size_t)n_slots * d->H * elem_bytes(d->dtype)}}, {{expert_idx, index_bytes}})) {
     int tokens = (d->T + kOneBlocks - 1) / kOneBlocks;
     if (tokens < kOneTokens) tokens = kOneTokens;
     const unsigned blocks = (unsigned)((d->T + tokens - 1) / tokens);

@@ -159,6 +159,26 @@ def test_permute_moe(T, E, k, H, dtype):
     assert np.array_equal(to_host(x_p)[:R], rx)
 
 
+def test_permute_over_its_own_indices():
+    """dst_pos written over expert_idx: a slot's index is read before its position takes its place, for few slots as for many."""
+    for T, E, k in ((1000, 8, 2), (8192, 5, 1), (9000, 16, 2)):
+        say("permute in place T=%d E=%d k=%d" % (T, E, k))
+        rng = np.random.default_rng(T)
+        ei = rng.integers(-1, E, size=(T, k)).astype(np.int32)
+        x = rng.standard_normal((T, 16)).astype(np.float32)
+        ref_x_p, ref_seg, ref_src, ref_dst = orc.permute(x, ei, E)
+        d = B.make_desc(T, 16, 16, E, k, "f32")
+        idx = to_device(ei)
+        seg = torch.empty(E + 1, dtype=torch.int32, device="cuda")
+        src = torch.empty(T * k, dtype=torch.int32, device="cuda")
+        x_p = torch.empty((T * k, 16), dtype=torch.float32, device="cuda")
+        ws = torch.empty(B.dynmo_permute_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+        B.dynmo_permute(d, to_device(x), idx, x_p, seg, src, idx, ws)
+        R = int(ref_seg[-1])
+        assert np.array_equal(to_host(idx), ref_dst) and np.array_equal(to_host(seg), ref_seg)
+        assert np.array_equal(to_host(src)[:R], ref_src[:R]) and np.array_equal(to_host(x_p)[:R], ref_x_p[:R])
+
+
 def test_permute_unrouted_empty_and_deterministic():
     say("permute unrouted/empty/determinism")
     rng = np.random.default_rng(9)
@@ -293,6 +313,36 @@ def test_f32_rows_beyond_32_bit_offsets(T, H, F):
     check("dx", dx, dG @ Wg.double() + dU @ Wu.double(), 16 * max(2 * F, H))
     for name, got, q in (("dWg", dWg, dG), ("dWu", dWu, dU)):
         check(name, got.view(1, -1), (q.t() @ x.double()).view(1, -1), max(T, H))
+
+
+@pytest.mark.parametrize("dtype,over", [("bf16", {"dWg": "dy_p"}), ("bf16", {"dWu": "dy_p", "dx_p": "x_p"}),
+                                        ("f32", {"dWg": "dy_p"}), ("f32", {"dWg": "Wg", "dWu": "Wu"})])
+def test_gradients_written_over_inputs(dtype, over):
+    """Gradients written over an input that only earlier products of the backward pass read (order: dA, dWd, dWg, dWu, dX for bf16,
+    dA, dX, dWd, dWg, dWu for fp32) are those of separate buffers, bit for bit."""
+    say("gradients over inputs %s %s" % (dtype, over))
+    T, H, F, E = 512, 256, 256, 2  # T rows of H as large as the E weights of F x H
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    d = B.make_desc(T, H, F, E, 1, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(77)
+
+    def normal(*shape):
+        return torch.empty(shape, dtype=td, device="cuda").normal_(0.0, 0.3, generator=gen)
+
+    seg = torch.tensor([0, 200, T], dtype=torch.int32, device="cuda")
+    given = {"dy_p": normal(T, H), "x_p": normal(T, H), "G": normal(T, F), "U": normal(T, F), "Wg": normal(E, F, H),
+             "Wu": normal(E, F, H), "Wd": normal(E, H, F)}
+    ws = torch.empty(B.dynmo_grouped_ffn_bwd_workspace_bytes(d), dtype=torch.uint8, device="cuda")
+    results = []
+    for placed in ({}, over):
+        b = {n: t.clone() for n, t in given.items()}
+        shapes = {"dx_p": (T, H), "dWg": (E, F, H), "dWu": (E, F, H), "dWd": (E, H, F)}
+        o = {n: b[placed[n]].view(s) if n in placed else torch.empty(s, dtype=td, device="cuda") for n, s in shapes.items()}
+        B.dynmo_grouped_ffn_bwd(d, b["dy_p"], b["x_p"], b["G"], b["U"], seg, b["Wg"], b["Wu"], b["Wd"], o["dx_p"], o["dWg"],
+                                o["dWu"], o["dWd"], ws)
+        results.append({n: t.clone() for n, t in o.items()})
+    for n, t in results[0].items():
+        assert torch.equal(t, results[1][n]), n
 
 
 def test_moe_layer_empty_expert_zero_dw():
