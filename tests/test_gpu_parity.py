@@ -20,6 +20,20 @@ def say(msg):
     print(msg, flush=True)
 
 
+def kernels(w):
+    """The kernel of each FFN product of a workload, so that a test can insist on the one it is written for."""
+    d = B.make_desc(w.T, w.H, w.F, w.E, w.k, w.dtype)
+    return {p: B.dynmo_grouped_ffn_kernel(d, p) for p in B.FFN_PRODUCTS}
+
+
+def chunks_of_last_round(counts, N, K, phases):
+    """Into how many chunks of k the 256x256 kernel splits the tiles of the last round of a down (one phase) or dX product
+    (two): 256 workgroups over 8 XCDs, at most half a round of tiles, chunks of at least 16 k tiles of 64."""
+    tail = sum(-(-c // 256) for c in counts) * -(-N // 256) % 256
+    patches = -(-tail // 32)
+    return max(1, min(8 // patches, -(-K // 64) * phases // 16)) if 0 < patches <= 4 else 1
+
+
 # --------------------------------------------------------------------------
 # routing
 # --------------------------------------------------------------------------
@@ -364,6 +378,8 @@ def test_moe_layer_empty_expert_zero_dw():
 def test_mod_layer_small(Bn, S, cap, H, F):
     say("mod layer B=%d S=%d cap=%d" % (Bn, S, cap))
     w = wl.scaled(wl.CONFIGS[4], T=Bn * S, B=Bn, S=S, cap=cap, H=H, F=F, seed=31)
+    if S >= 2048:
+        assert kernels(w)["gateup"] == kernels(w)["dA"] == "256x256"
     inp = wl.make_inputs(w, threads=1)
     layer = RoutedFFNLayer(w.T, H, F, 1, 1, "bf16", "mod")
     dev = {n: to_device(a) for n, a in inp.items()}
@@ -854,15 +870,21 @@ def test_moe_full_size_capacity_and_gather():
     assert torch.equal(layer.out, other.out)
 
 
-@pytest.mark.parametrize("H,F", [(512, 1536), (256, 4096), (768, 2048)])
-def test_split_last_round_small_problem(H, F):
-    """Few output tiles and a long contraction: the down and dX products split their tiles
-    along k over the XCDs (for F = 1536 into three chunks, the middle one straddling the
-    two phases of dX) and a second pass sums the partial tiles; full check against the oracle."""
+@pytest.mark.parametrize("H,F,down,dx", [(512, 1536, 0, 0), (256, 4096, 0, 8), (768, 2048, 0, 0), (256, 2600, 0, 5),
+                                         (512, 5200, 5, 8), (768, 8200, 8, 8)])
+def test_split_last_round_small_problem(H, F, down, dx):
+    """Few output tiles and a long contraction: the down and dX products on 256x256 tiles split their tiles along k over
+    the XCDs into `down` and `dx` chunks (dX with F = 2600 into five, the middle one straddling its two phases) and a second
+    pass sums the partial tiles; 0: the product is short enough for smaller tiles.  Full check against the oracle."""
     say("split-k small problem H=%d F=%d" % (H, F))
     w = wl.scaled(wl.CONFIGS[2], T=330, H=H, F=F, E=2, k=1, seed=81)
     inp = wl.make_inputs(w, threads=4)
     layer = run_moe(w, inp)
+    counts, _ = layer.load()
+    for product, chunks, phases in (("down", down, 1), ("dX", dx, 2)):
+        assert (kernels(w)[product] == "256x256") == (chunks > 0)
+        if chunks:
+            assert chunks_of_last_round(counts, H, F, phases) == chunks
     f = f32_inputs(inp)
     ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
     check_layer_full(layer, ref, w.dtype)
@@ -873,11 +895,14 @@ def test_split_last_round_small_problem(H, F):
 
 @pytest.mark.parametrize("T", [1, 15, 16, 17, 63, 64, 65, 127, 129, 191, 193, 255, 256, 257, 300, 511])
 def test_ragged_row_tile_every_row_block_count(T):
-    """One expert with T rows: the last row tile holds T mod 256 valid rows, and a wavefront of the grouped
-    GEMM has work in ceil((valid 16-row blocks - its position) / 4) of its four row blocks -- every count
-    from none to four occurs over these T, in all seven products; full check against the oracle."""
+    """One expert with T rows: the last 64-row tile holds T mod 64 valid rows in one to four 16-row blocks, dealt to two
+    wavefronts -- every count from none to two occurs over these T, in all seven products (the forward ones of up to 16 rows
+    go to the few-rows kernel, one row block); full check against the oracle.  The 256-row tiles: see
+    test_large_tiles_every_row_block_count."""
     say("ragged row tile T=%d" % T)
     w = wl.scaled(wl.CONFIGS[2], T=T, H=128, F=320, E=1, k=1, seed=8300 + T)
+    few = {"gateup": T <= 16, "down": T <= 8}
+    assert kernels(w) == {p: "few_rows" if few.get(p) else "64x64" for p in B.FFN_PRODUCTS}
     inp = wl.make_inputs(w, threads=2)
     layer = run_moe(w, inp)
     f = f32_inputs(inp)
@@ -885,10 +910,10 @@ def test_ragged_row_tile_every_row_block_count(T):
     check_layer_full(layer, ref, w.dtype)
 
 
-@pytest.mark.parametrize("counts", [(100, 300, 700, 1300, 1800, 3400), (3329, 257, 0, 1, 2049, 1537)])
-def test_tile_order_mixed_row_tile_counts(counts):
+@pytest.mark.parametrize("counts,dA", [((100, 300, 700, 1300, 1800, 3400), "128x256"), ((3329, 257, 0, 1, 2049, 1537), "256x256")])
+def test_tile_order_mixed_row_tile_counts(counts, dA):
     """Experts with 0, 1, 2, 3, 6, 7, 8, 9 and 14 row tiles in one layer whose products have 8 or 16 column
-    tiles: the grouped GEMM walks an expert's tiles in one chunk, in several chunks of about four (or eight) row
+    tiles: the 256x256 kernel (gate/up, down, dX and, in the second layer, dA) walks an expert's tiles in one chunk, in several chunks of about four (or eight) row
     tiles, or in column groups, depending on its row-tile count, deals runs of 32 tiles round robin to the XCDs,
     and every workgroup works out from the run it is in which operand lines it prefetches; a tile left out or
     done twice by any of that shows in the full check against the oracle (top-1 routing with exactly these
@@ -896,6 +921,7 @@ def test_tile_order_mixed_row_tile_counts(counts):
     say("tile order counts=%s" % (counts,))
     T, E = sum(counts), len(counts)
     w = wl.scaled(wl.CONFIGS[2], T=T, H=2048, F=2048, E=E, k=1, seed=8400 + counts[0])
+    assert kernels(w) == {"gateup": "256x256", "down": "256x256", "dA": dA, "dX": "256x256", "dW": "128x256"}
     inp = wl.make_inputs(w, threads=4)
     rng = np.random.default_rng(w.seed)
     expert_of = rng.permutation(np.repeat(np.arange(E), counts))
@@ -909,14 +935,21 @@ def test_tile_order_mixed_row_tile_counts(counts):
     check_layer_full(layer, ref, w.dtype)
 
 
-@pytest.mark.parametrize("T,H,F,E,k", [(600, 520, 1032, 8, 2), (1100, 264, 4104, 3, 1), (129, 72, 2056, 1, 1), (900, 1032, 200, 33, 4),
-                                       (64, 2056, 136, 2, 1), (700, 2056, 2056, 4, 2), (1100, 2056, 520, 16, 4)])
-def test_small_products_tile_edges(T, H, F, E, k):
-    """Products that go to the 128 x 256, 128 and 64 tiles (and, beside them, down and dX of a long k that do not): k not a
-    multiple of the k step, one row or column block past a tile, experts without rows; rows gathered inside the
-    first product give the same bits."""
+@pytest.mark.parametrize("T,H,F,E,k,expected", [
+    (600, 520, 1032, 8, 2, "128x128 64x64 64x64 64x64 128x128"), (1100, 264, 4104, 3, 1, "256x256 256x256 128x128 256x256 128x128"),
+    (129, 72, 2056, 1, 1, "64x64 64x64 64x64 256x256 64x64"), (900, 1032, 200, 33, 4, "128x128 256x256 64x64 128x256 128x128"),
+    (64, 2056, 136, 2, 1, "64x64 64x64 64x64 64x64 64x64"), (700, 2056, 2056, 4, 2, "128x128 128x128 128x128 256x256 128x256"),
+    (1100, 2056, 520, 16, 4, "128x128 256x256 128x128 256x256 128x256"),
+    (3700, 1032, 288, 8, 4, "256x256 128x256 128x128 128x256 128x128"),  # short sums: down and dX, whole k steps
+    (3700, 72, 1288, 8, 4, "256x256 64x64 128x256 64x64 64x64"),         # dA with a ragged k
+    (1200, 520, 600, 16, 4, "128x128 128x128 128x128 128x128 128x128")])
+def test_small_products_tile_edges(T, H, F, E, k, expected):
+    """Products that go to the 128 x 256, 128 and 64 tiles (`expected`: gate/up, down, dA, dX, dW), and beside them those that
+    do not: k not a multiple of the k step, one row or column block past a tile, experts without rows; rows gathered inside
+    the first product give the same bits."""
     say("small products T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
     w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=k, zipf_s=1.5, seed=8800 + T)
+    assert " ".join(kernels(w).values()) == expected
     inp = wl.make_inputs(w, threads=2)
     layer = run_moe(w, inp)
     f = f32_inputs(inp)
@@ -929,15 +962,17 @@ def test_small_products_tile_edges(T, H, F, E, k):
     assert torch.equal(layer.out, out)
 
 
-@pytest.mark.parametrize("counts,H,F", [((1,), 72, 136), ((16,), 200, 520), ((1, 0, 17, 3), 264, 2056), ((40, 0, 2, 1, 3, 5, 2, 65), 520, 4104),
-                                        ((8, 8), 2048, 4096)])
-def test_few_rows_per_expert(counts, H, F):
-    """Forward products of experts with few rows (weights straight into the matrix operands, k dealt to the
-    wavefronts): one to four row blocks and a second pass over them, experts without rows, k and weight rows that
-    fill no wavefront's share; with the rows gathered, and with the combine folded into the last product."""
+@pytest.mark.parametrize("counts,H,F,few", [((1,), 72, 136, "gateup down"), ((16,), 200, 520, "gateup"), ((1, 0, 17, 3), 264, 2056, "down"),
+                                            ((40, 0, 2, 1, 3, 5, 2, 65), 520, 4104, ""), ((8, 8), 2048, 4096, "down")])
+def test_few_rows_per_expert(counts, H, F, few):
+    """Whole layers with few rows per expert, forward and backward, some of their forward products (`few`) with the weights
+    straight into the matrix operands: one and two row blocks, experts without rows, k and weight rows that fill no wavefront's
+    share; with the rows gathered, and with the combine folded into the last product.  (More row blocks, row chunks and
+    wider workgroups: test_few_rows_forward.)"""
     say("few rows per expert counts=%s H=%d F=%d" % (counts, H, F))
     T, E = sum(counts), len(counts)
     w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=1, seed=9000 + T)
+    assert " ".join(p for p, kernel in kernels(w).items() if kernel == "few_rows") == few
     inp = wl.make_inputs(w, threads=2)
     rng = np.random.default_rng(w.seed)
     logits = rng.standard_normal((T, E)).astype(np.float32)
@@ -972,20 +1007,21 @@ def few_rows_layer(counts, k, H, F, seed):
     return layer, normal(1.0, T, H), (normal(0.02, E, F, H), normal(0.02, E, F, H), normal(0.02, E, H, F))
 
 
-@pytest.mark.parametrize("counts,k,H,F", [
-    ((70, 1, 0, 17, 33, 2, 0, 5), 1, 1024, 8192),       # gate/up, 64 weight rows per workgroup: 1, 2 and 4 row blocks, two chunks
-    ((33, 1, 0, 17, 2, 0, 5, 6), 1, 1032, 8200),        # the same with ragged k and columns; down, 16 weight rows
-    ((0, 40, 0, 2, 0, 0, 0, 3), 1, 2048, 2056),         # down, 32 weight rows, most experts without rows
-    ((130, 0, 1) + (2,) * 15 + (0,) * 30, 1, 2048, 2048),  # down, 64 weight rows, three chunks of one expert
-    ((33, 0, 1) + (2,) * 15 + (0,) * 30, 1, 2048, 2048),   # the same in one chunk
-    ((200, 4, 0, 2) + (0,) * 28, 2, 1024, 4096),        # more rows on an expert than tokens (both slots of a token on it)
+@pytest.mark.parametrize("counts,k,H,F,few", [
+    ((70, 1, 0, 17, 33, 2, 0, 5), 1, 1024, 8192, "gateup"),  # gate/up, 64 weight rows per workgroup: 1, 2 and 4 row blocks, two chunks
+    ((33, 1, 0, 17, 2, 0, 5, 6), 1, 1032, 8200, "gateup down"),  # the same with ragged k and columns; down, 16 weight rows
+    ((0, 40, 0, 2, 0, 0, 0, 3), 1, 2048, 2056, "down"),  # down, 32 weight rows, most experts without rows
+    ((130, 0, 1) + (2,) * 15 + (0,) * 30, 1, 2048, 2048, "gateup down"),  # down, 64 weight rows, three chunks of one expert
+    ((33, 0, 1) + (2,) * 15 + (0,) * 30, 1, 2048, 2048, "gateup down"),   # the same in one chunk
+    ((200, 4, 0, 2) + (0,) * 28, 2, 1024, 4096, "gateup down"),  # more rows on an expert than tokens (both slots of a token on it)
 ])
-def test_few_rows_forward(counts, k, H, F):
+def test_few_rows_forward(counts, k, H, F, few):
     """The forward products that stream weights straight into the matrix operands, every row-block count and row chunk, with
     the rows copied and gathered, with and without the combine folded in, against 64 bits on the GPU."""
     say("few rows forward counts=%s k=%d H=%d F=%d" % (counts, k, H, F))
     layer, x, (Wg, Wu, Wd) = few_rows_layer(counts, k, H, F, 9100 + H + F)
     T, E = layer.T, layer.E
+    assert " ".join(p for p in B.FFN_PRODUCTS if B.dynmo_grouped_ffn_kernel(layer.d, p) == "few_rows") == few
     out = layer.forward(x, Wg, Wu, Wd)
     seg = to_host(layer.seg_offsets)
     assert seg.tolist() == np.concatenate([[0], np.cumsum(counts)]).tolist()
@@ -1046,6 +1082,7 @@ def test_large_tiles_every_row_block_count():
     counts = [256 + 16 * i + 1 + 7 * i % 16 for i in range(16)]
     T, E = sum(counts), len(counts)
     w = wl.scaled(wl.CONFIGS[2], T=T, H=1024, F=9216, E=E, k=1, seed=8900)
+    assert set(kernels(w).values()) == {"256x256"}
     inp = wl.make_inputs(w, threads=4)
     rng = np.random.default_rng(w.seed)
     logits = rng.standard_normal((T, E)).astype(np.float32)
@@ -1087,7 +1124,8 @@ def test_layer_under_graph_capture():
     and synchronisations in between; every replay must reproduce the eager results bit
     for bit, also after the inputs changed in place."""
     say("graph capture")
-    w = wl.scaled(wl.CONFIGS[2], T=900, H=256, F=2048, E=4, k=2, seed=95)  # down and dX split their tiles
+    w = wl.scaled(wl.CONFIGS[2], T=900, H=256, F=4608, E=4, k=2, seed=95)  # down and dX split their tiles
+    assert kernels(w)["down"] == kernels(w)["dX"] == "256x256"
     inp = wl.make_inputs(w, threads=2)
     dev = {n: to_device(a) for n, a in inp.items()}
     layer = RoutedFFNLayer(w.T, w.H, w.F, w.E, w.k, w.dtype, "moe")
@@ -1122,6 +1160,8 @@ def test_layer_under_graph_capture():
             dev["x"].copy_(x0)
             dev["logits"].copy_(l0)
         run()
+        counts, _ = layer.load()
+        assert chunks_of_last_round(counts, w.H, w.F, 1) > 1 and chunks_of_last_round(counts, w.H, w.F, 2) > 1
         eager = snapshot()
         for n in names:
             if getattr(layer, n).dtype.is_floating_point:
@@ -1166,13 +1206,31 @@ def test_random_shapes(seed):
 FOLDED_CASES = [
     ("mod", wl.scaled(wl.CONFIGS[4], T=4 * 256, B=4, S=256, cap=32, H=128, F=256, seed=91)),     # one ragged tile
     ("mod", wl.scaled(wl.CONFIGS[4], T=3 * 400, B=3, S=400, cap=230, H=520, F=328, seed=92)),    # several tiles, tails
-    ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 330, B=2, S=330, cap=165, H=512, F=1536, seed=93)),   # last product splits k
+    ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 330, B=2, S=330, cap=165, H=512, F=1536, seed=93)),
+    ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 330, B=2, S=330, cap=165, H=512, F=4608, seed=99)),   # 256x256, split, residual
+    ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 2048, B=2, S=2048, cap=2000, H=2304, F=1032, seed=100)),  # 256x256, no split, residual
     ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 130, B=2, S=130, cap=0, H=64, F=64, seed=94)),        # nothing routed
     ("mod", wl.scaled(wl.CONFIGS[4], T=2 * 100, B=2, S=100, cap=100, H=36, F=50, dtype="f32", seed=95)),  # fp32 kernels
-    ("moe", wl.scaled(wl.CONFIGS[2], T=330, H=256, F=4096, E=2, k=1, seed=96)),                  # top-1, no residual, split
+    ("moe", wl.scaled(wl.CONFIGS[2], T=330, H=256, F=4096, E=2, k=1, seed=96)),                  # top-1, no residual, dX splits
+    ("moe", wl.scaled(wl.CONFIGS[2], T=330, H=256, F=4224, E=2, k=1, seed=101)),                 # and down
+    ("moe", wl.scaled(wl.CONFIGS[2], T=4096, H=2304, F=1032, E=2, k=1, seed=102)),               # 256x256, no split
     ("moe", wl.scaled(wl.CONFIGS[1], T=300, H=36, F=50, E=4, k=1, seed=97)),                     # top-1 fp32
-    ("moe", wl.scaled(wl.CONFIGS[2], T=8000, H=1032, F=264, E=8, k=1, seed=98)),                 # top-1, short sums: 128 x 256 tiles
+    ("moe", wl.scaled(wl.CONFIGS[2], T=8000, H=1032, F=264, E=8, k=1, seed=98)),                 # top-1, ragged k
+    ("moe", wl.scaled(wl.CONFIGS[2], T=14000, H=1032, F=288, E=8, k=1, seed=103)),               # short sums: 128 x 256 tiles
 ]
+FOLDED_KERNELS = {99: "256x256 split", 100: "256x256", 101: "256x256 split", 102: "256x256", 103: "128x256"}  # by seed: down and dX
+
+
+def check_folded_kernels(w, counts):
+    """That the folded stores of a case are those of the kernel the case is there for."""
+    if w.seed not in FOLDED_KERNELS:
+        return
+    kernel, split = FOLDED_KERNELS[w.seed].split()[0], "split" in FOLDED_KERNELS[w.seed]
+    for product, phases in (("down", 1), ("dX", 2)):
+        assert kernels(w)[product] == kernel
+        if kernel == "256x256":
+            assert (chunks_of_last_round(counts, w.H, w.F, phases) > 1) == split
+
 
 
 def route_for(layer, mode, w, dev):
@@ -1203,6 +1261,7 @@ def test_forward_with_folded_combine(mode, w):
     assert (out_b is x_b) == (mode != "moe")
     b.backward(dev["dout"], dev["Wg"], dev["Wu"], dev["Wd"])
     torch.cuda.synchronize()
+    check_folded_kernels(w, a.load()[0])
     f = f32_inputs(inp)
     if mode == "moe":
         ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
@@ -1258,6 +1317,7 @@ def test_backward_with_folded_scatter(mode, w):
     dx_b = b.backward_folded(g_b, dev["Wg"], dev["Wu"], dev["Wd"])
     assert (dx_b is g_b) == (mode != "moe")
     torch.cuda.synchronize()
+    check_folded_kernels(w, a.load()[0])
     f = f32_inputs(inp)
     if mode == "moe":
         ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
