@@ -11,8 +11,8 @@
 // time; every 64 rows of an expert are workgroups of their own, so that an expert that took many rows keeps as many
 // workgroups busy as its rows need instead of walking its weights again and again.
 //
-// Measured, 64 rows over 8 experts, H=4096 F=14336: gate/up 410 us on 256-row tiles -> 333 (5.6 TB/s of weights), down
-// 201 -> 168 (5.6 TB/s); 8 rows, H=1024 F=4096, down 20 -> 10.  Loading the two halves of a line with the lanes of one
+// Measured, 64 rows over 8 experts, H=4096 F=14336: gate/up 446 us on 256-row tiles -> 330 (5.7 TB/s of weights), down
+// 188 -> 159 (5.9 TB/s); 8 rows, H=1024 F=4096, down 20 -> 10.  Loading the two halves of a line with the lanes of one
 // instruction or of two, and three instead of two workgroups per compute unit, measured the same.
 #include "ffn_gemm.h"
 

@@ -1,9 +1,9 @@
 // Permutation of routed token rows into contiguous per-expert segments, and its
 // backward.  The index part is a stable counting sort done without ordered
-// atomics: for few slots in one launch together with the rows (permute_one_kernel), else per-chunk histograms, a scan over chunks, then an in-chunk stable rank
-// from wavefront ballots.  The row movement is a token-centric copy: each source
-// row is read once and written to its (up to k) destinations with 16-byte
-// accesses.
+// atomics: for few slots in one launch together with the rows (permute_one_kernel),
+// else per-chunk histograms, a scan over chunks, then an in-chunk stable rank from
+// wavefront ballots.  The row movement is a token-centric copy: each source row is
+// read once and written to its (up to k) destinations with 16-byte accesses.
 #include <mutex>
 
 #include "common.h"
