@@ -1202,6 +1202,9 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //         -16 %, 3.9 -13 %, 5.1 +4 %.  Down, whose stores are the smallest part, up to 3.7 rounds, and only with whole k steps
 //         (4096 columns, k = 688, 64 experts: +14 to +18 % throughout);
 //       - where experts have so few rows that the half-empty last row tiles are a good part of the work.
+//     Gate/up stays on 256 x 256 tiles: a smaller tile's gate and up halves share too few operand bytes (16384 x 2048 x 1024, 64:
+//     185 / 201; 6000 x 2048 x 4096, 16: 244 / 276; 128000 x 1024 x 1024, 64: 538 / 686).  It would gain only a few tiles above one
+//     round (6000 x 512 x 1024, 16, 280 tiles: 38 / 28), and loses 10 % and more a few tiles below it.
 //     Over 3374 shapes (3 to 64 experts, k 512 to 4096, 0.5 to 9 rounds) the time is 0.944 (dA), 0.937 (dX) and 0.954 (down) of
 //     256 x 256 tiles alone on average, and more than 5 % above theirs for 18, 35 and 45 of them: the host knows the rows, not
 //     the segments, and estimates the tiles.
