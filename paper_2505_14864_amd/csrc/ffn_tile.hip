@@ -12,7 +12,9 @@
 // more to the 128 x 128 tile than two further stages (weight gradients of 64 experts, 256 rows each, 2048 x 1024:
 // 428 -> 377 us; 128 x 256 tiles, same LDS traffic per MFMA as 256 x 256: 358).  Operands that lie [row][k] in memory
 // keep that layout in LDS, operands that lie [k][row] are read with ds_read_b64_tr_b16; 16-byte pieces
-// are placed so that both reads are free of bank conflicts:
+// are placed so that the sixteen lanes of a fragment's k group fall into different banks.  By the counters the [k][row]
+// reads are free of conflicts (weight gradients 0 %); of the LDS cycles of products with one [row][k] operand 22 % are
+// conflicts, with two (gate/up, down) 44 %: the hardware serves the lanes of a 16-byte read in other groups.
 //   [row][k]: 64 bytes per row; the piece with k = 8 c .. of row r sits at r * 64 + ((c ^ ((r >> 2) & 3)) << 4)
 //   [k][row]: 64-byte blocks of 32 rows; block b of k-row k is stored as block b ^ (k & 3) (64 rows:
 //             b ^ ((k >> 1) & 1)), its two 32-byte halves swapped when bit 3 of k is set
