@@ -30,6 +30,8 @@
  *   - limits: 1 <= k <= E <= 64 (k <= 8 for the combine calls); for DYNMO_BF16
  *     H and F must be multiples of 8, for DYNMO_F32 H a multiple of 4.  Violations return DYNMO_EINVAL /
  *     DYNMO_EUNSUPPORTED before anything is launched.
+ *     bf16 results are right for H and F up to 2^22 (a tile's rows are addressed with 32-bit byte
+ *     offsets); fp32 has no such limit.
  *     The fp32 path is limited to floor(T*k / 64) + min(E, T*k) <= 65535 (DYNMO_EUNSUPPORTED
  *     beyond).
  *   - NaN in logits or scores is undefined input, and so is a token whose logits are all
