@@ -16,9 +16,15 @@
 // against 55-65 % of the nominal rate in a register-only loop); one wavefront alone
 // issues it at only 60 %, so two share each SIMD.  Operand tiles go from global memory
 // straight into LDS (buffer loads with an LDS destination, 1 KB per wavefront
-// instruction), one such load every third MFMA slot: no staging registers, no LDS
-// store instructions, and no burst of memory instructions that would hold up a
-// wavefront's MFMAs.  The tiles are unpadded and swizzled instead: the loads place
+// instruction): no staging registers, no LDS store instructions.  A wavefront is held at
+// such a load while the memory pipeline takes it, and its MFMAs wait behind it, so only
+// one wavefront of each SIMD (0 .. 3) loads, two every three MFMA slots, and the other
+// one keeps the matrix unit busy meanwhile; those (4 .. 7) issue the L2 prefetch.
+// Against loads by all eight (us; T H F E k): dX 4096 4096 14336 8 2: 1672 -> 1605, 3000
+// 2048 4096 16 2: 249 -> 229; dA 8192 4096 688 16 4: 290 -> 274; down of 1000 tokens of
+// the first layer 402 -> 368.  Long dense products gain less (gate/up of the first layer
+// 1641 -> 1606): the part is power-limited there and its clock falls from 1.90 to
+// 1.83 GHz while the matrix units' share of busy cycles rises from 64 to 69 %.  The tiles are unpadded and swizzled instead: the loads place
 // each 16-byte piece where the fragment reads are free of bank conflicts.  Tiles whose
 // memory layout has K contiguous are kept [row][k] in LDS; tiles whose memory layout
 // has the row index contiguous are kept [k][row] and read with ds_read_b64_tr_b16,
@@ -42,7 +48,8 @@ namespace dynmo {
 constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int kMfmaThreads = 512;              // eight wavefronts: two per SIMD
 constexpr int kWaves = kMfmaThreads / 64;
-constexpr int kPieces = 32 / kWaves;           // 1 KB pieces of an operand tile per wavefront
+constexpr int kLoaders = 4;                     // wavefronts 0 .. 3, one per SIMD, move the operand tiles; 4 .. 7 prefetch
+constexpr int kPieces = 32 / kLoaders;          // 1 KB pieces of an operand tile per loading wavefront
 constexpr int kTileBytes = 256 * 64 * 2;       // one operand tile (256 rows x 64 k, bf16), unpadded
 constexpr int kStageBytes = 2 * kTileBytes;    // A then B
 constexpr int kEpPitch = 132;                  // floats per row of an epilogue LDS patch (128 + 4: rows 4 apart are 16 banks apart)
@@ -64,7 +71,8 @@ constexpr int kSplitHdrInts = 4 + 4 * kMaxSplitTiles;  // {split, patches, slots
 
 static_assert(2 * kStageBytes <= kLdsBytes, "the two stages must fit in front of the tile table");
 static_assert(kLdsTotal <= 160 * 1024, "LDS of one compute unit");
-static_assert(kPieces * kWaves == 32, "a tile is 32 pieces of 1 KB");
+static_assert(kPieces * kLoaders == 32, "a tile is 32 pieces of 1 KB");
+static_assert(kWaves == 2 * kLoaders, "a prefetching wavefront for every loading one");
 
 // ---- global memory -> LDS ---------------------------------------------------------
 // An operand tile is 256 "rows" x 64 k = 32 pieces of 1 KB.  One buffer load with an
@@ -81,19 +89,19 @@ static_assert(kPieces * kWaves == 32, "a tile is 32 pieces of 1 KB");
 //   [k][row]: 512 bytes per k-row in eight 64-byte blocks of 32 rows; block b of k-row k
 //             sits at k * 512 + (((b & 4) | ((b ^ k) & 3)) << 6), and its two 32-byte halves
 //             (16 rows each) are swapped when bit 3 of k is set
-// A prefetch into L2: four bytes per lane (one lane per 128-byte line) through the same path
-// as the real loads, so that it retires in order with them; the data is dropped in LDS.
-__device__ __forceinline__ void touch_to_lds(desc_t d, uint32_t lds_offset, uint32_t global_offset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+// A prefetch into L2: four bytes per lane (one lane per 128-byte line), dropped in LDS.
+// The branch around it is inside the assembly: the k loop's body stays one block.
+__device__ __forceinline__ void touch_to_lds(desc_t d, uint32_t lds_offset, uint32_t global_offset, int on) {
+  asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Luntouched%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"
+               "buffer_load_dword %1, %2, 0 offen lds\n.Luntouched%=:"
                :
-               : "s"(lds_offset), "v"(global_offset), "s"(d)
-               : "memory");
+               : "s"(lds_offset), "v"(global_offset), "s"(d), "s"(on)
+               : "memory", "scc");
 }
 
 // Waits of the k loop, written out because the loads above are invisible to the compiler.
 __device__ __forceinline__ void wait_loads_and_lds() { __builtin_amdgcn_s_waitcnt(0x0070); }  // vmcnt(0) lgkmcnt(0)
-// all loads but the youngest (the L2 prefetch issued after a k tile's pieces), and every LDS read
-__device__ __forceinline__ void wait_pieces_and_lds() { __builtin_amdgcn_s_waitcnt(0x0071); }  // vmcnt(1) lgkmcnt(0)
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }            // lgkmcnt(0)
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {  // at most N loads still in flight
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
@@ -386,6 +394,8 @@ __device__ __forceinline__ void tile_in_expert(int mt, int nt, int r, bool tall,
 //     faster than 4 x 8 runs that move along F; dWd, H x F, gets the same from the first order).
 constexpr int kTallFrom = 13;
 constexpr int kShortK = 1024;
+constexpr int kTouchLead = 3;    // k tiles that the L2 prefetch is ahead (4: +-1 %)
+constexpr int kTouchRowTiles = 4;  // gate/up: only for experts with at most that many row tiles
 constexpr int kMinTouchKt = 16;  // L2 prefetch: only for k ranges of at least that many k tiles
 __device__ __forceinline__ void tile_in_expert(bool dw, bool short_k, int mt, int nt, int r, int& mi, int& ni) {
   const bool long_rows = dw && mt >= nt;
@@ -501,8 +511,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     hdr[3] = tail_tiles;
   }
   const int wave_u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the gate/up pairing: LDS rows 128..255 of operand B (the upper four wavefronts' pieces) come from the second matrix
-  const bool second_b = MODE == MODE_GATEUP && wave_u >= kWaves / 2;
+  // the gate/up pairing: LDS rows 128..255 of operand B (the upper two loading wavefronts' pieces) come from the second matrix
+  const bool second_b = MODE == MODE_GATEUP && wave_u % kLoaders >= kLoaders / 2;
   const bool gathered = MODE == MODE_GATEUP && p.gather != nullptr;
   const uint32_t lda_b = (uint32_t)p.lda * 2, ldb_b = (uint32_t)p.ldb * 2;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;  // LDS addresses are 32-bit offsets
@@ -598,7 +608,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     return q;
   };
   // this wavefront's pieces of k tile q (pieces pa / pb) into the stage at LDS offset `stage`
-  const uint32_t wave_pieces = wave_u * kPieces * 1024;  // this wavefront's pieces inside an operand tile
+  const bool loader = wave_u < kLoaders;
+  const uint32_t wave_pieces = wave_u % kLoaders * kPieces * 1024;  // this wavefront's pieces inside an operand tile
   auto dma_a = [&](const Pieces& pa, const KTile& q, uint32_t stage, auto J) {
     constexpr int j = decltype(J)::value;
     load_to_lds<j * 1024>(q.a, stage + wave_pieces, A_TRANS || WHOLE_K || pa.kpos[j] < q.k_left ? pa.off[j] : kOob);
@@ -611,17 +622,19 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // of 4 x 8 output tiles, 8 share each A tile and 4 each B tile) and ask for the same lines at
   // about the same time, so every one of them sees the full memory latency on every k tile.
   // Three k tiles ahead, each line is therefore asked for once, by one of the workgroups that
-  // share it -- four bytes per 128-byte line, into a dump area; every wavefront issues one such
-  // instruction per k tile (lanes without a line are masked), which keeps the wait counts
-  // alike.  Purely a hint: nothing depends on the data.
-  // Prefetched: the products whose operands are both [row][k] (gate/up and down: 9 to 12 % faster
-  // when every expert has a multiple of four row tiles) and dX, both operands (Mixtral shape: 6 %
-  // faster; only one of the two operands: 4 to 14 % slower than none).  Not prefetched: dA (+-2 %)
+  // share it -- four bytes per 128-byte line, into a dump area -- in the k tile's last MFMA slot, behind
+  // the loads: data comes back to a compute unit in the order of the requests, and pieces behind the
+  // prefetch wait for it (in the first slot behind the barrier: gate/up of a Mixtral-shaped layer 1675 -> 1813 us).  The
+  // prefetching wavefronts load nothing else and never wait for it.  Purely a hint: nothing depends on the data.
+  // Prefetched (us without / with): down (Mixtral shape 864 / 797; 1000 tokens of it 406 / 368); dX unless its experts
+  // have many row tiles (Mixtral shape 1658 / 1605; one expert of 16384 rows, 2048 x 8192, 374 / 381); gate/up where
+  // an expert has few (1000 tokens of the Mixtral shape 649 / 614; up to 4 row tiles: 16 experts, 6000 rows, 2048 x 4096 239 /
+  // 224; the dense layer 380 / 401, 16 experts, 32768 rows, 4096 x 688 394 / 411).  Not prefetched: dA (+-2 %)
   // and the token-contracted products (2 to 3 % slower with it).
   constexpr bool TOUCHES = (!A_TRANS && !B_TRANS) || IS_DX;
   struct Touch {
-    uint32_t off;  // this lane's line, as a byte offset from the tile's (row0, k0) element, or kOob
-    bool second;   // gate/up pairing: this wavefront's lines are in the second matrix
+    int on;         // prefetch at all
+    uint32_t a, b;  // this lane's line of either operand tile, as a byte offset from the tile's (row0, k0) element, or kOob
   };
   // Who shares what is read off the tiles that really run side by side, not assumed: the experts'
   // tile counts are no multiples of 32, so a run starts anywhere in an expert's tile order and
@@ -631,9 +644,11 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // tiles, this workgroup's the `me`-th); tiles with the same expert and row tile share the A
   // tile, tiles with the same expert and column tile the B tile.
   auto touch_of = [&](const Tile& tt, int kts_of_tile, int base, int n_valid, int me) {
-    if constexpr (!TOUCHES) return Touch{kOob, false};
+    if constexpr (!TOUCHES) return Touch{0, kOob, kOob};
     // nothing is touched when the k range (of a phase, for dX) is short (11 k tiles: 4 % slower with the prefetch than without)
-    if (kts_of_tile < kMinTouchKt) return Touch{kOob, MODE == MODE_GATEUP && wave_u >= 6};
+    if (kts_of_tile < kMinTouchKt) return Touch{0, kOob, kOob};
+    const int row_tiles = table[kTableStride * tt.e + 2];
+    if ((MODE == MODE_GATEUP && row_tiles > kTouchRowTiles) || (IS_DX && row_tiles >= kTallFrom)) return Touch{0, kOob, kOob};
     const int tid = tid_now();
     const int lane = tid & 63, wave = tid >> 6;
     const int ni = tt.n0 / TILE_N, mi = (MODE == MODE_DW ? tt.m0 : tt.m0 - tt.k_begin) / tile_m;
@@ -651,44 +666,38 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     const unsigned long long below = (1ull << me) - 1;
     const int cnt_a = max(1, __builtin_popcountll(share_a)), rank_a = __builtin_popcountll(share_a & below);
     const int cnt_b = max(1, __builtin_popcountll(share_b)), rank_b = __builtin_popcountll(share_b & below);
-    Touch th;
-    th.off = kOob;
-    th.second = MODE == MODE_GATEUP && __builtin_amdgcn_readfirstlane(wave) >= 6;
     // The lines of an operand tile go round robin to its `cnt` sharers, this workgroup being the `rank`-th.
-    // Wavefronts 0..3 cover the 256 lines of the A tile, 4..7 those of the B tile (gate/up: 4, 5 the gate
-    // rows, 6, 7 the matching up rows).  (One contiguous block of lines per sharer instead measured the same,
-    // +-1 %.)  A tile nobody else in the run uses is touched all the same, by its one user: left out, it runs
-    // so much slower than its neighbours that a product of three rounds -- down on a Mixtral-shaped layer, where
-    // ten of 576 tiles are in that position -- ends 20 % later.
+    // Each of the prefetching wavefronts covers 64 lines of the A tile and 64 of the B tile (gate/up: two of them the gate
+    // rows, two the matching up rows).  (One contiguous block of lines per sharer instead measured the same, +-1 %; a
+    // workgroup's share packed into two instructions per k tile instead of eight: 2 to 4 % slower.)  A tile nobody else in the
+    // run uses is touched all the same, by its one user: left out, it runs so much slower than its neighbours that a
+    // product of three rounds -- down on a Mixtral-shaped layer, where ten of 576 tiles are in that position -- ends
+    // 20 % later.
+    Touch th{1, kOob, kOob};
     const int line = (wave & 3) * 64 + lane;
-    if (wave < 4) {
-      const int rows_left = tt.m_end - tt.m0;
-      if (!A_TRANS) {
-        if (line < rows_left && line % cnt_a == rank_a)
-          th.off = (uint32_t)(gathered ? p.gather[tt.m0 + line] / p.gather_div : line) * lda_b;
-      } else {
-        // [k][row] tile: k-row line / 4, 64-row quarter line % 4 (128 bytes); the record count masks the k range
-        if ((line & 3) * 64 < rows_left && line % cnt_a == rank_a) th.off = (uint32_t)(line >> 2) * lda_b + (line & 3) * 128;
-      }
+    const int rows_left = tt.m_end - tt.m0, cols_left = n_end - tt.n0;
+    if (!A_TRANS) {
+      if (line < rows_left && line % cnt_a == rank_a)
+        th.a = (uint32_t)(gathered ? p.gather[tt.m0 + line] / p.gather_div : line) * lda_b;
     } else {
-      const int cols_left = n_end - tt.n0;
-      if (!B_TRANS) {
-        const int row = MODE == MODE_GATEUP ? line % 128 : line;
-        if (row < cols_left && line % cnt_b == rank_b) th.off = (uint32_t)row * ldb_b;
-      } else {
-        if ((line & 3) * 64 < cols_left && line % cnt_b == rank_b) th.off = (uint32_t)(line >> 2) * ldb_b + (line & 3) * 128;
-      }
+      // [k][row] tile: k-row line / 4, 64-row quarter line % 4 (128 bytes); the record count masks the k range
+      if ((line & 3) * 64 < rows_left && line % cnt_a == rank_a) th.a = (uint32_t)(line >> 2) * lda_b + (line & 3) * 128;
+    }
+    if (!B_TRANS) {
+      const int row = MODE == MODE_GATEUP ? line % 128 : line;
+      if (row < cols_left && line % cnt_b == rank_b) th.b = (uint32_t)row * ldb_b;
+    } else {
+      if ((line & 3) * 64 < cols_left && line % cnt_b == rank_b) th.b = (uint32_t)(line >> 2) * ldb_b + (line & 3) * 128;
     }
     return th;
   };
   const uint32_t lds_dump = lds0 + kLdsBytes + kTableBytes + wave_u * 256;
   auto touch = [&](const KTile& q, const Touch& th) {
-    if constexpr (TOUCHES) touch_to_lds(wave_u >= 4 ? q.b : q.a, lds_dump, th.off);
-  };
-  // the k loop's wait for the pieces of the next k tile: the prefetch, if any, is the youngest load and may stay out
-  auto wait_pieces = [&]() {
-    if constexpr (TOUCHES) wait_pieces_and_lds();
-    else wait_loads_and_lds();
+    if constexpr (TOUCHES) {
+      const int on = __builtin_amdgcn_readfirstlane(th.on);
+      touch_to_lds(q.a, lds_dump, th.a, on);
+      touch_to_lds(q.b, lds_dump, th.b, on);
+    }
   };
   const int n_rounds = my_rounds + (has_part ? 1 : 0);
   auto tile_at = [&](int round) {
@@ -733,10 +742,9 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   //   wait for this wavefront's pieces of tile kt + 1 and for its LDS reads; barrier:
   //   now tile kt + 1 is complete and nobody reads the stage of tile kt any more
   //   step 1, rows 1..3: MFMAs | fragments of step 0 of tile kt + 1 as their registers fall
-  //           free; one piece of tile kt + 2 every third MFMA into the stage of tile kt
+  //           free; the loading wavefronts' pieces of tile kt + 2 into the stage of tile kt
   // so LDS latency is covered by MFMAs in flight (and by the SIMD's other wavefront), a
-  // piece has a whole k tile to land, and the memory instructions are spread out: a burst
-  // of them would hold up the wavefront's own MFMAs.  Past the last tile the loads are
+  // piece has a whole k tile to land, and the memory instructions are spread out.  Past the last tile the loads are
   // masked (zeros, no memory access), which keeps the loop body free of branches.
   Frag<A_TRANS> fa[4];
   Frag<B_TRANS> fb[8];
@@ -745,11 +753,12 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
 #pragma unroll
   for (int j = 0; j < 8; ++j) fb[j] = Frag<B_TRANS>{};
   constexpr int RA = kReadsPerFrag<A_TRANS>, RB = kReadsPerFrag<B_TRANS>;
-  const Pieces pa = pieces_a(t), pb = pieces_b(t);
   // first 16-row block of this wavefront in each operand tile (gate/up: 64 gate rows, and the 64 matching up rows 128 further on)
   FragAddr<A_TRANS, 4> fra = frag_addr<A_TRANS, 4, 4>(lds0, wave_u >> 1);
   FragAddr<B_TRANS, 8> frb = frag_addr<B_TRANS, 8, 1>(lds0, MODE == MODE_GATEUP ? (wave_u & 1) * 4 : (wave_u & 1) * 8);
-  KIter kit = kiter_at(t, kr, kt_lo, second_b);  // the k tiles to load, in order
+  KIter kit = kiter_at(t, kr, kt_lo, second_b);  // the k tiles to load or to prefetch, in order
+  Pieces pa, pb;                                 // of a loading wavefront
+  Touch th{0, kOob, kOob};                       // of a prefetching one
   // A fragment of row block I / B fragment of column block J for k step H
   // (the stage read is the one fra / frb point into)
   auto read_a = [&](auto I, auto H) {
@@ -768,30 +777,29 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   const std::integral_constant<int, 1> c1;
   const std::integral_constant<int, 2> c2_;
 
-  // What this workgroup prefetches is worked out with the first two k tiles on their way, where it costs
-  // no time -- unless that takes a global load itself (the gather indices), which would wait for them.
+  // What this workgroup prefetches is worked out with the first two k tiles on their way, where it costs no time.
   auto touch_now = [&]() {
     return parted ? touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), tb.total - tail_tiles + (xcd / split) * slots, min(slots, tail_tiles - (xcd / split) * slots), slot)
                   : touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), run_base(round), run_len(round), place(round));
   };
-  Touch th{kOob, false};
-  if (gathered) th = touch_now();
-  {
+  if (loader) {
+    pa = pieces_a(t);
+    pb = pieces_b(t);
     const KTile q0 = knext(kit);
     if (!first_in_flight) {
       static_for<kPieces>([&](auto J) { dma_a(pa, q0, lds0, J); });
       static_for<kPieces>([&](auto J) { dma_b(pb, q0, lds0, J); });
     }
-  }
-  {
     const KTile q1 = knext(kit);
     static_for<kPieces>([&](auto J) { dma_a(pa, q1, lds0 + kStageBytes, J); });
     static_for<kPieces>([&](auto J) { dma_b(pb, q1, lds0 + kStageBytes, J); });
+    wait_loads_but<2 * kPieces>();  // the first tile has landed
+  } else if constexpr (TOUCHES) {
+    th = touch_now();
+    knext(kit);
+    knext(kit);
+    for (int i = 2; i < kTouchLead; ++i) touch(knext(kit), th);
   }
-  if (!gathered) th = touch_now();
-  KIter kit_touch = kiter_at(t, kr, kt_lo + 2, th.second);  // the k tiles to prefetch, in order
-  if constexpr (TOUCHES) touch(knext(kit_touch), th);
-  wait_loads_but<2 * kPieces + (TOUCHES ? 1 : 0)>();  // the first tile has landed
   wg_barrier();
   const int valid16 = min(16, (t.m_end - t.m0 + 15) / 16);  // valid 16-row blocks of the tile (a prefix)
   const bool cols_ok = (MODE == MODE_GATEUP ? t.n0 + (wave_u & 1) * 64 : t.n0 + (wave_u & 1) * 128) < n_end;
@@ -801,15 +809,16 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // Order of a step's fragment reads: A 0 .. ROWS-2 (each after its row), B 0 .. 7 (in the last
   // row, each after its last MFMA), A ROWS-1.  Reads complete in order, so what a MFMA has to
   // wait for is the number of reads issued after its youngest fragment.
-  auto work = [&](auto ROWS_C) {
+  auto work = [&](auto ROWS_C, auto LOADER_C) {
     constexpr int ROWS = decltype(ROWS_C)::value, LAST = ROWS - 1;
+    constexpr bool LOADER = decltype(LOADER_C)::value;
     const std::integral_constant<int, LAST> c_last;
     static_for<LAST>([&](auto I) { read_a(I, c0); });
     static_for<8>([&](auto J) { read_b(J, c0); });
     read_a(c_last, c0);
     // all MFMAs of one k step; WHAT = 0: first step of a k tile (fragments of step 1 follow as registers fall
     // free), 1: row 0 of step 1 only, 2: rows 1.. of step 1 with the refill, 3: rows 1.. of step 1 without
-    auto mfmas = [&](auto WHAT_C, uint32_t freed, const KTile& q2, const KTile& q3) {
+    auto mfmas = [&](auto WHAT_C, uint32_t freed, const KTile& q2) {
       constexpr int WHAT = decltype(WHAT_C)::value;
       constexpr int FIRST_SLOT = WHAT >= 2 ? 8 : 0, END_SLOT = WHAT == 1 ? 8 : 8 * ROWS;
       constexpr int REFILL_SLOTS = 8 * ROWS - 8;  // MFMA slots behind the barrier (none if ROWS == 1)
@@ -831,12 +840,17 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (WHAT == 2) {
-          // one piece of the refill every REFILL_SLOTS / 8 slots, the L2 prefetch in the last slot
-          constexpr int every = REFILL_SLOTS / 8, s = m - 8;
-          if constexpr (s % every == 0) {
-            constexpr int piece = s / every;
-            if constexpr (piece < kPieces) dma_a(pa, q2, freed, std::integral_constant<int, piece>{});
-            else dma_b(pb, q2, freed, std::integral_constant<int, piece - kPieces>{});
+          constexpr int s = m - 8;
+          if constexpr (LOADER) {  // the pieces of the refill, evenly over the slots
+            static_for<2 * kPieces>([&](auto P) {
+              constexpr int piece = decltype(P)::value;
+              if constexpr (piece * REFILL_SLOTS / (2 * kPieces) == s) {
+                if constexpr (piece < kPieces) dma_a(pa, q2, freed, std::integral_constant<int, piece>{});
+                else dma_b(pb, q2, freed, std::integral_constant<int, piece - kPieces>{});
+              }
+            });
+          } else if constexpr (s == REFILL_SLOTS - 1) {
+            touch(q2, th);
           }
         }
         mfma(std::integral_constant<int, i>{}, std::integral_constant<int, j>{});
@@ -845,33 +859,36 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
           if constexpr (i == LAST) read_b(std::integral_constant<int, j>{}, H);
           if constexpr (j == 7) read_a(std::integral_constant<int, i>{}, H);
         }
-        if constexpr (WHAT == 2 && m == 8 * ROWS - 1) touch(q3, th);
         __builtin_amdgcn_sched_barrier(0);
       });
     };
     const std::integral_constant<int, 2> c2;
-    auto step0 = [&]() { mfmas(c0, 0u, KTile{}, KTile{}); };
+    auto step0 = [&]() { mfmas(c0, 0u, KTile{}); };
     auto step1_row0_and_barrier = [&]() {
-      mfmas(c1, 0u, KTile{}, KTile{});
-      wait_pieces();
+      mfmas(c1, 0u, KTile{});
+      if constexpr (LOADER) wait_loads_and_lds();
+      else wait_lds();
       wg_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
     // behind the barrier: fra / frb move on to the next tile's stage; its first fragments and the refill of the
     // stage just freed go between the remaining MFMAs of step 1 (all at once if there are none)
-    auto step1_rest = [&](uint32_t to_next, uint32_t freed, const KTile& q2, const KTile& q3) {
+    auto step1_rest = [&](uint32_t to_next, uint32_t freed, const KTile& q2) {
       fra.shift(to_next);
       frb.shift(to_next);
       if constexpr (ROWS == 1) {
-        static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
-        static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
-        touch(q3, th);
+        if constexpr (LOADER) {
+          static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
+          static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
+        } else {
+          touch(q2, th);
+        }
         static_for<8>([&](auto J) { read_b(J, c0); });
         read_a(c0, c0);
         __builtin_amdgcn_sched_barrier(0);
       } else {
         if constexpr (LAST > 0) read_a(c0, c0);
-        mfmas(c2, freed, q2, q3);
+        mfmas(c2, freed, q2);
       }
     };
     __builtin_amdgcn_sched_barrier(0);
@@ -880,32 +897,38 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     for (int kt = kt_lo; kt + 1 < kt_hi; ++kt) {
       const int stage = (kt - kt_lo) & 1;
       const uint32_t to_next = stage ? 0u - (uint32_t)kStageBytes : (uint32_t)kStageBytes;
-      const KTile q2 = knext(kit);
-      KTile q3{};
-      if constexpr (TOUCHES) q3 = knext(kit_touch);
-      step1_rest(to_next, lds0 + stage * kStageBytes, q2, q3);
+      KTile q2{};
+      if constexpr (LOADER || TOUCHES) q2 = knext(kit);
+      step1_rest(to_next, lds0 + stage * kStageBytes, q2);
       step0();
       step1_row0_and_barrier();
     }
-    if constexpr (ROWS > 1) mfmas(std::integral_constant<int, 3>{}, 0u, KTile{}, KTile{});
+    if constexpr (ROWS > 1) mfmas(std::integral_constant<int, 3>{}, 0u, KTile{});
   };
   if (my_rows == 0) {
     // No valid rows or columns in this wavefront's part: it only keeps up the staging -- moves its
     // pieces and meets the barriers -- and leaves the SIMD and the LDS to the others.
     for (int kt = kt_lo; kt < kt_hi; ++kt) {
-      wait_pieces();
+      if (loader) wait_loads_and_lds();
       wg_barrier();
-      const uint32_t freed = lds0 + ((kt - kt_lo) & 1) * kStageBytes;
-      const KTile q2 = knext(kit);
-      static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
-      static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
-      if constexpr (TOUCHES) touch(knext(kit_touch), th);
+      if (loader) {
+        const uint32_t freed = lds0 + ((kt - kt_lo) & 1) * kStageBytes;
+        const KTile q2 = knext(kit);
+        static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
+        static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
+      } else if constexpr (TOUCHES) {
+        touch(knext(kit), th);
+      }
     }
   } else if (kt_lo < kt_hi) {  // (an expert without rows has nothing to contract: its tiles of MODE_DW stay zero)
-    if (my_rows == 4) work(std::integral_constant<int, 4>{});
-    else if (my_rows == 3) work(std::integral_constant<int, 3>{});
-    else if (my_rows == 2) work(c2_);
-    else work(c1);
+    auto work_as = [&](auto LOADER_C) {
+      if (my_rows == 4) work(std::integral_constant<int, 4>{}, LOADER_C);
+      else if (my_rows == 3) work(std::integral_constant<int, 3>{}, LOADER_C);
+      else if (my_rows == 2) work(c2_, LOADER_C);
+      else work(c1, LOADER_C);
+    };
+    if (loader) work_as(std::true_type{});
+    else work_as(std::false_type{});
   }
   // every piece (masked ones included) has landed and nobody reads the stages any more
   wait_loads_and_lds();
@@ -914,6 +937,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // tile can be on its way into stage 0 while the results are stored.
   first_in_flight = round + 1 < n_rounds;
   if (first_in_flight) {
+    if (loader) {
     const Tile tn = tile_at(round + 1);
     const KRange rn = krange(tn, CAN_SPLIT && round + 1 == my_rounds);
     const Pieces pan = pieces_a(tn), pbn = pieces_b(tn);
@@ -921,6 +945,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     const KTile qn = knext(kn);
     static_for<kPieces>([&](auto J) { dma_a(pan, qn, lds0, J); });
     static_for<kPieces>([&](auto J) { dma_b(pbn, qn, lds0, J); });
+    }
   }
 
   // ---- epilogue.  Accumulator element r of block (i, j) is row 16 (4 i + wm) + (lane/16)*4 + r,
