@@ -1,4 +1,4 @@
-// What the bf16 grouped-GEMM kernels (ffn_mfma.hip, ffn_tile.hip, ffn_skinny.hip) share: the product's parameters, the global -> LDS
+// What the bf16 grouped-GEMM kernels (ffn_mfma.hip, ffn_tile.hip, ffn_dw.hip, ffn_skinny.hip) share: the product's parameters, the global -> LDS
 // loads, and the element-wise parts of their epilogues.
 #pragma once
 
@@ -109,11 +109,12 @@ enum TileKind {
   TILE_64 = DYNMO_KERNEL_64x64,
   FEW_ROWS = DYNMO_KERNEL_FEW_ROWS
 };
-// ffn_tile.hip: a row-segmented product (any mode but MODE_DW; MODE_GATEUP not on 128 x 256 tiles), and the three weight gradients.
+// ffn_tile.hip: a row-segmented product (any mode but MODE_DW; MODE_GATEUP not on 128 x 256 tiles).
 // DYNMO_EINVAL for a kind that is none of its tiles.
 int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st);
-int32_t ffn_tile_dw(TileKind kind, const dynmo_desc* d, const int32_t* seg, const bf16_t* dy_p, const bf16_t* x_p,
-                    const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
+// ffn_dw.hip: the three weight gradients on the same tiles
+int32_t ffn_dw_tiles(TileKind kind, const dynmo_desc* d, const int32_t* seg, const bf16_t* dy_p, const bf16_t* x_p,
+                     const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st);
 
 // ffn_skinny.hip: MODE_GATEUP, MODE_DOWN or MODE_DOWN_FOLD with few rows per expert; at most `max_experts` experts have
 // rows, none of them more than `max_rows` unless a token takes an expert twice (right in any case)

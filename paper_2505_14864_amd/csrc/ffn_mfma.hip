@@ -1204,7 +1204,7 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
   return launch_mfma_as<MODE, false>(p, max_tiles, id, st);
 }
 
-// Which kernel takes a product: this file's, or ffn_tile.hip with the given tile.  The host knows rows, experts and
+// Which kernel takes a product: this file's, or ffn_tile.hip (the weight gradients: ffn_dw.hip) with the given tile.  The host knows rows, experts and
 // sizes, not the segments: an expert is counted with half a row tile for its ragged end.
 //   * While the 256 x 256 tiles of a product fill about half of the chip or less, smaller tiles win, by more
 //     the fewer they are.  Measured (us, 256 / 128 / 64; rows x H x F, experts):
@@ -1233,7 +1233,7 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipS
 //     Over 3374 shapes (3 to 64 experts, k 512 to 4096, 0.5 to 9 rounds) the time is 0.944 (dA), 0.937 (dX) and 0.954 (down) of
 //     256 x 256 tiles alone on average, and more than 5 % above theirs for 18, 35 and 45 of them: the host knows the rows, not
 //     the segments, and estimates the tiles.
-//   * The three weight gradients go in one launch there, and the 256 x 256 kernel's epilogue has nothing to hide
+//   * The three weight gradients go in one launch on smaller tiles, and the 256 x 256 kernel's epilogue has nothing to hide
 //     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts (us for all three, 256 /
 //     128 x 256): 16 experts, 32768 x 4096 x 688, 768 tiles: 669 / 604; 64, 16384 x 2048 x 1024, 2048: 404 / 384; 8,
 //     8192 x 2048 x 4096, 1024: 441 / 406.  Not for long sums that fill the chip (4, 16384 x 4096 x 4096, 1024 tiles:
@@ -1421,8 +1421,8 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.
   const TileKind dw_kind = kernel_for(d, MODE_DW);
   if (dw_kind != TILE_256) {
-    rc = ffn_tile_dw(dw_kind, d, seg, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
-                     (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);
+    rc = ffn_dw_tiles(dw_kind, d, seg, (const bf16_t*)dy_p, (const bf16_t*)x_p, (const bf16_t*)A,
+                      (const bf16_t*)dG, (const bf16_t*)dU, (bf16_t*)dWg, (bf16_t*)dWu, (bf16_t*)dWd, st);
     if (rc) return rc;
   } else {
     if ((rc = dw(dy_p, d->H, A, d->F, dWd, K_FFN_DWD))) return rc;

@@ -1,5 +1,5 @@
-// Grouped SwiGLU FFN on the gfx950 matrix cores (bf16 in, fp32 accumulate): the kernel for products
-// that are too small, or cut into too many short pieces, for the 256 x 256 tiles of ffn_mfma.hip.
+// Grouped SwiGLU FFN on the gfx950 matrix cores (bf16 in, fp32 accumulate): the kernel for row-segmented
+// products that are too small, or cut into too many short pieces, for the 256 x 256 tiles of ffn_mfma.hip.
 //
 // One workgroup of four wavefronts (2 x 2) per output tile of 128 x 256 (64 x 128 per wavefront), 128 x 128
 // (64 x 64) or 64 x 64 (32 x 32), not persistent: the hardware deals the workgroups, and two (three, five) of
@@ -8,12 +8,10 @@
 // traffic per MFMA and wins where a tile's k range is long and the tiles fill the chip.
 //
 // k goes in steps of 32 (one MFMA deep) through a ring of three (64 x 64: four) LDS stages; buffer loads with an
-// LDS destination fill a stage two (three) steps before it is read.  A third workgroup per compute unit is worth
-// more to the 128 x 128 tile than two further stages (weight gradients of 64 experts, 256 rows each, 2048 x 1024:
-// 428 -> 377 us; 128 x 256 tiles, same LDS traffic per MFMA as 256 x 256: 358).  Operands that lie [row][k] in memory
+// LDS destination fill a stage two (three) steps before it is read.  Operands that lie [row][k] in memory
 // keep that layout in LDS, operands that lie [k][row] are read with ds_read_b64_tr_b16; 16-byte pieces
 // are placed so that the sixteen lanes of a fragment's k group fall into different banks.  By the counters the [k][row]
-// reads are free of conflicts (weight gradients 0 %); of the LDS cycles of products with one [row][k] operand 22 % are
+// reads are free of conflicts; of the LDS cycles of products with one [row][k] operand 22 % are
 // conflicts, with two (gate/up, down) 44 %: the hardware serves the lanes of a 16-byte read in other groups.
 //   [row][k]: 64 bytes per row; the piece with k = 8 c .. of row r sits at r * 64 + ((c ^ ((r >> 2) & 3)) << 4)
 //   [k][row]: 64-byte blocks of 32 rows; block b of k-row k is stored as block b ^ (k & 3) (64 rows:
@@ -26,20 +24,9 @@ constexpr int kTileThreads = 256;
 constexpr int kTileK = 32;
 constexpr int kChunkTiles = 4;  // row tiles that are walked together, column tile by column tile
 
-// One weight gradient dW[e] = P_e^T Q_e (M x N per expert)
-struct DwSet {
-  const bf16_t* P;
-  const bf16_t* Q;
-  bf16_t* C;
-  int M, N;
-  int tiles;  // output tiles per expert
-};
-
 struct TileParams {
   GemmParams g;
-  DwSet dw[3];  // MODE_DW: the products of this launch
-  int sets;
-  int group;    // consecutive tiles of the list that go to one XCD
+  int group;  // consecutive tiles of the list that go to one XCD
 };
 
 // WBM x WBN blocks of 16 x 16 per wavefront
@@ -146,10 +133,9 @@ template <int MODE, int WBM, int WBN, bool WHOLE_K>
 __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void ffn_tile_kernel(const TileParams tp) {
   using S = TileShape<WBM, WBN>;
   __shared__ __attribute__((aligned(1024))) char smem[S::kLds];
-  constexpr bool A_KROW = MODE == MODE_DW;
   constexpr bool IS_DX = MODE == MODE_DX || MODE == MODE_DX_FOLD;
   constexpr bool FOLDS = MODE == MODE_DOWN_FOLD || MODE == MODE_DX_FOLD;
-  constexpr bool B_KROW = MODE == MODE_DA || IS_DX || MODE == MODE_DW;
+  constexpr bool B_KROW = MODE == MODE_DA || IS_DX;
   constexpr int TM = S::kRows, TILE_N = MODE == MODE_GATEUP ? S::kCols / 2 : S::kCols;
   const GemmParams& p = tp.g;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -161,69 +147,43 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void
   const int pos = (slot / tp.group * 8 + (blockIdx.x & 7)) * tp.group + slot % tp.group;
 
   // ---- which tile
-  int e, m0, m_end, n0, n_end, k_begin = 0, k_end = p.K;
-  const bf16_t *A1 = p.A1, *B1 = p.B1;
-  bf16_t* C0 = p.C0;
-  long lda = p.lda, ldb = p.ldb, ldc = p.ldc;
-  if constexpr (MODE == MODE_DW) {
-    const int per_expert = tp.dw[0].tiles + (tp.sets > 1 ? tp.dw[1].tiles + tp.dw[2].tiles : 0);
-    e = pos / per_expert;
-    if (e >= p.E) return;
-    int r = pos - e * per_expert, set = 0;
-    while (r >= tp.dw[set].tiles) r -= tp.dw[set++].tiles;
-    const DwSet& w = tp.dw[set];
-    int mi, ni;
-    tile_of(r, (w.M + TM - 1) / TM, (w.N + TILE_N - 1) / TILE_N, &mi, &ni);
-    k_begin = __builtin_amdgcn_readfirstlane(p.seg[e]);
-    k_end = __builtin_amdgcn_readfirstlane(p.seg[e + 1]);
-    m0 = mi * TM;
-    m_end = w.M;
-    n0 = ni * TILE_N;
-    n_end = w.N;
-    A1 = w.P;
-    B1 = w.Q;
-    C0 = w.C + (long)e * w.M * w.N;
-    lda = w.M;
-    ldb = ldc = w.N;
-  } else {
-    // lane e of every wavefront counts the row tiles of expert e; a prefix sum and a ballot find the owner
-    const int nt = (p.N + TILE_N - 1) / TILE_N;
-    const int begin = lane < p.E ? p.seg[lane] : 0, end = lane < p.E ? p.seg[lane + 1] : 0;
-    const int mt = (end - begin + TM - 1) / TM;
-    int upto = mt;
+  // lane e of every wavefront counts the row tiles of expert e; a prefix sum and a ballot find the owner
+  const int nt = (p.N + TILE_N - 1) / TILE_N;
+  const int begin = lane < p.E ? p.seg[lane] : 0, end = lane < p.E ? p.seg[lane + 1] : 0;
+  const int mt = (end - begin + TM - 1) / TM;
+  int upto = mt;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(upto, d, 64);
-      if (lane >= d) upto += o;
-    }
-    const unsigned long long owners = __ballot(upto * nt > pos);
-    if (owners == 0) return;  // past the last tile
-    e = __builtin_ctzll(owners);
-    const int mt_e = __builtin_amdgcn_readlane(mt, e);
-    int mi, ni;
-    tile_of(pos - (__builtin_amdgcn_readlane(upto, e) - mt_e) * nt, mt_e, nt, &mi, &ni);
-    m0 = __builtin_amdgcn_readlane(begin, e) + mi * TM;
-    m_end = __builtin_amdgcn_readlane(end, e);
-    n0 = ni * TILE_N;
-    n_end = p.N;
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(upto, d, 64);
+    if (lane >= d) upto += o;
   }
+  const unsigned long long owners = __ballot(upto * nt > pos);
+  if (owners == 0) return;  // past the last tile
+  const int e = __builtin_ctzll(owners);
+  const int mt_e = __builtin_amdgcn_readlane(mt, e);
+  int mi, ni;
+  tile_of(pos - (__builtin_amdgcn_readlane(upto, e) - mt_e) * nt, mt_e, nt, &mi, &ni);
+  const int m0 = __builtin_amdgcn_readlane(begin, e) + mi * TM, m_end = __builtin_amdgcn_readlane(end, e);
+  const int n0 = ni * TILE_N, n_end = p.N;
+  bf16_t* const C0 = p.C0;
+  const long lda = p.lda, ldb = p.ldb, ldc = p.ldc;
 
   // ---- operands
   const uint32_t lda_b = (uint32_t)lda * 2, ldb_b = (uint32_t)ldb * 2;
   const bool gathered = MODE == MODE_GATEUP && p.gather != nullptr;
   const bool second_b = MODE == MODE_GATEUP && wave >= 2;  // operand B: gate rows, then the matching up rows
-  TilePieces<S::kRows, A_KROW> pa;
+  TilePieces<S::kRows, false> pa;
   TilePieces<S::kCols, B_KROW> pb;
   pa.init(lda_b, m_end - m0, S::kRows, gathered ? p.gather + m0 : nullptr, p.gather_div);
   pb.init(ldb_b, n_end - n0, TILE_N, nullptr, 1);
-  const long b_off = MODE == MODE_DW ? 0 : (long)e * p.b_expert_stride;
-  auto a_at = [&](const bf16_t* A, int k) { return A_KROW ? A + (long)k * lda + m0 : A + (gathered ? 0 : (long)m0 * lda) + k; };
+  const long b_off = (long)e * p.b_expert_stride;
+  auto a_at = [&](const bf16_t* A, int k) { return A + (gathered ? 0 : (long)m0 * lda) + k; };
   auto b_at = [&](const bf16_t* B, int k) { return B_KROW ? B + b_off + (long)k * ldb + n0 : B + b_off + (long)n0 * ldb + k; };
-  const int kt_phase = (k_end - k_begin + kTileK - 1) / kTileK;
+  const int kt_phase = (p.K + kTileK - 1) / kTileK;
   const int n_kt = kt_phase * (IS_DX ? 2 : 1);
-  const bf16_t* na = a_at(A1, k_begin);
-  const bf16_t* nb = b_at(second_b ? p.B2 : B1, k_begin);
-  int k_left = k_end - k_begin, issued = 0;
+  const bf16_t* na = a_at(p.A1, 0);
+  const bf16_t* nb = b_at(second_b ? p.B2 : p.B1, 0);
+  int k_left = p.K, issued = 0;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
   // the next k step into the stage at byte `stage`; past the last one the loads fetch nothing
   auto issue = [&](uint32_t stage) {
@@ -231,19 +191,19 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void
     const uint32_t k_rows = (uint32_t)max(0, min(left, kTileK));
     const uint32_t any = left > 0 ? 0x7ffffffeu : 0u;
     // a [k][row] operand's k-rows are whole records, so the record count is its k mask
-    const desc_t da = make_desc(na, A_KROW ? k_rows * lda_b : any), db = make_desc(nb, B_KROW ? k_rows * ldb_b : any);
+    const desc_t da = make_desc(na, any), db = make_desc(nb, B_KROW ? k_rows * ldb_b : any);
     const uint32_t to_a = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesA * 1024);
     const uint32_t to_b = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesB * 1024);
     static_for<S::kPiecesA>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      load_to_lds<j * 1024>(da, to_a, A_KROW || WHOLE_K || pa.kpos[j] < left ? pa.off[j] : kOob);
+      load_to_lds<j * 1024>(da, to_a, WHOLE_K || pa.kpos[j] < left ? pa.off[j] : kOob);
     });
     static_for<S::kPiecesB>([&](auto J) {
       constexpr int j = decltype(J)::value;
       load_to_lds<S::kBytesA + j * 1024>(db, to_b, B_KROW || WHOLE_K || pb.kpos[j] < left ? pb.off[j] : kOob);
     });
     ++issued;
-    na += A_KROW ? (long)kTileK * lda : kTileK;
+    na += kTileK;
     nb += B_KROW ? (long)kTileK * ldb : kTileK;
     k_left -= kTileK;
     if (IS_DX && issued == kt_phase) {  // the second phase: dU Wu
@@ -257,7 +217,7 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void
   // rows are a prefix, and every wavefront keeps its share) and columns 16 WBN wn .. .
   uint32_t fa[WBM], fb[WBN];
 #pragma unroll
-  for (int i = 0; i < WBM; ++i) fa[i] = lds0 + frag_offset<S::kRows, A_KROW>(wm + 2 * i);
+  for (int i = 0; i < WBM; ++i) fa[i] = lds0 + frag_offset<S::kRows, false>(wm + 2 * i);
 #pragma unroll
   for (int j = 0; j < WBN; ++j) {
     const int n16 = MODE != MODE_GATEUP ? wn * WBN + j : j < WBN / 2 ? wn * (WBN / 2) + j : WBN + wn * (WBN / 2) + j - WBN / 2;
@@ -281,7 +241,7 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void
       bf16x8_t a[WBM], b[WBN];
       if constexpr (ROWS > 0) {
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) a[i] = read_tile_frag<S::kRows, A_KROW>(fa[i] + stage);
+        for (int i = 0; i < ROWS; ++i) a[i] = read_tile_frag<S::kRows, false>(fa[i] + stage);
 #pragma unroll
         for (int j = 0; j < WBN; ++j) b[j] = read_tile_frag<S::kCols, B_KROW>(fb[j] + stage);
 #pragma unroll
@@ -399,11 +359,9 @@ static int32_t launch_tile(TileParams tp, int tiles, const ProfRoles& id, hipStr
   tp.group = tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
   const int run = 8 * tp.group;
   const unsigned blocks = (unsigned)((tiles + run - 1) / run * run);
-  if constexpr (MODE != MODE_DW) {
-    if (tp.g.K % kTileK == 0) {
-      DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, true><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
-      return DYNMO_OK;
-    }
+  if (tp.g.K % kTileK == 0) {
+    DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, true><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
+    return DYNMO_OK;
   }
   DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, false><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
   return DYNMO_OK;
@@ -440,33 +398,6 @@ int32_t ffn_tile_rows(int mode, TileKind kind, const dynmo_desc* d, const GemmPa
     case MODE_DX_FOLD: return launch_shape<MODE_DX_FOLD>(kind, tp, tiles, id, st);
   }
   return DYNMO_EINVAL;
-}
-
-int32_t ffn_tile_dw(TileKind kind, const dynmo_desc* d, const int32_t* seg, const bf16_t* dy_p, const bf16_t* x_p,
-                    const bf16_t* A, const bf16_t* dG, const bf16_t* dU, bf16_t* dWg, bf16_t* dWu, bf16_t* dWd, hipStream_t st) {
-  const int E = d->E, H = d->H, F = d->F;
-  const int r = rows_of(kind), c = cols_of(kind);
-  const int hf = ((H + r - 1) / r) * ((F + c - 1) / c), fh = ((F + r - 1) / r) * ((H + c - 1) / c);
-  const DwSet all[3] = {{dy_p, A, dWd, H, F, hf}, {dG, x_p, dWg, F, H, fh}, {dU, x_p, dWu, F, H, fh}};
-  const KernelId ids[3] = {K_FFN_DWD, K_FFN_DWG, K_FFN_DWU};
-  TileParams tp = {};
-  tp.g.seg = seg;
-  tp.g.E = E;
-  // One launch for the three products; one each if a gradient is to be written over the rows
-  const size_t rows = (size_t)d->T * d->k * H * 2, weights = (size_t)E * F * H * 2;
-  tp.sets = any_overlap({{dWd, weights}, {dWg, weights}, {dWu, weights}}, {{dy_p, rows}, {x_p, rows}}) ? 1 : 3;
-  for (int s = 0; s < 3; s += tp.sets) {
-    int tiles = 0;
-    ProfRoles roles;  // equal flops
-    for (int i = 0; i < tp.sets; ++i) {
-      tp.dw[i] = all[s + i];
-      tiles += all[s + i].tiles;
-      roles.add(ids[s + i], 1.0);
-    }
-    const int32_t rc = launch_shape<MODE_DW>(kind, tp, E * tiles, roles, st);
-    if (rc) return rc;
-  }
-  return DYNMO_OK;
 }
 
 }  // namespace dynmo

@@ -962,6 +962,31 @@ def test_small_products_tile_edges(T, H, F, E, k, expected):
     assert torch.equal(layer.out, out)
 
 
+@pytest.mark.parametrize("E,H,F,kernel", [(64, 776, 776, "128x256"), (64, 520, 520, "128x256"), (63, 512, 512, "128x128")])
+def test_weight_gradient_workgroups_walk_tiles(E, H, F, kernel):
+    """Weight gradients whose workgroups take four, two and two tiles each (tiles / 1024 of them, of 128 x 256 or 128 x 128): the
+    loads run up to two k steps of 32 rows ahead into the next tile, which may be another expert's, of other operands or of none.
+    Experts without rows, with fewer rows than the steps that run ahead, with one row more or less than a whole step; tiles
+    with a ragged last row block and columns (776 = 6 x 128 + 8, 3 x 256 + 8) beside full ones."""
+    few = [0, 1, 31, 32, 33, 63, 64, 65, 0, 0, 96, 97, 7, 2]
+    counts = [few[i % len(few)] for i in range(E - 1)] + [300]
+    T = sum(counts)
+    say("weight gradients, E=%d H=%d F=%d rows=%d" % (E, H, F, T))
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=1, seed=9100 + H)
+    assert kernels(w)["dW"] == kernel
+    inp = wl.make_inputs(w, threads=4)
+    rng = np.random.default_rng(w.seed)
+    expert_of = rng.permutation(np.repeat(np.arange(E), counts))
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[np.arange(T), expert_of] += 20.0
+    inp["logits"] = logits
+    layer = run_moe(w, inp)
+    assert to_host(layer.seg_offsets).tolist() == np.concatenate([[0], np.cumsum(counts)]).tolist()
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(layer, ref, w.dtype)
+
+
 @pytest.mark.parametrize("counts,H,F,few", [((1,), 72, 136, "gateup down"), ((16,), 200, 520, "gateup"), ((1, 0, 17, 3), 264, 2056, "down"),
                                             ((40, 0, 2, 1, 3, 5, 2, 65), 520, 4104, ""), ((8, 8), 2048, 4096, "down")])
 def test_few_rows_per_expert(counts, H, F, few):
