@@ -10,7 +10,8 @@
 // bandwidth is near its limit even for a 64x64 tile; what costs is latency.  Hence small
 // tiles and several workgroups per compute unit (36 KB of LDS each): 64x64 outputs, four
 // wavefronts of 32x32 (2x2 blocks), k in steps of 32 through two LDS stages, with two
-// further k tiles on their way in registers.  Vector fp32 instructions reach half of the
+// further k tiles on their way in registers; products of few such tiles take 32x32 outputs,
+// a block per wavefront, with four k tiles on their way.  Vector fp32 instructions reach half of the
 // MFMA rate at best.
 //
 // Measured against a 64x64 vector-ALU kernel with one k step of 16 in flight:
@@ -28,17 +29,24 @@ namespace dynmo {
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int TM = 64, TN = 64, TK = 32;  // output tile and k step
-constexpr int kThreads = 256;             // 2 x 2 wavefronts of 32 x 32 outputs
+constexpr int TK = 32;         // k step
+constexpr int kThreads = 256;  // 2 x 2 wavefronts
+// Output tiles of 32 NB x 32 NB: NB x NB blocks of 16 x 16 per wavefront, NB 16-byte chunks of either operand per thread and k step.
+template <int NB>
+constexpr int kTile = 32 * NB;
+// k steps on their way in registers
+template <int NB>
+constexpr int kSets = NB == 1 ? 4 : 2;
 // LDS layouts of an operand tile (64 rows x 32 k).  [row][k]: 36 floats per row, so that the
 // 16-byte reads of sixteen rows fall into sixteen different bank groups (36 s mod 64).
 // [k][row]: 68 floats per k-row, so that k-rows 4 apart -- the four lane groups of a fragment
 // -- are 16 banks apart.  Share of the LDS cycles that are conflicts all the same: 32 % with two [row][k] operands, 16 %
 // with one, 7 % in the gradients; the matrix units wait for little of it (busy 55 to 76 % of the cycles).
 constexpr int kPitchRowK = TK + 4;
-constexpr int kPitchKRow = TM + 4;
-constexpr int kOperandFloats = TM * kPitchRowK;
-static_assert(kOperandFloats >= TK * kPitchKRow, "either layout fits");
+template <int NB>
+constexpr int kPitchKRow = kTile<NB> + 4;
+template <int NB>
+constexpr int kOperandFloats = kTile<NB> * kPitchRowK > TK * kPitchKRow<NB> ? kTile<NB> * kPitchRowK : TK * kPitchKRow<NB>;
 constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond every record count: the load delivers zero
 
 // Finds row tile `tile` of the expert segments.  Lane e of every wavefront counts the tiles of
@@ -46,10 +54,11 @@ constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond every record cou
 struct RowTile {
   int e, m0, m_end;
 };
+template <int NB>
 __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, int E, int tile, RowTile* t) {
   const int lane = threadIdx.x & 63;
   const int begin = lane < E ? seg[lane] : 0, end = lane < E ? seg[lane + 1] : 0;
-  const int n = (end - begin + TM - 1) / TM;
+  const int n = (end - begin + kTile<NB> - 1) / kTile<NB>;
   int upto = n;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -59,12 +68,12 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, i
   const unsigned long long owners = __ballot(upto > tile);
   if (owners == 0) return false;  // past the last tile
   t->e = __builtin_ctzll(owners);
-  t->m0 = __builtin_amdgcn_readlane(begin, t->e) + (tile - __builtin_amdgcn_readlane(upto - n, t->e)) * TM;
+  t->m0 = __builtin_amdgcn_readlane(begin, t->e) + (tile - __builtin_amdgcn_readlane(upto - n, t->e)) * kTile<NB>;
   t->m_end = __builtin_amdgcn_readlane(end, t->e);
   return true;
 }
 
-// One operand of a product: 64 rows by k.
+// One operand of a product: the tile's rows by k.
 //   KROW = false: element (row, k) at base + row * ld + k, with `rows` valid rows.  With `rowmap`, row r is row
 //     rowmap[r] / rowdiv.  PAIR: LDS rows 0..31 are 32 rows of one matrix and rows 32..63 the same rows of
 //     another one (`base2`): every thread's first chunk then belongs to the one and its second to the other.
@@ -72,14 +81,17 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, i
 // VEC = floats per load: the largest of 4, 2, 1 that divides ld (and so every offset and limit).
 // WIDE: a tile may span 2 GiB and more (64 rows of at least 2^23 floats), where the 32-bit offsets and the record
 // count of a buffer load end; the loads are then ordinary ones from 64-bit addresses.
-template <bool KROW, int VEC, bool WIDE, bool PAIR = false>
+template <int NB, bool KROW, int VEC, bool WIDE, bool PAIR = false>
 struct Operand {
   using offset_t = std::conditional_t<WIDE, long, uint32_t>;
   const float *base, *base2;  // (row 0, k 0) of the tile, wave-uniform
   long ld;
-  offset_t off[2];    // byte offsets of this thread's two chunks of four floats, from (row 0, k 0 of the k tile)
-  int kpos[2];        // their k inside the k tile
-  int left[2];        // [k][row]: valid floats from there on (<= 0: none); [row][k]: valid row or not
+  offset_t off[NB];   // byte offsets of this thread's chunks of four floats, from (row 0, k 0 of the k tile)
+  int kpos[NB];       // their k inside the k tile
+  int left[NB];       // [k][row]: valid floats from there on (<= 0: none); [row][k]: valid row or not
+
+  static constexpr int kFloats = kOperandFloats<NB>;
+  static_assert(!PAIR || NB == 2, "every thread's first chunk belongs to one matrix of a pair and its second to the other");
 
   __device__ __forceinline__ void init(const float* b, long ld_, int rows, const float* b2 = nullptr,
                                        const int32_t* rowmap = nullptr, int rowdiv = 1) {
@@ -87,16 +99,16 @@ struct Operand {
     base2 = b2;
     ld = ld_;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
       const int c = threadIdx.x + i * kThreads;
       if constexpr (KROW) {
-        kpos[i] = c / (TM / 4);
-        const int row = c % (TM / 4) * 4;
+        kpos[i] = c / (kTile<NB> / 4);
+        const int row = c % (kTile<NB> / 4) * 4;
         off[i] = (offset_t)(kpos[i] * ld + row) * 4;
         left[i] = rows - row;
       } else {
         kpos[i] = c % (TK / 4) * 4;
-        int row = c / (TK / 4) - (PAIR && i ? TM / 2 : 0);
+        int row = c / (TK / 4) - (PAIR && i ? kTile<NB> / 2 : 0);
         left[i] = row < rows;
         if (rowmap != nullptr) row = left[i] ? rowmap[row] / rowdiv : 0;
         off[i] = (offset_t)(row * ld + kpos[i]) * 4;
@@ -104,10 +116,10 @@ struct Operand {
     }
   }
 
-  // the two chunks of the k tile that starts at k0 (`k_left` valid k from there on); `shift`: floats to add to the base
-  __device__ __forceinline__ void fetch(f32x4_t (&r)[2], long k0, int k_left, long shift) const {
+  // the chunks of the k tile that starts at k0 (`k_left` valid k from there on); `shift`: floats to add to the base
+  __device__ __forceinline__ void fetch(f32x4_t (&r)[NB], long k0, int k_left, long shift) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
       const float* p = (PAIR && i ? base2 : base) + shift + (KROW ? k0 * ld : k0);
       const bool ok = KROW ? kpos[i] < k_left : left[i] != 0;
       const int n = !ok ? 0 : KROW ? left[i] : k_left - kpos[i];  // valid floats of the chunk
@@ -138,11 +150,11 @@ struct Operand {
     }
   }
 
-  __device__ __forceinline__ void put(float* s, const f32x4_t (&r)[2]) const {
+  __device__ __forceinline__ void put(float* s, const f32x4_t (&r)[NB]) const {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
       const int c = threadIdx.x + i * kThreads;
-      const int at = KROW ? c / (TM / 4) * kPitchKRow + c % (TM / 4) * 4 : c / (TK / 4) * kPitchRowK + kpos[i];
+      const int at = KROW ? c / (kTile<NB> / 4) * kPitchKRow<NB> + c % (kTile<NB> / 4) * 4 : c / (TK / 4) * kPitchRowK + kpos[i];
       *(f32x4_t*)(s + at) = r[i];
     }
   }
@@ -157,7 +169,7 @@ struct Operand {
     } else {
       f32x4_t f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * kPitchKRow + row];
+      for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * kPitchKRow<NB> + row];
       return f;
     }
   }
@@ -165,12 +177,13 @@ struct Operand {
 
 // acc[i][j] += sum over k of A(row block i) * B(row block j); the k range is `phases` stretches of K, the second
 // one at (A + a_shift, B + b_shift).  Wavefront (wm, wn): A rows 32 wm + 16 i, B rows b_row[j].
-template <typename OpA, typename OpB>
-__device__ __forceinline__ void mac(f32x4_t (&acc)[2][2], const OpA& a, const OpB& b, int K, int phases, long a_shift,
-                                    long b_shift, int a_row, const int (&b_row)[2], float* lds) {
+template <int NA, int NB, typename OpA, typename OpB>
+__device__ __forceinline__ void mac(f32x4_t (&acc)[NA][NB], const OpA& a, const OpB& b, int K, int phases, long a_shift,
+                                    long b_shift, int a_row, const int (&b_row)[NB], float* lds) {
+  constexpr int S = kSets<NA>, kStage = OpA::kFloats + OpB::kFloats;
   const int per_phase = (K + TK - 1) / TK, n_kt = per_phase * phases;
   if (n_kt == 0) return;
-  f32x4_t ra[2][2], rb[2][2];  // two k tiles on their way
+  f32x4_t ra[S][NA], rb[S][NB];  // k tiles on their way
   // past the last k tile nothing is fetched (zeros)
   auto fetch = [&](int kt, int set) {
     const bool second = kt >= per_phase && phases > 1;
@@ -180,52 +193,57 @@ __device__ __forceinline__ void mac(f32x4_t (&acc)[2][2], const OpA& a, const Op
     b.fetch(rb[set], k0, k_left, second ? b_shift : 0);
   };
   auto put = [&](int set, int stage) {
-    a.put(lds + stage * 2 * kOperandFloats, ra[set]);
-    b.put(lds + stage * 2 * kOperandFloats + kOperandFloats, rb[set]);
+    a.put(lds + stage * kStage, ra[set]);
+    b.put(lds + stage * kStage + OpA::kFloats, rb[set]);
   };
-  fetch(0, 0);
-  fetch(1, 1);
+#pragma unroll
+  for (int i = 0; i < S; ++i) fetch(i, i);
   put(0, 0);
-  fetch(2, 0);
+  fetch(S, 0);
   __syncthreads();
-  // k tile kt is in LDS stage kt % 2, tiles kt + 1 and kt + 2 are on their way
-  auto step = [&](int kt, int stage) {
-    put(1 - stage, 1 - stage);
-    fetch(kt + 3, 1 - stage);
+  // k tile kt (= `at` modulo S) is in LDS stage kt % 2, tiles kt + 1 to kt + S are on their way
+  auto step = [&](int kt, int at) {
+    const int set = (at + 1) % S, stage = at % 2;
+    put(set, 1 - stage);
+    fetch(kt + 1 + S, set);
     __builtin_amdgcn_sched_barrier(0);  // the loads go out before the MFMAs, not when registers fall free
-    const float* sa = lds + stage * 2 * kOperandFloats;
-    const float* sb = sa + kOperandFloats;
+    const float* sa = lds + stage * kStage;
+    const float* sb = sa + OpA::kFloats;
 #pragma unroll
     for (int kk = 0; kk < TK / 16; ++kk) {
-      f32x4_t fa[2], fb[2];
+      f32x4_t fa[NA], fb[NB];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = OpA::frag(sa, a_row + 16 * i, kk);
+      for (int i = 0; i < NA; ++i) fa[i] = OpA::frag(sa, a_row + 16 * i, kk);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j] = OpB::frag(sb, b_row[j], kk);
+      for (int j = 0; j < NB; ++j) fb[j] = OpB::frag(sb, b_row[j], kk);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < NA; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
     }
     __syncthreads();
   };
-  for (int kt = 0; kt + 1 < n_kt; kt += 2) {
-    step(kt, 0);
-    step(kt + 1, 1);
+  int kt = 0;
+  for (; kt + S <= n_kt; kt += S) {
+#pragma unroll
+    for (int i = 0; i < S; ++i) step(kt + i, i);
   }
-  if (n_kt & 1) step(n_kt - 1, 0);
+#pragma unroll
+  for (int i = 0; i < S - 1; ++i)
+    if (kt + i < n_kt) step(kt + i, i);
 }
 
 // Position of this wavefront and lane in the output tile: block (i, j) holds rows row + 16 i + r, r = 0..3.
+template <int NB>
 struct OutPos {
   int wm, wn, row, col;
   __device__ __forceinline__ OutPos() {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     wm = wave >> 1;
     wn = wave & 1;
-    row = wm * 32 + (lane >> 4) * 4;
+    row = wm * 16 * NB + (lane >> 4) * 4;
     col = lane & 15;
   }
 };
@@ -244,11 +262,12 @@ struct F32Params {
   FoldedCombine fold;               // scatter == nullptr: nothing folded
 };
 
-__device__ __forceinline__ void store_row_product(const F32Params& p, const f32x4_t (&acc)[2][2], const RowTile& t, int n0,
+template <int NB>
+__device__ __forceinline__ void store_row_product(const F32Params& p, const f32x4_t (&acc)[NB][NB], const RowTile& t, int n0,
                                                   int N) {
-  const OutPos o;
+  const OutPos<NB> o;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = t.m0 + o.row + 16 * i + r;
@@ -256,8 +275,8 @@ __device__ __forceinline__ void store_row_product(const F32Params& p, const f32x
       const int token = p.fold.scatter ? p.fold.scatter[m] : 0;
       const float scale = p.fold.scatter && p.fold.scale ? p.fold.scale[token] : 1.f;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = n0 + o.wn * 32 + 16 * j + o.col;
+      for (int j = 0; j < NB; ++j) {
+        const int n = n0 + o.wn * 16 * NB + 16 * j + o.col;
         if (n >= N) continue;
         const float v = acc[i][j][r];
         if (p.C) p.C[(long)m * N + n] = v;
@@ -270,30 +289,31 @@ __device__ __forceinline__ void store_row_product(const F32Params& p, const f32x
     }
 }
 
-// G = X Wg^T, U = X Wu^T, A = silu(G) U: 64 rows x 32 columns of each.  LDS rows 0..31 of operand B are gate
+constexpr int kPairCols = 32;  // columns of G and of U per tile
+// G = X Wg^T, U = X Wu^T, A = silu(G) U: 32 NB rows x 32 columns of each.  LDS rows 0..31 of operand B are gate
 // rows, 32..63 the matching up rows, and a wavefront takes sixteen of either.
-template <bool WIDE>
+template <int NB, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  __shared__ __attribute__((aligned(16))) float lds[2 * (kOperandFloats<NB> + kOperandFloats<2>)];
   RowTile t;
-  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
-  const long first_col = ((long)blockIdx.z * gridDim.x + blockIdx.x) * (TN / 2);
+  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
+  const long first_col = ((long)blockIdx.z * gridDim.x + blockIdx.x) * kPairCols;
   if (first_col >= p.F) return;
   const int n0 = (int)first_col;
   const long first = ((long)t.e * p.F + n0) * p.H;
-  Operand<false, 4, WIDE> a;
-  Operand<false, 4, WIDE, true> b;
+  Operand<NB, false, 4, WIDE> a;
+  Operand<2, false, 4, WIDE, true> b;
   if (p.gather) a.init(p.x, p.H, t.m_end - t.m0, nullptr, p.gather + t.m0, p.gather_div);
   else a.init(p.x + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
   b.init(p.Wg + first, p.H, p.F - n0, p.Wu + first);
-  f32x4_t acc[2][2] = {};
-  const OutPos o;
+  f32x4_t acc[NB][2] = {};
+  const OutPos<NB> o;
   const int b_row[2] = {o.wn * 16, 32 + o.wn * 16};
-  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 32, b_row, lds);
+  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 16 * NB, b_row, lds);
   const int n = n0 + o.wn * 16 + o.col;
   if (n >= p.F) return;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = t.m0 + o.row + 16 * i + r;
@@ -307,57 +327,61 @@ __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p)
 }
 
 // Y = A Wd^T
-template <int VF, bool WIDE>
+template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
-  const int n0 = blockIdx.x * TN;
-  Operand<false, VF, WIDE> a, b;
+  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * kTile<NB>;
+  Operand<NB, false, VF, WIDE> a, b;
   a.init(p.A + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
   b.init(p.Wd + ((long)t.e * p.H + n0) * p.F, p.F, p.H - n0);
-  f32x4_t acc[2][2] = {};
-  const OutPos o;
-  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
-  mac(acc, a, b, p.F, 1, 0, 0, o.wm * 32, b_row, lds);
+  f32x4_t acc[NB][NB] = {};
+  const OutPos<NB> o;
+  int b_row[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) b_row[j] = o.wn * 16 * NB + 16 * j;
+  mac(acc, a, b, p.F, 1, 0, 0, o.wm * 16 * NB, b_row, lds);
   store_row_product(p, acc, t, n0, p.H);
 }
 
 // dA = dY Wd; with the saved G, U: A, dG, dU
-template <int VF, bool WIDE>
+template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  if (!find_row_tile(p.seg, p.E, blockIdx.y, &t)) return;
-  const int n0 = blockIdx.x * TN;
-  Operand<false, 4, WIDE> a;
-  Operand<true, VF, WIDE> b;
+  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
+  const int n0 = blockIdx.x * kTile<NB>;
+  Operand<NB, false, 4, WIDE> a;
+  Operand<NB, true, VF, WIDE> b;
   a.init(p.dy + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
   b.init(p.Wd + (long)t.e * p.H * p.F + n0, p.F, p.F - n0);
-  f32x4_t acc[2][2] = {};
-  const OutPos o;
-  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
-  // what the stores need of G and U is on its way during the product (T=256 H=128 F=256: 12.4 -> 9.6 us)
-  float g[2][4][2], u[2][4][2];
+  f32x4_t acc[NB][NB] = {};
+  const OutPos<NB> o;
+  int b_row[NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < NB; ++j) b_row[j] = o.wn * 16 * NB + 16 * j;
+  // what the stores need of G and U is on its way during the product (T=256 H=128 F=256: 12.4 -> 9.6 us)
+  float g[NB][4][NB], u[NB][4][NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NB; ++j) {
         const int m = min(t.m0 + o.row + 16 * i + r, t.m_end - 1), n = min(n0 + b_row[j] + o.col, p.F - 1);
         g[i][r][j] = p.G[(long)m * p.F + n];
         u[i][r][j] = p.U[(long)m * p.F + n];
       }
-  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 32, b_row, lds);
+  mac(acc, a, b, p.H, 1, 0, 0, o.wm * 16 * NB, b_row, lds);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = t.m0 + o.row + 16 * i + r;
       if (m >= t.m_end) continue;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NB; ++j) {
         const int n = n0 + b_row[j] + o.col;
         if (n >= p.F) continue;
         const long at = (long)m * p.F + n;
@@ -367,42 +391,46 @@ __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
 }
 
 // dX = dG Wg + dU Wu, tile `tile` of the list (column tiles side by side)
-template <int VF, bool WIDE>
+template <int NB, int VF, bool WIDE>
 __device__ __forceinline__ void input_grad(const F32Params& p, int tile, float* lds) {
-  const int th = (p.H + TN - 1) / TN;
+  const int th = (p.H + kTile<NB> - 1) / kTile<NB>;
   RowTile t;
-  if (!find_row_tile(p.seg, p.E, tile / th, &t)) return;
-  const int n0 = tile % th * TN;
-  Operand<false, VF, WIDE> a;
-  Operand<true, 4, WIDE> b;
+  if (!find_row_tile<NB>(p.seg, p.E, tile / th, &t)) return;
+  const int n0 = tile % th * kTile<NB>;
+  Operand<NB, false, VF, WIDE> a;
+  Operand<NB, true, 4, WIDE> b;
   a.init(p.dG + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
   b.init(p.Wg + (long)t.e * p.F * p.H + n0, p.H, p.H - n0);
-  f32x4_t acc[2][2] = {};
-  const OutPos o;
-  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
-  mac(acc, a, b, p.F, 2, p.dU - p.dG, p.Wu - p.Wg, o.wm * 32, b_row, lds);
+  f32x4_t acc[NB][NB] = {};
+  const OutPos<NB> o;
+  int b_row[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) b_row[j] = o.wn * 16 * NB + 16 * j;
+  mac(acc, a, b, p.F, 2, p.dU - p.dG, p.Wu - p.Wg, o.wm * 16 * NB, b_row, lds);
   store_row_product(p, acc, t, n0, p.H);
 }
 
 // dW[m, n] = sum over the rows of an expert of P[row, m] Q[row, n]   (zeros if it has none)
-template <int VM, int VN, bool WIDE>
+template <int NB, int VM, int VN, bool WIDE>
 __device__ __forceinline__ void weight_grad(const float* P, int M, const float* Q, int N, float* dW, int k_begin, int k_end,
                                             int m0, int n0, float* lds) {
-  Operand<true, VM, WIDE> a;
-  Operand<true, VN, WIDE> b;
+  Operand<NB, true, VM, WIDE> a;
+  Operand<NB, true, VN, WIDE> b;
   a.init(P + (long)k_begin * M + m0, M, M - m0);
   b.init(Q + (long)k_begin * N + n0, N, N - n0);
-  f32x4_t acc[2][2] = {};
-  const OutPos o;
-  const int b_row[2] = {o.wn * 32, o.wn * 32 + 16};
-  mac(acc, a, b, k_end - k_begin, 1, 0, 0, o.wm * 32, b_row, lds);
+  f32x4_t acc[NB][NB] = {};
+  const OutPos<NB> o;
+  int b_row[NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < NB; ++j) b_row[j] = o.wn * 16 * NB + 16 * j;
+  mac(acc, a, b, k_end - k_begin, 1, 0, 0, o.wm * 16 * NB, b_row, lds);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = m0 + o.row + 16 * i + r;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < NB; ++j) {
         const int n = n0 + b_row[j] + o.col;
         if (m < M && n < N) dW[(long)m * N + n] = acc[i][j][r];
       }
@@ -414,47 +442,76 @@ __device__ __forceinline__ void weight_grad(const float* P, int M, const float* 
 //   T=1500 H=516 F=1030 E=8 k=2 (459 dX tiles, 3672 others):   four launches 242 us, one 204 (fp32 matrix rate: 131)
 //   T=256 H=128 F=256 E=4 k=2 (24 and 96):                      36, 17
 // This launch covers the list from `first` to `end`; `dx_tiles`, `dw_tiles`: tiles of dX and of each dW.
-template <int VF, bool WIDE>
+template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, int first, int end, int dx_tiles, int dw_tiles) {
-  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats];
+  __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   int r = first + (int)(blockIdx.y * gridDim.x + blockIdx.x);
   if (r >= end) return;
-  if (r < dx_tiles) return input_grad<VF, WIDE>(p, r, lds);
+  if (r < dx_tiles) return input_grad<NB, VF, WIDE>(p, r, lds);
   r -= dx_tiles;
   const int which = r / dw_tiles;  // 0 = dWd (P = dY, Q = A), 1 = dWg (dG, x_p), 2 = dWu (dU, x_p)
   r -= which * dw_tiles;
-  const int tf = (p.F + TN - 1) / TN, th = (p.H + TN - 1) / TN;
+  const int tf = (p.F + kTile<NB> - 1) / kTile<NB>, th = (p.H + kTile<NB> - 1) / kTile<NB>;
   const int e = r / (tf * th), tile = r - e * tf * th, width = which == 0 ? tf : th;
-  const int m0 = tile / width * TM, n0 = tile % width * TN;
+  const int m0 = tile / width * kTile<NB>, n0 = tile % width * kTile<NB>;
   const int k_begin = p.seg[e], k_end = p.seg[e + 1];
   const long FH = (long)p.F * p.H * e;
-  if (which == 0) weight_grad<4, VF, WIDE>(p.dy, p.H, p.A, p.F, p.dWd + FH, k_begin, k_end, m0, n0, lds);
-  else weight_grad<VF, 4, WIDE>(which == 1 ? p.dG : p.dU, p.F, p.x, p.H, (which == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
+  if (which == 0) weight_grad<NB, 4, VF, WIDE>(p.dy, p.H, p.A, p.F, p.dWd + FH, k_begin, k_end, m0, n0, lds);
+  else weight_grad<NB, VF, 4, WIDE>(which == 1 ? p.dG : p.dU, p.F, p.x, p.H, (which == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
 }
 
 constexpr unsigned kMaxWidth = 1 << 20;  // of a grid: its width in threads is a 32-bit number
 
-template <int VF, bool WIDE>
-static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
-  const unsigned m_tiles = max_m_tiles(d, TM);
-  if (m_tiles == 0) return DYNMO_OK;
-  const unsigned cols = (d->F + TN / 2 - 1) / (TN / 2), width = cols < kMaxWidth ? cols : kMaxWidth;
+// Which products go on tiles of 32 x 32 (gate/up: 32 rows), by how many tiles of 64 x 64 they have.  A k step of a 64 x 64 tile
+// keeps its wavefronts' matrix units busy for 1024 cycles, and with few tiles that chain is the time of the product; with many the
+// doubled traffic per flop weighs.  us on 64 / 32, tiles of 64 in brackets (T H F E k; times with the events around each launch):
+//               256 128 256 4 2   303 256 768 5 3   1024 256 512 4 2   800 512 1024 4 2   1500 516 1030 8 2   2048 1024 1024 8 2
+//   gate/up     10 /  8  (96)     19 / 17  (456)    25 / 22  (576)     47 / 42  (928)     88 /  90  (1782)   174 / 173  (2304)
+//   down        13 /  8  (24)     24 / 12   (76)    19 / 15  (144)     31 / 26  (232)     58 /  55   (486)   102 /  87  (1152)
+//   dA          11 /  7  (48)     14 / 13  (228)    20 / 16  (288)     30 / 28  (464)     59 /  60   (918)   103 /  97  (1152)
+//   gradients   19 / 11 (120)     50 / 29  (796)    40 / 35  (528)     85 / 85 (1768)    183 / 217  (4158)   364 / 397  (7296)
+constexpr int64_t kSmallGateup = 1024, kSmallDown = 1152, kSmallDA = 512, kSmallGrads = 1536;
+static unsigned tiles_of(int n, int tile) { return (unsigned)((n + (int64_t)tile - 1) / tile); }
+
+template <int NB, int VF, bool WIDE>
+static int32_t gateup_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const unsigned cols = tiles_of(d->F, kPairCols), width = cols < kMaxWidth ? cols : kMaxWidth;
   DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st,
-                     f32_gateup_kernel<WIDE><<<dim3(width, m_tiles, (cols + width - 1) / width), dim3(kThreads), 0, st>>>(p));
-  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<VF, WIDE><<<dim3((d->H + TN - 1) / TN, m_tiles), dim3(kThreads), 0, st>>>(p));
+                     f32_gateup_kernel<NB, WIDE><<<dim3(width, max_m_tiles(d, kTile<NB>), (cols + width - 1) / width), dim3(kThreads), 0, st>>>(p));
+  return DYNMO_OK;
+}
+template <int NB, int VF, bool WIDE>
+static int32_t down_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st,
+                     f32_down_kernel<NB, VF, WIDE><<<dim3(tiles_of(d->H, kTile<NB>), max_m_tiles(d, kTile<NB>)), dim3(kThreads), 0, st>>>(p));
+  return DYNMO_OK;
+}
+template <int NB, int VF, bool WIDE>
+static int32_t dA_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  DYNMO_TIMED_LAUNCH(K_FFN_DA, st,
+                     f32_dA_kernel<NB, VF, WIDE><<<dim3(tiles_of(d->F, kTile<NB>), max_m_tiles(d, kTile<NB>)), dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 
 template <int VF, bool WIDE>
-static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
-  const unsigned m_tiles = max_m_tiles(d, TM), tf = (d->F + TN - 1) / TN, th = (d->H + TN - 1) / TN;
-  if (m_tiles > 0) DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<VF, WIDE><<<dim3(tf, m_tiles), dim3(kThreads), 0, st>>>(p));
+static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const int64_t m_tiles = max_m_tiles(d, 64);
+  if (m_tiles == 0) return DYNMO_OK;
+  const bool small_g = !WIDE && m_tiles * tiles_of(d->F, kPairCols) <= kSmallGateup, small_d = !WIDE && m_tiles * tiles_of(d->H, 64) <= kSmallDown;
+  const int32_t rc = small_g ? gateup_f32<1, VF, false>(d, p, st) : gateup_f32<2, VF, WIDE>(d, p, st);
+  if (rc) return rc;
+  return small_d ? down_f32<1, VF, false>(d, p, st) : down_f32<2, VF, WIDE>(d, p, st);
+}
+
+template <int NB, int VF, bool WIDE>
+static int32_t grads_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const unsigned tf = tiles_of(d->F, kTile<NB>), th = tiles_of(d->H, kTile<NB>);
   // the weight gradients are written for every expert, rows or not
-  const int dx_tiles = (int)(th * m_tiles), dw_tiles = (int)(tf * th * d->E);
+  const int dx_tiles = (int)(th * max_m_tiles(d, kTile<NB>)), dw_tiles = (int)(tf * th * d->E);
   auto launch = [&](const ProfRoles& roles, int first, int n) -> int32_t {
     if (n == 0) return DYNMO_OK;
     const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
-    DYNMO_TIMED_LAUNCH(roles, st, f32_grads_kernel<VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(
+    DYNMO_TIMED_LAUNCH(roles, st, f32_grads_kernel<NB, VF, WIDE><<<dim3(width, (n + width - 1) / width), dim3(kThreads), 0, st>>>(
                                       p, first, first + n, dx_tiles, dw_tiles));
     return DYNMO_OK;
   };
@@ -472,6 +529,16 @@ static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
   if (dx_tiles > 0) roles.add(K_FFN_DX, 2.0);
   for (KernelId id : ids) roles.add(id, 1.0);
   return launch(roles, 0, dx_tiles + 3 * dw_tiles);
+}
+
+template <int VF, bool WIDE>
+static int32_t bwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+  const int64_t m_tiles = max_m_tiles(d, 64), tf = tiles_of(d->F, 64), th = tiles_of(d->H, 64);
+  if (m_tiles > 0) {
+    const int32_t rc = !WIDE && m_tiles * tf <= kSmallDA ? dA_f32<1, VF, false>(d, p, st) : dA_f32<2, VF, WIDE>(d, p, st);
+    if (rc) return rc;
+  }
+  return !WIDE && th * m_tiles + 3 * tf * th * d->E <= kSmallGrads ? grads_f32<1, VF, false>(d, p, st) : grads_f32<2, VF, WIDE>(d, p, st);
 }
 
 // Whether 64 rows of an operand can span 2 GiB (the rows of a gathered input as a whole stay below that)

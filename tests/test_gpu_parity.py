@@ -278,6 +278,23 @@ def test_f32_layer_tile_edges(T, H, F, E, k):
     check_layer_full(layer, ref, w.dtype)
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [(700, 2564, 1154, 8, 2), (1100, 132, 2050, 3, 2), (520, 644, 230, 12, 1), (33, 36, 35, 4, 2)])
+def test_f32_layer_both_tile_sizes(T, H, F, E, k):
+    """Products on tiles of 64 x 64 (the first layer: all of them; the second: gate/up and dA; the third: the gradients) and of 32 x 32
+    (all others), with ragged rows, columns and k steps."""
+    say("f32 tile sizes T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
+    w = wl.scaled(wl.CONFIGS[1], T=T, H=H, F=F, E=E, k=k, bias=(), zipf_s=1.0, seed=9300 + T)
+    inp = wl.make_inputs(w, threads=4)
+    layer = run_moe(w, inp)
+    ref = orc.moe_layer(inp["logits"], inp["x"], inp["Wg"], inp["Wu"], inp["Wd"], w.k, inp["dout"])
+    check_layer_full(layer, ref, w.dtype)
+    out = layer.out.clone()
+    dev = {n: to_device(a) for n, a in inp.items()}
+    layer.out.zero_()
+    layer.forward_gather(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+    assert torch.equal(layer.out, out)
+
+
 @pytest.mark.parametrize("T,H,F", [(64, 4, 8600001), (40, 4, 17500002), (40, 17500000, 3)])
 def test_f32_rows_beyond_32_bit_offsets(T, H, F):
     """fp32 layers of which 64 rows span more than 2 GiB (8600001: from row 62 on, both operands [row][k]; 17.5 M: k-rows
