@@ -1,14 +1,18 @@
-"""Builds the C-ABI library from csrc/ with hipcc for gfx950 (in-tree)."""
+"""Builds the C-ABI library from csrc/ with hipcc for gfx950, and the Python call module, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+
+import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdynmo.so")
+CALLS = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -37,10 +41,24 @@ def _compile(src):
     return obj
 
 
+def _build_calls():
+    """csrc/fastcall.cpp: host code only (tensors in, library calls out)."""
+    from torch.utils import cpp_extension  # here: only a build needs it
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-missing-field-initializers",
+           *("-I" + p for p in cpp_extension.include_paths()), "-I" + sysconfig.get_paths()["include"],
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch.compiled_with_cxx11_abi()), os.path.join(CSRC, "fastcall.cpp"), "-o", CALLS,
+           *("-L" + p for p in cpp_extension.library_paths()), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for fastcall.cpp:\n" + r.stderr)
+
+
 def build_library(jobs: int = 8) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        calls = ex.submit(_build_calls)
         objs = list(ex.map(_compile, sources()))
+        calls.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
