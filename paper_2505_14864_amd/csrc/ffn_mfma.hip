@@ -19,7 +19,8 @@
 // instruction): no staging registers, no LDS store instructions.  A wavefront is held at
 // such a load while the memory pipeline takes it, and its MFMAs wait behind it, so only
 // one wavefront of each SIMD (0 .. 3) loads, two every three MFMA slots, and the other
-// one keeps the matrix unit busy meanwhile; those (4 .. 7) issue the L2 prefetch.
+// one keeps the matrix unit busy meanwhile; those (4 .. 7) load a tile's second k tile and
+// issue the L2 prefetch.
 // Against loads by all eight (us; T H F E k): dX 4096 4096 14336 8 2: 1672 -> 1605, 3000
 // 2048 4096 16 2: 249 -> 229; dA 8192 4096 688 16 4: 290 -> 274; down of 1000 tokens of
 // the first layer 402 -> 368.  Long dense products gain less (gate/up of the first layer
@@ -102,10 +103,6 @@ __device__ __forceinline__ void touch_to_lds(desc_t d, uint32_t lds_offset, uint
 // Waits of the k loop, written out because the loads above are invisible to the compiler.
 __device__ __forceinline__ void wait_loads_and_lds() { __builtin_amdgcn_s_waitcnt(0x0070); }  // vmcnt(0) lgkmcnt(0)
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }            // lgkmcnt(0)
-template <int N>
-__device__ __forceinline__ void wait_loads_but() {  // at most N loads still in flight
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-}
 __device__ __forceinline__ void wg_barrier() { __builtin_amdgcn_s_barrier(); }
 
 // The thread index behind a compiler barrier.  Offsets derived from it are recomputed where
@@ -123,7 +120,7 @@ __device__ __forceinline__ int tid_now() {
 // a ragged last tile).
 struct Pieces {
   uint32_t off[kPieces];  // byte offset from the tile's (row0, k0) element, or kOob
-  int kpos[kPieces];      // k index of the lane's 16 bytes inside the 64-wide k tile
+  int kpos[2];            // [row][k]: k index of the lane's 16 bytes inside the 64-wide k tile, of even and of odd pieces
 };
 
 // [row][k] memory: piece q holds LDS rows 8 q .. 8 q + 7; lane l fills slot l % 8 of row
@@ -132,14 +129,14 @@ struct Pieces {
 __device__ __forceinline__ Pieces pieces_rowk(uint32_t ld_bytes, int rows_left, int wrap) {
   Pieces ps;
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
 #pragma unroll
   for (int j = 0; j < kPieces; ++j) {
     const int lrow = (wave * kPieces + j) * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((lrow >> 1) & 7);
     const int row = lrow % wrap;
     ps.off[j] = row < rows_left ? (uint32_t)row * ld_bytes + c * 16 : kOob;
-    ps.kpos[j] = c * 8;
+    if (j < 2) ps.kpos[j] = c * 8;
   }
   return ps;
 }
@@ -148,9 +145,9 @@ __device__ __forceinline__ Pieces pieces_rowk(uint32_t ld_bytes, int rows_left, 
 // k-row 2 q + l / 32, i.e. quarter (l % 4) of stored block (l % 32) / 4 (quarters 0, 1 and
 // 2, 3 are the block's two halves).
 __device__ __forceinline__ Pieces pieces_krow(uint32_t ld_bytes, int rows_left) {
-  Pieces ps;
+  Pieces ps = {};
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
 #pragma unroll
   for (int j = 0; j < kPieces; ++j) {
     const int k = (wave * kPieces + j) * 2 + (lane >> 5);
@@ -159,7 +156,6 @@ __device__ __forceinline__ Pieces pieces_krow(uint32_t ld_bytes, int rows_left) 
     const int quarter = (slot & 3) ^ (((k >> 3) & 1) << 1);
     const int col = blk * 32 + quarter * 8;
     ps.off[j] = col < rows_left ? (uint32_t)k * ld_bytes + col * 2 : kOob;
-    ps.kpos[j] = k;
   }
   return ps;
 }
@@ -171,14 +167,14 @@ __device__ __forceinline__ Pieces pieces_rowk_gather(uint32_t ld_bytes, int row0
                                                      const int32_t* __restrict__ rowmap, int rowdiv) {
   Pieces ps;
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
 #pragma unroll
   for (int j = 0; j < kPieces; ++j) {
     const int lrow = (wave * kPieces + j) * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((lrow >> 1) & 7);
     ps.off[j] = kOob;
     if (lrow < rows_left) ps.off[j] = (uint32_t)(rowmap[row0 + lrow] / rowdiv) * ld_bytes + c * 16;
-    ps.kpos[j] = c * 8;
+    if (j < 2) ps.kpos[j] = c * 8;
   }
   return ps;
 }
@@ -612,11 +608,11 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   const uint32_t wave_pieces = wave_u % kLoaders * kPieces * 1024;  // this wavefront's pieces inside an operand tile
   auto dma_a = [&](const Pieces& pa, const KTile& q, uint32_t stage, auto J) {
     constexpr int j = decltype(J)::value;
-    load_to_lds<j * 1024>(q.a, stage + wave_pieces, A_TRANS || WHOLE_K || pa.kpos[j] < q.k_left ? pa.off[j] : kOob);
+    load_to_lds<j * 1024>(q.a, stage + wave_pieces, A_TRANS || WHOLE_K || pa.kpos[j & 1] < q.k_left ? pa.off[j] : kOob);
   };
   auto dma_b = [&](const Pieces& pb, const KTile& q, uint32_t stage, auto J) {
     constexpr int j = decltype(J)::value;
-    load_to_lds<kTileBytes + j * 1024>(q.b, stage + wave_pieces, B_TRANS || WHOLE_K || pb.kpos[j] < q.k_left ? pb.off[j] : kOob);
+    load_to_lds<kTileBytes + j * 1024>(q.b, stage + wave_pieces, B_TRANS || WHOLE_K || pb.kpos[j & 1] < q.k_left ? pb.off[j] : kOob);
   };
   // L2 prefetch.  The workgroups of an XCD that run side by side share operand tiles (in a run
   // of 4 x 8 output tiles, 8 share each A tile and 4 each B tile) and ask for the same lines at
@@ -782,23 +778,23 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     return parted ? touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), tb.total - tail_tiles + (xcd / split) * slots, min(slots, tail_tiles - (xcd / split) * slots), slot)
                   : touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), run_base(round), run_len(round), place(round));
   };
-  if (loader) {
-    pa = pieces_a(t);
-    pb = pieces_b(t);
-    const KTile q0 = knext(kit);
+  // The first k tile is loaded by the loading wavefronts, the second one by the others.
+  pa = pieces_a(t);
+  pb = pieces_b(t);
+  const KTile q0 = knext(kit), q1 = knext(kit);
+  if (!loader) {
+    static_for<kPieces>([&](auto J) { dma_a(pa, q1, lds0 + kStageBytes, J); });
+    static_for<kPieces>([&](auto J) { dma_b(pb, q1, lds0 + kStageBytes, J); });
+    if constexpr (TOUCHES) {
+      th = touch_now();
+      for (int i = 2; i < kTouchLead; ++i) touch(knext(kit), th);
+    }
+  } else {
     if (!first_in_flight) {
       static_for<kPieces>([&](auto J) { dma_a(pa, q0, lds0, J); });
       static_for<kPieces>([&](auto J) { dma_b(pb, q0, lds0, J); });
     }
-    const KTile q1 = knext(kit);
-    static_for<kPieces>([&](auto J) { dma_a(pa, q1, lds0 + kStageBytes, J); });
-    static_for<kPieces>([&](auto J) { dma_b(pb, q1, lds0 + kStageBytes, J); });
-    wait_loads_but<2 * kPieces>();  // the first tile has landed
-  } else if constexpr (TOUCHES) {
-    th = touch_now();
-    knext(kit);
-    knext(kit);
-    for (int i = 2; i < kTouchLead; ++i) touch(knext(kit), th);
+    wait_loads_and_lds();  // the first tile has landed
   }
   wg_barrier();
   const int valid16 = min(16, (t.m_end - t.m0 + 15) / 16);  // valid 16-row blocks of the tile (a prefix)
@@ -864,9 +860,9 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     };
     const std::integral_constant<int, 2> c2;
     auto step0 = [&]() { mfmas(c0, 0u, KTile{}); };
-    auto step1_row0_and_barrier = [&]() {
+    auto step1_row0_and_barrier = [&](bool first) {
       mfmas(c1, 0u, KTile{});
-      if constexpr (LOADER) wait_loads_and_lds();
+      if (LOADER || first) wait_loads_and_lds();
       else wait_lds();
       wg_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -893,7 +889,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     };
     __builtin_amdgcn_sched_barrier(0);
     step0();
-    step1_row0_and_barrier();
+    step1_row0_and_barrier(true);
     for (int kt = kt_lo; kt + 1 < kt_hi; ++kt) {
       const int stage = (kt - kt_lo) & 1;
       const uint32_t to_next = stage ? 0u - (uint32_t)kStageBytes : (uint32_t)kStageBytes;
@@ -901,7 +897,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
       if constexpr (LOADER || TOUCHES) q2 = knext(kit);
       step1_rest(to_next, lds0 + stage * kStageBytes, q2);
       step0();
-      step1_row0_and_barrier();
+      step1_row0_and_barrier(false);
     }
     if constexpr (ROWS > 1) mfmas(std::integral_constant<int, 3>{}, 0u, KTile{});
   };
@@ -909,7 +905,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     // No valid rows or columns in this wavefront's part: it only keeps up the staging -- moves its
     // pieces and meets the barriers -- and leaves the SIMD and the LDS to the others.
     for (int kt = kt_lo; kt < kt_hi; ++kt) {
-      if (loader) wait_loads_and_lds();
+      if (loader || kt == kt_lo) wait_loads_and_lds();
       wg_barrier();
       if (loader) {
         const uint32_t freed = lds0 + ((kt - kt_lo) & 1) * kStageBytes;
