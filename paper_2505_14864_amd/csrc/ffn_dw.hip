@@ -14,8 +14,6 @@
 //     that a lane holds four neighbours of a row, one 8-byte LDS store, where accumulators in column order were four
 //     4-byte ones in fp32;
 //   * a step's fragments are read while the step before is computed.
-#include <algorithm>
-
 #include "ffn_gemm.h"
 
 namespace dynmo {
@@ -135,6 +133,15 @@ struct DwFrag {
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "+v"(hi) : "v"(addr), "n"(4 * K_STRIDE) : "memory");
   }
 };
+
+// The same as ordinary reads, which the compiler waits for
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+template <int K_STRIDE>
+__device__ __forceinline__ bf16x8_t read_now(uint32_t addr) {
+  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)addr);
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)(addr + 4 * K_STRIDE));
+  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 // Waits until at most N LDS reads are outstanding (they complete in order); nothing moves across.
 template <int N>
@@ -341,7 +348,39 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
       }
       body(std::false_type{}, std::false_type{});
     };
-    if (my_rows == WBM) {
+    // 64 x 64 tiles, which are never walked: four MFMAs per step and five workgroups per compute unit, where reading ahead only
+    // costs (one expert, 2608 rows, 128 x 4736: 22.7 us so, 25.4 with the loop above).
+    auto plain_loop = [&](auto ROWS_C) {
+      constexpr int ROWS = decltype(ROWS_C)::value;
+      const int lane = lane_now();
+      uint32_t ra[WBM], rb[WBN];
+#pragma unroll
+      for (int i = 0; i < WBM; ++i) ra[i] = lds0 + frag_offset<TM>(lane, wm + 2 * i);
+#pragma unroll
+      for (int j = 0; j < WBN; ++j) rb[j] = lds0 + S::kBytesA + frag_offset<TN>(lane, wn * WBN + j);
+      for (int kt = 0; kt < n_kt; ++kt) {
+        wait_stage<(NS - 2) * S::kLoads>();
+        __builtin_amdgcn_s_barrier();
+        issue(last_of_ring(stage));
+        if constexpr (ROWS > 0) {
+          bf16x8_t a[ROWS], b[WBN];
+#pragma unroll
+          for (int i = 0; i < ROWS; ++i) a[i] = read_now<TM * 2>(ra[i] + stage);
+#pragma unroll
+          for (int j = 0; j < WBN; ++j) b[j] = read_now<TN * 2>(rb[j] + stage);
+#pragma unroll
+          for (int j = 0; j < WBN; ++j)
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+        }
+        stage = following(stage);
+      }
+    };
+    if constexpr (WBN == 2) {
+      if (my_rows == 2) plain_loop(std::integral_constant<int, 2>{});
+      else if (my_rows == 1) plain_loop(std::integral_constant<int, 1>{});
+      else plain_loop(std::integral_constant<int, 0>{});
+    } else if (my_rows == WBM) {
       loop(std::integral_constant<int, WBM>{});
     } else if (my_rows == 0) {  // a wavefront without work only keeps up the loads and the barriers
       __builtin_amdgcn_s_barrier();
@@ -355,10 +394,9 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
         stage = following(stage);
       }
       stage = following(stage);
-    } else if (WBM == 2 || my_rows == 1) {
-      loop(std::integral_constant<int, 1>{});
-    } else if constexpr (WBM == 4) {
-      if (my_rows == 2) loop(std::integral_constant<int, 2>{});
+    } else {
+      if (my_rows == 1) loop(std::integral_constant<int, 1>{});
+      else if (my_rows == 2) loop(std::integral_constant<int, 2>{});
       else loop(std::integral_constant<int, 3>{});
     }
     if (more) wait_stage<(NS - 2) * S::kLoads>();  // the next tile's first k step has landed
@@ -398,13 +436,13 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
 template <int WBM, int WBN>
 static int32_t launch_dw(DwParams p, double rows, const ProfRoles& roles, hipStream_t st) {
   const int tiles = p.E * p.per_expert;
-  // Runs of 32 tiles (an XCD's 32 compute units walk two at a time): with fewer, workgroups that share operand tiles are spread
-  // over more L2s; 128 leave XCDs without work at the end.  Several tiles per workgroup where a tile is short, up to 32 k steps on
-  // average, as long as two workgroups per slot of the chip remain.  us with one tile in runs of 16 / four in runs of 32; before this
-  // kernel: 64 experts, 16384 rows, 2048 x 1024 361 / 342, 368; 16, 6000, 2048 x 4096 412 / 394, 421; 8, 8192, 2048 x 4096 416 / 406,
-  // 428.  Longer tiles hide their ends behind the other workgroup's arithmetic (16, 32768, 4096 x 688: 531 / 539, 569).
-  p.group = tiles >= 2048 ? 32 : tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
-  p.walk = rows <= 1024.0 * p.E ? std::max(1, std::min(4, tiles / 1024)) : 1;
+  // Runs of 16 tiles, of 32 where there are many (128: XCDs without work at the end).  Several tiles per workgroup where a tile is
+  // short, up to 32 k steps on average, and the chip is filled many times.  us with one tile in runs of 16 / four in runs of 32; before
+  // this kernel: 64 experts, 16384 rows, 2048 x 1024, 12288 tiles 361 / 342, 368; 16, 6000, 2048 x 4096 412 / 394, 421; 8, 8192, 2048 x
+  // 4096, 6144 tiles 416 / 406, 428.  Longer tiles hide their ends behind the other workgroup's arithmetic (16, 32768, 4096 x 688: 531 /
+  // 539, 569), and with fewer the last round gets coarser (57, 21548 uneven, 256 x 1688, 2394 tiles: two in runs of 32 129, before 118).
+  p.group = tiles >= 4096 ? 32 : tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
+  p.walk = WBN > 2 && tiles >= 4096 && rows <= 1024.0 * p.E ? 4 : 1;
   const int run = 8 * p.group * p.walk;
   const unsigned blocks = (unsigned)((tiles + run - 1) / run * 8 * p.group);
   DYNMO_TIMED_LAUNCH(roles, st, ffn_dw_kernel<WBM, WBN><<<dim3(blocks), dim3(kDwThreads), 0, st>>>(p));

@@ -979,9 +979,9 @@ def test_small_products_tile_edges(T, H, F, E, k, expected):
     assert torch.equal(layer.out, out)
 
 
-@pytest.mark.parametrize("E,H,F,kernel", [(64, 776, 776, "128x256"), (64, 520, 520, "128x256"), (63, 512, 512, "128x128")])
+@pytest.mark.parametrize("E,H,F,kernel", [(64, 776, 776, "128x256"), (64, 520, 520, "128x256"), (63, 512, 512, "128x128"), (18, 264, 264, "64x64")])
 def test_weight_gradient_workgroups_walk_tiles(E, H, F, kernel):
-    """Weight gradients whose workgroups take four, two and two tiles each (tiles / 1024 of them, of 128 x 256 or 128 x 128): the
+    """Weight gradients whose workgroups take four tiles each (the first layer, 5376 tiles of 128 x 256) or one: the
     loads run up to two k steps of 32 rows ahead into the next tile, which may be another expert's, of other operands or of none.
     Experts without rows, with fewer rows than the steps that run ahead, with one row more or less than a whole step; tiles
     with a ragged last row block and columns (776 = 6 x 128 + 8, 3 x 256 + 8) beside full ones."""
