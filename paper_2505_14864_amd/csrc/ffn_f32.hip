@@ -55,7 +55,7 @@ struct RowTile {
   int e, m0, m_end;
 };
 template <int NB>
-__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, int E, int tile, RowTile* t) {
+__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, int E, int tile, int cols, bool eighths, RowTile* t, int* col) {
   const int lane = threadIdx.x & 63;
   const int begin = lane < E ? seg[lane] : 0, end = lane < E ? seg[lane + 1] : 0;
   const int n = (end - begin + kTile<NB> - 1) / kTile<NB>;
@@ -64,6 +64,14 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, i
   for (int d = 1; d < 64; d <<= 1) {
     const int o = __shfl_up(upto, d, 64);
     if (lane >= d) upto += o;
+  }
+  if (eighths) {
+    // workgroup `tile` of the list runs on XCD tile % 8, which takes a contiguous eighth of the tiles
+    const int total = __builtin_amdgcn_readlane(upto, 63) * cols, eighth = (total + 7) / 8, slot = tile >> 3;
+    if (slot >= eighth) return false;
+    const int at = (tile & 7) * eighth + slot;
+    tile = at / cols;
+    *col = at - tile * cols;
   }
   const unsigned long long owners = __ballot(upto > tile);
   if (owners == 0) return false;  // past the last tile
@@ -260,6 +268,7 @@ struct F32Params {
   const int32_t* gather;            // GATEUP: row p is x[gather[p] / gather_div], or nullptr
   int gather_div;
   FoldedCombine fold;               // scatter == nullptr: nothing folded
+  bool eighths;                     // row products: a contiguous eighth of the tiles per XCD (the grid is a list then)
 };
 
 template <int NB>
@@ -296,8 +305,9 @@ template <int NB, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[2 * (kOperandFloats<NB> + kOperandFloats<2>)];
   RowTile t;
-  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
-  const long first_col = ((long)blockIdx.z * gridDim.x + blockIdx.x) * kPairCols;
+  int col = 0;
+  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.F + kPairCols - 1) / kPairCols, p.eighths, &t, &col)) return;
+  const long first_col = (p.eighths ? col : (long)blockIdx.z * gridDim.x + blockIdx.x) * kPairCols;
   if (first_col >= p.F) return;
   const int n0 = (int)first_col;
   const long first = ((long)t.e * p.F + n0) * p.H;
@@ -331,8 +341,9 @@ template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
-  const int n0 = blockIdx.x * kTile<NB>;
+  int col = blockIdx.x;
+  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.H + kTile<NB> - 1) / kTile<NB>, p.eighths, &t, &col)) return;
+  const int n0 = col * kTile<NB>;
   Operand<NB, false, VF, WIDE> a, b;
   a.init(p.A + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
   b.init(p.Wd + ((long)t.e * p.H + n0) * p.F, p.F, p.H - n0);
@@ -350,8 +361,9 @@ template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  if (!find_row_tile<NB>(p.seg, p.E, blockIdx.y, &t)) return;
-  const int n0 = blockIdx.x * kTile<NB>;
+  int col = blockIdx.x;
+  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.F + kTile<NB> - 1) / kTile<NB>, p.eighths, &t, &col)) return;
+  const int n0 = col * kTile<NB>;
   Operand<NB, false, 4, WIDE> a;
   Operand<NB, true, VF, WIDE> b;
   a.init(p.dy + (long)t.m0 * p.H, p.H, t.m_end - t.m0);
@@ -395,8 +407,9 @@ template <int NB, int VF, bool WIDE>
 __device__ __forceinline__ void input_grad(const F32Params& p, int tile, float* lds) {
   const int th = (p.H + kTile<NB> - 1) / kTile<NB>;
   RowTile t;
-  if (!find_row_tile<NB>(p.seg, p.E, tile / th, &t)) return;
-  const int n0 = tile % th * kTile<NB>;
+  int col = tile % th;
+  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? tile : tile / th, th, p.eighths, &t, &col)) return;
+  const int n0 = col * kTile<NB>;
   Operand<NB, false, VF, WIDE> a;
   Operand<NB, true, 4, WIDE> b;
   a.init(p.dG + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
@@ -470,26 +483,38 @@ constexpr unsigned kMaxWidth = 1 << 20;  // of a grid: its width in threads is a
 //   down        13 /  8  (24)     24 / 12   (76)    19 / 15  (144)     31 / 26  (232)     58 /  55   (486)   102 /  87  (1152)
 //   dA          11 /  7  (48)     14 / 13  (228)    20 / 16  (288)     30 / 28  (464)     59 /  60   (918)   103 /  97  (1152)
 //   gradients   19 / 11 (120)     50 / 29  (796)    40 / 35  (528)     85 / 85 (1768)    183 / 217  (4158)   364 / 397  (7296)
-constexpr int64_t kSmallGateup = 1024, kSmallDown = 1152, kSmallDA = 512, kSmallGrads = 1536;
+constexpr int64_t kSmallGateup = 1024, kSmallDown = 1152, kSmallDA = 512, kSmallGrads = 1700;
 static unsigned tiles_of(int n, int tile) { return (unsigned)((n + (int64_t)tile - 1) / tile); }
 
+// The grid of a row product: a list, of which every XCD takes a contiguous eighth, so that its L2 holds the weights of an expert or
+// two and the rows that go with them; column tiles side by side in all XCDs made each of them fetch everything (us before / so, 1500
+// 516 1030 8 2: gate/up 90 / 83, down 54 / 48, dA 60 / 56, gradients, of which dX, 182 / 176; 2048 1024 1024 8 2 +-1 %).  Column by row
+// tiles where the list would be too long for 32-bit indices.
+constexpr int64_t kEighths = 1 << 24;
+static dim3 row_grid(F32Params& p, unsigned cols, unsigned rows) {
+  const int64_t tiles = (int64_t)cols * rows;
+  p.eighths = tiles <= kEighths;
+  if (p.eighths) return dim3((unsigned)((tiles + 7) / 8 * 8));
+  const unsigned width = cols < kMaxWidth ? cols : kMaxWidth;
+  return dim3(width, rows, (cols + width - 1) / width);
+}
+
 template <int NB, int VF, bool WIDE>
-static int32_t gateup_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
-  const unsigned cols = tiles_of(d->F, kPairCols), width = cols < kMaxWidth ? cols : kMaxWidth;
-  DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st,
-                     f32_gateup_kernel<NB, WIDE><<<dim3(width, max_m_tiles(d, kTile<NB>), (cols + width - 1) / width), dim3(kThreads), 0, st>>>(p));
+static int32_t gateup_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
+  const dim3 grid = row_grid(p, tiles_of(d->F, kPairCols), max_m_tiles(d, kTile<NB>));
+  DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st, f32_gateup_kernel<NB, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 template <int NB, int VF, bool WIDE>
-static int32_t down_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
-  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st,
-                     f32_down_kernel<NB, VF, WIDE><<<dim3(tiles_of(d->H, kTile<NB>), max_m_tiles(d, kTile<NB>)), dim3(kThreads), 0, st>>>(p));
+static int32_t down_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
+  const dim3 grid = row_grid(p, tiles_of(d->H, kTile<NB>), max_m_tiles(d, kTile<NB>));
+  DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<NB, VF, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 template <int NB, int VF, bool WIDE>
-static int32_t dA_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
-  DYNMO_TIMED_LAUNCH(K_FFN_DA, st,
-                     f32_dA_kernel<NB, VF, WIDE><<<dim3(tiles_of(d->F, kTile<NB>), max_m_tiles(d, kTile<NB>)), dim3(kThreads), 0, st>>>(p));
+static int32_t dA_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
+  const dim3 grid = row_grid(p, tiles_of(d->F, kTile<NB>), max_m_tiles(d, kTile<NB>));
+  DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<NB, VF, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 
@@ -504,10 +529,13 @@ static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
 }
 
 template <int NB, int VF, bool WIDE>
-static int32_t grads_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) {
+static int32_t grads_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
   const unsigned tf = tiles_of(d->F, kTile<NB>), th = tiles_of(d->H, kTile<NB>);
   // the weight gradients are written for every expert, rows or not
-  const int dx_tiles = (int)(th * max_m_tiles(d, kTile<NB>)), dw_tiles = (int)(tf * th * d->E);
+  int dx_tiles = (int)(th * max_m_tiles(d, kTile<NB>));
+  const int dw_tiles = (int)(tf * th * d->E);
+  p.eighths = dx_tiles <= kEighths;
+  if (p.eighths) dx_tiles = (dx_tiles + 7) / 8 * 8;
   auto launch = [&](const ProfRoles& roles, int first, int n) -> int32_t {
     if (n == 0) return DYNMO_OK;
     const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;
