@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "f32_grid.h"
 #include "ffn.h"
 #include "profile.h"
 
@@ -49,13 +50,20 @@ template <int NB>
 constexpr int kOperandFloats = kTile<NB> * kPitchRowK > TK * kPitchKRow<NB> ? kTile<NB> * kPitchRowK : TK * kPitchKRow<NB>;
 constexpr uint32_t kOutside = 0x80000000u;  // an offset beyond every record count: the load delivers zero
 
-// Finds row tile `tile` of the expert segments.  Lane e of every wavefront counts the tiles of
+// A workgroup's place in its grid
+struct Place {
+  bool list;
+  unsigned x, y, z, width;
+  __device__ __forceinline__ static Place here(bool list) { return {list, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x}; }
+};
+
+// The row tile and column tile of a workgroup; false if it has none.  Lane e of every wavefront counts the tiles of
 // expert e and a prefix sum and a ballot find the owner: one load latency, however many experts.
 struct RowTile {
   int e, m0, m_end;
 };
 template <int NB>
-__device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, int E, int tile, int cols, bool eighths, RowTile* t, int* col) {
+__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ seg, int E, const Place& w, int64_t cols, RowTile* t, int* col) {
   const int lane = threadIdx.x & 63;
   const int begin = lane < E ? seg[lane] : 0, end = lane < E ? seg[lane + 1] : 0;
   const int n = (end - begin + kTile<NB> - 1) / kTile<NB>;
@@ -65,18 +73,10 @@ __device__ __forceinline__ bool find_row_tile(const int32_t* __restrict__ seg, i
     const int o = __shfl_up(upto, d, 64);
     if (lane >= d) upto += o;
   }
-  if (eighths) {
-    // workgroup `tile` of the list runs on XCD tile % 8, which takes a contiguous eighth of the tiles
-    const int total = __builtin_amdgcn_readlane(upto, 63) * cols, eighth = (total + 7) / 8, slot = tile >> 3;
-    if (slot >= eighth) return false;
-    const int at = (tile & 7) * eighth + slot;
-    tile = at / cols;
-    *col = at - tile * cols;
-  }
-  const unsigned long long owners = __ballot(upto > tile);
-  if (owners == 0) return false;  // past the last tile
-  t->e = __builtin_ctzll(owners);
-  t->m0 = __builtin_amdgcn_readlane(begin, t->e) + (tile - __builtin_amdgcn_readlane(upto - n, t->e)) * kTile<NB>;
+  int row = 0;
+  if (!tile_of_workgroup(w.list, w.x, w.y, w.z, w.width, __builtin_amdgcn_readlane(upto, 63), cols, &row, col)) return false;
+  t->e = __builtin_ctzll(__ballot(upto > row));
+  t->m0 = __builtin_amdgcn_readlane(begin, t->e) + (row - __builtin_amdgcn_readlane(upto - n, t->e)) * kTile<NB>;
   t->m_end = __builtin_amdgcn_readlane(end, t->e);
   return true;
 }
@@ -268,7 +268,7 @@ struct F32Params {
   const int32_t* gather;            // GATEUP: row p is x[gather[p] / gather_div], or nullptr
   int gather_div;
   FoldedCombine fold;               // scatter == nullptr: nothing folded
-  bool eighths;                     // row products: a contiguous eighth of the tiles per XCD (the grid is a list then)
+  bool list;                        // row products: the grid is a list (row_grid)
 };
 
 template <int NB>
@@ -306,10 +306,8 @@ __global__ __launch_bounds__(kThreads) void f32_gateup_kernel(const F32Params p)
   __shared__ __attribute__((aligned(16))) float lds[2 * (kOperandFloats<NB> + kOperandFloats<2>)];
   RowTile t;
   int col = 0;
-  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.F + kPairCols - 1) / kPairCols, p.eighths, &t, &col)) return;
-  const long first_col = (p.eighths ? col : (long)blockIdx.z * gridDim.x + blockIdx.x) * kPairCols;
-  if (first_col >= p.F) return;
-  const int n0 = (int)first_col;
+  if (!find_tile<NB>(p.seg, p.E, Place::here(p.list), tiles_of(p.F, kPairCols), &t, &col)) return;
+  const int n0 = col * kPairCols;
   const long first = ((long)t.e * p.F + n0) * p.H;
   Operand<NB, false, 4, WIDE> a;
   Operand<2, false, 4, WIDE, true> b;
@@ -341,8 +339,8 @@ template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_down_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  int col = blockIdx.x;
-  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.H + kTile<NB> - 1) / kTile<NB>, p.eighths, &t, &col)) return;
+  int col = 0;
+  if (!find_tile<NB>(p.seg, p.E, Place::here(p.list), tiles_of(p.H, kTile<NB>), &t, &col)) return;
   const int n0 = col * kTile<NB>;
   Operand<NB, false, VF, WIDE> a, b;
   a.init(p.A + (long)t.m0 * p.F, p.F, t.m_end - t.m0);
@@ -361,8 +359,8 @@ template <int NB, int VF, bool WIDE>
 __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kOperandFloats<NB>];
   RowTile t;
-  int col = blockIdx.x;
-  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? blockIdx.x : blockIdx.y, (p.F + kTile<NB> - 1) / kTile<NB>, p.eighths, &t, &col)) return;
+  int col = 0;
+  if (!find_tile<NB>(p.seg, p.E, Place::here(p.list), tiles_of(p.F, kTile<NB>), &t, &col)) return;
   const int n0 = col * kTile<NB>;
   Operand<NB, false, 4, WIDE> a;
   Operand<NB, true, VF, WIDE> b;
@@ -405,10 +403,11 @@ __global__ __launch_bounds__(kThreads) void f32_dA_kernel(const F32Params p) {
 // dX = dG Wg + dU Wu, tile `tile` of the list (column tiles side by side)
 template <int NB, int VF, bool WIDE>
 __device__ __forceinline__ void input_grad(const F32Params& p, int tile, float* lds) {
-  const int th = (p.H + kTile<NB> - 1) / kTile<NB>;
+  const unsigned th = (unsigned)tiles_of(p.H, kTile<NB>);
   RowTile t;
-  int col = tile % th;
-  if (!find_row_tile<NB>(p.seg, p.E, p.eighths ? tile : tile / th, th, p.eighths, &t, &col)) return;
+  int col = 0;
+  const Place place = p.list ? Place{true, (unsigned)tile, 0, 0, 0} : Place{false, tile % th, tile / th, 0, th};
+  if (!find_tile<NB>(p.seg, p.E, place, th, &t, &col)) return;
   const int n0 = col * kTile<NB>;
   Operand<NB, false, VF, WIDE> a;
   Operand<NB, true, 4, WIDE> b;
@@ -473,8 +472,6 @@ __global__ __launch_bounds__(kThreads) void f32_grads_kernel(const F32Params p, 
   else weight_grad<NB, VF, 4, WIDE>(which == 1 ? p.dG : p.dU, p.F, p.x, p.H, (which == 1 ? p.dWg : p.dWu) + FH, k_begin, k_end, m0, n0, lds);
 }
 
-constexpr unsigned kMaxWidth = 1 << 20;  // of a grid: its width in threads is a 32-bit number
-
 // Which products go on tiles of 32 x 32 (gate/up: 32 rows), by how many tiles of 64 x 64 they have.  A k step of a 64 x 64 tile
 // keeps its wavefronts' matrix units busy for 1024 cycles, and with few tiles that chain is the time of the product; with many the
 // doubled traffic per flop weighs.  us on 64 / 32, tiles of 64 in brackets (T H F E k; times with the events around each launch):
@@ -484,36 +481,28 @@ constexpr unsigned kMaxWidth = 1 << 20;  // of a grid: its width in threads is a
 //   dA          11 /  7  (48)     14 / 13  (228)    20 / 16  (288)     30 / 28  (464)     59 /  60   (918)   103 /  97  (1152)
 //   gradients   19 / 11 (120)     50 / 29  (796)    40 / 35  (528)     85 / 85 (1768)    183 / 217  (4158)   364 / 397  (7296)
 constexpr int64_t kSmallGateup = 1024, kSmallDown = 1152, kSmallDA = 512, kSmallGrads = 1700;
-static unsigned tiles_of(int n, int tile) { return (unsigned)((n + (int64_t)tile - 1) / tile); }
 
-// The grid of a row product: a list, of which every XCD takes a contiguous eighth, so that its L2 holds the weights of an expert or
-// two and the rows that go with them; column tiles side by side in all XCDs made each of them fetch everything (us before / so, 1500
-// 516 1030 8 2: gate/up 90 / 83, down 54 / 48, dA 60 / 56, gradients, of which dX, 182 / 176; 2048 1024 1024 8 2 +-1 %).  Column by row
-// tiles where the list would be too long for 32-bit indices.
-constexpr int64_t kEighths = 1 << 24;
-static dim3 row_grid(F32Params& p, unsigned cols, unsigned rows) {
-  const int64_t tiles = (int64_t)cols * rows;
-  p.eighths = tiles <= kEighths;
-  if (p.eighths) return dim3((unsigned)((tiles + 7) / 8 * 8));
-  const unsigned width = cols < kMaxWidth ? cols : kMaxWidth;
-  return dim3(width, rows, (cols + width - 1) / width);
+static dim3 grid_of(F32Params& p, int64_t cols, int64_t rows) {
+  const RowGrid g = row_grid(cols, rows);
+  p.list = g.list;
+  return dim3(g.x, g.y, g.z);
 }
 
 template <int NB, int VF, bool WIDE>
 static int32_t gateup_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
-  const dim3 grid = row_grid(p, tiles_of(d->F, kPairCols), max_m_tiles(d, kTile<NB>));
+  const dim3 grid = grid_of(p, tiles_of(d->F, kPairCols), max_m_tiles(d, kTile<NB>));
   DYNMO_TIMED_LAUNCH(K_FFN_GATEUP, st, f32_gateup_kernel<NB, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 template <int NB, int VF, bool WIDE>
 static int32_t down_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
-  const dim3 grid = row_grid(p, tiles_of(d->H, kTile<NB>), max_m_tiles(d, kTile<NB>));
+  const dim3 grid = grid_of(p, tiles_of(d->H, kTile<NB>), max_m_tiles(d, kTile<NB>));
   DYNMO_TIMED_LAUNCH(K_FFN_DOWN, st, f32_down_kernel<NB, VF, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 template <int NB, int VF, bool WIDE>
 static int32_t dA_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
-  const dim3 grid = row_grid(p, tiles_of(d->F, kTile<NB>), max_m_tiles(d, kTile<NB>));
+  const dim3 grid = grid_of(p, tiles_of(d->F, kTile<NB>), max_m_tiles(d, kTile<NB>));
   DYNMO_TIMED_LAUNCH(K_FFN_DA, st, f32_dA_kernel<NB, VF, WIDE><<<grid, dim3(kThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
@@ -530,12 +519,12 @@ static int32_t fwd_f32(const dynmo_desc* d, const F32Params& p, hipStream_t st) 
 
 template <int NB, int VF, bool WIDE>
 static int32_t grads_f32(const dynmo_desc* d, F32Params p, hipStream_t st) {
-  const unsigned tf = tiles_of(d->F, kTile<NB>), th = tiles_of(d->H, kTile<NB>);
+  const unsigned tf = (unsigned)tiles_of(d->F, kTile<NB>), th = (unsigned)tiles_of(d->H, kTile<NB>);
   // the weight gradients are written for every expert, rows or not
   int dx_tiles = (int)(th * max_m_tiles(d, kTile<NB>));
   const int dw_tiles = (int)(tf * th * d->E);
-  p.eighths = dx_tiles <= kEighths;
-  if (p.eighths) dx_tiles = (dx_tiles + 7) / 8 * 8;
+  p.list = dx_tiles <= kMaxList;
+  if (p.list) dx_tiles = (dx_tiles + 7) / 8 * 8;
   auto launch = [&](const ProfRoles& roles, int first, int n) -> int32_t {
     if (n == 0) return DYNMO_OK;
     const int width = n < (int)kMaxWidth ? n : (int)kMaxWidth;

@@ -295,6 +295,51 @@ def test_f32_layer_both_tile_sizes(T, H, F, E, k):
     assert torch.equal(layer.out, out)
 
 
+@pytest.mark.parametrize("H,F", [((1 << 26) + 4, 1), (4, (1 << 26) + 64)])
+def test_f32_more_column_tiles_than_a_grid_is_wide(H, F):
+    """16 experts with a row each and rows of 2^20 + 1 tiles: every column of y (the first layer), of dG, dU and A (the second; they show
+    in the weight gradients, which are outer products), against 64 bits.  Per row (2-norm) 1e-5, and 4 * 2^-24 sqrt(n / 2) of a
+    sum of n terms; a tile that was left out is off by its share of the row, 1e-3 and more, and checked by itself at the row's end."""
+    say("f32 grid H=%d F=%d" % (H, F))
+    torch.cuda.empty_cache()
+    E = 16
+    d = B.make_desc(E, H, F, E, 1, "f32")
+    gen = torch.Generator(device="cuda").manual_seed(F)
+
+    def normal(sigma, *shape):
+        return torch.empty(shape, dtype=torch.float32, device="cuda").normal_(0.0, sigma, generator=gen)
+
+    def empty(*shape):  # not zeros: a tile that is not written shows
+        return torch.full(shape, 7.0, dtype=torch.float32, device="cuda")
+
+    def check(name, got, ref, terms=1):
+        tol = max(1e-5, 4 * 2.0 ** -24 * (terms / 2) ** 0.5)
+        for part, g, r in (("", got, ref), (" at its end", got[-256:], ref[-256:])):
+            err = float((g.double() - r).norm() / r.norm())
+            assert err <= tol, "%s%s: %.2e > %.1e" % (name, part, err, tol)
+
+    x, Wg, Wu, Wd = normal(1.0, E, H), normal(H ** -0.5, E, F, H), normal(H ** -0.5, E, F, H), normal(F ** -0.5, E, H, F)
+    seg = torch.arange(E + 1, dtype=torch.int32, device="cuda")
+    y, G, U = empty(E, H), empty(E, F), empty(E, F)
+    ws = torch.empty(max(B.dynmo_grouped_ffn_fwd_workspace_bytes(d), B.dynmo_grouped_ffn_bwd_workspace_bytes(d)),
+                     dtype=torch.uint8, device="cuda")
+    B.dynmo_grouped_ffn_fwd(d, x, seg, Wg, Wu, Wd, y, G, U, ws)
+    if F == 1:
+        for e in range(E):
+            a = (G[e].double() * torch.sigmoid(G[e].double()) * U[e].double())
+            check("y of expert %d" % e, y[e], a * Wd[e, :, 0].double())
+        return
+    dy, dx, dWg, dWu, dWd = normal(1.0, E, H), empty(E, H), empty(E, F, H), empty(E, F, H), empty(E, H, F)
+    B.dynmo_grouped_ffn_bwd(d, dy, x, G, U, seg, Wg, Wu, Wd, dx, dWg, dWu, dWd, ws)
+    for e in range(E):
+        g, u, dA = G[e].double(), U[e].double(), dy[e].double() @ Wd[e].double()
+        check("G of expert %d" % e, G[e], (Wg[e].double() * x[e].double()).sum(1), H)
+        sig = torch.sigmoid(g)
+        check("dWd of expert %d" % e, dWd[e, 1], dy[e, 1].double() * g * sig * u)
+        check("dWg of expert %d" % e, dWg[e, :, 2], x[e, 2].double() * dA * u * sig * (1 + g * (1 - sig)))
+        check("dWu of expert %d" % e, dWu[e, :, 3], x[e, 3].double() * dA * g * sig)
+
+
 @pytest.mark.parametrize("T,H,F", [(64, 4, 8600001), (40, 4, 17500002), (40, 17500000, 3)])
 def test_f32_rows_beyond_32_bit_offsets(T, H, F):
     """fp32 layers of which 64 rows span more than 2 GiB (8600001: from row 62 on, both operands [row][k]; 17.5 M: k-rows
