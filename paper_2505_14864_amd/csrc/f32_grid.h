@@ -6,7 +6,7 @@
 namespace dynmo {
 
 constexpr int64_t kMaxWidth = 1 << 20;        // of a grid that need not be wider: its width in threads is a 32-bit number
-constexpr int64_t kMaxList = 1 << 24;           // workgroups of a list
+constexpr int64_t kMaxList = (1 << 24) - 8;   // workgroups of a list, of 256 threads each: fewer than 2^32 threads in a dimension
 
 constexpr int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 

@@ -39,9 +39,21 @@ def walk(tmp_path_factory):
     return str(d / "walk")
 
 
+def dims(walk, cols, limit, rows):
+    r = subprocess.run([walk, str(cols), str(limit), str(rows)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    return [int(v) for v in r.stdout.split()]
+
+
 @pytest.mark.parametrize("cols,limit,rows", [(1, 1, 1), (33, 31, 24), (33, 31, 31), (33, 31, 0), ((1 << 21) - 1, 8, 8),
                                              ((1 << 20) + 1, 16, 16), ((1 << 20) + 1, 16, 5), ((1 << 21) + 5, 9, 9), (3, 65535, 65535),
                                              (513, 65535, 11)])
 def test_every_tile_has_one_workgroup(walk, cols, limit, rows):
-    r = subprocess.run([walk, str(cols), str(limit), str(rows)], capture_output=True, text=True)
-    assert r.returncode == 0, r.stdout
+    dims(walk, cols, limit, rows)
+
+
+@pytest.mark.parametrize("cols,limit", [((1 << 21) - 1, 8), (258111, 65), (1 << 18, 64), ((1 << 20) + 1, 16)])
+def test_grids_can_be_launched(walk, cols, limit):
+    """2^24 - 8, - 1, 2^24 and 2^24 + 16 tiles: fewer than 2^32 threads in every dimension (workgroups of 256), y and z of 16 bits."""
+    x, y, z = dims(walk, cols, limit, limit)
+    assert max(x, y, z) * 256 < 1 << 32 and max(y, z) < 1 << 16
