@@ -1,7 +1,7 @@
 """Binding of libdynmo.so: one Python function per C-ABI call, same names.
 
 Argument marshalling only: ctypes, and for the calls that launch kernels a small native module (csrc/fastcall.cpp), which
-does the same conversions and checks (a call of route_topk 3.8 -> 3.4 us on the host, of permute 4.7 -> 3.5; a forward pass of a
+does the same conversions of plain arguments and leaves the others, and all refusals, to ctypes (a call of route_topk 3.8 -> 3.4 us on the host, of permute 4.7 -> 3.5; a forward pass of a
 few tokens 24.3 -> 20.4).  Tensors are torch tensors on the GPU (torch is used
 for device memory and streams, nothing else); every step runs in the library's
 kernels.  There is no fallback: if the library is missing, loading raises.
@@ -144,8 +144,27 @@ def _fail(call, status):
     raise DynmoError(call, status, lib().dynmo_last_hip_error())
 
 
+def _by_ctypes(name, kinds):
+    """The call of a library function whose arguments are of these kinds (csrc/fastcall.cpp), through ctypes."""
+    def call(*args):
+        words = []
+        for kind, a in zip(kinds, args):
+            if kind == "d":
+                words.append(C.byref(a))
+            elif kind == "t":
+                words.append(_ptr(a))
+            elif kind == "w":
+                words += [_ptr(a), a.numel()]
+            elif kind == "i":
+                words.append(a)
+            else:
+                words.append(_stream(a))
+        _check(name, getattr(lib(), name)(*words))
+    return call
+
+
 class _Launch:
-    """A library call that launches kernels: `kinds` names its arguments one by one (csrc/fastcall.cpp), the stream last.  The
+    """A library call that launches kernels: `kinds` names its arguments one by one, the stream last.  The
     native function takes this object's place in _launch on the first call."""
 
     def __init__(self, name, kinds):
@@ -153,7 +172,7 @@ class _Launch:
 
     def __call__(self, *args):
         address = C.cast(getattr(lib(), self.name), C.c_void_p).value
-        native = _calls().function(self.name, address, self.kinds)
+        native = _calls().function(self.name, address, self.kinds, _by_ctypes(self.name, self.kinds))
         setattr(_launch, self.name, native)
         return native(*args)
 
@@ -166,10 +185,8 @@ def _calls():
     if _fastcall is None:
         if not os.path.exists(CALLS_PATH):
             raise RuntimeError("_fastcall.so is not built: run `python -m paper_2505_14864_amd.build` (or __graft_entry__.build())")
-        if torch.cuda.is_available():
-            torch.cuda.current_device()  # torch's own initialisation
         from . import _fastcall as module
-        module.setup(_fail, _ptr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        module.setup(_fail, Desc, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
         _fastcall = module
     return _fastcall
 

@@ -1,5 +1,6 @@
 // Calls of the C ABI from Python without ctypes: one object per library function, which turns its arguments into machine words
-// and jumps.  A forward pass of a few tokens is five calls, each of which took longer on the host (3.8 to 4.7 us, 2.2 of them the
+// and jumps.  Only plain arguments are taken here; a call with any other one (a subclass of Tensor, a ctypes integer, and all that is
+// refused) goes through ctypes as a whole, which decides what is accepted and how the rest is refused.  A forward pass of a few tokens is five calls, each of which took longer on the host (3.8 to 4.7 us, 2.2 of them the
 // launch) than its kernel on the GPU.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -16,18 +17,19 @@ namespace {
 
 constexpr int kMaxWords = 20;
 
-// What the Python side hands over: raises the error of a status; the pointer of something that is no plain tensor; torch's current
-// device; the raw handle of a device's current stream
-PyObject *g_fail = nullptr, *g_pointer = nullptr, *g_device = nullptr, *g_stream = nullptr;
+// What the Python side hands over: raises the error of a status; the descriptor's type; torch's current device (which initialises torch's
+// GPU state, and refuses to in a forked child); the raw handle of a device's current stream
+PyObject *g_fail = nullptr, *g_desc = nullptr, *g_device = nullptr, *g_stream = nullptr;
 
 struct Function {
   PyObject_HEAD
   vectorcallfunc call;
   void* address;
   PyObject* name;
+  PyObject* by_ctypes;  // the same call with the same arguments
   Py_ssize_t n_args;
-  // one letter per argument: d descriptor, t tensor or None, w workspace tensor (its pointer and number of elements),
-  // i integer, s stream or None
+  // one letter per argument: d descriptor, t contiguous GPU tensor or None, w workspace tensor (its pointer and number of
+  // elements), i int, s stream or None
   char kinds[kMaxWords];
 };
 
@@ -53,54 +55,46 @@ constexpr auto jumps(std::index_sequence<N...>) {
 }
 constexpr auto kJumps = jumps(std::make_index_sequence<kMaxWords + 1>());
 
-// the device pointer of a contiguous GPU tensor (0 for None); false with an exception set
-bool pointer_of(PyObject* o, uint64_t* p) {
-  if (o == Py_None) {
-    *p = 0;
-    return true;
-  }
-  if (THPVariable_CheckExact(o)) {
-    const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda() || !t.is_contiguous()) {
-      PyErr_SetString(PyExc_ValueError, "expected a contiguous GPU tensor");
-      return false;
-    }
-    *p = (uint64_t)t.data_ptr();
-    return true;
-  }
-  PyObject* r = PyObject_CallOneArg(g_pointer, o);
-  if (!r) return false;
-  *p = r == Py_None ? 0 : PyLong_AsUnsignedLongLong(r);
-  Py_DECREF(r);
-  return !PyErr_Occurred();
+enum Taken { kPlain, kOther, kError };  // kError: with an exception set
+
+Taken descriptor_of(PyObject* o, uint64_t* p) {
+  if ((PyObject*)Py_TYPE(o) != g_desc) return kOther;
+  Py_buffer b;  // the caller holds the descriptor, and its memory does not move
+  if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) < 0) return kError;
+  *p = (uint64_t)b.buf;
+  PyBuffer_Release(&b);
+  return kPlain;
 }
 
-bool elements_of(PyObject* o, uint64_t* n) {
-  if (THPVariable_CheckExact(o)) {
-    *n = (uint64_t)THPVariable_Unpack(o).numel();
-    return true;
-  }
-  PyObject* r = PyObject_CallMethod(o, "numel", nullptr);
-  if (!r) return false;
-  *n = PyLong_AsUnsignedLongLong(r);
-  Py_DECREF(r);
-  return !PyErr_Occurred();
+Taken tensor_of(PyObject* o, uint64_t* p, uint64_t* n) {
+  if (!THPVariable_CheckExact(o)) return kOther;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  if (!t.is_cuda() || !t.is_contiguous()) return kOther;
+  *p = (uint64_t)t.data_ptr();
+  if (n) *n = (uint64_t)t.numel();
+  return kPlain;
 }
 
-bool stream_of(PyObject* o, uint64_t* s) {
+Taken integer_of(PyObject* o, uint64_t* v) {
+  if (!PyLong_Check(o)) return kOther;
+  *v = PyLong_AsUnsignedLongLongMask(o);
+  return PyErr_Occurred() ? kError : kPlain;
+}
+
+Taken stream_of(PyObject* o, uint64_t* s) {
   PyObject* r;
   if (o == Py_None) {
     PyObject* device = PyObject_CallNoArgs(g_device);
-    if (!device) return false;
+    if (!device) return kError;
     r = PyObject_CallOneArg(g_stream, device);
     Py_DECREF(device);
   } else {
     r = PyObject_GetAttrString(o, "cuda_stream");
   }
-  if (!r) return false;
-  *s = PyLong_AsUnsignedLongLong(r);
+  if (!r) return kError;
+  const Taken taken = integer_of(r, s);
   Py_DECREF(r);
-  return !PyErr_Occurred();
+  return taken;
 }
 
 PyObject* call_function(PyObject* self, PyObject* const* args, size_t nargsf, PyObject* kwnames) {
@@ -114,33 +108,23 @@ PyObject* call_function(PyObject* self, PyObject* const* args, size_t nargsf, Py
   int n = 0;
   for (Py_ssize_t i = 0; i < f->n_args; ++i) {
     PyObject* o = args[i];
-    bool ok = true;
+    Taken taken = kPlain;
     switch (f->kinds[i]) {
-      case 'd': {  // the caller holds the descriptor, and its memory does not move
-        Py_buffer b;
-        if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) < 0) return nullptr;
-        w[n++] = (uint64_t)b.buf;
-        ok = b.len >= (Py_ssize_t)(6 * sizeof(int32_t));
-        PyBuffer_Release(&b);
-        if (!ok) PyErr_SetString(PyExc_TypeError, "expected a descriptor");
+      case 'd': taken = descriptor_of(o, &w[n++]); break;
+      case 't':
+        if (o == Py_None) w[n] = 0;
+        else taken = tensor_of(o, &w[n], nullptr);
+        ++n;
         break;
-      }
-      case 't': ok = pointer_of(o, &w[n++]); break;
       case 'w':
-        ok = pointer_of(o, &w[n]) && elements_of(o, &w[n + 1]);
+        taken = tensor_of(o, &w[n], &w[n + 1]);
         n += 2;
         break;
-      case 'i': {
-        PyObject* v = PyNumber_Index(o);
-        if (!v) return nullptr;
-        w[n++] = PyLong_AsUnsignedLongLongMask(v);
-        Py_DECREF(v);
-        ok = !PyErr_Occurred();
-        break;
-      }
-      default: ok = stream_of(o, &w[n++]); break;
+      case 'i': taken = integer_of(o, &w[n++]); break;
+      default: taken = stream_of(o, &w[n++]); break;
     }
-    if (!ok) return nullptr;
+    if (taken == kOther) return PyObject_Vectorcall(f->by_ctypes, args, (size_t)f->n_args, nullptr);
+    if (taken == kError) return nullptr;
   }
   int32_t status;
   Py_BEGIN_ALLOW_THREADS
@@ -157,17 +141,18 @@ PyObject* call_function(PyObject* self, PyObject* const* args, size_t nargsf, Py
 
 void free_function(PyObject* self) {
   Py_XDECREF(((Function*)self)->name);
+  Py_XDECREF(((Function*)self)->by_ctypes);
   Py_TYPE(self)->tp_free(self);
 }
 
 PyTypeObject g_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
-// function(name, address, kinds)
+// function(name, address, kinds, by_ctypes)
 PyObject* make_function(PyObject*, PyObject* args) {
-  PyObject* name;
+  PyObject *name, *by_ctypes;
   unsigned long long address;
   const char* kinds;
-  if (!PyArg_ParseTuple(args, "UKs", &name, &address, &kinds)) return nullptr;
+  if (!PyArg_ParseTuple(args, "UKsO", &name, &address, &kinds, &by_ctypes)) return nullptr;
   const size_t n = strlen(kinds);
   size_t words = n;
   for (const char* k = kinds; *k; ++k) words += *k == 'w';
@@ -181,16 +166,18 @@ PyObject* make_function(PyObject*, PyObject* args) {
   f->address = (void*)(uintptr_t)address;
   Py_INCREF(name);
   f->name = name;
+  Py_INCREF(by_ctypes);
+  f->by_ctypes = by_ctypes;
   f->n_args = (Py_ssize_t)n;
   memcpy(f->kinds, kinds, n);
   return (PyObject*)f;
 }
 
-// setup(fail, pointer, device, stream)
+// setup(fail, desc, device, stream)
 PyObject* setup(PyObject*, PyObject* args) {
   PyObject* v[4];
   if (!PyArg_ParseTuple(args, "OOOO", &v[0], &v[1], &v[2], &v[3])) return nullptr;
-  PyObject** to[4] = {&g_fail, &g_pointer, &g_device, &g_stream};
+  PyObject** to[4] = {&g_fail, &g_desc, &g_device, &g_stream};
   for (int i = 0; i < 4; ++i) {
     Py_INCREF(v[i]);
     Py_XDECREF(*to[i]);

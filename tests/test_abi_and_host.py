@@ -5,6 +5,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import dynmo_oracle as orc
 from paper_2505_14864_amd import binding as B
@@ -396,3 +397,49 @@ def test_partition_shadow_matches_oracle():
     assert B.dynmo_partition_shadow(loads, None, 3)[1] == B.dynmo_partition(loads, 3)[1] == 14.0
     with pytest.raises(B.DynmoError):
         B.dynmo_partition_shadow([1.0, float("nan")], [0, 0], 2)
+
+
+class FakeStream:
+    cuda_stream = 0
+
+
+def native_and_ctypes(name, kinds, args):
+    """What a launching call with these arguments raises through the native module, and through ctypes."""
+    native = B._calls().function(name, B.C.cast(getattr(B.lib(), name), B.C.c_void_p).value, kinds, B._by_ctypes(name, kinds))
+    raised = []
+    for call in (native, B._by_ctypes(name, kinds)):
+        with pytest.raises(Exception) as e:
+            call(*args)
+        raised.append((e.type, str(e.value)))
+    return raised
+
+
+DESC = B.make_desc(8, 16, 16, 4, 2, "f32")
+CAPACITY = ("dynmo_route_capacity", "dtiiitts")
+
+
+@pytest.mark.parametrize("call,args,error", [
+    (CAPACITY, (bytes(24), None, 1, 8, 2, None, None, FakeStream), TypeError),
+    (CAPACITY, (np.zeros(6, np.int32), None, 1, 8, 2, None, None, FakeStream), TypeError),
+    (CAPACITY, (B.C.c_int32(8), None, 1, 8, 2, None, None, FakeStream), B.C.ArgumentError),
+    (CAPACITY, (None, None, 1, 8, 2, None, None, FakeStream), TypeError),
+    (CAPACITY, (DESC, None, 1.0, 8, 2, None, None, FakeStream), B.C.ArgumentError),
+    (CAPACITY, (DESC, None, 1, None, 2, None, None, FakeStream), B.C.ArgumentError),
+    (CAPACITY, (DESC, torch.zeros(8), 1, 8, 2, None, None, FakeStream), ValueError),
+    (CAPACITY, (DESC, torch.zeros(8, 2)[:, 0], 1, 8, 2, None, None, FakeStream), ValueError),
+    (CAPACITY, (DESC, 5, 1, 8, 2, None, None, FakeStream), AttributeError),
+    (CAPACITY, (DESC, None, 1, 8, 2, None, None, 0), AttributeError),
+    (("dynmo_route_drop", "dtitws"), (DESC, None, 2, None, None, FakeStream), AttributeError),
+    # accepted: these reach the library, which refuses the null pointers
+    (CAPACITY, (DESC, None, 1, 8, 2, None, None, FakeStream), B.DynmoError),
+    (CAPACITY, (DESC, None, B.C.c_int32(1), np.int32(8), 2 ** 40 + True, None, None, FakeStream), B.DynmoError)])
+def test_native_calls_take_what_ctypes_takes(call, args, error):
+    native, by_ctypes = native_and_ctypes(*call, args)
+    assert native == by_ctypes and native[0] is error
+
+
+def test_native_calls_refuse_a_forked_child(monkeypatch):
+    """Without a stream a call asks for torch's current one, which a process forked from one that uses the GPU is refused."""
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    native, by_ctypes = native_and_ctypes(*CAPACITY, (DESC, None, 1, 8, 2, None, None, None))
+    assert native == by_ctypes and "forked" in native[1]
