@@ -17,17 +17,17 @@
 //   [k][row]: 64-byte blocks of 32 rows; block b of k-row k is stored as block b ^ (k & 3) (64 rows:
 //             b ^ ((k >> 1) & 1)), its two 32-byte halves swapped when bit 3 of k is set
 #include "ffn_gemm.h"
+#include "tile_list.h"
 
 namespace dynmo {
 
 constexpr int kTileThreads = 256;
 constexpr int kTileK = 32;
-constexpr int kEighths = 512;   // tiles
 constexpr int kChunkTiles = 4;  // row tiles that are walked together, column tile by column tile
 
 struct TileParams {
   GemmParams g;
-  int group;  // consecutive tiles of the list that go to one XCD
+  TileList list;
 };
 
 // WBM x WBN blocks of 16 x 16 per wavefront
@@ -158,14 +158,8 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : 3) void ffn_tile_kerne
     const int o = __shfl_up(upto, d, 64);
     if (lane >= d) upto += o;
   }
-  // Workgroup b runs on XCD b % 8.  With up to two tiles per compute unit every XCD takes an eighth of the list: its tiles share
-  // operand tiles in its L2, and those small products are bound by what has to pass between the L2s and memory (the dX of 8
-  // experts, 1200 rows, 520 x 1032: 71 MB in runs of three tiles, of 22 that it needs).  us of all row products, in runs of
-  // tiles / 64 / in eighths (T H F E k): 2747 344 1664 2 1 100 / 88, 1061 512 1136 3 3 87 / 77, 600 520 1032 8 2 58 / 55.
-  // More tiles go in runs of `group` (1280 tiles of 128 x 256, dX of 64 experts: 193 / 200).
-  const int slot = blockIdx.x >> 3, xcd = blockIdx.x & 7, total = __builtin_amdgcn_readlane(upto, 63) * nt, eighth = (total + 7) / 8;
-  int pos = (slot / tp.group * 8 + xcd) * tp.group + slot % tp.group;
-  if (total <= kEighths) pos = slot < eighth ? xcd * eighth + slot : total;
+  const int total = __builtin_amdgcn_readlane(upto, 63) * nt;
+  const int pos = list_position(tp.list, blockIdx.x, total, TM, S::kCols, p.E, __ballot(mt > 1) == 0);
   const unsigned long long owners = __ballot(upto * nt > pos);
   if (owners == 0) return;  // past the last tile
   const int e = __builtin_ctzll(owners);
@@ -371,14 +365,12 @@ __global__ __launch_bounds__(kTileThreads, WBN == 8 ? 2 : 3) void ffn_tile_kerne
 
 template <int MODE, int WBM, int WBN>
 static int32_t launch_tile(TileParams tp, int tiles, const ProfRoles& id, hipStream_t st) {
-  tp.group = tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
-  const int run = 8 * tp.group;
-  const unsigned blocks = (unsigned)((tiles + run - 1) / run * run);
+  tp.list = tile_list(tiles);
   if (tp.g.K % kTileK == 0) {
-    DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, true><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
+    DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, true><<<dim3(tp.list.blocks), dim3(kTileThreads), 0, st>>>(tp));
     return DYNMO_OK;
   }
-  DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, false><<<dim3(blocks), dim3(kTileThreads), 0, st>>>(tp));
+  DYNMO_TIMED_LAUNCH(id, st, ffn_tile_kernel<MODE, WBM, WBN, false><<<dim3(tp.list.blocks), dim3(kTileThreads), 0, st>>>(tp));
   return DYNMO_OK;
 }
 
