@@ -186,7 +186,8 @@ def _calls():
         if not os.path.exists(CALLS_PATH):
             raise RuntimeError("_fastcall.so is not built: run `python -m paper_2505_14864_amd.build` (or __graft_entry__.build())")
         from . import _fastcall as module
-        module.setup(_fail, Desc, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
+        module.setup(_fail, Desc, torch.cuda.current_device, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        os.register_at_fork(after_in_child=module.forked)
         _fastcall = module
     return _fastcall
 

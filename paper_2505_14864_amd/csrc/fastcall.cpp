@@ -17,9 +17,11 @@ namespace {
 
 constexpr int kMaxWords = 20;
 
-// What the Python side hands over: raises the error of a status; the descriptor's type; torch's current device (which initialises torch's
-// GPU state, and refuses to in a forked child); the raw handle of a device's current stream
-PyObject *g_fail = nullptr, *g_desc = nullptr, *g_device = nullptr, *g_stream = nullptr;
+// What the Python side hands over: raises the error of a status; the descriptor's type; torch's current device, by the call that
+// initialises torch's GPU state (and refuses to in a forked child) and by the quick one that follows; the raw handle of a device's
+// current stream
+PyObject *g_fail = nullptr, *g_desc = nullptr, *g_first_device = nullptr, *g_device = nullptr, *g_stream = nullptr;
+bool g_initialised = false;  // in this process
 
 struct Function {
   PyObject_HEAD
@@ -84,8 +86,9 @@ Taken integer_of(PyObject* o, uint64_t* v) {
 Taken stream_of(PyObject* o, uint64_t* s) {
   PyObject* r;
   if (o == Py_None) {
-    PyObject* device = PyObject_CallNoArgs(g_device);
+    PyObject* device = PyObject_CallNoArgs(g_initialised ? g_device : g_first_device);
     if (!device) return kError;
+    g_initialised = true;
     r = PyObject_CallOneArg(g_stream, device);
     Py_DECREF(device);
   } else {
@@ -173,12 +176,12 @@ PyObject* make_function(PyObject*, PyObject* args) {
   return (PyObject*)f;
 }
 
-// setup(fail, desc, device, stream)
+// setup(fail, desc, first_device, device, stream)
 PyObject* setup(PyObject*, PyObject* args) {
-  PyObject* v[4];
-  if (!PyArg_ParseTuple(args, "OOOO", &v[0], &v[1], &v[2], &v[3])) return nullptr;
-  PyObject** to[4] = {&g_fail, &g_desc, &g_device, &g_stream};
-  for (int i = 0; i < 4; ++i) {
+  PyObject* v[5];
+  if (!PyArg_ParseTuple(args, "OOOOO", &v[0], &v[1], &v[2], &v[3], &v[4])) return nullptr;
+  PyObject** to[5] = {&g_fail, &g_desc, &g_first_device, &g_device, &g_stream};
+  for (int i = 0; i < 5; ++i) {
     Py_INCREF(v[i]);
     Py_XDECREF(*to[i]);
     *to[i] = v[i];
@@ -186,7 +189,16 @@ PyObject* setup(PyObject*, PyObject* args) {
   Py_RETURN_NONE;
 }
 
-PyMethodDef g_methods[] = {{"function", make_function, METH_VARARGS, nullptr}, {"setup", setup, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+// forked(): this process is a child
+PyObject* forked(PyObject*, PyObject*) {
+  g_initialised = false;
+  Py_RETURN_NONE;
+}
+
+PyMethodDef g_methods[] = {{"function", make_function, METH_VARARGS, nullptr},
+                           {"setup", setup, METH_VARARGS, nullptr},
+                           {"forked", forked, METH_NOARGS, nullptr},
+                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, g_methods};
 
 }  // namespace

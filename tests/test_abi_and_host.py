@@ -438,8 +438,34 @@ def test_native_calls_take_what_ctypes_takes(call, args, error):
     assert native == by_ctypes and native[0] is error
 
 
-def test_native_calls_refuse_a_forked_child(monkeypatch):
-    """Without a stream a call asks for torch's current one, which a process forked from one that uses the GPU is refused."""
-    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
-    native, by_ctypes = native_and_ctypes(*CAPACITY, (DESC, None, 1, 8, 2, None, None, None))
-    assert native == by_ctypes and "forked" in native[1]
+def test_native_calls_refuse_a_forked_child():
+    """Without a stream a call asks for torch's current one, which a process forked from one that uses the GPU is refused: its first call asks
+    torch again, whatever its parent had initialised."""
+    asked = []
+    module = B._calls()
+
+    def refuse():
+        raise RuntimeError("forked")
+
+    module.setup(B._fail, B.Desc, lambda: asked.append("first") or 0, lambda: asked.append("again") or 0, lambda device: 0)
+    try:
+        module.forked()  # as if nothing had been called
+        native = module.function("dynmo_route_topk", B.C.cast(B.lib().dynmo_route_topk, B.C.c_void_p).value, "dttts", refuse)
+        for _ in range(2):
+            with pytest.raises(B.DynmoError):  # null pointers: the library was called
+                native(DESC, None, None, None, None)
+        assert asked == ["first", "again"]
+        child = os.fork()
+        if child == 0:
+            status = 1
+            try:
+                module.setup(B._fail, B.Desc, refuse, lambda: 0, lambda device: 0)
+                native(DESC, None, None, None, None)
+            except RuntimeError as e:
+                status = 0 if str(e) == "forked" else 2
+            finally:
+                os._exit(status)
+        assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
+    finally:
+        module.forked()
+        module.setup(B._fail, B.Desc, torch.cuda.current_device, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
