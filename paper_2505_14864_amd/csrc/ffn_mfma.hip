@@ -20,7 +20,9 @@
 // such a load while the memory pipeline takes it, and its MFMAs wait behind it, so only
 // one wavefront of each SIMD (0 .. 3) loads, two every three MFMA slots, and the other
 // one keeps the matrix unit busy meanwhile; those (4 .. 7) load a tile's second k tile and
-// issue the L2 prefetch.
+// issue the L2 prefetch.  Where an expert has few rows all eight load and prefetch (SHARE;
+// share_for()), in instances of their own: with both in one kernel its code grew from 30 to
+// 50 KB, which alone cost gate/up of few k tiles 1 to 3 % on average.
 // Against loads by all eight (us; T H F E k): dX 4096 4096 14336 8 2: 1672 -> 1605, 3000
 // 2048 4096 16 2: 249 -> 229; dA 8192 4096 688 16 4: 290 -> 274; down of 1000 tokens of
 // the first layer 402 -> 368.  Long dense products gain less (gate/up of the first layer
@@ -50,6 +52,7 @@ constexpr int BM = 256, BN = 256, BK = 64;
 constexpr int kMfmaThreads = 512;              // eight wavefronts: two per SIMD
 constexpr int kWaves = kMfmaThreads / 64;
 constexpr int kLoaders = 4;                     // wavefronts 0 .. 3, one per SIMD, move the operand tiles; 4 .. 7 prefetch
+constexpr int kShare = 32 / kWaves;             // 1 KB pieces of an operand tile per wavefront where all load
 constexpr int kPieces = 32 / kLoaders;          // 1 KB pieces of an operand tile per loading wavefront
 constexpr int kTileBytes = 256 * 64 * 2;       // one operand tile (256 rows x 64 k, bf16), unpadded
 constexpr int kStageBytes = 2 * kTileBytes;    // A then B
@@ -102,6 +105,14 @@ __device__ __forceinline__ void touch_to_lds(desc_t d, uint32_t lds_offset, uint
 
 // Waits of the k loop, written out because the loads above are invisible to the compiler.
 __device__ __forceinline__ void wait_loads_and_lds() { __builtin_amdgcn_s_waitcnt(0x0070); }  // vmcnt(0) lgkmcnt(0)
+// Waits until at most OFF of this wavefront's loads, ON with the prefetch on, and none of its LDS reads are outstanding.  The
+// branch is inside the assembly: the k loop's body stays one block.
+template <int OFF, int ON>
+__device__ __forceinline__ void wait_loads_but(int prefetching) {
+  asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Loff%=\n\ts_waitcnt vmcnt(%1) lgkmcnt(0)\n\ts_branch .Lwaited%=\n"
+               ".Loff%=:\n\ts_waitcnt vmcnt(%2) lgkmcnt(0)\n.Lwaited%=:" ::"s"(prefetching), "n"(ON), "n"(OFF)
+               : "memory", "scc");
+}
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }            // lgkmcnt(0)
 __device__ __forceinline__ void wg_barrier() { __builtin_amdgcn_s_barrier(); }
 
@@ -126,13 +137,14 @@ struct Pieces {
 // [row][k] memory: piece q holds LDS rows 8 q .. 8 q + 7; lane l fills slot l % 8 of row
 // 8 q + l / 8, which the swizzle assigns to k piece (l % 8) ^ ((row >> 1) & 7).
 // `wrap` = 128 for the gate/up pairing (LDS rows 128..255 are rows 0..127 of a second matrix).
+template <int N = kPieces>
 __device__ __forceinline__ Pieces pieces_rowk(uint32_t ld_bytes, int rows_left, int wrap) {
   Pieces ps;
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
+  const int lane = tid & 63, wave = tid >> 6 & (32 / N - 1);
 #pragma unroll
-  for (int j = 0; j < kPieces; ++j) {
-    const int lrow = (wave * kPieces + j) * 8 + (lane >> 3);
+  for (int j = 0; j < N; ++j) {
+    const int lrow = (wave * N + j) * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((lrow >> 1) & 7);
     const int row = lrow % wrap;
     ps.off[j] = row < rows_left ? (uint32_t)row * ld_bytes + c * 16 : kOob;
@@ -144,13 +156,14 @@ __device__ __forceinline__ Pieces pieces_rowk(uint32_t ld_bytes, int rows_left, 
 // [k][row] memory: piece q holds k-rows 2 q and 2 q + 1; lane l fills 16-byte slot l % 32 of
 // k-row 2 q + l / 32, i.e. quarter (l % 4) of stored block (l % 32) / 4 (quarters 0, 1 and
 // 2, 3 are the block's two halves).
+template <int N = kPieces>
 __device__ __forceinline__ Pieces pieces_krow(uint32_t ld_bytes, int rows_left) {
   Pieces ps = {};
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
+  const int lane = tid & 63, wave = tid >> 6 & (32 / N - 1);
 #pragma unroll
-  for (int j = 0; j < kPieces; ++j) {
-    const int k = (wave * kPieces + j) * 2 + (lane >> 5);
+  for (int j = 0; j < N; ++j) {
+    const int k = (wave * N + j) * 2 + (lane >> 5);
     const int slot = lane & 31, stored = slot >> 2;
     const int blk = (stored & 4) | ((stored ^ k) & 3);
     const int quarter = (slot & 3) ^ (((k >> 3) & 1) << 1);
@@ -163,14 +176,15 @@ __device__ __forceinline__ Pieces pieces_krow(uint32_t ld_bytes, int rows_left) 
 // [row][k] memory whose rows are fetched through an index: LDS row r is row
 // rowmap[row0 + r] / rowdiv of the operand, so the offsets are taken from the operand's
 // first row (the buffer base then points at (row 0, k0)).
+template <int N = kPieces>
 __device__ __forceinline__ Pieces pieces_rowk_gather(uint32_t ld_bytes, int row0, int rows_left,
                                                      const int32_t* __restrict__ rowmap, int rowdiv) {
   Pieces ps;
   const int tid = tid_now();
-  const int lane = tid & 63, wave = tid >> 6 & (kLoaders - 1);
+  const int lane = tid & 63, wave = tid >> 6 & (32 / N - 1);
 #pragma unroll
-  for (int j = 0; j < kPieces; ++j) {
-    const int lrow = (wave * kPieces + j) * 8 + (lane >> 3);
+  for (int j = 0; j < N; ++j) {
+    const int lrow = (wave * N + j) * 8 + (lane >> 3);
     const int c = (lane & 7) ^ ((lrow >> 1) & 7);
     ps.off[j] = kOob;
     if (lrow < rows_left) ps.off[j] = (uint32_t)(rowmap[row0 + lrow] / rowdiv) * ld_bytes + c * 16;
@@ -420,10 +434,11 @@ __device__ __forceinline__ Tile decode_tile(const int* table, const TileTable& t
 
 // WHOLE_K: the contraction length is a multiple of the k tile, so the [row][k] operands need no
 // per-lane k mask (the [k][row] operands never do: their k range is the buffer's record count).
-template <int MODE, bool WHOLE_K>
+template <int MODE, bool WHOLE_K, bool SHARE>
 __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool A_TRANS = MODE == MODE_DW;
+  constexpr int kOwn = SHARE ? kShare : kPieces;  // 1 KB pieces of an operand tile per loading wavefront
   constexpr bool IS_DX = MODE == MODE_DX || MODE == MODE_DX_FOLD;
   constexpr bool FOLDS = MODE == MODE_DOWN_FOLD || MODE == MODE_DX_FOLD;
   constexpr bool B_TRANS = MODE == MODE_DA || IS_DX || MODE == MODE_DW;
@@ -507,18 +522,18 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     hdr[3] = tail_tiles;
   }
   const int wave_u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // the gate/up pairing: LDS rows 128..255 of operand B (the upper two loading wavefronts' pieces) come from the second matrix
-  const bool second_b = MODE == MODE_GATEUP && wave_u % kLoaders >= kLoaders / 2;
+  // the gate/up pairing: LDS rows 128..255 of operand B (the upper half of its pieces) come from the second matrix
+  const bool second_b = MODE == MODE_GATEUP && (SHARE ? wave_u >= kWaves / 2 : wave_u % kLoaders >= kLoaders / 2);
   const bool gathered = MODE == MODE_GATEUP && p.gather != nullptr;
   const uint32_t lda_b = (uint32_t)p.lda * 2, ldb_b = (uint32_t)p.ldb * 2;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;  // LDS addresses are 32-bit offsets
   auto pieces_a = [&](const Tile& tt) {
-    return A_TRANS   ? pieces_krow(lda_b, tt.m_end - tt.m0)
-           : gathered ? pieces_rowk_gather(lda_b, tt.m0, tt.m_end - tt.m0, p.gather, p.gather_div)
-                      : pieces_rowk(lda_b, tt.m_end - tt.m0, 256);
+    return A_TRANS   ? pieces_krow<kOwn>(lda_b, tt.m_end - tt.m0)
+           : gathered ? pieces_rowk_gather<kOwn>(lda_b, tt.m0, tt.m_end - tt.m0, p.gather, p.gather_div)
+                      : pieces_rowk<kOwn>(lda_b, tt.m_end - tt.m0, 256);
   };
   auto pieces_b = [&](const Tile& tt) {
-    return B_TRANS ? pieces_krow(ldb_b, n_end - tt.n0) : pieces_rowk(ldb_b, n_end - tt.n0, MODE == MODE_GATEUP ? 128 : 256);
+    return B_TRANS ? pieces_krow<kOwn>(ldb_b, n_end - tt.n0) : pieces_rowk<kOwn>(ldb_b, n_end - tt.n0, MODE == MODE_GATEUP ? 128 : 256);
   };
   // operand descriptors of one k tile (wave-uniform), and how many k are left in it
   struct KTile {
@@ -604,8 +619,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     return q;
   };
   // this wavefront's pieces of k tile q (pieces pa / pb) into the stage at LDS offset `stage`
-  const bool loader = wave_u < kLoaders;
-  const uint32_t wave_pieces = wave_u % kLoaders * kPieces * 1024;  // this wavefront's pieces inside an operand tile
+  const bool loader = SHARE || wave_u < kLoaders;
+  const uint32_t wave_pieces = wave_u % (32 / kOwn) * kOwn * 1024;  // this wavefront's pieces inside an operand tile
   auto dma_a = [&](const Pieces& pa, const KTile& q, uint32_t stage, auto J) {
     constexpr int j = decltype(J)::value;
     load_to_lds<j * 1024>(q.a, stage + wave_pieces, A_TRANS || WHOLE_K || pa.kpos[j & 1] < q.k_left ? pa.off[j] : kOob);
@@ -614,6 +629,10 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     constexpr int j = decltype(J)::value;
     load_to_lds<kTileBytes + j * 1024>(q.b, stage + wave_pieces, B_TRANS || WHOLE_K || pb.kpos[j & 1] < q.k_left ? pb.off[j] : kOob);
   };
+  auto load_tile = [&](const Pieces& pa, const Pieces& pb, const KTile& q, uint32_t stage) {
+    static_for<kOwn>([&](auto J) { dma_a(pa, q, stage, J); });
+    static_for<kOwn>([&](auto J) { dma_b(pb, q, stage, J); });
+  };
   // L2 prefetch.  The workgroups of an XCD that run side by side share operand tiles (in a run
   // of 4 x 8 output tiles, 8 share each A tile and 4 each B tile) and ask for the same lines at
   // about the same time, so every one of them sees the full memory latency on every k tile.
@@ -621,7 +640,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // share it -- four bytes per 128-byte line, into a dump area -- in the k tile's last MFMA slot, behind
   // the loads: data comes back to a compute unit in the order of the requests, and pieces behind the
   // prefetch wait for it (in the first slot behind the barrier: gate/up of a Mixtral-shaped layer 1675 -> 1813 us).  The
-  // prefetching wavefronts load nothing else and never wait for it.  Purely a hint: nothing depends on the data.
+  // prefetching wavefronts, which load only a tile's second k tile, never wait for it, and where all load it may stay out when
+  // they wait for their pieces.  Purely a hint: nothing depends on the data.
   // Prefetched (us without / with): down (Mixtral shape 864 / 797; 1000 tokens of it 406 / 368); dX unless its experts
   // have many row tiles (Mixtral shape 1658 / 1605; one expert of 16384 rows, 2048 x 8192, 374 / 381); gate/up where
   // an expert has few (1000 tokens of the Mixtral shape 649 / 614; up to 4 row tiles: 16 experts, 6000 rows, 2048 x 4096 239 /
@@ -632,6 +652,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     int on;         // prefetch at all
     uint32_t a, b;  // this lane's line of either operand tile, as a byte offset from the tile's (row0, k0) element, or kOob
   };
+  // this lane's line of the 256 of an operand tile
+  auto touch_line = [&]() { return tid_now() & 255; };
   // Who shares what is read off the tiles that really run side by side, not assumed: the experts'
   // tile counts are no multiples of 32, so a run starts anywhere in an expert's tile order and
   // may span two experts (a fixed partition by tile index left half of the B lines untouched in
@@ -639,7 +661,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // run this workgroup's tile belongs to (`base` = the run's first list position, `n_valid`
   // tiles, this workgroup's the `me`-th); tiles with the same expert and row tile share the A
   // tile, tiles with the same expert and column tile the B tile.
-  auto touch_of = [&](const Tile& tt, int kts_of_tile, int base, int n_valid, int me) {
+  auto touch_of = [&](const Tile& tt, int a_row, int kts_of_tile, int base, int n_valid, int me) {
     if constexpr (!TOUCHES) return Touch{0, kOob, kOob};
     // nothing is touched when the k range (of a phase, for dX) is short (11 k tiles: 4 % slower with the prefetch than without)
     if (kts_of_tile < kMinTouchKt) return Touch{0, kOob, kOob};
@@ -663,18 +685,19 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     const int cnt_a = max(1, __builtin_popcountll(share_a)), rank_a = __builtin_popcountll(share_a & below);
     const int cnt_b = max(1, __builtin_popcountll(share_b)), rank_b = __builtin_popcountll(share_b & below);
     // The lines of an operand tile go round robin to its `cnt` sharers, this workgroup being the `rank`-th.
-    // Each of the prefetching wavefronts covers 64 lines of the A tile and 64 of the B tile (gate/up: two of them the gate
+    // Each of the prefetching wavefronts covers 64 lines of the A tile and 64 of the B tile (where all load, 0 .. 3 those of the A
+    // tile and 4 .. 7, which have fewer rows to compute, those of the B tile; gate/up: two of them the gate
     // rows, two the matching up rows).  (One contiguous block of lines per sharer instead measured the same, +-1 %; a
     // workgroup's share packed into two instructions per k tile instead of eight: 2 to 4 % slower.)  A tile nobody else in the
     // run uses is touched all the same, by its one user: left out, it runs so much slower than its neighbours that a
     // product of three rounds -- down on a Mixtral-shaped layer, where ten of 576 tiles are in that position -- ends
     // 20 % later.
     Touch th{1, kOob, kOob};
-    const int line = (wave & 3) * 64 + lane;
+    const int line = touch_line();
     const int rows_left = tt.m_end - tt.m0, cols_left = n_end - tt.n0;
     if (!A_TRANS) {
       if (line < rows_left && line % cnt_a == rank_a)
-        th.a = (uint32_t)(gathered ? p.gather[tt.m0 + line] / p.gather_div : line) * lda_b;
+        th.a = (uint32_t)a_row * lda_b;
     } else {
       // [k][row] tile: k-row line / 4, 64-row quarter line % 4 (128 bytes); the record count masks the k range
       if ((line & 3) * 64 < rows_left && line % cnt_a == rank_a) th.a = (uint32_t)(line >> 2) * lda_b + (line & 3) * 128;
@@ -691,8 +714,21 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   auto touch = [&](const KTile& q, const Touch& th) {
     if constexpr (TOUCHES) {
       const int on = __builtin_amdgcn_readfirstlane(th.on);
-      touch_to_lds(q.a, lds_dump, th.a, on);
-      touch_to_lds(q.b, lds_dump, th.b, on);
+      if constexpr (SHARE) {
+        desc_t d = q.a;
+        if (wave_u >= kLoaders) {
+          d = q.b;
+          if (MODE == MODE_GATEUP && wave_u < kLoaders + 2) {  // a gate row, where this wavefront's pieces are up rows
+            const uint64_t at = ((uint64_t)d.y << 32 | d.x) + ((uint64_t)p.B1 - (uint64_t)p.B2);
+            d.x = (uint32_t)at;
+            d.y = (uint32_t)(at >> 32) & 0xffffu;
+          }
+        }
+        touch_to_lds(d, lds_dump, wave_u < kLoaders ? th.a : th.b, on);
+      } else {
+        touch_to_lds(q.a, lds_dump, th.a, on);
+        touch_to_lds(q.b, lds_dump, th.b, on);
+      }
     }
   };
   const int n_rounds = my_rounds + (has_part ? 1 : 0);
@@ -753,7 +789,7 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   FragAddr<A_TRANS, 4> fra = frag_addr<A_TRANS, 4, 4>(lds0, wave_u >> 1);
   FragAddr<B_TRANS, 8> frb = frag_addr<B_TRANS, 8, 1>(lds0, MODE == MODE_GATEUP ? (wave_u & 1) * 4 : (wave_u & 1) * 8);
   KIter kit = kiter_at(t, kr, kt_lo, second_b);  // the k tiles to load or to prefetch, in order
-  Pieces pa, pb;                                 // of a loading wavefront
+  Pieces pa, pb;                                 // of the k tiles that this wavefront loads
   Touch th{0, kOob, kOob};                       // of a prefetching one
   // A fragment of row block I / B fragment of column block J for k step H
   // (the stage read is the one fra / frb point into)
@@ -774,28 +810,33 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   const std::integral_constant<int, 2> c2_;
 
   // What this workgroup prefetches is worked out with the first two k tiles on their way, where it costs no time.
-  auto touch_now = [&]() {
-    return parted ? touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), tb.total - tail_tiles + (xcd / split) * slots, min(slots, tail_tiles - (xcd / split) * slots), slot)
-                  : touch_of(t, min(kt_hi - kt_lo, kr.kt_per_phase), run_base(round), run_len(round), place(round));
+  auto touch_now = [&](int touch_row) {
+    return parted ? touch_of(t, touch_row, min(kt_hi - kt_lo, kr.kt_per_phase), tb.total - tail_tiles + (xcd / split) * slots, min(slots, tail_tiles - (xcd / split) * slots), slot)
+                  : touch_of(t, touch_row, min(kt_hi - kt_lo, kr.kt_per_phase), run_base(round), run_len(round), place(round));
   };
-  // The first k tile is loaded by the loading wavefronts, the second one by the others.
+  // Tiles of many rows: the first k tile is loaded by the loading wavefronts, the second one by the others.
   pa = pieces_a(t);
   pb = pieces_b(t);
   const KTile q0 = knext(kit), q1 = knext(kit);
-  if (!loader) {
-    static_for<kPieces>([&](auto J) { dma_a(pa, q1, lds0 + kStageBytes, J); });
-    static_for<kPieces>([&](auto J) { dma_b(pb, q1, lds0 + kStageBytes, J); });
-    if constexpr (TOUCHES) {
-      th = touch_now();
-      for (int i = 2; i < kTouchLead; ++i) touch(knext(kit), th);
-    }
-  } else {
-    if (!first_in_flight) {
-      static_for<kPieces>([&](auto J) { dma_a(pa, q0, lds0, J); });
-      static_for<kPieces>([&](auto J) { dma_b(pb, q0, lds0, J); });
-    }
-    wait_loads_and_lds();  // the first tile has landed
+  KTile ahead{};  // SHARE: the next k tile to load, the last one prefetched
+  const bool prefetches = TOUCHES && (SHARE || !loader);
+  int touch_row = touch_line();
+  if (prefetches && gathered) {  // loaded here: behind the pieces the index would wait for them
+    touch_row = touch_row < t.m_end - t.m0 ? p.gather[t.m0 + touch_row] / p.gather_div : 0;
+    asm volatile("" : "+v"(touch_row));
   }
+  if (loader && !first_in_flight) load_tile(pa, pb, q0, lds0);
+  if (SHARE || !loader) load_tile(pa, pb, q1, lds0 + kStageBytes);
+  if (prefetches) {
+    th = touch_now(touch_row);
+    for (int i = 2; i < kTouchLead; ++i) {
+      ahead = knext(kit);
+      touch(ahead, th);
+    }
+  }
+  // the first k tile has landed
+  if (SHARE) wait_loads_but<2 * kOwn, 2 * kOwn + kTouchLead - 2>(__builtin_amdgcn_readfirstlane(th.on));
+  else if (loader) wait_loads_and_lds();
   wg_barrier();
   const int valid16 = min(16, (t.m_end - t.m0 + 15) / 16);  // valid 16-row blocks of the tile (a prefix)
   const bool cols_ok = (MODE == MODE_GATEUP ? t.n0 + (wave_u & 1) * 64 : t.n0 + (wave_u & 1) * 128) < n_end;
@@ -808,13 +849,19 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   auto work = [&](auto ROWS_C, auto LOADER_C) {
     constexpr int ROWS = decltype(ROWS_C)::value, LAST = ROWS - 1;
     constexpr bool LOADER = decltype(LOADER_C)::value;
+    constexpr int PIECES = LOADER ? 2 * kOwn : 0;
+    auto refill_piece = [&](auto P, uint32_t freed, const KTile& q2) {
+      constexpr int piece = decltype(P)::value;
+      if constexpr (piece < kOwn) dma_a(pa, q2, freed, P);
+      else dma_b(pb, q2, freed, std::integral_constant<int, piece - kOwn>{});
+    };
     const std::integral_constant<int, LAST> c_last;
     static_for<LAST>([&](auto I) { read_a(I, c0); });
     static_for<8>([&](auto J) { read_b(J, c0); });
     read_a(c_last, c0);
     // all MFMAs of one k step; WHAT = 0: first step of a k tile (fragments of step 1 follow as registers fall
     // free), 1: row 0 of step 1 only, 2: rows 1.. of step 1 with the refill, 3: rows 1.. of step 1 without
-    auto mfmas = [&](auto WHAT_C, uint32_t freed, const KTile& q2) {
+    auto mfmas = [&](auto WHAT_C, uint32_t freed, const KTile& q2, const KTile& q3) {
       constexpr int WHAT = decltype(WHAT_C)::value;
       constexpr int FIRST_SLOT = WHAT >= 2 ? 8 : 0, END_SLOT = WHAT == 1 ? 8 : 8 * ROWS;
       constexpr int REFILL_SLOTS = 8 * ROWS - 8;  // MFMA slots behind the barrier (none if ROWS == 1)
@@ -837,17 +884,10 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
         }
         if constexpr (WHAT == 2) {
           constexpr int s = m - 8;
-          if constexpr (LOADER) {  // the pieces of the refill, evenly over the slots
-            static_for<2 * kPieces>([&](auto P) {
-              constexpr int piece = decltype(P)::value;
-              if constexpr (piece * REFILL_SLOTS / (2 * kPieces) == s) {
-                if constexpr (piece < kPieces) dma_a(pa, q2, freed, std::integral_constant<int, piece>{});
-                else dma_b(pb, q2, freed, std::integral_constant<int, piece - kPieces>{});
-              }
-            });
-          } else if constexpr (s == REFILL_SLOTS - 1) {
-            touch(q2, th);
-          }
+          static_for<PIECES>([&](auto P) {  // the pieces of the refill, evenly over the slots
+            if constexpr (decltype(P)::value * REFILL_SLOTS / PIECES == s) refill_piece(P, freed, q2);
+          });
+          if constexpr ((SHARE || !LOADER) && s == REFILL_SLOTS - 1) touch(q3, th);
         }
         mfma(std::integral_constant<int, i>{}, std::integral_constant<int, j>{});
         if constexpr (WHAT == 0 || WHAT == 2) {
@@ -859,32 +899,29 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
       });
     };
     const std::integral_constant<int, 2> c2;
-    auto step0 = [&]() { mfmas(c0, 0u, KTile{}); };
+    auto step0 = [&]() { mfmas(c0, 0u, KTile{}, KTile{}); };
     auto step1_row0_and_barrier = [&](bool first) {
-      mfmas(c1, 0u, KTile{});
-      if (LOADER || first) wait_loads_and_lds();
-      else wait_lds();
+      mfmas(c1, 0u, KTile{}, KTile{});
+      if (!LOADER && !first) wait_lds();
+      else if (TOUCHES && SHARE && !first) wait_loads_but<0, 1>(__builtin_amdgcn_readfirstlane(th.on));
+      else wait_loads_and_lds();
       wg_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
     // behind the barrier: fra / frb move on to the next tile's stage; its first fragments and the refill of the
     // stage just freed go between the remaining MFMAs of step 1 (all at once if there are none)
-    auto step1_rest = [&](uint32_t to_next, uint32_t freed, const KTile& q2) {
+    auto step1_rest = [&](uint32_t to_next, uint32_t freed, const KTile& q2, const KTile& q3) {
       fra.shift(to_next);
       frb.shift(to_next);
       if constexpr (ROWS == 1) {
-        if constexpr (LOADER) {
-          static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
-          static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
-        } else {
-          touch(q2, th);
-        }
+        static_for<PIECES>([&](auto P) { refill_piece(P, freed, q2); });
+        if constexpr (SHARE || !LOADER) touch(q3, th);
         static_for<8>([&](auto J) { read_b(J, c0); });
         read_a(c0, c0);
         __builtin_amdgcn_sched_barrier(0);
       } else {
         if constexpr (LAST > 0) read_a(c0, c0);
-        mfmas(c2, freed, q2);
+        mfmas(c2, freed, q2, q3);
       }
     };
     __builtin_amdgcn_sched_barrier(0);
@@ -893,25 +930,35 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
     for (int kt = kt_lo; kt + 1 < kt_hi; ++kt) {
       const int stage = (kt - kt_lo) & 1;
       const uint32_t to_next = stage ? 0u - (uint32_t)kStageBytes : (uint32_t)kStageBytes;
-      KTile q2{};
-      if constexpr (LOADER || TOUCHES) q2 = knext(kit);
-      step1_rest(to_next, lds0 + stage * kStageBytes, q2);
+      KTile q2{}, q3{};
+      if constexpr (SHARE && TOUCHES) {
+        q2 = ahead;
+        q3 = ahead = knext(kit);
+      } else if constexpr (LOADER) {
+        q2 = knext(kit);
+      } else if constexpr (TOUCHES) {
+        q3 = knext(kit);
+      }
+      step1_rest(to_next, lds0 + stage * kStageBytes, q2, q3);
       step0();
       step1_row0_and_barrier(false);
     }
-    if constexpr (ROWS > 1) mfmas(std::integral_constant<int, 3>{}, 0u, KTile{});
+    if constexpr (ROWS > 1) mfmas(std::integral_constant<int, 3>{}, 0u, KTile{}, KTile{});
   };
   if (my_rows == 0) {
     // No valid rows or columns in this wavefront's part: it only keeps up the staging -- moves its
     // pieces and meets the barriers -- and leaves the SIMD and the LDS to the others.
     for (int kt = kt_lo; kt < kt_hi; ++kt) {
-      if (loader || kt == kt_lo) wait_loads_and_lds();
+      if (kt == kt_lo || (loader && !SHARE)) wait_loads_and_lds();
+      else if (SHARE) wait_loads_but<0, 1>(__builtin_amdgcn_readfirstlane(th.on));
       wg_barrier();
-      if (loader) {
-        const uint32_t freed = lds0 + ((kt - kt_lo) & 1) * kStageBytes;
-        const KTile q2 = knext(kit);
-        static_for<kPieces>([&](auto J) { dma_a(pa, q2, freed, J); });
-        static_for<kPieces>([&](auto J) { dma_b(pb, q2, freed, J); });
+      const uint32_t freed = lds0 + ((kt - kt_lo) & 1) * kStageBytes;
+      if (SHARE && TOUCHES) {
+        load_tile(pa, pb, ahead, freed);
+        ahead = knext(kit);
+        touch(ahead, th);
+      } else if (loader) {
+        load_tile(pa, pb, knext(kit), freed);
       } else if constexpr (TOUCHES) {
         touch(knext(kit), th);
       }
@@ -923,7 +970,8 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
       else if (my_rows == 2) work(c2_, LOADER_C);
       else work(c1, LOADER_C);
     };
-    if (loader) work_as(std::true_type{});
+    if constexpr (SHARE) work_as(std::true_type{});
+    else if (loader) work_as(std::true_type{});
     else work_as(std::false_type{});
   }
   // every piece (masked ones included) has landed and nobody reads the stages any more
@@ -932,16 +980,12 @@ __global__ __launch_bounds__(kMfmaThreads, 1) void ffn_mfma_kernel(const GemmPar
   // The epilogue uses patches behind stage 0, so the first k tile of this workgroup's next
   // tile can be on its way into stage 0 while the results are stored.
   first_in_flight = round + 1 < n_rounds;
-  if (first_in_flight) {
-    if (loader) {
+  if (first_in_flight && loader) {
     const Tile tn = tile_at(round + 1);
     const KRange rn = krange(tn, CAN_SPLIT && round + 1 == my_rounds);
     const Pieces pan = pieces_a(tn), pbn = pieces_b(tn);
     KIter kn = kiter_at(tn, rn, rn.kt_lo, second_b);
-    const KTile qn = knext(kn);
-    static_for<kPieces>([&](auto J) { dma_a(pan, qn, lds0, J); });
-    static_for<kPieces>([&](auto J) { dma_b(pbn, qn, lds0, J); });
-    }
+    load_tile(pan, pbn, knext(kn), lds0);
   }
 
   // ---- epilogue.  Accumulator element r of block (i, j) is row 16 (4 i + wm) + (lane/16)*4 + r,
@@ -1167,12 +1211,12 @@ static int persistent_blocks(int max_tiles) {
   return want < cus ? want : cus;
 }
 
-template <int MODE, bool WHOLE_K>
+template <int MODE, bool WHOLE_K, bool SHARE>
 static int32_t launch_mfma_as(const GemmParams& p, int max_tiles, KernelId id, hipStream_t st) {
   static bool attr_set[kMaxDevices] = {};  // the LDS size is a per-device function attribute
   bool& done = attr_set[current_device()];
   if (!done) {
-    DYNMO_HIP_TRY(hipFuncSetAttribute((const void*)ffn_mfma_kernel<MODE, WHOLE_K>,
+    DYNMO_HIP_TRY(hipFuncSetAttribute((const void*)ffn_mfma_kernel<MODE, WHOLE_K, SHARE>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTotal));
     done = true;
   }
@@ -1181,7 +1225,7 @@ static int32_t launch_mfma_as(const GemmParams& p, int max_tiles, KernelId id, h
   const bool may_split = (MODE == MODE_DOWN || MODE == MODE_DOWN_FOLD || MODE == MODE_DX || MODE == MODE_DX_FOLD) && p.partial != nullptr;
   const int blocks = persistent_blocks(may_split ? kMaxPersistent : max_tiles);
   ProfScope prof(id, st);
-  ffn_mfma_kernel<MODE, WHOLE_K><<<dim3(blocks), dim3(kMfmaThreads), kLdsTotal, st>>>(p);
+  ffn_mfma_kernel<MODE, WHOLE_K, SHARE><<<dim3(blocks), dim3(kMfmaThreads), kLdsTotal, st>>>(p);
   DYNMO_LAUNCH_CHECK();
   if (may_split) {
     ffn_split_reduce_kernel<<<dim3(kReduceParts * kMaxSplitTiles), dim3(256), 0, st>>>(p.partial, p.C0, p.ldc, p.N, p.scatter,
@@ -1192,12 +1236,16 @@ static int32_t launch_mfma_as(const GemmParams& p, int max_tiles, KernelId id, h
 }
 
 template <int MODE>
-static int32_t launch_mfma(const GemmParams& p, int max_tiles, KernelId id, hipStream_t st) {
+static int32_t launch_mfma(const GemmParams& p, int max_tiles, bool share, KernelId id, hipStream_t st) {
   // MODE_DW contracts over an expert's rows, which both of its operands hold as [k][row] records
-  if constexpr (MODE != MODE_DW) {
-    if (p.K % BK == 0) return launch_mfma_as<MODE, true>(p, max_tiles, id, st);
+  if constexpr (MODE == MODE_DW) {
+    return launch_mfma_as<MODE, false, false>(p, max_tiles, id, st);
+  } else if constexpr (MODE == MODE_DA) {
+    return p.K % BK == 0 ? launch_mfma_as<MODE, true, false>(p, max_tiles, id, st) : launch_mfma_as<MODE, false, false>(p, max_tiles, id, st);
+  } else {
+    if (share) return p.K % BK == 0 ? launch_mfma_as<MODE, true, true>(p, max_tiles, id, st) : launch_mfma_as<MODE, false, true>(p, max_tiles, id, st);
+    return p.K % BK == 0 ? launch_mfma_as<MODE, true, false>(p, max_tiles, id, st) : launch_mfma_as<MODE, false, false>(p, max_tiles, id, st);
   }
-  return launch_mfma_as<MODE, false>(p, max_tiles, id, st);
 }
 
 // Which kernel takes a product: this file's, or ffn_tile.hip (the weight gradients: ffn_dw.hip) with the given tile.  The host knows rows, experts and
@@ -1306,6 +1354,18 @@ int32_t ffn_mfma_kernel_of(const dynmo_desc* d, int32_t product) {
   return DYNMO_EINVAL;
 }
 
+// Whether all wavefronts load (SHARE), by the rows of an expert on average: with one or two row blocks per wavefront the sixteen
+// loads of a loading one have nothing to go between.  us, two roles / shared (T H F E k):
+//   gate/up  80 784 520 64 4: 40.0 / 36.8; 1760 1000 2048 32 2 (110 rows): 115 / 107; 118 256 3192 29 2: 28.7 / 26.7; but 1248 2048 1024
+//            32 2 (78 rows): 56.8 / 62.0; 3835 1792 11136 11 1 (349): 341 / 356.  A ragged last k tile masks every load
+//   down     320 1000 2048 64 4 (20): 78 / 74; 720 of it (45): 81 / 78; 312 288 6528 33 7 (66): 88 / 92
+//   dX       118 256 3192 29 2 (8): 36.3 / 33.6; 720 1000 2048 64 4 (45): 166 / 172
+static bool share_for(const dynmo_desc* d, int mode, int K) {
+  const int64_t rows = (int64_t)d->T * d->k, experts = d->E < rows ? d->E : rows;
+  if (mode == MODE_GATEUP) return rows <= 128 * experts && (K <= 1024 || K % BK != 0);
+  return rows <= (mode == MODE_DOWN || mode == MODE_DOWN_FOLD ? 64 : 16) * experts;
+}
+
 template <int MODE>
 static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, KernelId id, hipStream_t st) {
   const TileKind kind = kernel_for(d, MODE);
@@ -1317,7 +1377,7 @@ static int32_t launch_rows_product(const dynmo_desc* d, const GemmParams& p, Ker
   }
   if (kind != TILE_256) return ffn_tile_rows(MODE, kind, d, p, id, st);
   constexpr int tile_n = MODE == MODE_GATEUP ? BN / 2 : BN;
-  return launch_mfma<MODE>(p, max_m_tiles(d, BM) * ((p.N + tile_n - 1) / tile_n), id, st);
+  return launch_mfma<MODE>(p, max_m_tiles(d, BM) * ((p.N + tile_n - 1) / tile_n), share_for(d, MODE, p.K), id, st);
 }
 
 bool ffn_mfma_supported(const dynmo_desc* d) {
@@ -1411,7 +1471,7 @@ int32_t ffn_bwd_mfma(const dynmo_desc* d, const void* dy_p, const void* x_p, con
     p.ldb = N;
     p.C0 = (bf16_t*)out;
     p.ldc = N;
-    return launch_mfma<MODE_DW>(p, d->E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN), id, st);
+    return launch_mfma<MODE_DW>(p, d->E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN), false, id, st);
   };
   // Order: the three weight gradients first, dX last, so that the pass that follows the
   // call (the scatter of dx_p back to token order) finds dx_p still in the last-level cache.

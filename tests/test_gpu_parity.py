@@ -1024,6 +1024,31 @@ def test_small_products_tile_edges(T, H, F, E, k, expected):
     assert torch.equal(layer.out, out)
 
 
+@pytest.mark.parametrize("T,H,F,E,k,product", [(200, 1032, 1544, 32, 2, "gateup"), (300, 264, 2568, 16, 2, "gateup"), (100, 520, 4360, 4, 2, "down"),
+                                               (40, 264, 2312, 8, 2, "dX"), (37, 520, 4136, 1, 1, "down")])
+def test_few_rows_on_256x256_tiles(T, H, F, E, k, product):
+    """Products on 256 x 256 tiles whose loads and prefetch are shared by all wavefronts: gate/up of up to 128 rows per expert (the
+    first layer, of 17 k tiles with a ragged last one, and prefetched; the second, of five, not), down of up to 64 (the third; the last
+    one with the combine folded in), dX of up to 16, k split (the fourth).  With and without gathered rows."""
+    say("few rows on 256x256 tiles T=%d H=%d F=%d E=%d k=%d" % (T, H, F, E, k))
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=k, seed=9400 + T)
+    assert kernels(w)[product] == "256x256"
+    inp = wl.make_inputs(w, threads=4)
+    layer = run_moe(w, inp)
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(layer, ref, w.dtype)
+    out = layer.out.clone()
+    dev = {n: to_device(a) for n, a in inp.items()}
+    layer.out.zero_()
+    layer.forward_gather(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+    assert torch.equal(layer.out, out)
+    if k == 1:
+        layer.out.zero_()
+        layer.forward_folded(dev["x"], dev["Wg"], dev["Wu"], dev["Wd"])
+        assert torch.equal(layer.out, out)
+
+
 @pytest.mark.parametrize("E,H,F,kernel", [(64, 776, 776, "128x256"), (64, 520, 520, "128x256"), (63, 512, 512, "128x128"), (18, 264, 264, "64x64")])
 def test_weight_gradient_workgroups_walk_tiles(E, H, F, kernel):
     """Weight gradients whose workgroups take four tiles each (the first layer, 5376 tiles of 128 x 256) or one: the
