@@ -8,13 +8,15 @@
 //
 // What bounds it: with 64 experts of about 256 rows (2048 x 1024; 12288 tiles of eight k steps) the time is the same without the
 // MFMAs, and half without the loads: memory and the start of a tile.  Hence
-//   * a workgroup walks several tiles: the loads run NS - 1 k steps ahead of the arithmetic across the end of a tile, so that
-//     the next tile's first steps are on their way while the last ones of this tile are computed and stored;
 //   * the results leave through a bf16 patch in the one LDS stage that is free then: the MFMAs have their operands swapped, so
 //     that a lane holds four neighbours of a row, one 8-byte LDS store, where accumulators in column order were four
 //     4-byte ones in fp32;
-//   * a step's fragments are read while the step before is computed.
+//   * 128 x 256 tiles, where there are thousands of short ones (AHEAD): a workgroup walks several of them; the loads run NS - 1 k
+//     steps ahead of the arithmetic across the end of a tile, so that the next tile's first steps are on their way while the
+//     last ones of this tile are computed and stored;
+//   * there, and where tiles are long, a step's fragments are read while the step before is computed.
 #include "ffn_gemm.h"
+#include "tile_list.h"
 
 namespace dynmo {
 
@@ -37,8 +39,8 @@ struct DwParams {
   DwSet dw[3];  // the products of this launch
   int sets;
   int per_expert;  // tiles of them per expert
-  int group;       // consecutive tiles of the list that go to one XCD
-  int walk;        // tiles per workgroup
+  TileList list;
+  int walk;        // tiles per workgroup (AHEAD)
 };
 
 // WBM x WBN blocks of 16 x 16 per wavefront
@@ -155,7 +157,7 @@ __device__ __forceinline__ void wait_stage() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N < 63 ? N : 63) : "memory");
 }
 
-template <int WBM, int WBN>
+template <int WBM, int WBN, bool AHEAD>
 __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void ffn_dw_kernel(const DwParams p) {
   using S = DwShape<WBM, WBN>;
   __shared__ __attribute__((aligned(1024))) char smem[S::kLds];
@@ -172,8 +174,8 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
     bf16_t* C;
   };
   auto job_at = [&](int step, Job& j) {
-    const int slot = blockIdx.x >> 3;
-    const int pos = ((slot / p.group * p.walk + step) * 8 + (blockIdx.x & 7)) * p.group + slot % p.group;
+    const int slot = blockIdx.x >> 3, run = run_of(p.list, slot);
+    const int pos = ((AHEAD ? run * p.walk + step : run) * 8 + (blockIdx.x & 7)) * p.list.group + slot - run * p.list.group;
     const int e = pos / p.per_expert;
     if (e >= p.E) return false;  // past the last tile
     int r = pos - e * p.per_expert, set = 0;
@@ -244,8 +246,10 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
   auto following = [](uint32_t s) { return s + S::kStage == S::kLds ? 0u : s + S::kStage; };
   auto last_of_ring = [&](uint32_t s) { return s == 0 ? (uint32_t)(S::kLds - S::kStage) : s - S::kStage; };
   static_for<NS - 1>([&](auto J) { issue(decltype(J)::value * S::kStage); });
-  wait_stage<(NS - 2) * S::kLoads>();  // the first k step has landed
-  __builtin_amdgcn_s_barrier();
+  if constexpr (AHEAD) {
+    wait_stage<(NS - 2) * S::kLoads>();  // the first k step has landed
+    __builtin_amdgcn_s_barrier();
+  }
   // A whole tile's stores per wavefront, which the first wait of the next tile need not include.
   constexpr int kStores = WBM * (WBN / 2);
   bool stores_out = false;
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
   for (int step = 0;; ++step) {
     // Every tile is walked in at least NS - 1 steps (zeros past the last one), so that the loads that run ahead of the
     // arithmetic are never more than one tile ahead.
-    const bool more_asked = step + 1 < p.walk;
+    const bool more_asked = AHEAD && step + 1 < p.walk;
     const int n_kt = max(steps_of(job), more_asked ? NS - 1 : 1);
     Job next;
     const bool more = more_asked && job_at(step + 1, next);
@@ -348,8 +352,8 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
       }
       body(std::false_type{}, std::false_type{});
     };
-    // 64 x 64 tiles, which are never walked: four MFMAs per step and five workgroups per compute unit, where reading ahead only
-    // costs (one expert, 2608 rows, 128 x 4736: 22.7 us so, 25.4 with the loop above).
+    // Short tiles that are not walked: the other workgroups of the compute unit cover what the loop above reads ahead for, and its code
+    // is more than twice as long.
     auto plain_loop = [&](auto ROWS_C) {
       constexpr int ROWS = decltype(ROWS_C)::value;
       const int lane = lane_now();
@@ -376,8 +380,10 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
         stage = following(stage);
       }
     };
-    if constexpr (WBN == 2) {
-      if (my_rows == 2) plain_loop(std::integral_constant<int, 2>{});
+    if constexpr (!AHEAD) {
+      if (my_rows == WBM) plain_loop(std::integral_constant<int, WBM>{});
+      else if (WBM > 3 && my_rows == 3) plain_loop(std::integral_constant<int, WBM - 1>{});
+      else if (my_rows == 2) plain_loop(std::integral_constant<int, WBM < 2 ? WBM : 2>{});
       else if (my_rows == 1) plain_loop(std::integral_constant<int, 1>{});
       else plain_loop(std::integral_constant<int, 0>{});
     } else if (my_rows == WBM) {
@@ -441,11 +447,19 @@ static int32_t launch_dw(DwParams p, double rows, const ProfRoles& roles, hipStr
   // this kernel: 64 experts, 16384 rows, 2048 x 1024, 12288 tiles 361 / 342, 368; 16, 6000, 2048 x 4096 412 / 394, 421; 8, 8192, 2048 x
   // 4096, 6144 tiles 416 / 406, 428.  Longer tiles hide their ends behind the other workgroup's arithmetic (16, 32768, 4096 x 688: 531 /
   // 539, 569), and with fewer the last round gets coarser (57, 21548 uneven, 256 x 1688, 2394 tiles: two in runs of 32 129, before 118).
-  p.group = tiles >= 4096 ? 32 : tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1;
-  p.walk = WBN > 2 && tiles >= 4096 && rows <= 1024.0 * p.E ? 4 : 1;
-  const int run = 8 * p.group * p.walk;
-  const unsigned blocks = (unsigned)((tiles + run - 1) / run * 8 * p.group);
-  DYNMO_TIMED_LAUNCH(roles, st, ffn_dw_kernel<WBM, WBN><<<dim3(blocks), dim3(kDwThreads), 0, st>>>(p));
+  // AHEAD, one tile per workgroup, us with / without (T H F E k): 6794 3328 1152 7 2 (1941 rows per expert): 266 / 279; 8192 4096 688 16 4
+  // (2048): 503 / 509; 13639 944 912 16 1 (852): 97.8 / 96.9; 80 2048 1024 8 2 (20): 24.3 / 23.6; on 128 x 128 tiles 3168 1152 768 6 1 (528):
+  // 31.9 / 30.0, 1511 2240 392 14 3 (324): 43.9 / 42.6; one expert, 2608 rows, 128 x 4736, 64 x 64: 25.4 / 22.7.
+  p.walk = WBN == 8 && tiles >= 4096 && rows <= 1024.0 * p.E ? 4 : 1;
+  p.list = tile_list(tiles, tiles >= 4096 ? 32 : 16, p.walk);
+  const dim3 grid(p.list.blocks);
+  if constexpr (WBN == 8) {
+    if (p.walk > 1 || rows > 1024.0 * p.E) {
+      DYNMO_TIMED_LAUNCH(roles, st, ffn_dw_kernel<WBM, WBN, true><<<grid, dim3(kDwThreads), 0, st>>>(p));
+      return DYNMO_OK;
+    }
+  }
+  DYNMO_TIMED_LAUNCH(roles, st, ffn_dw_kernel<WBM, WBN, false><<<grid, dim3(kDwThreads), 0, st>>>(p));
   return DYNMO_OK;
 }
 

@@ -13,11 +13,12 @@ struct TileList {
   uint32_t inv_group;  // 2^31 / group, rounded up: (2 x * inv_group) / 2^32 is x / group, of any x for a power of two, else below 2^23
   unsigned blocks;     // workgroups
 };
-// `tiles`: the most that there can be
-constexpr TileList tile_list(int tiles) {
-  const int group = tiles >= 1024 ? 16 : tiles >= 128 ? tiles / 64 : 1, run = 8 * group;
-  return {group, ((1u << 31) + group - 1) / group, (unsigned)(((int64_t)tiles + run - 1) / run * run)};
+// `tiles`: the most that there can be; `longest`: the group of 1024 and more; `walk`: tiles per workgroup
+constexpr TileList tile_list(int tiles, int longest = 16, int walk = 1) {
+  const int group = tiles >= 1024 ? longest : tiles >= 128 ? tiles / 64 : 1, run = 8 * group * walk;
+  return {group, ((1u << 31) + group - 1) / group, (unsigned)(((int64_t)tiles + run - 1) / run * 8 * group)};
 }
+constexpr int run_of(const TileList& l, int slot) { return (int)((uint64_t)(2 * (uint32_t)slot) * l.inv_group >> 32); }
 
 // The position in the list of workgroup `block` (XCD block % 8), `total` tiles long; from `total` on if it has none.  Tiles of
 // rows x cols; `one_each`: no expert has more than one row tile.
@@ -38,7 +39,7 @@ constexpr TileList tile_list(int tiles) {
 // More tiles go in runs of `group` (1280 tiles of 128 x 256, dX of 64 experts: 193 / 200).
 constexpr int list_position(const TileList& l, unsigned block, int total, int rows, int cols, int experts, bool one_each) {
   const int slot = (int)(block >> 3), xcd = (int)(block & 7), eighth = (total + 7) >> 3;
-  const int run = (int)((uint64_t)(2 * (uint32_t)slot) * l.inv_group >> 32);
+  const int run = run_of(l, slot);
   const bool even = cols > 128 ? total > kNearlyTwo : one_each || experts <= (rows == 64 ? 7 : 16);
   const bool eighths = total <= kOneEach || (total <= 2 * kOneEach && even);
   int pos = eighths ? (slot < eighth ? xcd * eighth + slot : total) : (run * 8 + xcd) * l.group + slot - run * l.group;
