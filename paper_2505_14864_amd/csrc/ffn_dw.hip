@@ -442,19 +442,24 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
 template <int WBM, int WBN>
 static int32_t launch_dw(DwParams p, double rows, const ProfRoles& roles, hipStream_t st) {
   const int tiles = p.E * p.per_expert;
-  // Runs of 16 tiles, of 32 where there are many (128: XCDs without work at the end).  Several tiles per workgroup where a tile is
-  // short, up to 32 k steps on average, and the chip is filled many times.  us with one tile in runs of 16 / four in runs of 32; before
-  // this kernel: 64 experts, 16384 rows, 2048 x 1024, 12288 tiles 361 / 342, 368; 16, 6000, 2048 x 4096 412 / 394, 421; 8, 8192, 2048 x
-  // 4096, 6144 tiles 416 / 406, 428.  Longer tiles hide their ends behind the other workgroup's arithmetic (16, 32768, 4096 x 688: 531 /
-  // 539, 569), and with fewer the last round gets coarser (57, 21548 uneven, 256 x 1688, 2394 tiles: two in runs of 32 129, before 118).
-  // AHEAD, one tile per workgroup, us with / without (T H F E k): 6794 3328 1152 7 2 (1941 rows per expert): 266 / 279; 8192 4096 688 16 4
-  // (2048): 503 / 509; 13639 944 912 16 1 (852): 97.8 / 96.9; 80 2048 1024 8 2 (20): 24.3 / 23.6; on 128 x 128 tiles 3168 1152 768 6 1 (528):
-  // 31.9 / 30.0, 1511 2240 392 14 3 (324): 43.9 / 42.6; one expert, 2608 rows, 128 x 4736, 64 x 64: 25.4 / 22.7.
-  p.walk = WBN == 8 && tiles >= 4096 && rows <= 1024.0 * p.E ? 4 : 1;
-  p.list = tile_list(tiles, tiles >= 4096 ? 32 : 16, p.walk);
+  // Several tiles per workgroup where a tile is short and the chip is filled many times, else one; read ahead there and where tiles
+  // are long; runs of 32 there if there are many, else of 16.  us, four tiles in runs of 32 / one ahead in runs of 16, of 32 / one in the plain loop (H F, experts;
+  // rows per expert):
+  //   2048 1024, 32       128: 126 / 135, 133 / 133     512: 238 / 243, 246 / 247     1024: 392 / 389, 389 / 389     1536: 553 / 544, 542 / 554
+  //   1024 1024, 64        64: 105 / 111, 113 / 108     512: 259 / 254, 262 / 256     1024: 426 / 401, 419 / 403
+  //   2048 4096, 8        200: 142 / 152, 152 / 151     700: 286 / 288, 290 / 289     1024: 377 / 385, 387 / 384     1300: 454 / 459, 464 / 455
+  //   4096 688, 16       2048: 538 / 511, 522 / 541, with four slots per token - / 506, 501 / -     (four tiles in runs of 16: 569; up to 5 %
+  //                            slower than of 32 everywhere but at 1024 1024)
+  //   4096 2048, 8        875: 322 / 330, - / -
+  //   2048 1024, 16 (3072 tiles)   300: 92 / 88, 88 / 87     1000: 201 / 191, 196 / 193     3328 1152, 7 (2457)   1941: - / 266, - / 279
+  // On 128 x 128 tiles the plain loop is the faster one at all lengths (1152 768, 6 experts, 528 rows: 31.9 / 30.0; 184 9216, 2, 11221: 478 /
+  // 478), as on 64 x 64 (128 4736, 1, 2608: 25.4 / 22.7).
+  p.walk = WBN == 8 && tiles >= 4096 && rows <= 896.0 * p.E ? 4 : 1;
+  const bool ahead = p.walk > 1 || rows > 1400.0 * p.E;
+  p.list = tile_list(tiles, WBN == 8 && ahead && tiles >= 4096 ? 32 : 16, p.walk);
   const dim3 grid(p.list.blocks);
   if constexpr (WBN == 8) {
-    if (p.walk > 1 || rows > 1024.0 * p.E) {
+    if (ahead) {
       DYNMO_TIMED_LAUNCH(roles, st, ffn_dw_kernel<WBM, WBN, true><<<grid, dim3(kDwThreads), 0, st>>>(p));
       return DYNMO_OK;
     }
