@@ -21,8 +21,6 @@
 namespace dynmo {
 
 constexpr int kDwThreads = 256;
-constexpr int kDwK = 32;
-constexpr int kChunkTiles = 4;  // row tiles that are taken together, column tile by column tile
 
 // One weight gradient dW[e] = P_e^T Q_e (M x N per expert)
 struct DwSet {
@@ -48,7 +46,7 @@ template <int WBM, int WBN>
 struct DwShape {
   static constexpr int kRows = 32 * WBM, kCols = 32 * WBN;  // of the output tile
   static constexpr int kStages = WBN == 2 ? 4 : 3;
-  static constexpr int kBytesA = kRows * kDwK * 2, kBytesB = kCols * kDwK * 2;
+  static constexpr int kBytesA = kRows * kTileK * 2, kBytesB = kCols * kTileK * 2;
   static constexpr int kStage = kBytesA + kBytesB;
   static constexpr int kPiecesA = kBytesA / 4096, kPiecesB = kBytesB / 4096;  // pieces of 1 KB a wavefront loads per stage
   static constexpr int kLoads = kPiecesA + kPiecesB;
@@ -65,51 +63,22 @@ __device__ __forceinline__ int lane_now() {
   return l;
 }
 
-// [k][row]: where block `b` of k-row `k` is stored, and the other way round
-template <int ROWS>
-__device__ __forceinline__ int swizzled(int b, int k) {
-  return ROWS == 64 ? b ^ ((k >> 1) & 1) : b ^ (k & 3);
-}
-
 // Byte offsets, from the tile's (row 0, k 0) element, of the 16 bytes this lane moves in each of the
 // wavefront's pieces (kOob: nothing).
 template <int ROWS>
 struct DwPieces {
-  static constexpr int N = ROWS * kDwK * 2 / 4096;
+  static constexpr int N = ROWS * kTileK * 2 / 4096;
   uint32_t off[N];
 
   __device__ __forceinline__ void init(uint32_t ld_bytes, int rows_left) {
     const int lane = lane_now(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    constexpr int kLanesPerK = ROWS * 2 / 16;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const int q = wave * N + j;
-      const int k = q * (64 / kLanesPerK) + lane / kLanesPerK, slot = lane % kLanesPerK;
-      const int blk = swizzled<ROWS>(slot >> 2, k);
-      const int col = blk * 32 + ((slot & 3) ^ (((k >> 3) & 1) << 1)) * 8;
-      off[j] = col < rows_left ? (uint32_t)k * ld_bytes + col * 2 : kOob;
+      off[j] = krow_piece<ROWS>(q, lane, ld_bytes, rows_left);
     }
   }
 };
-
-// LDS byte offset (inside an operand's stage) from which this lane reads its fragment of a 16-row block: lane l holds, for row
-// l % 16 of the block, the eight k values (l / 16) * 8 .. + 7.
-template <int ROWS>
-__device__ __forceinline__ uint32_t frag_offset(int lane, int block16) {
-  const int s = lane & 15, g = lane >> 4;
-  const int k = g * 8 + (s >> 2);
-  const int blk = block16 >> 1, half = block16 & 1;
-  return k * (ROWS * 2) + swizzled<ROWS>(blk, k) * 64 + (((g & 1) ^ half) << 5) + (s & 3) * 8;
-}
-
-// Tile r of mt x nt tiles: row tiles in chunks of kChunkTiles, a chunk walked column tile by column tile.
-__device__ __forceinline__ void tile_of(int r, int mt, int nt, int* mi, int* ni) {
-  const int c = r / (kChunkTiles * nt);
-  const int h = min(kChunkTiles, mt - c * kChunkTiles);
-  r -= c * kChunkTiles * nt;
-  *ni = r / h;
-  *mi = c * kChunkTiles + r - *ni * h;
-}
 
 // Where 16-byte unit `unit` of row `row` of an epilogue patch with ROW_BYTES per row is kept: the accumulators are
 // written by sixteen lanes of one column group, each into its own row, and read back along rows.
@@ -151,12 +120,6 @@ __device__ __forceinline__ void wait_lds() {
   asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N < 15 ? N : 15) : "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
-// Waits until at most N of this wavefront's loads and stores, and none of its LDS reads, are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_stage() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N < 63 ? N : 63) : "memory");
-}
-
 template <int WBM, int WBN, bool AHEAD>
 __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void ffn_dw_kernel(const DwParams p) {
   using S = DwShape<WBM, WBN>;
@@ -201,7 +164,7 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
   const bf16_t *na = nullptr, *nb = nullptr;
   uint32_t lda_b = 0, ldb_b = 0;
   int k_left = 0;  // rows left to load
-  auto steps_of = [&](const Job& j) { return (j.k_end - j.k_begin + kDwK - 1) / kDwK; };
+  auto steps_of = [&](const Job& j) { return (j.k_end - j.k_begin + kTileK - 1) / kTileK; };
   auto stream_from = [&](const Job& j) {
     lda_b = (uint32_t)j.M * 2;
     ldb_b = (uint32_t)j.N * 2;
@@ -219,14 +182,14 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
   // the k mask; past the last step the loads fetch nothing
   auto next_step = [&](uint32_t stage) {
     Descs q;
-    const uint32_t k_rows = (uint32_t)max(0, min(k_left, kDwK));
+    const uint32_t k_rows = (uint32_t)max(0, min(k_left, kTileK));
     q.a = make_desc(na, k_rows * lda_b);
     q.b = make_desc(nb, k_rows * ldb_b);
     q.to_a = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesA * 1024);
     q.to_b = __builtin_amdgcn_readfirstlane(lds0 + stage + wave * S::kPiecesB * 1024);
-    na += (long)kDwK * (lda_b / 2);
-    nb += (long)kDwK * (ldb_b / 2);
-    k_left -= kDwK;
+    na += (long)kTileK * (lda_b / 2);
+    nb += (long)kTileK * (ldb_b / 2);
+    k_left -= kTileK;
     return q;
   };
   auto load_piece = [&](const Descs& q, auto J) {
@@ -282,9 +245,9 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
       const int lane = lane_now();
       uint32_t ra[WBM], rb[WBN];
 #pragma unroll
-      for (int i = 0; i < WBM; ++i) ra[i] = lds0 + frag_offset<TM>(lane, wm + 2 * i);
+      for (int i = 0; i < WBM; ++i) ra[i] = lds0 + krow_frag<TM>(lane, wm + 2 * i);
 #pragma unroll
-      for (int j = 0; j < WBN; ++j) rb[j] = lds0 + S::kBytesA + frag_offset<TN>(lane, wn * WBN + j);
+      for (int j = 0; j < WBN; ++j) rb[j] = lds0 + S::kBytesA + krow_frag<TN>(lane, wn * WBN + j);
       DwFrag fa[ROWS], fb[WBN];
       auto read_a = [&](int i, uint32_t from) { fa[i].template read<TM * 2>(ra[i] + from); };
       auto read_b = [&](int j, uint32_t from) { fb[j].template read<TN * 2>(rb[j] + from); };
@@ -359,9 +322,9 @@ __global__ __launch_bounds__(kDwThreads, WBN == 8 ? 2 : WBN == 4 ? 3 : 4) void f
       const int lane = lane_now();
       uint32_t ra[WBM], rb[WBN];
 #pragma unroll
-      for (int i = 0; i < WBM; ++i) ra[i] = lds0 + frag_offset<TM>(lane, wm + 2 * i);
+      for (int i = 0; i < WBM; ++i) ra[i] = lds0 + krow_frag<TM>(lane, wm + 2 * i);
 #pragma unroll
-      for (int j = 0; j < WBN; ++j) rb[j] = lds0 + S::kBytesA + frag_offset<TN>(lane, wn * WBN + j);
+      for (int j = 0; j < WBN; ++j) rb[j] = lds0 + S::kBytesA + krow_frag<TN>(lane, wn * WBN + j);
       for (int kt = 0; kt < n_kt; ++kt) {
         wait_stage<(NS - 2) * S::kLoads>();
         __builtin_amdgcn_s_barrier();

@@ -101,6 +101,52 @@ __device__ __forceinline__ void swiglu_bwd_bf16(float dA, float g, float u, floa
   *du = dA * gs;
 }
 
+// ---- what ffn_tile.hip and ffn_dw.hip share: tiles whose k goes in steps of 32
+constexpr int kTileK = 32;
+constexpr int kChunkTiles = 4;  // row tiles that are walked together, column tile by column tile
+
+// Waits until at most N of this wavefront's loads and stores, and none of its LDS reads, are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_stage() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
+}
+
+// Tile r of mt x nt tiles: row tiles in chunks of kChunkTiles, a chunk walked column tile by column tile.
+__device__ __forceinline__ void tile_of(int r, int mt, int nt, int* mi, int* ni) {
+  const int c = r / (kChunkTiles * nt);
+  const int h = min(kChunkTiles, mt - c * kChunkTiles);
+  r -= c * kChunkTiles * nt;
+  *ni = r / h;
+  *mi = c * kChunkTiles + r - *ni * h;
+}
+
+// An operand that lies [k][row] in memory: in LDS the k-row k of ROWS rows is ROWS / 32 blocks of 64 bytes; block b is stored as block
+// b ^ (k & 3) (64 rows: b ^ ((k >> 1) & 1)), its two 32-byte halves swapped when bit 3 of k is set.
+// where block `b` of k-row `k` is stored, and the other way round
+template <int ROWS>
+__device__ __forceinline__ int swizzled(int b, int k) {
+  return ROWS == 64 ? b ^ ((k >> 1) & 1) : b ^ (k & 3);
+}
+// byte offset, from the tile's (row 0, k 0) element, of the 16 bytes that `lane` moves in piece q (1 KB); kOob outside the rows
+template <int ROWS>
+__device__ __forceinline__ uint32_t krow_piece(int q, int lane, uint32_t ld_bytes, int rows_left) {
+  constexpr int kLanesPerK = ROWS * 2 / 16;
+  const int k = q * (64 / kLanesPerK) + lane / kLanesPerK, slot = lane % kLanesPerK;
+  const int blk = swizzled<ROWS>(slot >> 2, k);
+  const int col = blk * 32 + ((slot & 3) ^ (((k >> 3) & 1) << 1)) * 8;
+  return col < rows_left ? (uint32_t)k * ld_bytes + col * 2 : kOob;
+}
+// LDS byte offset (inside the operand's stage) from which `lane` reads its fragment of a 16-row block with ds_read_b64_tr_b16: lane
+// l holds, for row l % 16 of the block, the eight k values (l / 16) * 8 .. + 7
+template <int ROWS>
+__device__ __forceinline__ uint32_t krow_frag(int lane, int block16) {
+  const int s = lane & 15, g = lane >> 4;
+  const int k = g * 8 + (s >> 2);
+  const int blk = block16 >> 1, half = block16 & 1;
+  return k * (ROWS * 2) + swizzled<ROWS>(blk, k) * 64 + (((g & 1) ^ half) << 5) + (s & 3) * 8;
+}
+
 // Which kernel takes a product (the DYNMO_KERNEL_* values of dynmo.h): ffn_mfma.hip, ffn_tile.hip with one of its tiles, ffn_skinny.hip
 enum TileKind {
   TILE_256 = DYNMO_KERNEL_256x256,

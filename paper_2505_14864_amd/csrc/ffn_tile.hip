@@ -22,8 +22,6 @@
 namespace dynmo {
 
 constexpr int kTileThreads = 256;
-constexpr int kTileK = 32;
-constexpr int kChunkTiles = 4;  // row tiles that are walked together, column tile by column tile
 
 struct TileParams {
   GemmParams g;
@@ -46,30 +44,17 @@ struct TileShape {
   static_assert(4 * kPatchBytes <= kLds, "the epilogue patches reuse the stages");
 };
 
-// Waits until at most N of this wavefront's loads and none of its LDS reads are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_stage() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
-}
-
-// [k][row]: where block `b` of k-row `k` is stored, and the other way round
-template <int ROWS>
-__device__ __forceinline__ int swizzled(int b, int k) {
-  return ROWS == 64 ? b ^ ((k >> 1) & 1) : b ^ (k & 3);
-}
-
 // [row][k]: what the slot of a 16-byte piece is mixed with, by (row / 4) % 4: 0, 2, 3, 1.  The hardware serves a 16-byte read
 // in groups of sixteen lanes, 0..3, 12..15, 20..27 the first: rows 0..3 and 12..15 of one k group, 4..11 of the next.
 __device__ __forceinline__ int rowk_swizzle(int quad) { return ((quad << 1) & 2) ^ ((quad >> 1) * 3); }
 
 // Byte offsets, from the tile's (row 0, k 0) element, of the 16 bytes this lane moves in each of the
-// wavefront's pieces (kOob: nothing), and their k.
+// wavefront's pieces (kOob: nothing), and their k where that needs a mask.
 template <int ROWS, bool KROW>
 struct TilePieces {
   static constexpr int N = ROWS * kTileK * 2 / 4096;
   uint32_t off[N];
-  int kpos[N];
+  int kpos[N];  // [row][k]
 
   // [row][k]: a piece is 16 rows; WRAP: rows from there on are rows 0.. of a second matrix
   __device__ __forceinline__ void init(uint32_t ld_bytes, int rows_left, int wrap, const int32_t* __restrict__ rowmap, int rowdiv) {
@@ -85,13 +70,7 @@ struct TilePieces {
         off[j] = ok ? (uint32_t)row * ld_bytes + c * 16 : kOob;
         kpos[j] = c * 8;
       } else {
-        constexpr int kLanesPerK = ROWS * 2 / 16;
-        const int k = q * (64 / kLanesPerK) + lane / kLanesPerK, slot = lane % kLanesPerK;
-        const int stored = slot >> 2;
-        const int blk = swizzled<ROWS>(stored, k);
-        const int col = blk * 32 + ((slot & 3) ^ (((k >> 3) & 1) << 1)) * 8;
-        off[j] = col < rows_left ? (uint32_t)k * ld_bytes + col * 2 : kOob;
-        kpos[j] = k;
+        off[j] = krow_piece<ROWS>(q, lane, ld_bytes, rows_left);
       }
     }
   }
@@ -105,10 +84,7 @@ __device__ __forceinline__ uint32_t frag_offset(int block16) {
   if constexpr (!KROW) {
     return (block16 * 16 + s) * 64 + ((g ^ rowk_swizzle(s >> 2)) << 4);
   } else {
-    const int k = g * 8 + (s >> 2);
-    const int blk = block16 >> 1, half = block16 & 1;
-    const int stored = swizzled<ROWS>(blk, k);
-    return k * (ROWS * 2) + stored * 64 + (((g & 1) ^ half) << 5) + (s & 3) * 8;
+    return krow_frag<ROWS>(lane, block16);
   }
 }
 
@@ -124,15 +100,6 @@ __device__ __forceinline__ bf16x8_t read_tile_frag(uint32_t addr) {
     const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(uintptr_t)(addr + 4 * ROWS * 2));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
-}
-
-// Tile r of mt x nt tiles: row tiles in chunks of kChunkTiles, a chunk walked column tile by column tile.
-__device__ __forceinline__ void tile_of(int r, int mt, int nt, int* mi, int* ni) {
-  const int c = r / (kChunkTiles * nt);
-  const int h = min(kChunkTiles, mt - c * kChunkTiles);
-  r -= c * kChunkTiles * nt;
-  *ni = r / h;
-  *mi = c * kChunkTiles + r - *ni * h;
 }
 
 template <int MODE, int WBM, int WBN, bool WHOLE_K>
