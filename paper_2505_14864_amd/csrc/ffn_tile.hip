@@ -2,13 +2,16 @@
 // products that are too small, or cut into too many short pieces, for the 256 x 256 tiles of ffn_mfma.hip.
 //
 // One workgroup of four wavefronts (2 x 2) per output tile of 128 x 256 (64 x 128 per wavefront), 128 x 128
-// (64 x 64) or 64 x 64 (32 x 32), not persistent: the hardware deals the workgroups, and two (three, five) of
+// (64 x 64) or 64 x 64 (32 x 32), not persistent: the hardware deals the workgroups, and two (three, three) of
 // them share a compute unit, so that one's prologue and epilogue run under the other's matrix instructions.
 // The 256 x 256 kernel keeps one workgroup per compute unit and cannot overlap them; it needs two thirds of the L2
 // traffic per MFMA and wins where a tile's k range is long and the tiles fill the chip.
 //
 // k goes in steps of 32 (one MFMA deep) through a ring of three LDS stages of one step (64 x 64: two); buffer loads with an
-// LDS destination fill a stage two stages before it is read.  Deeper rings are no faster (64 x 64 tiles, eight stages of one step: 0 to
+// LDS destination fill a stage two stages before it is read.  Two steps per barrier cost 64 x 64 tiles two of five workgroups per
+// compute unit and gain on every product all the same, also where a handful of rows waits for weights out of HBM (one step in
+// four stages / two in three, us; rows x H x F, experts): dX 16 x 1024 x 2048, 8 22.8 / 21.2, 64 x 2048 x 2048, 4 29.4 / 26.5, 256 x
+// 1024 x 1024, 1 15.0 / 14.2; dA 32 x 4096 x 4096, 1 22.5 / 19.8; gate/up and down 0 to 4 %, none of 44 slower by more than 1 %.  Deeper rings are no faster (64 x 64 tiles, eight stages of one step: 0 to
 // 7 % slower), nor are two steps per stage of 128 x 128 (0 to 20 % slower: a workgroup less per compute unit).  Operands that lie [row][k] in memory
 // keep that layout in LDS, operands that lie [k][row] are read with ds_read_b64_tr_b16; 16-byte pieces
 // are placed so that the lanes that the hardware serves together fall into different banks (placed for the sixteen lanes of a k group
