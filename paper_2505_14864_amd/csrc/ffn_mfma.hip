@@ -1278,20 +1278,27 @@ static int32_t launch_mfma(const GemmParams& p, int max_tiles, bool share, Kerne
 //     256 x 256 tiles alone on average, and more than 5 % above theirs for 18, 35 and 45 of them: the host knows the rows, not
 //     the segments, and estimates the tiles.
 //   * The three weight gradients go in one launch on smaller tiles, and the 256 x 256 kernel's epilogue has nothing to hide
-//     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts (us for all three, 256 /
-//     128 x 256): 16 experts, 32768 x 4096 x 688, 768 tiles: 669 / 604; 64, 16384 x 2048 x 1024, 2048: 404 / 384; 8,
-//     8192 x 2048 x 4096, 1024: 441 / 406.  Not for long sums that fill the chip (4, 16384 x 4096 x 4096, 1024 tiles:
-//     1245 / 1339), many tiles (8, 8192 x 4096 x 14336, 7168 tiles: 2634 / 2773) or a single expert, whose tiles
-//     all take the same time (8192 x 2048 x 8192, 256: 603 / 679); there smaller tiles pay up to 128 tiles (256 / 128 / 64;
-//     6144 x 2048 x 4096, 128: 403 / 320 / 586; 8192 x 3072 x 3072, 144: 561 / 682; 6144 x 512 x 1024, 8: 337 / 173 / 106).
+//     behind when an expert has few rows, while its fixed tile lists suffer from uneven experts.  All three, 256 / 128 x 256 in us, even
+//     routing and (skewed), experts, rows x H x F, 256 x 256 tiles:
+//       up to 128 tiles per expert  64, 16384 x 2048 x 1536, 3072: 564 / 484 (709 / 503)     64, 32768 x 2048 x 4096, 8192: 2112 / 1951 (2189 / 1974)
+//         16, 40960 x 2048 x 4096, 2048: 1737 / 1638 (2177 / 1677)     8, 32768 x 2048 x 4096, 1024: 1344 / 1258 (1779 / 1263)
+//         16, 65536 x 2048 x 2048, 1024: 1375 / 1284 (1606 / 1259)     32, 32768 x 2048 x 2816, 2816: 1180 / 1060 (1371 / 1080)
+//       more per expert             4, 16384 x 4096 x 4096, 1024: 1259 / 1237 (1262 / 1249)    4, 32768: 2383 / 2463 (2367 / 2482)
+//         8, 16384 x 4096 x 8192, 4096: 2660 / 2669 (2669 / 2672)      8, 8192 x 4096 x 14336, 7168: 2610 / 2656 (2661 / 2682)
+//         16, 16384 x 4096 x 6144, 6144: 2247 / 2309 (2344 / 2326)     16, 16384 x 4096 x 4096, 4096: 1632 / 1531 (1623 / 1554)
+//     Hence beyond 128 tiles per expert not for long sums that fill the chip nor for many tiles.  A single expert's tiles all take
+//     the same time; there smaller ones pay while 256 x 256 tiles leave a good part of one round idle (256 / 128 x 256 / 128 x 128):
+//       8192 x 1536 x 4096, 96: 523 / 298 / 391     8192 x 2560 x 4096, 160: 569 / 404 / 691     2048 x 3072 x 4096, 192: 153 / 133 / 136
+//       8192 x 3328 x 4096, 208: 557 / 513 / 905    8192 x 3584 x 4096, 224: 583 / 595 / 979     8192 x 4096 x 8192, 512: 1179 / 1219 / 1551
 static TileKind tile_for(const dynmo_desc* d, int mode, int N, int K) {
   const double rows = (double)d->T * d->k;
   const double ragged = d->E > 1 ? 0.5 * (d->E < rows ? d->E : rows) : 0.0;
   auto cols = [](int n, int tile) { return (double)((n + tile - 1) / tile); };
   if (mode == MODE_DW) {
-    const double tiles = d->E * cols(d->H, BM) * cols(d->F, BM);
-    if (tiles > (d->E == 1 ? 128 : 2048) || (tiles > 512 && rows > 2560.0 * d->E)) return TILE_256;
-    if (tiles >= 256) return TILE_128x256;
+    const double per_expert = cols(d->H, BM) * cols(d->F, BM), tiles = d->E * per_expert;
+    if (d->E == 1 && tiles > 208) return TILE_256;
+    if (per_expert > 128 && (tiles > 2048 || (tiles > 512 && rows > 2560.0 * d->E))) return TILE_256;
+    if (tiles >= (d->E == 1 ? 96 : 256)) return TILE_128x256;
     return 3 * d->E * cols(d->H, 128) * cols(d->F, 128) > 512 ? TILE_128 : TILE_64;
   }
   if (mode == MODE_GATEUP) N *= 2;

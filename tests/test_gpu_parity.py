@@ -1074,6 +1074,20 @@ def test_weight_gradient_workgroups_walk_tiles(E, H, F, kernel):
     check_layer_full(layer, ref, w.dtype)
 
 
+@pytest.mark.parametrize("E,T,H,F,kernel", [(33, 90, 16, 16384, "128x256"), (17, 60, 16, 32784, "256x256"), (1, 70, 2312, 2568, "128x256"),
+                                            (1, 70, 2056, 2312, "128x128"), (1, 40, 3336, 3848, "256x256")])
+def test_weight_gradient_tiles_by_tiles_per_expert(E, T, H, F, kernel):
+    """The weight gradients on both sides of where 128 x 256 tiles end: many tiles of up to 128 per expert and of one more, one expert of
+    90, 110 and 224 tiles of 256 x 256.  Same tolerance as every bf16 layer: the sums are over few rows."""
+    say("weight gradients, E=%d T=%d H=%d F=%d" % (E, T, H, F))
+    w = wl.scaled(wl.CONFIGS[2], T=T, H=H, F=F, E=E, k=1, seed=9300 + E)
+    assert kernels(w)["dW"] == kernel
+    inp = wl.make_inputs(w, threads=4)
+    f = f32_inputs(inp)
+    ref = orc.moe_layer(f["logits"], f["x"], f["Wg"], f["Wu"], f["Wd"], w.k, f["dout"])
+    check_layer_full(run_moe(w, inp), ref, w.dtype)
+
+
 @pytest.mark.parametrize("counts,H,F,few", [((1,), 72, 136, "gateup down"), ((16,), 200, 520, "gateup"), ((1, 0, 17, 3), 264, 2056, "down"),
                                             ((40, 0, 2, 1, 3, 5, 2, 65), 520, 4104, ""), ((8, 8), 2048, 4096, "down")])
 def test_few_rows_per_expert(counts, H, F, few):
